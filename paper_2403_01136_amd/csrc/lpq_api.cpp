@@ -537,21 +537,24 @@ lpq_status check_attention_args(const lpq_layer_cfg* cfg, const lpq_layer_state*
     return LPQ_OK;
 }
 
+// fresh (T = 1 only): the caches do not hold the new token yet; the attention kernel appends it.
 lpq_status run_attention(const void* qkv, const lpq_layer_cfg* cfg, const lpq_layer_state* st, int32_t n_seqs, int32_t T, int32_t pos0,
-                         void* out, hipStream_t stream)
+                         bool fresh, void* out, hipStream_t stream)
 {
+    if (T > 1)
+        return launch_attention_prefill(qkv, st->k_cache, st->vt_cache, st->alibi_slopes, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim,
+                                        cfg->max_seq, out, stream) == hipSuccess ? LPQ_OK : LPQ_ERR_DEVICE;
+    const int n = fresh ? pos0 : pos0 + 1;
+    int range = 0, splits = 0;
+    attention_decode_plan(n_seqs, cfg->n_heads, n, &range, &splits);
+    const size_t floats = attention_decode_workspace_floats(n_seqs, cfg->n_heads, cfg->head_dim, splits);
     float* part = nullptr;
-    if (T == 1) {
-        int range = 0, splits = 0;
-        attention_decode_plan(n_seqs, cfg->n_heads, pos0 + 1, &range, &splits);
-        const size_t floats = attention_decode_workspace_floats(n_seqs, cfg->n_heads, cfg->head_dim, splits);
-        if (floats) {
-            lpq_status s = workspace(false, floats * sizeof(float), &part);
-            if (s != LPQ_OK) return s;
-        }
+    if (floats) {
+        lpq_status s = workspace(false, floats * sizeof(float), &part);
+        if (s != LPQ_OK) return s;
     }
-    return launch_attention(qkv, st->k_cache, st->vt_cache, st->alibi_slopes, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim, cfg->max_seq,
-                            out, part, stream) == hipSuccess ? LPQ_OK : LPQ_ERR_DEVICE;
+    return launch_attention_decode(qkv, st->k_cache, st->vt_cache, st->alibi_slopes, n_seqs, n, fresh, cfg->n_heads, cfg->head_dim, cfg->max_seq,
+                                   out, part, stream) == hipSuccess ? LPQ_OK : LPQ_ERR_DEVICE;
 }
 
 }  // namespace
@@ -645,7 +648,7 @@ lpq_status lpq_attention(const void* qkv, const lpq_layer_cfg* cfg, const lpq_la
     lpq_status s = check_attention_args(cfg, st, n_seqs, T, pos0);
     if (s != LPQ_OK) return s;
     if (misaligned(qkv) || misaligned(out)) return LPQ_ERR_ALIGN;
-    return run_attention(qkv, cfg, st, n_seqs, T, pos0, out, static_cast<hipStream_t>(hip_stream));
+    return run_attention(qkv, cfg, st, n_seqs, T, pos0, false, out, static_cast<hipStream_t>(hip_stream));
 }
 
 size_t lpq_decoder_layer_workspace(const lpq_layer* layer, const lpq_layer_cfg* cfg, int32_t M)
@@ -689,9 +692,10 @@ lpq_status lpq_decoder_layer(const lpq_layer* layer, const lpq_layer_cfg* cfg, c
     };
     if (launch_layernorm(x, st->ln1_gamma, st->ln1_beta, cfg->ln_eps, (int)M, (int)h, h1, stream) != hipSuccess) return LPQ_ERR_DEVICE;
     if ((s = linear(&layer->qkv, h1, qkv, nullptr, LPQ_ACT_NONE)) != LPQ_OK) return s;
-    if (launch_kv_append(qkv, st->k_cache, st->vt_cache, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim, cfg->max_seq, stream) != hipSuccess)
+    // one new token per sequence: the attention kernel writes it to the caches itself
+    if (T > 1 && launch_kv_append(qkv, st->k_cache, st->vt_cache, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim, cfg->max_seq, stream) != hipSuccess)
         return LPQ_ERR_DEVICE;
-    if ((s = run_attention(qkv, cfg, st, n_seqs, T, pos0, att, stream)) != LPQ_OK) return s;
+    if ((s = run_attention(qkv, cfg, st, n_seqs, T, pos0, T == 1, att, stream)) != LPQ_OK) return s;
     if ((s = linear(&layer->out, att, y, x, LPQ_ACT_NONE)) != LPQ_OK) return s;                    // y = x + out-projection
     if (launch_layernorm(y, st->ln2_gamma, st->ln2_beta, cfg->ln_eps, (int)M, (int)h, h1, stream) != hipSuccess) return LPQ_ERR_DEVICE;
     if ((s = linear(&layer->fc1, h1, ff, nullptr, cfg->activation)) != LPQ_OK) return s;

@@ -244,3 +244,63 @@ def test_decoder_layer_decode_step_in_a_hip_graph(orc):
         assert np.array_equal(u16(y_graph), u16(y_eager)), "replay %d" % replay
         assert torch.equal(st.k_cache, k_eager) and torch.equal(st.vt_cache, v_eager), "replay %d caches" % replay
         assert torch.isfinite(other).all()
+
+
+@pytest.mark.parametrize("B,H,d,T,pos0", [
+    (1, 3, 128, 127, 0), (2, 9, 64, 128, 0), (1, 2, 128, 129, 63), (1, 1, 64, 257, 64), (3, 3, 128, 31, 97), (1, 2, 64, 33, 1),   # prefill: 32- and
+    (1, 2, 128, 1, 62), (2, 1, 64, 1, 63), (1, 3, 128, 1, 64), (1, 1, 64, 1, 255), (2, 2, 128, 1, 256), (1, 1, 128, 1, 1999),     # 128-query, 64-key edges
+])
+def test_attention_tile_edges_and_growing_scores(B, H, d, T, pos0):
+    """Lengths around the kernels' tiles, scores that grow along the positions (a running maximum that moves at every tile,
+    by a little and by much) beside flat ones, NaN behind the written positions.
+    Tolerance: the file's (weights and results in fp16)."""
+    import torch
+    S = (pos0 + T + 63) // 64 * 64
+    st, _, slopes = make_state(B, H, d, S, T, B == 2)
+    r = rng("edges", B, H, d, T, pos0)
+    h = H * d
+    qkv = f16(r.standard_normal((B * T, 3 * h)))
+    qkv[:, :h:d] = 4.0                                     # feature 0 of every head's queries
+    k = f16(r.standard_normal((B, H, S, d)))
+    vt = f16(r.standard_normal((B, H, d, S)))
+    grow = np.array([0.0, 0.02, 0.5])[np.arange(H) % 3]    # per head: score growth per position (natural units)
+    k[:, :, :, 0] = (grow[None, :, None] * np.arange(S)[None, None, :] * np.sqrt(d) / 4.0).astype(np.float16)
+    k[:, :, pos0 + T:], vt[:, :, :, pos0 + T:] = np.nan, np.nan
+    st.k_cache.copy_(to_dev(k)), st.vt_cache.copy_(to_dev(vt))
+    lpq.lpq_kv_append(to_dev(qkv), st, B, T, pos0)
+    out = lpq.lpq_attention(to_dev(qkv), st, B, T, pos0)
+    OL.kv_append(k, vt, qkv, B, T, pos0, H)
+    ref = OL.attention(qkv, k[:, :, :pos0 + T], vt[:, :, :, :pos0 + T], B, T, pos0, H, slopes)
+    check_output(out, ref, "attention edges B%d H%d d%d T%d pos0 %d" % (B, H, d, T, pos0))
+
+
+@pytest.mark.parametrize("pos0", [0, 1, 63, 64, 200, 1300])
+def test_decode_layer_appends_in_the_attention_kernel(pos0):
+    """A decode step of the whole layer writes the same cache bits as lpq_kv_append of its own QKV output does, beside positions that
+    hold NaN, and leaves every other position alone; one split over positions and several."""
+    import torch
+    B, H, d, f = 2, 2, 64, 256
+    h, S = H * d, (pos0 + 1 + 63) // 64 * 64
+    st, ln, _ = make_state(B, H, d, S, pos0)
+    r = rng("fresh", pos0)
+    W = {n: f16(r.standard_normal((N, K)) / np.sqrt(K)) for n, (K, N) in {"qkv": (h, 3 * h), "out": (h, h), "fc1": (h, f), "fc2": (f, h)}.items()}
+    layer = {n: lpq.lpq_quantize_pack(to_dev(w), 4, 1) for n, w in W.items()}
+    k, vt = f16(r.standard_normal((B, H, S, d))), f16(r.standard_normal((B, H, d, S)))
+    k[:, :, pos0:], vt[:, :, :, pos0:] = np.nan, np.nan
+    x = f16(r.standard_normal((B, h)))
+    st.k_cache.copy_(to_dev(k)), st.vt_cache.copy_(to_dev(vt))
+    y, _ = lpq.lpq_decoder_layer(layer, st, lpq.LPQ_DECODE, B, 1, pos0, to_dev(x))
+    got_k, got_v = u16(st.k_cache).copy(), u16(st.vt_cache).copy()
+    # the same operators one by one
+    st.k_cache.copy_(to_dev(k)), st.vt_cache.copy_(to_dev(vt))
+    h1 = lpq.lpq_layernorm(to_dev(x), *st.ln1, 1e-5)
+    qkv = lpq.lpq_qlinear_decode(layer["qkv"], h1)
+    lpq.lpq_kv_append(qkv, st, B, 1, pos0)
+    assert np.array_equal(got_k, u16(st.k_cache)) and np.array_equal(got_v, u16(st.vt_cache))
+    att = lpq.lpq_attention(qkv, st, B, 1, pos0)
+    x1 = lpq.lpq_qlinear_fused(layer["out"], att, lpq.LPQ_DECODE, residual=to_dev(x))
+    ff = lpq.lpq_qlinear_fused(layer["fc1"], lpq.lpq_layernorm(x1, *st.ln2, 1e-5), lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU)
+    ref = lpq.lpq_qlinear_fused(layer["fc2"], ff, lpq.LPQ_DECODE, residual=x1)
+    # the two attention calls add the new token's part in another order: roundings of the layer's operators may flip
+    a, b = y.double().cpu().numpy(), ref.double().cpu().numpy()
+    assert np.all(np.isfinite(a)) and np.linalg.norm(a - b) <= 2e-3 * np.linalg.norm(b)
