@@ -709,7 +709,7 @@ lpq_status lpq_variance_indicator(const void* w_fp16, int32_t K, int32_t N, cons
     if (K < 128 || K % 128 != 0 || N < 1 || M < 1) return LPQ_ERR_SHAPE;
     if (misaligned(w_fp16) || misaligned(x) || (reinterpret_cast<uintptr_t>(omega) & 7u)) return LPQ_ERR_ALIGN;
     float* ws = nullptr;
-    lpq_status st = workspace(false, indicator_workspace_bytes(N, (long)M * K / 8), &ws);
+    lpq_status st = workspace(false, indicator_workspace_bytes(), &ws);
     if (st != LPQ_OK) return st;
     return launch_indicator(w_fp16, K, N, x, M, stochastic != 0, omega, ws, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                ? LPQ_OK : LPQ_ERR_DEVICE;

@@ -136,7 +136,7 @@ hipError_t static_scratch(void** ptr, size_t* bytes);
 hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s);     // small launches, M <= 32: cum_weight = workgroups before
 hipError_t launch_prefill(int variant, const PrefillArgs& a, hipStream_t s);      // both kernels, if any linear is K-split
 // variance indicator (lpq_indicator.hip)
-size_t indicator_workspace_bytes(int N, long n8);
+size_t indicator_workspace_bytes();
 hipError_t launch_indicator(const void* w, int K, int N, const void* x, int M, int stochastic, double* omega, void* ws, hipStream_t s);
 // the rest of the decoder layer (lpq_layer.hip)
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, float eps, int M, int h, void* y, hipStream_t s);

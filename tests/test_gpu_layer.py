@@ -304,3 +304,16 @@ def test_decode_layer_appends_in_the_attention_kernel(pos0):
     # the two attention calls add the new token's part in another order: roundings of the layer's operators may flip
     a, b = y.double().cpu().numpy(), ref.double().cpu().numpy()
     assert np.all(np.isfinite(a)) and np.linalg.norm(a - b) <= 2e-3 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("N,K,M", [(7, 128, 4099), (9, 2176, 1), (8200, 256, 3), (8193, 384, 700), (17, 4096, 2048)])
+def test_variance_indicator_block_edges(N, K, M):
+    """Rows that do not fill a workgroup's eight waves, more rows than waves (a wave takes several), K behind and on multiples of the
+    2048 columns whose loads go out together, X smaller and larger than W.  Tolerance as above."""
+    r = rng("ind-edges", N, K, M)
+    w, x = f16(0.02 * r.standard_normal((N, K))), f16(r.standard_normal((M, K)) + 0.25)
+    for stochastic in (False, True):
+        got = lpq.lpq_variance_indicator(to_dev(w), to_dev(x), stochastic).cpu().numpy()
+        ref = OI.indicator(w, x, stochastic)
+        for i, key in enumerate(OI.ORDER):
+            assert abs(got[i] - ref[key]) <= 1e-5 * abs(ref[key]) + 1e-300, (key, got[i], ref[key])
