@@ -371,9 +371,11 @@ lpq_status lpq_workspace_reserve(size_t bytes);
 size_t lpq_workspace_bytes(void);
 
 /* Routing of decode launches, process-wide, for tests that must reach either kernel family with small shapes:
- * a launch that streams at most rows_max_mib MiB of codes (default 192) takes the kernel that gives a group of
- * 16-row tiles a workgroup, others the even-share kernel; rows_tiles = 2..5 forces that group size (0 = the
- * library's choice).  Negative values restore the defaults.  Errors: SHAPE. */
+ * a launch of up to 16 token rows that streams at most rows_max_mib MiB of codes (default 192), and one of 17 to 64 rows
+ * whose weights are at most the number the library keeps for that default, scaled by rows_max_mib / 192, take the
+ * kernels that give a few row tiles a workgroup, others the even-share kernel; rows_tiles = 2..5 forces the number of
+ * 16-row tiles per workgroup up to 16 rows (0 = the library's choice).  Negative values restore the defaults.
+ * Errors: SHAPE. */
 lpq_status lpq_set_decode_routing(int32_t rows_max_mib, int32_t rows_tiles);
 
 /* Test helper, not on the hot path: w_fp32[n][k] = scale * code + zero (fp32 multiply, then

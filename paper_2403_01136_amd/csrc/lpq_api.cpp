@@ -2,6 +2,7 @@
 // Every argument check happens before the first HIP call (see include/lpq.h).
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 #include <vector>
 
@@ -185,7 +186,7 @@ uint32_t variant_cost_x16(int variant)
 // plus T tiles of weights).  T = 3 and 5 cut a 64-row block across workgroups (e.g. 1280 tiles = 256 x 5);
 // at T = 5 the kernel holds the whole register file and runs a third slower per byte.  A split costs a second
 // kernel.  The estimate below (microseconds) is only used to rank the choices.
-void rows_plan(const LinDesc& L, int tok_tiles, int cus, int* tiles, int* splits)
+void rows_plan(const LinDesc& L, int cus, int* tiles, int* splits)
 {
     static const double tile_us[5] = {0.024, 0.032, 0.064, 0.064, 0.128};     // per tile and step, by variant
     const int KT = L.kt, n_tiles = L.N / 16;
@@ -198,7 +199,7 @@ void rows_plan(const LinDesc& L, int tok_tiles, int cus, int* tiles, int* splits
         if (L.variant == 4 && T > 2 && T != 4) continue;                     // fp16 weights: one or two tiles (4 stands for 2)
         const int rt = (L.variant == 4 && T > 2) ? 2 : T;
         if (n_tiles % rt != 0) continue;
-        const double step_us = 0.06 * tok_tiles + rt * tile_us[L.variant] + (rt == 5 ? 0.09 : 0.0);
+        const double step_us = 0.06 + rt * tile_us[L.variant] + (rt == 5 ? 0.09 : 0.0);
         for (int s = 1; s <= 8; ++s) {
             const long wgs = (long)(n_tiles / rt) * s;
             // a split is there to fill the chip, not to add rounds; a wave wants several steps per stage of its ring
@@ -208,6 +209,49 @@ void rows_plan(const LinDesc& L, int tok_tiles, int cus, int* tiles, int* splits
             if (est < best * 0.98) best = est, *tiles = T, *splits = s;
         }
     }
+}
+
+// Row blocks per workgroup (DecodeArgs::row_tiles) and K splits (LinDesc::aux) of a launch of the decode kernel for 17-64 token
+// rows.  A launch is fastest when its workgroups just fill the compute units once and their ranges of K are equally long:
+// every number of row blocks and many range lengths t are tried (fewer for launches of many linears), each linear
+// gets ceil(KT / t) splits, and the estimate (microseconds) ranks them: a step's arithmetic on the SIMDs of a workgroup,
+// its activations through LDS, a workgroup's start and end, a reduce launch and its traffic per split linear.  The splits'
+// sums stay within `max_floats`.
+void mid_plan(DecodeArgs& p, int cus, size_t max_floats)
+{
+    static const double step_us[4] = {0.5, 0.75, 1.0, 1.25};                     // of four row blocks at 2, 3, 4 token tiles
+    const int tiles = (p.M + 15) / 16;
+    int kt_max = 1;
+    for (int i = 0; i < p.n_lin; ++i) kt_max = std::max(kt_max, (int)p.lin[i].kt);
+    double best = 1e30;
+    int best_t = kt_max;
+    p.row_tiles = 4;
+    for (int rb = 4; rb >= (tiles <= 2 ? 1 : 2); rb /= 2) {
+        const int slots = tiles == 1 ? 16 / rb : tiles == 2 && rb <= 2 ? 8 : 4;                    // steps per iteration (MidCfg in lpq_decode.hip)
+        const double step = 0.25 * rb * step_us[tiles - 1] + 0.032 * tiles;
+        for (int t = kt_max; t >= 4; t = std::min(t - 1, p.n_lin == 1 ? t * 63 / 64 : t * 7 / 8)) {
+            double wgs = 0.0, reduce = 0.0, floats = 0.0, sum = 0.0, longest = 0.0, shortest = 1e30;
+            for (int i = 0; i < p.n_lin; ++i) {
+                const LinDesc& L = p.lin[i];
+                const int s = (L.kt + t - 1) / t, len = (L.kt + s - 1) / s;
+                const double n = (double)mid_superblocks(L, rb) * s, us = (len + slots - 1) / slots * slots * step + 4.0;
+                wgs += n;
+                sum += n * us;
+                longest = std::max(longest, us);
+                shortest = std::min(shortest, us);
+                if (s > 1) {
+                    floats += (double)s * p.M * L.N;
+                    reduce = 4.5 + floats * 8.0 / 4.0e6;
+                }
+            }
+            if (floats > (double)max_floats) break;                         // shorter ranges only need more
+            // up to two rounds of workgroups are counted whole; more, or of unlike lengths (longest first), fill up better
+            const double est = reduce + (wgs <= cus ? longest : p.n_lin == 1 && wgs <= 2.0 * cus ? 2.0 * longest
+                                                                             : std::max(longest, sum / cus + 0.5 * shortest));
+            if (est < best * 0.99) best = est, best_t = t, p.row_tiles = rb;
+        }
+    }
+    for (int i = 0; i < p.n_lin; ++i) p.lin[i].aux = (p.lin[i].kt + best_t - 1) / best_t;
 }
 
 // Bytes that decode_prepare_kernel leaves for a linear in a decode launch of up to 32 token rows per pass.  The group
@@ -244,6 +288,27 @@ bool reads_in_place(const std::vector<LinearCall>& calls, size_t begin, size_t e
         if (variant_of(d) == 0) w3 += bytes;
     }
     return w3 >= 0.25 * all;
+}
+
+// Whether a decode launch of 17 to 64 token rows goes to the kernel of few row blocks per workgroup instead of the even-share
+// kernel.  That one has some 30 us of preparation, fix-up pass and partial tiles, this one a higher cost per 3- or 4-bit weight
+// (both tiles' FMAs against the zero term outside the loop; at 33-64 rows a product per group against weights
+// dequantised once), so the line lies at a number of weights; 8- and 16-bit codes cost about the same in both.  Measured, us,
+// even-share / this, at 32, 48 and 64 rows: a 4-bit layer of 5120 (315 M weights) 79 / 46, 88 / 55, 93 / 66; a 3- and a 4-bit layer
+// of 5120 (629 M) 107 / 88, 131 / 119, 138 / 139; a 3- and a 4-bit layer of 7168 (1.2 G) 163 / 156, 216 / 201, 226 / 244; a 3-bit layer of
+// 14336 (2.7 G) 250 / 305, 375 / 379, 389 / 459; 8 bit, 7168 -> 28672 77 / 42, 98 / 54, 99 / 60; an 8-bit layer of 9216 (0.85 G) 223 / 198,
+// 239 / 197, 244 / 212; fp16, 7168 -> 28672 96 / 66, 101 / 73, 106 / 75.
+// rows_max_mib of lpq_set_decode_routing (default 192) moves the line in proportion.
+bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
+{
+    static const double weights34[3] = {1.0e9, 1.0e9, 0.55e9};              // 17-32, 33-48, 49-64 rows
+    double load = 0.0;
+    for (size_t c = begin; c < end; ++c) {
+        const lpq_qdesc& d = calls[c].w->d;
+        const double weights = (double)d.K * (double)d.N;
+        load += d.bits <= 4 ? weights / weights34[(M + 15) / 16 - 2] : weights * d.bits / 8.0 / 1.0e9;
+    }
+    return load <= g_rows_max_mb.load() / 192.0;
 }
 
 // Decode-phase dispatch of a list of independent linears: grouped launches of at most
@@ -316,66 +381,64 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         }
         if (total >= ((uint64_t)1 << 50)) return LPQ_ERR_UNSUPPORTED;
         a.total_weight = total;
-        // A launch that streams little (a single linear of a decoder layer) has too few steps to spread evenly:
-        // it goes to the kernel that gives every group of 16-row tiles a workgroup whose waves split K (no fix-up
-        // pass), up to 32 token rows per pass.
+        // A launch that streams little (a single linear of a decoder layer) has too few steps to spread evenly and pays the
+        // fix-up pass: it goes to the kernels whose workgroups take a few tiles of W over K (no pieces to add).  Which of
+        // them: from 17 token rows on the one that shares the activations through LDS; up to 16 the one that reads them
+        // straight from L2 and streams from deeper rings -- except a single linear of 13 to 16 rows that the former
+        // runs without splitting K (at 16 rows, 3 and 4 bit, us: 5120 -> 15360 15.8 against 13.7, 7168 -> 28672 31 / 26, 4096 -> 12288
+        // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower).
+        const bool mid_load = M > 16 && M <= 64 && mid_route(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M);
         const int64_t rows_max_bytes = (int64_t)g_rows_max_mb.load() << 20;
         int64_t stream_bytes = 0;
         for (size_t c = li * per_launch; c < std::min(n, (li + 1) * per_launch); ++c)
             stream_bytes += (int64_t)calls[c].w->d.K * calls[c].w->d.N * calls[c].w->d.bits / 8;
-        // 33-64 token rows take two passes of that kernel if the weights are few enough (128 MB) for the second
-        // pass to find most of them in the caches; measured on a decoder layer, 7-15 % faster than the even-share kernel.
-        if (stream_bytes <= rows_max_bytes && (M <= 32 || (M <= 64 && stream_bytes <= std::min<int64_t>(rows_max_bytes, (int64_t)128 << 20)))) {
+        if (mid_load || (M <= 16 && stream_bytes <= rows_max_bytes)) {
             // longest K first: the last workgroups to start are then the shortest
             std::stable_sort(a.lin, a.lin + a.n_lin, [](const LinDesc& x, const LinDesc& y) { return x.kt > y.kt; });
             int cus = 0;
             st = device_cus(&cus);
             if (st != LPQ_OK) return st;
-            // 32 token rows per pass (33-64 rows: two passes, the second reads the weights again, mostly from the caches)
-            for (int m0 = 0; m0 < M; m0 += 32) {
-                DecodeArgs p = a;
-                p.M = std::min(32, M - m0);
-                p.m0 = 0;
-                for (int i = 0; i < p.n_lin; ++i) {
-                    LinDesc& L = p.lin[i];
-                    L.x += (size_t)m0 * L.K();
-                    L.y += (size_t)m0 * L.N;
-                    if (L.residual) L.residual += (size_t)m0 * L.N;
-                }
-                const int tok_tiles = p.M <= 16 ? 1 : 2;
-                int tiles = 4, splits1 = 0;
-                if (p.n_lin == 1) rows_plan(p.lin[0], tok_tiles, cus, &tiles, &splits1);
-                const int forced = g_rows_tiles.load();
+            bool mid = mid_load;
+            if (mid || (M > 12 && a.n_lin == 1)) {
+                mid_plan(a, cus, partial_bytes / sizeof(float));
+                mid = mid || a.lin[0].aux == 1;
+            }
+            const int forced = g_rows_tiles.load();
+            int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
+            if (!mid) {
+                if (a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
                 if (forced >= 2 && forced <= 5 && forced != tiles) tiles = forced, splits1 = 0;
-                auto group_tiles = [&](const LinDesc& L) { return rows_group_tiles(L.variant, tiles); };
-                for (int i = 0; i < p.n_lin; ++i)
-                    if ((p.lin[i].N / 16) % group_tiles(p.lin[i]) != 0) tiles = 4, splits1 = 0;    // groups must tile every linear exactly
-                int64_t blocks = 0, row_blocks = 0;
-                for (int i = 0; i < p.n_lin; ++i) row_blocks += p.lin[i].N / 16 / group_tiles(p.lin[i]);
-                int64_t partial_floats = 0;
-                for (int i = 0; i < p.n_lin; ++i) {
-                    LinDesc& L = p.lin[i];
+                for (int i = 0; i < a.n_lin; ++i)
+                    if ((a.lin[i].N / 16) % rows_group_tiles(a.lin[i].variant, tiles) != 0) tiles = 4, splits1 = 0;    // groups must tile every linear exactly
+            }
+            int64_t blocks = 0, row_blocks = 0, partial_floats = 0;
+            for (int i = 0; i < a.n_lin; ++i) row_blocks += a.lin[i].N / 16 / rows_group_tiles(a.lin[i].variant, tiles);
+            for (int i = 0; i < a.n_lin; ++i) {
+                LinDesc& L = a.lin[i];
+                if (!mid) {
                     // K splits (L.aux) of a launch of several linears: only if it leaves most compute units without a
                     // workgroup, and only down to 32 steps per workgroup
                     const int KT = L.kt;
                     const int want = (int)std::max<int64_t>(1, 320 / std::max<int64_t>(1, row_blocks));
                     L.aux = splits1 > 0 ? splits1 : std::max(1, std::min(std::min(want, KT / 32), 8));
-                    L.step_weight = (uint32_t)partial_floats;             // float offset of this linear's partial sums
-                    if (L.aux > 1) partial_floats += (int64_t)L.aux * 16 * tok_tiles * L.N;
-                    L.cum_weight = (uint64_t)blocks;
-                    blocks += (int64_t)rows_row_blocks(L, tiles) * L.aux;
                 }
-                if (blocks > 0x7fffffffLL || partial_floats > 0x7fffffffLL) return LPQ_ERR_UNSUPPORTED;
-                if (partial_floats) {
-                    st = workspace(static_ws, (size_t)partial_floats * sizeof(float), &ws);
-                    if (st != LPQ_OK) return st;
-                }
-                p.partial = ws;
-                p.n_blocks = (int32_t)blocks;
-                p.row_tiles = tiles;
-                p.waves = (blocks <= 64 && tok_tiles == 1) ? 8 : 4;      // very few blocks: more waves per block keep more loads in flight
-                if (launch_decode_rows(p, stream) != hipSuccess) return LPQ_ERR_DEVICE;
+                L.step_weight = (uint32_t)partial_floats;                 // float offset of this linear's partial sums
+                if (L.aux > 1) partial_floats += (int64_t)L.aux * M * L.N;
+                L.cum_weight = (uint64_t)blocks;
+                blocks += (int64_t)(mid ? mid_superblocks(L, a.row_tiles) : rows_row_blocks(L, tiles)) * L.aux;
             }
+            if (blocks > 0x7fffffffLL || partial_floats > 0x7fffffffLL) return LPQ_ERR_UNSUPPORTED;
+            if (partial_floats) {
+                st = workspace(static_ws, (size_t)partial_floats * sizeof(float), &ws);
+                if (st != LPQ_OK) return st;
+            }
+            a.partial = ws;
+            a.n_blocks = (int32_t)blocks;
+            if (!mid) {
+                a.row_tiles = tiles;
+                a.waves = blocks <= 64 ? 8 : 4;          // very few blocks: more waves per block keep more loads in flight
+            }
+            if ((mid ? launch_decode_mid(a, stream) : launch_decode_rows(a, stream)) != hipSuccess) return LPQ_ERR_DEVICE;
             continue;
         }
         // A small launch (one linear of a decoder layer) is not cut into more ranges than it has chunks of

@@ -44,7 +44,8 @@ enum { MAX_LIN_PER_LAUNCH = 48 };   // keeps DecodeArgs under 4 KB of kernel arg
 struct DecodeArgs {
     int32_t n_lin, M, m0, waves;         // m0: first token row of this pass (M > 64 is run 64 rows at a time)
     int32_t n_blocks, slot_floats;       // slot_floats: floats per partial tile = 64 tokens x rows per workgroup
-    int32_t row_tiles, pad;              // small-launch kernel only: 16-row tiles per workgroup (2 .. 5; fp16 weights: at most 2)
+    int32_t row_tiles, pad;              // small-launch kernels: 16-row tiles per workgroup (2 .. 5; fp16 weights: at most 2);
+                                         // from 17 token rows on: 64-row blocks per workgroup (1, 2 or 4)
     uint64_t total_weight;
     uint64_t range_q;                    // total_weight / n_blocks and
     uint32_t range_rem, pad2;            // total_weight % n_blocks: range b begins at range_q * b + range_rem * b / n_blocks
@@ -123,6 +124,9 @@ __host__ __device__ inline int lin_row_superblocks(const LinDesc& L, int waves) 
 __host__ __device__ inline int rows_group_tiles(int variant, int row_tiles) { return (variant == 4 && row_tiles > 2) ? 2 : row_tiles; }
 __host__ __device__ inline int rows_row_blocks(const LinDesc& L, int row_tiles) { return L.N / 16 / rows_group_tiles(L.variant, row_tiles); }
 
+// decode_mid_kernel: workgroups in a linear, at `blocks` 64-row blocks each
+__host__ __device__ inline int mid_superblocks(const LinDesc& L, int blocks) { return (L.N / 64 + blocks - 1) / blocks; }
+
 int variant_of(const lpq_qdesc& d);           // -1 if the (bits, scheme) pair is not supported
 size_t tile_bytes_of(int variant);
 
@@ -133,7 +137,8 @@ hipError_t launch_unpack_dequant(const lpq_qweight& w, float* out, hipStream_t s
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s);
 // device address and size of the static scratch array of the current device (for the entry point that allocates nothing)
 hipError_t static_scratch(void** ptr, size_t* bytes);
-hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s);     // small launches, M <= 32: cum_weight = workgroups before
+hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s);     // small launches, M <= 16: cum_weight = workgroups before
+hipError_t launch_decode_mid(const DecodeArgs& a, hipStream_t s);      // small launches, M <= 64: aux = K splits, cum_weight = workgroups before
 hipError_t launch_prefill(int variant, const PrefillArgs& a, hipStream_t s);      // both kernels, if any linear is K-split
 // variance indicator (lpq_indicator.hip)
 size_t indicator_workspace_bytes();

@@ -883,7 +883,7 @@ __global__ __launch_bounds__(256) void decode_fixup_kernel(const DecodeArgs a)
     }
 }
 
-// ---- small launches (one linear of a decoder layer, up to 32 token rows = MT token tiles of 16) ---------------
+// ---- small launches (one linear of a decoder layer, up to 16 token rows) ---------------
 // The even-share kernel above needs a launch with many steps to spread; a single linear has few, and cutting
 // its units into short ranges leaves each workgroup waiting on memory latency and pays a fix-up pass.  Here a
 // workgroup owns a group of TILES consecutive 16-row tiles of W (at most 2 for fp16 weights) over the whole of
@@ -894,11 +894,11 @@ __global__ __launch_bounds__(256) void decode_fixup_kernel(const DecodeArgs a)
 // global memory: they are small and stay in L2; no LDS staging, no barrier in the loop), and the waves'
 // accumulators are added through LDS at the end, in wave order.  A linear with few tiles and a long K (the
 // second feed-forward matrix) is also split over L.aux workgroups per group, each taking a range of the steps
-// and leaving fp32 sums in partial[split][16 MT][N] (at float offset L.step_weight of the launch's partial buffer)
+// and leaving fp32 sums in partial[split][M][N] (at float offset L.step_weight of the launch's partial buffer)
 // for a small second kernel; otherwise there are no partial tiles and no second kernel.  rows_row_blocks(L, row_tiles) is the
 // linear's number of groups, a.lin[i].cum_weight the number of workgroups of the linears before i, a.n_blocks
 // their total.
-template <int V, int WAVES, int TILES, int MT>
+template <int V, int WAVES, int TILES>
 __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int split, float* __restrict__ partial, float* __restrict__ red)
 {
     constexpr int RT = (V == V_F16 && TILES > 2) ? 2 : TILES;      // 16-row tiles per workgroup; rb counts groups of RT tiles
@@ -907,9 +907,9 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
     constexpr bool POST = V != V_F16;
     constexpr int STAGES = (V == V_W3 || V == V_W4) ? 4 : 3;
     constexpr int LOADS = RT * (VInfo<V>::TILE_BYTES >= 1024 ? VInfo<V>::TILE_BYTES / 1024 : 1) +
-                          (SCHEME == SCH_ASYM ? (ALIGNED ? 2 : 4) : 0) + 4 * MT;
+                          (SCHEME == SCH_ASYM ? (ALIGNED ? 2 : 4) : 0) + 4;
     static_assert((STAGES - 1) * LOADS < 64, "vmcnt is a 6-bit counter");
-    constexpr int NV = (RT * MT + (SCHEME == SCH_SYM ? MT : 0)) * 4;   // floats a lane hands to the reduction
+    constexpr int NV = (RT + (SCHEME == SCH_SYM ? 1 : 0)) * 4;   // floats a lane hands to the reduction
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // a scalar: the row block and the tile addresses derive from it
     const int r = lane & 15, kq = lane >> 4;
@@ -919,15 +919,13 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
     const int splits = L.aux, share = KT / splits, extra = KT % splits;
     const int kt0 = split * share + min(split, extra), kt1 = kt0 + share + (split < extra ? 1 : 0);
     const int n_w = kt1 - kt0 > wave ? (kt1 - kt0 - wave + WAVES - 1) / WAVES : 0;      // this wave's steps
-    const uint16_t* __restrict__ xrow[MT];                          // token tile m holds rows 16 m .. 16 m + 15; rows past M repeat the last one
-#pragma unroll
-    for (int m = 0; m < MT; ++m) xrow[m] = L.x + (size_t)min(r + 16 * m, M - 1) * L.K() + 8 * kq;
+    const uint16_t* __restrict__ xrow = L.x + (size_t)min(r, M - 1) * L.K() + 8 * kq;       // rows past M repeat the last one
 
     struct Stage {
         WRaw<V> w[RT];
         u32x2 s, z;                 // scales and zeros of rows 4 r .. 4 r + 3 of the first tile's block
         u32x2 s1, z1;               // !ALIGNED: and of the next block (the group spans two)
-        h8 a[MT][4];
+        h8 a[4];
     };
     Stage st[STAGES];
     // step i of this wave; past its last step the loads repeat a valid step (they keep the count of loads in
@@ -947,45 +945,33 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
             }
         }
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b.a[m][j] = *reinterpret_cast<const h8*>(xrow[m] + (size_t)kt * 128 + 32 * j);
+        for (int j = 0; j < 4; ++j) b.a[j] = *reinterpret_cast<const h8*>(xrow + (size_t)kt * 128 + 32 * j);
     };
 
-    f4 acc[RT][MT], xsum[MT];
+    f4 acc[RT], xsum = f4{0, 0, 0, 0};
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        xsum[m] = f4{0, 0, 0, 0};
-#pragma unroll
-        for (int t = 0; t < RT; ++t) acc[t][m] = f4{0, 0, 0, 0};
-    }
+    for (int t = 0; t < RT; ++t) acc[t] = f4{0, 0, 0, 0};
     auto compute = [&](const Stage& b) {
         if constexpr (POST) {
             h8 wj[2][RT];
             const _Float16 one = (_Float16)1.0f;
             const h8 ones = {one, one, one, one, one, one, one, one};
             const f4 zero4 = {0, 0, 0, 0};
-            f4 d[RT][MT], xs[MT];
+            f4 d[RT], xs;
 #pragma unroll
             for (int t = 0; t < RT; ++t) wj[0][t] = unpack_subnormal_step<V>(b.w[t], 0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 // one scheduling group per tile: its matrix instructions of step j and the unpacking of the same tile
                 // for step j + 1, so that the vector work sits between matrix instructions, not in front of them
-#pragma unroll
-                for (int m = 0; m < MT; ++m) {
-                    if constexpr (SCHEME == SCH_ASYM) xs[m] = mfma16(b.a[m][j], ones, j == 0 ? zero4 : xs[m]);
-                    else                               xsum[m] = mfma16(b.a[m][j], ones, xsum[m]);
-                }
+                if constexpr (SCHEME == SCH_ASYM) xs = mfma16(b.a[j], ones, j == 0 ? zero4 : xs);
+                else                               xsum = mfma16(b.a[j], ones, xsum);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int t = 0; t < RT; ++t) {
                     if (j < 3) wj[(j + 1) & 1][t] = unpack_subnormal_step<V>(b.w[t], j + 1);
-#pragma unroll
-                    for (int m = 0; m < MT; ++m) {
-                        if constexpr (SCHEME == SCH_ASYM) d[t][m] = mfma16(b.a[m][j], wj[j & 1][t], j == 0 ? zero4 : d[t][m]);
-                        else                               acc[t][m] = mfma16(b.a[m][j], wj[j & 1][t], acc[t][m]);
-                    }
+                    if constexpr (SCHEME == SCH_ASYM) d[t] = mfma16(b.a[j], wj[j & 1][t], j == 0 ? zero4 : d[t]);
+                    else                               acc[t] = mfma16(b.a[j], wj[j & 1][t], acc[t]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -1003,18 +989,14 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
                     const float sf = (float)__builtin_bit_cast(_Float16, sh) * 16777216.0f;     // scale * 2^24
                     const float zf = (float)__builtin_bit_cast(_Float16, zh);
 #pragma unroll
-                    for (int m = 0; m < MT; ++m)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[t][m][v] = __builtin_fmaf(sf, d[t][m][v], __builtin_fmaf(zf, xs[m][v], acc[t][m][v]));
+                    for (int v = 0; v < 4; ++v) acc[t][v] = __builtin_fmaf(sf, d[t][v], __builtin_fmaf(zf, xs[v], acc[t][v]));
                 }
             }
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int t = 0; t < RT; ++t)
-#pragma unroll
-                    for (int m = 0; m < MT; ++m) acc[t][m] = mfma16(b.a[m][j], __builtin_bit_cast(h8, b.w[t].q[j]), acc[t][m]);
+                for (int t = 0; t < RT; ++t) acc[t] = mfma16(b.a[j], __builtin_bit_cast(h8, b.w[t].q[j]), acc[t]);
         }
     };
 
@@ -1037,34 +1019,29 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) mine[(4 * (t * MT + m) + v) * 64 + lane] = acc[t][m][v];
+        for (int v = 0; v < 4; ++v) mine[(4 * t + v) * 64 + lane] = acc[t][v];
     if constexpr (SCHEME == SCH_SYM) {
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) mine[(4 * (RT * MT + m) + v) * 64 + lane] = xsum[m][v];
+        for (int v = 0; v < 4; ++v) mine[(4 * RT + v) * 64 + lane] = xsum[v];
     }
     __syncthreads();
     constexpr int ROWS = 16 * RT;
-    for (int idx = tid; idx < 16 * MT * ROWS; idx += 64 * WAVES) {
+    for (int idx = tid; idx < 16 * ROWS; idx += 64 * WAVES) {
         const int tok = idx / ROWS, rl = idx % ROWS;
         if (tok >= M) continue;
-        const int m = tok >> 4, tl = tok & 15;
-        const int rr = rl / RT, t = rl % RT, v = tl & 3, ln = 16 * (tl >> 2) + rr;
+        const int rr = rl / RT, t = rl % RT, v = tok & 3, ln = 16 * (tok >> 2) + rr;
         float sum = 0.0f, xs = 0.0f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) sum += red[((size_t)w * NV + 4 * (t * MT + m) + v) * 64 + ln];
+        for (int w = 0; w < WAVES; ++w) sum += red[((size_t)w * NV + 4 * t + v) * 64 + ln];
         const long row = ((g0 + t) >> 2) * 64 + 4 * rr + ((g0 + t) & 3);
         if constexpr (SCHEME == SCH_SYM) {
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) xs += red[((size_t)w * NV + 4 * (RT * MT + m) + v) * 64 + ln];
+            for (int w = 0; w < WAVES; ++w) xs += red[((size_t)w * NV + 4 * RT + v) * 64 + ln];
             sum = (sum * 16777216.0f - 128.0f * xs) * (float)__builtin_bit_cast(_Float16, L.scales[row]);   // undo 2^-24 and the +128 offset
         }
         const size_t o = (size_t)tok * L.N + row;
         if (splits > 1) {
-            partial[((size_t)split * 16 * MT) * L.N + o] = sum;
+            partial[(size_t)split * M * L.N + o] = sum;
             continue;
         }
         if (L.bias) sum += (float)__builtin_bit_cast(_Float16, L.bias[row]);
@@ -1074,13 +1051,12 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
     }
 }
 
-// One token tile (up to 16 token rows): two workgroups of four waves per compute unit.  Two token tiles (17-32
-// rows) double the activations of a stage, and five tiles of W fill the 256 registers of that occupancy: those
-// kernels take up to 512 registers per lane and one four-wave workgroup per unit.
-template <int WAVES, int TILES, int MT>
-__global__ __launch_bounds__(64 * WAVES, (MT == 2 || TILES == 5) ? 1 : 8 / WAVES) void decode_rows_kernel(const DecodeArgs a)
+// Two workgroups of four waves per compute unit; five tiles of W fill the 256 registers of that occupancy: that
+// kernel takes up to 512 registers per lane and one four-wave workgroup per unit.
+template <int WAVES, int TILES>
+__global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode_rows_kernel(const DecodeArgs a)
 {
-    __shared__ float red[WAVES * (TILES * MT + MT) * 4 * 64];
+    __shared__ float red[WAVES * (TILES + 1) * 4 * 64];
     const int b = blockIdx.x;
     int li = 0, hi = a.n_lin - 1;                    // last linear whose first workgroup is <= b
     while (li < hi) {
@@ -1094,21 +1070,274 @@ __global__ __launch_bounds__(64 * WAVES, (MT == 2 || TILES == 5) ? 1 : 8 / WAVES
     const int split = (int)(wg / row_blocks);
     float* partial = a.partial + L.step_weight;
     switch (L.variant) {
-    case V_W3: run_rows<V_W3, WAVES, TILES, MT>(L, a.M, rb, split, partial, red); break;
-    case V_W4: run_rows<V_W4, WAVES, TILES, MT>(L, a.M, rb, split, partial, red); break;
-    case V_W8: run_rows<V_W8, WAVES, TILES, MT>(L, a.M, rb, split, partial, red); break;
-    case V_I8: run_rows<V_I8, WAVES, TILES, MT>(L, a.M, rb, split, partial, red); break;
-    default:   run_rows<V_F16, WAVES, TILES, MT>(L, a.M, rb, split, partial, red); break;
+    case V_W3: run_rows<V_W3, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
+    case V_W4: run_rows<V_W4, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
+    case V_W8: run_rows<V_W8, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
+    case V_I8: run_rows<V_I8, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
+    default:   run_rows<V_F16, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
     }
 }
 
-// Second kernel of a K-split linear of a small launch: adds the splits in order, then bias, activation,
-// residual and the one rounding; four consecutive rows of one token per thread.
-__global__ __launch_bounds__(256) void decode_rows_reduce_kernel(const DecodeArgs a, int li)
+// ---- small launches of 17 to 64 token rows (MT = 2 .. 4 token tiles of 16) -------------------------------------
+// Bound by the vector and matrix work of a step (unpacking, two FMAs per output for scale and zero, 20 MT matrix
+// instructions: some 1400 cycles at MT = 2, 2400 at MT = 4), not by the 3-4 KB it streams.  What counts is that every SIMD
+// has two waves at work, that they all have the same share, and that the codes are unpacked once for all token rows.
+// A workgroup of eight waves takes RB 64-row blocks of W over a range of K, wave w block w % RB; the KW = 8 / RB waves of
+// a block take C steps each of the KW * C that an iteration holds.  The activations of the next iteration go to LDS meanwhile
+// (global-to-LDS loads, two buffers, 16-byte chunks XOR-swizzled by token); a wave's packed weights are two
+// register stages that are refilled as soon as they are used up.  The KW sums of an output meet in LDS at the end.  The host
+// picks RB and splits K over workgroups so that these just fill the chip (mid_plan in lpq_api.cpp): RB = 4 reads the activations
+// least, RB = 1 needs no split (and no reduce kernel) where W has about as many row blocks as the chip has compute units.
+// Before, two token tiles per wave in the kernel above, and two passes of it from 33 rows on.  One linear, 3 bit, us before and
+// now: 7168 -> 21504 at 32 rows 50 / 31, at 43 rows 75 / 35, at 64 rows 97 / 43; 5120 -> 5120 at 43 rows 28 / 18.
+template <int MT, int RB> struct MidCfg {
+    enum { KW = 8 / RB, C = MT == 1 ? 2 : MT == 2 ? (RB == 1 ? 1 : 2) : (RB == 4 ? 2 : 1), SLOTS = KW * C };     // SLOTS * MT <= 16: 128 KB of LDS
+    static constexpr size_t SMEM = (size_t)2 * SLOTS * 16 * MT * 256;
+};
+
+template <int V, int MT, int RB>
+__device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int split, float* __restrict__ partial, uint8_t* __restrict__ smem)
 {
+    constexpr int SCHEME = VInfo<V>::SCHEME, TILE = VInfo<V>::TILE_BYTES, LANE_BYTES = V == V_W3 ? 12 : 16;
+    constexpr int LOADS = 4 * (TILE >= 1024 ? TILE / 1024 : 1) + (SCHEME == SCH_ASYM ? 2 : 0);       // vector-memory loads of a stage
+    // Tiles whose group products are held at a time: all four where the registers allow it, else two, and the activations
+    // are read from LDS twice.
+    constexpr int TG = MT <= 2 ? 4 : 2;
+    constexpr int KW = MidCfg<MT, RB>::KW, C = MidCfg<MT, RB>::C, SLOTS = MidCfg<MT, RB>::SLOTS;
+    constexpr int FILL = SLOTS * MT / 2 < 1 ? 1 : SLOTS * MT / 2;               // 1 KB loads per wave and iteration of activations
+    constexpr int SLOT = 16 * MT * 128;                // halves of one step's activations
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kw = wave / RB, rw = wave % RB;
+    const int r = lane & 15, kq = lane >> 4;
+    const int KT = L.kt, K = L.K(), NB = L.N / 64;
+    const int rb = sb * RB + rw, rbc = min(rb, NB - 1);       // a wave past the end of W stages activations and stores nothing
+    const int splits = L.aux, share = KT / splits, extra = KT % splits;
+    const int kt0 = split * share + min(split, extra), kt1 = kt0 + share + (split < extra ? 1 : 0);
+    const int n_it = (kt1 - kt0 + SLOTS - 1) / SLOTS;
+    uint16_t* const xbuf = reinterpret_cast<uint16_t*>(smem);             // [2][SLOTS][16 MT tokens][128]
+
+    // token rows past M repeat the last one, steps past the range its last one: neither reaches an output
+    auto fill = [&](int it, int buf) {
+#pragma unroll
+        for (int q = 0; q < FILL; ++q) {
+            const int id = wave * FILL + q, slot = id / (4 * MT), row0 = 4 * (id % (4 * MT));
+            const int tok = row0 + (lane >> 4), ch = (lane & 15) ^ (tok & 15);
+            uint32_t off = ((uint32_t)min(tok, M - 1) * (uint32_t)K + 8u * (uint32_t)ch) * 2u;
+            asm volatile("" : "+v"(off));              // widened next to the load: scalar base, 32-bit lane offset
+            const uint8_t* base = reinterpret_cast<const uint8_t*>(L.x + (size_t)128 * min(kt0 + it * SLOTS + slot, kt1 - 1));
+            __builtin_amdgcn_global_load_lds((gptr_t)(base + off), (lptr_t)(xbuf + (buf * SLOTS + slot) * SLOT + row0 * 128), 16, 0, 0);
+        }
+    };
+    struct Stage {
+        WRaw<V> w[4];
+        u32x2 s, z;                                    // fp16 scale / zero of the lane's rows 4 r .. 4 r + 3
+    };
+    Stage st[2];
+    uint32_t woff = (uint32_t)(LANE_BYTES * lane), soff = (uint32_t)(8 * r);
+    auto step_of = [&](int it, int c) { return kt0 + it * SLOTS + C * kw + c; };
+    auto issue = [&](Stage& b, int kt) {
+        const uint8_t* base = L.codes + ((size_t)rbc * KT + min(kt, kt1 - 1)) * (4 * (size_t)TILE);
+        asm volatile("" : "+v"(woff));
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b.w[t] = load_tile_at<V>(base + woff + t * TILE);
+        if constexpr (SCHEME == SCH_ASYM) {
+            const size_t row0 = ((size_t)min(kt, kt1 - 1) * L.N + (size_t)rbc * 64) * 2;
+            asm volatile("" : "+v"(soff));
+            b.s = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(L.scales) + row0 + soff);
+            b.z = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(L.zeros) + row0 + soff);
+        }
+    };
+    f4 acc[4][MT], xsum[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        xsum[m] = f4{0, 0, 0, 0};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t][m] = f4{0, 0, 0, 0};
+    }
+    auto compute = [&](const Stage& b, const uint16_t* xs) {
+        const _Float16 one = (_Float16)1.0f;
+        const h8 ones = {one, one, one, one, one, one, one, one};
+        const f4 zero4 = {0, 0, 0, 0};
+        h8 xa[2][MT];
+        auto read_x = [&](h8 (&o)[MT], int j) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m) o[m] = *reinterpret_cast<const h8*>(xs + (16 * m + r) * 128 + 8 * ((4 * j + kq) ^ r));
+        };
+        f4 xg[MT];                                     // grouped scheme: the step's sums of x
+        read_x(xa[0], 0);
+#pragma unroll
+        for (int hf = 0; hf < 4 / TG; ++hf) {          // tiles TG hf .. TG hf + TG - 1
+            f4 d[TG][MT];
+            h8 wj[2][TG];
+#pragma unroll
+            for (int t = 0; t < TG; ++t) wj[0][t] = unpack_subnormal_step<V>(b.w[TG * hf + t], 0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0), ahead of the next reads: with global-to-LDS loads under way
+                                                       // the compiler would wait for those too
+                if (j < 3) read_x(xa[(j + 1) & 1], j + 1);
+                else if (hf + 1 < 4 / TG) read_x(xa[0], 0);
+                if (hf == 0) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        if constexpr (SCHEME == SCH_ASYM) xg[m] = mfma16(xa[j & 1][m], ones, j == 0 ? zero4 : xg[m]);
+                        if constexpr (SCHEME == SCH_SYM)  xsum[m] = mfma16(xa[j & 1][m], ones, xsum[m]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                // one scheduling group per tile: its matrix instructions and the unpacking of the same tile for step j + 1
+#pragma unroll
+                for (int t = 0; t < TG; ++t) {
+                    if (j < 3) wj[(j + 1) & 1][t] = unpack_subnormal_step<V>(b.w[TG * hf + t], j + 1);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        if constexpr (SCHEME == SCH_ASYM) d[t][m] = mfma16(xa[j & 1][m], wj[j & 1][t], j == 0 ? zero4 : d[t][m]);
+                        else                              acc[TG * hf + t][m] = mfma16(xa[j & 1][m], wj[j & 1][t], acc[TG * hf + t][m]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if constexpr (SCHEME == SCH_ASYM) {
+#pragma unroll
+                for (int t = 0; t < TG; ++t) {
+                    const int tile = TG * hf + t;
+                    const uint32_t sp = b.s[tile >> 1], zp = b.z[tile >> 1];
+                    const uint16_t sh = (uint16_t)((tile & 1) ? (sp >> 16) : (sp & 0xffffu)), zh = (uint16_t)((tile & 1) ? (zp >> 16) : (zp & 0xffffu));
+                    const float sf = (float)__builtin_bit_cast(_Float16, sh) * 16777216.0f;     // scale * 2^24
+                    const float zf = (float)__builtin_bit_cast(_Float16, zh);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            acc[tile][m][v] = __builtin_fmaf(sf, d[t][m][v], __builtin_fmaf(zf, xg[m][v], acc[tile][m][v]));
+                }
+            }
+        }
+    };
+
+    // One iteration: C steps from stages FIRST .., each refilled with the step two stages on.
+    auto iteration = [&](int it, auto first) {
+        constexpr int FIRST = decltype(first)::value;
+        wait_vmem_all_but<C * LOADS>();                // the activations of this iteration; the refills behind them stay under way
+        __syncthreads();                               // everybody's; the other buffer is no longer read
+        fill(it + 1, (it + 1) & 1);                    // past the last iteration: repeats a step that nobody reads
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (step_of(it, c) < kt1) compute(st[FIRST + c], xbuf + ((it & 1) * SLOTS + C * kw + c) * SLOT);
+            issue(st[FIRST + c], step_of(it + 2 / C, c));
+        }
+    };
+    fill(0, 0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) issue(st[i], step_of(i / C, i % C));
+    if constexpr (C == 2) {
+        for (int it = 0; it < n_it; ++it) iteration(it, std::integral_constant<int, 0>());
+    } else {
+        for (int it = 0; it < n_it; it += 2) {
+            iteration(it, std::integral_constant<int, 0>());
+            if (it + 1 >= n_it) break;
+            iteration(it + 1, std::integral_constant<int, 1>());
+        }
+    }
+
+    // The KW waves of a row block: an item is (token tile m, v), i.e. the lane's four rows of token 16 m + 4 kq + v; wave kw
+    // finishes items kw * OWN .. + OWN - 1 and hands the others over.
+    wait_vmem_all_but<0>();                            // the last fill: the buffer is overwritten
+    __syncthreads();
+    constexpr int OWN = 4 * MT < KW ? 1 : 4 * MT / KW, OTHERS = 4 * MT < KW ? 4 * MT : 4 * MT - OWN, FL = SCHEME == SCH_SYM ? 5 : 4;         // floats of an item: four rows, and the sum of x
+    static_assert((size_t)8 * OTHERS * FL * 256 <= MidCfg<MT, RB>::SMEM, "the hand-over fits the activations' buffers");
+    float* const red = reinterpret_cast<float*>(smem);
+    auto slot = [&](int k, int item, int i) -> float& {                      // what wave k of this row block hands over
+        const int at = item < k * OWN ? item : item - OWN;
+        return red[((size_t)((k * RB + rw) * OTHERS + at) * FL + i) * 64 + lane];
+    };
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int item = 4 * m + v;
+            if (item / OWN == kw) continue;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) slot(kw, item, t) = acc[t][m][v];
+            if constexpr (SCHEME == SCH_SYM) slot(kw, item, 4) = xsum[m][v];
+        }
+    __syncthreads();
+    if (rb >= NB) return;
+    const size_t row = (size_t)rb * 64 + 4 * r;        // the lane's four rows (one per tile)
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    h4 sc = {0, 0, 0, 0}, bs = {0, 0, 0, 0};
+    if constexpr (SCHEME == SCH_SYM) sc = *reinterpret_cast<const h4*>(L.scales + row);
+    if (L.bias) bs = *reinterpret_cast<const h4*>(L.bias + row);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int item = 4 * m + v, tok = 16 * m + 4 * kq + v;
+            if (item / OWN != kw) continue;
+            f4 o;
+            float xt = SCHEME == SCH_SYM ? xsum[m][v] : 0.0f;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) o[t] = acc[t][m][v];
+#pragma unroll
+            for (int k = 1; k < KW; ++k) {
+                const int other = (kw + k) % KW;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[t] += slot(other, item, t);
+                if constexpr (SCHEME == SCH_SYM) xt += slot(other, item, 4);
+            }
+            if constexpr (SCHEME == SCH_SYM)           // undo 2^-24 and the +128 offset
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[t] = (o[t] * 16777216.0f - 128.0f * xt) * (float)sc[t];
+            if (tok >= M) continue;
+            const size_t at = (size_t)tok * L.N + row;
+            if (splits > 1) {
+                *reinterpret_cast<f4*>(partial + (size_t)split * M * L.N + at) = o;
+                continue;
+            }
+            h4 res = {0, 0, 0, 0}, out;
+            if (L.residual) res = *reinterpret_cast<const h4*>(L.residual + at);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float val = apply_activation(L.bias ? o[t] + (float)bs[t] : o[t], L.act);
+                if (L.residual) val += (float)res[t];
+                out[t] = (_Float16)val;
+            }
+            *reinterpret_cast<h4*>(L.y + at) = out;
+        }
+    }
+}
+
+template <int MT, int RB>
+__global__ __launch_bounds__(512, 2) void decode_mid_kernel(const DecodeArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
+    const int b = blockIdx.x;
+    int li = 0, hi = a.n_lin - 1;                      // last linear whose first workgroup is <= b
+    while (li < hi) {
+        const int mid = (li + hi + 1) >> 1;
+        if (a.lin[mid].cum_weight <= (uint64_t)b) li = mid; else hi = mid - 1;
+    }
     const LinDesc& L = a.lin[li];
+    const int wg = b - (int)L.cum_weight, superblocks = mid_superblocks(L, RB);      // split-major: a split's superblocks are neighbours
+    const int sb = wg % superblocks, split = wg / superblocks;
+    float* partial = a.partial + L.step_weight;
+    switch (L.variant) {
+    case V_W3: run_mid<V_W3, MT, RB>(L, a.M, sb, split, partial, smem_raw); break;
+    case V_W4: run_mid<V_W4, MT, RB>(L, a.M, sb, split, partial, smem_raw); break;
+    case V_W8: run_mid<V_W8, MT, RB>(L, a.M, sb, split, partial, smem_raw); break;
+    case V_I8: run_mid<V_I8, MT, RB>(L, a.M, sb, split, partial, smem_raw); break;
+    default:   run_mid<V_F16, MT, RB>(L, a.M, sb, split, partial, smem_raw); break;
+    }
+}
+
+// Second kernel of a small launch with K-split linears (one launch, blockIdx.y the linear): adds the splits in order, then bias, activation,
+// residual and the one rounding; four consecutive rows of one token per thread.
+__global__ __launch_bounds__(256) void decode_rows_reduce_kernel(const DecodeArgs a)
+{
+    const LinDesc& L = a.lin[blockIdx.y];
+    if (L.aux <= 1) return;
     const float* __restrict__ partial = a.partial + L.step_weight;
-    const size_t quads = (size_t)a.M * L.N / 4, plane = (size_t)(a.M <= 16 ? 16 : 32) * L.N;
+    const size_t quads = (size_t)a.M * L.N / 4, plane = (size_t)a.M * L.N;
     for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < quads; q += (size_t)gridDim.x * 256) {
         const size_t e = 4 * q;
         const int n = (int)(e % L.N);
@@ -1201,29 +1430,71 @@ static hipError_t launch_waves(const DecodeArgs& a, hipStream_t s)
     return whole ? launch_tok<16, WAVES, 16>(a, s) : launch_tok<16, WAVES, 8>(a, s);
 }
 
+// adds the K splits of the launch's linears, if any
+static hipError_t launch_rows_reduce(const DecodeArgs& a, hipStream_t s)
+{
+    size_t quads = 0;                                  // of the largest split linear
+    for (int li = 0; li < a.n_lin; ++li)
+        if (a.lin[li].aux > 1) quads = std::max(quads, (size_t)a.M * a.lin[li].N / 4);
+    if (!quads) return hipSuccess;
+    decode_rows_reduce_kernel<<<dim3((unsigned)std::min<size_t>((quads + 255) / 256, 4096), (unsigned)a.n_lin), 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+template <int MT, int RB>
+static hipError_t launch_mid_tiles(const DecodeArgs& a, hipStream_t s)
+{
+    // more LDS than the 64 KB that need no opt-in: raise the kernel's limit once per device
+    static std::once_flag flags[64];
+    static hipError_t results[64];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    std::call_once(flags[dev], [&] {
+        results[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_mid_kernel<MT, RB>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)MidCfg<MT, RB>::SMEM);
+    });
+    if (results[dev] != hipSuccess) return results[dev];
+    decode_mid_kernel<MT, RB><<<(unsigned)a.n_blocks, 512, MidCfg<MT, RB>::SMEM, s>>>(a);
+    e = hipGetLastError();
+    return e == hipSuccess ? launch_rows_reduce(a, s) : e;
+}
+
+hipError_t launch_decode_mid(const DecodeArgs& a, hipStream_t s)
+{
+    const int tiles = (a.M + 15) / 16;
+    switch (10 * tiles + a.row_tiles) {                // token tiles, row blocks per workgroup
+    case 11: return launch_mid_tiles<1, 1>(a, s);
+    case 12: return launch_mid_tiles<1, 2>(a, s);
+    case 14: return launch_mid_tiles<1, 4>(a, s);
+    case 21: return launch_mid_tiles<2, 1>(a, s);
+    case 22: return launch_mid_tiles<2, 2>(a, s);
+    case 24: return launch_mid_tiles<2, 4>(a, s);
+    case 32: return launch_mid_tiles<3, 2>(a, s);
+    case 34: return launch_mid_tiles<3, 4>(a, s);
+    case 42: return launch_mid_tiles<4, 2>(a, s);
+    case 44: return launch_mid_tiles<4, 4>(a, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s)
 {
     const unsigned grid = (unsigned)a.n_blocks;
 #define LPQ_ROWS_CASE(T)                                                                      \
     case T:                                                                                   \
-        if (a.M > 16)          decode_rows_kernel<4, T, 2><<<grid, 256, 0, s>>>(a);           \
-        else if (a.waves == 8) decode_rows_kernel<8, T, 1><<<grid, 512, 0, s>>>(a);           \
-        else                   decode_rows_kernel<4, T, 1><<<grid, 256, 0, s>>>(a);           \
+        if (a.waves == 8) decode_rows_kernel<8, T><<<grid, 512, 0, s>>>(a);                   \
+        else              decode_rows_kernel<4, T><<<grid, 256, 0, s>>>(a);                   \
         break;
-    if (a.M > 32) return hipErrorInvalidValue;
+    if (a.M > 16) return hipErrorInvalidValue;
     switch (a.row_tiles) {
         LPQ_ROWS_CASE(2) LPQ_ROWS_CASE(3) LPQ_ROWS_CASE(4) LPQ_ROWS_CASE(5)
     default: return hipErrorInvalidValue;
     }
 #undef LPQ_ROWS_CASE
-    hipError_t e = hipGetLastError();
-    for (int li = 0; li < a.n_lin && e == hipSuccess; ++li) {
-        if (a.lin[li].aux <= 1) continue;
-        const size_t quads = (size_t)a.M * a.lin[li].N / 4;
-        decode_rows_reduce_kernel<<<(unsigned)std::min<size_t>((quads + 255) / 256, 4096), 256, 0, s>>>(a, li);
-        e = hipGetLastError();
-    }
-    return e;
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_rows_reduce(a, s) : e;
 }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s)

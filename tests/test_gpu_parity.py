@@ -373,3 +373,57 @@ def test_config0_full(orc, phase):
     for name in wl.LINEARS:
         w, x = host[0][name]
         check_output(ys[0][name], orc.qlinear(x, w, bits, scheme), name)
+
+
+@pytest.mark.parametrize("bits,scheme", [(3, 1), (4, 1), (8, 1), (8, 2), (16, 0)], ids=["w3", "w4", "w8", "i8", "f16"])
+@pytest.mark.parametrize("K,N", [(128, 64), (384, 320), (4736, 192), (1152, 1088)])
+def test_decode_17_to_64_rows_edges(orc, bits, scheme, K, N):
+    """The kernel for 17-64 token rows at the edges of its token tiles, with row blocks that do not fill a workgroup, fewer steps of K than
+    an iteration holds, steps that do not fill the last one, ranges of K over several workgroups (reduced by a second kernel) and one,
+    with bias, activation and a residual in place.  Tolerances: the file's."""
+    import torch
+    w = wl.weight_np(N, K, "mid", bits, scheme)
+    r = np.random.default_rng(wl.stream_seed("mid", K, N))
+    bias = (0.1 * r.standard_normal(N)).astype(np.float16)
+    qw = lpq.lpq_quantize_pack(to_dev(w), bits, scheme, bias=to_dev(bias))
+    x = wl.act_np(64, K, True, "mid", K)
+    res = r.standard_normal((64, N)).astype(np.float16)
+    ref = np.maximum(orc.qlinear(x, w, bits, scheme, bias), 0.0) + res.astype(np.float64)
+    for M in (17, 31, 32, 33, 48, 49, 63, 64):
+        y = to_dev(res[:M]).clone()
+        lpq.lpq_qlinear_fused(qw, to_dev(x[:M]), lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU, residual=y, y=y)
+        check_output(y, ref[:M], "decode %d rows, %d bits, %d -> %d" % (M, bits, K, N))
+
+
+@pytest.mark.parametrize("M", [12, 13, 16])
+@pytest.mark.parametrize("bits,scheme", [(3, 1), (8, 2), (16, 0)], ids=["w3", "i8", "f16"])
+def test_decode_13_to_16_rows_without_a_split(orc, bits, scheme, M):
+    """A single wide linear of a short K: from 13 rows on it changes kernels (no split of K needed)."""
+    K, N = 384, 64 * 237
+    w = wl.weight_np(N, K, "mid16", bits)
+    x = wl.act_np(M, K, False, "mid16", M)
+    y = lpq.lpq_qlinear_decode(lpq.lpq_quantize_pack(to_dev(w), bits, scheme), to_dev(x))
+    check_output(y, orc.qlinear(x, w, bits, scheme), "decode %d rows" % M)
+
+
+@pytest.mark.parametrize("M", [20, 40, 60])
+def test_decode_17_to_64_rows_stage_of_unlike_linears(orc, M):
+    """One launch of two layers in two formats whose linears have different K (different numbers of splits), against the even-share kernel's
+    route on the same buffers and the oracle."""
+    import torch
+    h, f = 256, 1536
+    shapes = {"qkv": (h, 3 * h), "out": (h, h), "fc1": (h, f), "fc2": (f, h)}
+    host = [{n: wl.weight_np(N, K, "mid-stage", i, n) for n, (K, N) in shapes.items()} for i in range(2)]
+    layers = [{n: lpq.lpq_quantize_pack(to_dev(w), b, s) for n, w in host[i].items()} for i, (b, s) in enumerate([(3, 1), (8, 2)])]
+    xh = [{n: wl.act_np(M, K, False, "mid-stage", i, n, M) for n, (K, N) in shapes.items()} for i in range(2)]
+    xs = [{n: to_dev(x) for n, x in d.items()} for d in xh]
+    for route in (-1, 0):
+        ys = [{n: torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for n, (K, N) in shapes.items()} for _ in range(2)]
+        lpq.lpq_set_decode_routing(route, 0)
+        try:
+            lpq.lpq_stage_linears(lpq.Stage(layers, xs, ys), lpq.LPQ_DECODE)
+        finally:
+            lpq.lpq_set_decode_routing(-1, -1)
+        for i, (b, s) in enumerate([(3, 1), (8, 2)]):
+            for n in shapes:
+                check_output(ys[i][n], orc.qlinear(xh[i][n], host[i][n], b, s), "stage layer %d %s route %d" % (i, n, route))
