@@ -208,8 +208,8 @@ lpq_status lpq_stage_linears(const lpq_layer *layers, int32_t n_layers, lpq_phas
  * (one copy per device, held until the process ends) instead of the growing workspace, and the call never allocates or
  * frees.  That array covers a decode-phase call of any number of rows (64 MiB of partial tiles per pass of 64 rows; up to
  * 16 rows 16 MiB and, for 3-bit linears, 2 bytes per token row and column of the launch's activations: ten
- * BLOOM-176B-shaped layers at 16 rows take 31 MiB), and a prefill-phase call none of whose launches is
- * split over K (stage-wide launches are not); a call that would need more returns LPQ_ERR_BUFSIZE and launches nothing
+ * BLOOM-176B-shaped layers at 16 rows take 31 MiB), and a prefill-phase call (a launch whose K splits' partial sums do
+ * not fit runs without the splits); a call that would need more returns LPQ_ERR_BUFSIZE and launches nothing
  * further.  All calls on a device share the array, which keeps the last call's contents (nothing in it has to
  * start at zero: every partial tile read was written by the same call); calls that overlap on one device race.
  * Errors: as lpq_stage_linears, plus BUFSIZE as above. */
@@ -364,7 +364,8 @@ lpq_status lpq_workspace_policy(size_t have_bytes, int32_t reserved, size_t need
 
 /* Make the current device's workspace at least `bytes` large now (one allocation, unless it already is) and forbid
  * later growth on this device: from here on no call allocates, and a call that would need more returns
- * LPQ_ERR_BUFSIZE.  For callers that capture graphs or must not allocate while serving.  Errors: DEVICE, BUFSIZE. */
+ * LPQ_ERR_BUFSIZE (prefill launches and decode attention, which need workspace only to split their work further, run
+ * unsplit instead).  For callers that capture graphs or must not allocate while serving.  Errors: DEVICE, BUFSIZE. */
 lpq_status lpq_workspace_reserve(size_t bytes);
 
 /* Bytes of the current device's workspace block (0 before first use). */

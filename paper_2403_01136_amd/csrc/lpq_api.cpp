@@ -480,28 +480,33 @@ int prefill_token_groups(int m_blocks, int n_blocks)
     return best;
 }
 
-// K splits of one prefill linear that is launched with too few tiles to fill the chip (a single linear of a
-// decoder layer at a small micro-batch; a K = 4h linear whose tiles are four times as long as its launch's
-// others).  Estimated time of s splits, in units of one 128-column step of a tile: rounds of workgroups over
-// the compute units times steps per workgroup, plus writing and re-reading s fp32 copies of the output
-// (8 bytes per element and split; measured ~10 TB/s, most of it served by the caches, against ~4.1 us per
-// step) and the second kernel's launch.  Fitted to sweeps of the split count over OPT-13B's four shapes at
-// 256-4096 tokens: the choice is the best measured one or within a few per cent of it.
-int prefill_k_splits(int tiles, int KT, int32_t M, int32_t N, int cus)
+// K splits of one prefill linear that is launched with too few tiles to fill the chip (a single linear of a decoder layer at a
+// small micro-batch): *whole tiles are computed as they are -- full rounds of the compute units, if the launch has this
+// linear only --, the rest in *splits ranges of K.  Estimated time in units of one 128-column step of a tile (about 4.1 us):
+// rounds of workgroups times steps per workgroup, a round that is not full at 0.85 + 0.15 of its share (the chip is
+// power-limited: fewer busy units run faster), plus the fp32 partial sums written and read (8 bytes per element and split,
+// 8 TB/s, most of it served by the caches) and the second kernel's launch.  4 bit, us before (all tiles split alike, an XCD's share
+// a rectangle of tiles, so shares up to a fifth out of balance) and now: 5120 -> 15360 at 1191 rows 280 / 209, 20480 -> 5120 at 1191
+// 320 / 250 and at 700 244 / 150, 5120 -> 5120 at 700 86 / 56, 7168 -> 21504 at 200 129 / 86.
+void prefill_k_splits(int variant, int tiles, int KT, int32_t M, int32_t N, int cus, bool alone, int* whole, int* splits)
 {
-    if (tiles >= 2 * cus) return 1;
-    static const int cand[7] = {1, 2, 3, 4, 5, 6, 8};
-    int best = 1;
-    double best_cost = 1e30;
-    for (int i = 0; i < 7; ++i) {
-        const int s = cand[i];
-        if (s > 1 && KT / s < 8) break;                                    // keep the pipeline's fill and drain small
-        const double rounds = (double)(((long)tiles * s + cus - 1) / cus);
-        double cost = rounds * (double)((KT + s - 1) / s);
-        if (s > 1) cost += 8.0 * s * (double)M * (double)N / 1.0e13 / 4.1e-6 + 1.0;
-        if (cost < best_cost * 0.97) best_cost = cost, best = s;          // a split must pay clearly
-    }
-    return best;
+    *whole = 0;
+    *splits = 1;
+    if (tiles >= 2 * cus) return;
+    auto rounds = [&](double units) {
+        const double full = std::floor(units / cus), part = units / cus - full;
+        return full + (part > 0.0 ? 0.85 + 0.15 * part : 0.0);
+    };
+    // a split must pay clearly in the eight-wave kernel (160 tiles of 40 steps: 3 and 4 bit 4 % faster split, 8 bit and fp16 slower)
+    double best = rounds(tiles) * KT * (variant <= 1 ? 1.0 : 0.97);
+    const double tile_elements = (double)M * N / tiles;
+    for (int w = 0; w < tiles && (w == 0 || alone); w += cus)
+        for (int s = 2; s <= 8 && KT / s >= 8; ++s) {                      // keep the pipeline's fill and drain small
+            const int rest = tiles - w;
+            const double cost = (double)(w / cus) * KT + rounds((double)rest * s) * ((KT + s - 1) / s) + 1.5 +
+                                8.0 * s * tile_elements * rest / 8.0e12 / 4.1e-6;
+            if (cost < best) best = cost, *whole = w, *splits = s;
+        }
 }
 
 // Prefill-phase dispatch of a list of independent linears: one grouped launch per storage variant
@@ -519,47 +524,62 @@ lpq_status run_prefill_rows(const std::vector<LinearCall>& calls, int32_t M, int
         std::stable_sort(mine.begin(), mine.end(), [](const LinearCall* a, const LinearCall* b) { return a->w->d.K > b->w->d.K; });
         for (size_t first = 0; first < mine.size(); first += MAX_PREFILL_LIN) {
             PrefillArgs a;
-            a.M = M;
-            a.n_lin = 0;
-            a.tokens_per_tile = BM;
-            long tiles = 0, launch_tiles = 0;
-            size_t partial_floats = 0;
-            for (size_t i = first; i < std::min(mine.size(), first + (size_t)MAX_PREFILL_LIN); ++i)
-                launch_tiles += (long)m_blocks * ((mine[i]->w->d.N + 255) / 256);
-            for (size_t i = first; i < std::min(mine.size(), first + (size_t)MAX_PREFILL_LIN); ++i) {
-                const lpq_qweight& w = *mine[i]->w;
-                PrefillLin& L = a.lin[a.n_lin++];
-                L.codes = static_cast<const uint8_t*>(w.codes);
-                L.scales = static_cast<const uint16_t*>(w.scales);
-                L.zeros = static_cast<const uint16_t*>(w.zeros);
-                L.x = static_cast<const uint16_t*>(mine[i]->x);
-                L.y = static_cast<uint16_t*>(mine[i]->y);
-                L.bias = static_cast<const uint16_t*>(w.bias);
-                L.residual = static_cast<const uint16_t*>(mine[i]->residual);
-                L.act = mine[i]->act;
-                L.K = w.d.K;
-                L.N = w.d.N;
-                L.n_blocks = (w.d.N + 255) / 256;
-                L.token_groups = prefill_token_groups(m_blocks, L.n_blocks);
-                L.tile_begin = (int32_t)tiles;
-                L.pad = 0;
-                // splitting is judged per launch: a launch with many tiles fills the chip whatever its linears' shapes
-                L.k_splits = launch_tiles >= 2L * cus ? 1 : prefill_k_splits((int)launch_tiles, w.d.K / 128, M, w.d.N, cus);
-                L.partial = nullptr;
-                if (L.k_splits > 1) partial_floats += (size_t)L.k_splits * M * w.d.N;
-                tiles += 8L * L.k_splits * prefill_xcd_tiles(m_blocks, L.n_blocks, L.token_groups);
-            }
-            if (tiles > 0x7fffffffL) return LPQ_ERR_UNSUPPORTED;
-            a.total_tiles = (int32_t)tiles;
-            if (partial_floats) {
-                float* ws = nullptr;
-                lpq_status st = workspace(static_ws, partial_floats * sizeof(float), &ws);
+            float* ws = nullptr;
+            // a second time, without K splits, if there is no room for the splits' sums (a reservation, the static scratch array)
+            for (bool split : {true, false}) {
+                a.M = M;
+                a.n_lin = 0;
+                a.tokens_per_tile = BM;
+                long tiles = 0, launch_tiles = 0;
+                size_t partial_floats = 0;
+                for (size_t i = first; i < std::min(mine.size(), first + (size_t)MAX_PREFILL_LIN); ++i)
+                    launch_tiles += (long)m_blocks * ((mine[i]->w->d.N + 255) / 256);
+                for (size_t i = first; i < std::min(mine.size(), first + (size_t)MAX_PREFILL_LIN); ++i) {
+                    const lpq_qweight& w = *mine[i]->w;
+                    PrefillLin& L = a.lin[a.n_lin++];
+                    L.codes = static_cast<const uint8_t*>(w.codes);
+                    L.scales = static_cast<const uint16_t*>(w.scales);
+                    L.zeros = static_cast<const uint16_t*>(w.zeros);
+                    L.x = static_cast<const uint16_t*>(mine[i]->x);
+                    L.y = static_cast<uint16_t*>(mine[i]->y);
+                    L.bias = static_cast<const uint16_t*>(w.bias);
+                    L.residual = static_cast<const uint16_t*>(mine[i]->residual);
+                    L.act = mine[i]->act;
+                    L.K = w.d.K;
+                    L.N = w.d.N;
+                    L.n_blocks = (w.d.N + 255) / 256;
+                    L.token_groups = prefill_token_groups(m_blocks, L.n_blocks);
+                    L.tile_begin = (int32_t)tiles;
+                    // splitting is judged per launch: a launch with many tiles fills the chip whatever its linears' shapes
+                    L.whole_tiles = 0;
+                    L.k_splits = 1;
+                    if (split && launch_tiles < 2L * cus)
+                        prefill_k_splits(variant, (int)launch_tiles, w.d.K / 128, M, w.d.N, cus, mine.size() == 1, &L.whole_tiles, &L.k_splits);
+                    L.partial = nullptr;
+                    if (L.k_splits > 1) {
+                        partial_floats += (size_t)L.k_splits * M * split_cols(L, m_blocks);
+                        long share = 0;                                        // workgroups of the busiest XCD
+                        for (int x = 0; x < 8; ++x) {
+                            const PrefillShare sh = prefill_split_share(L, m_blocks, x);
+                            share = std::max(share, (long)sh.whole + sh.units);
+                        }
+                        tiles += 8L * share;
+                    } else {
+                        tiles += 8L * prefill_xcd_tiles(m_blocks, L.n_blocks, L.token_groups);
+                    }
+                }
+                if (tiles > 0x7fffffffL) return LPQ_ERR_UNSUPPORTED;
+                a.total_tiles = (int32_t)tiles;
+                if (!partial_floats) break;
+                const lpq_status st = workspace(static_ws, partial_floats * sizeof(float), &ws);
+                if (st == LPQ_ERR_BUFSIZE) continue;
                 if (st != LPQ_OK) return st;
                 for (int i = 0; i < a.n_lin; ++i) {
                     if (a.lin[i].k_splits <= 1) continue;
                     a.lin[i].partial = ws;
-                    ws += (size_t)a.lin[i].k_splits * M * a.lin[i].N;
+                    ws += (size_t)a.lin[i].k_splits * M * split_cols(a.lin[i], m_blocks);
                 }
+                break;
             }
             if (launch_prefill(variant, a, stream) != hipSuccess) return LPQ_ERR_DEVICE;
         }
@@ -613,11 +633,12 @@ lpq_status run_attention(const void* qkv, const lpq_layer_cfg* cfg, const lpq_la
     const size_t floats = attention_decode_workspace_floats(n_seqs, cfg->n_heads, cfg->head_dim, splits);
     float* part = nullptr;
     if (floats) {
-        lpq_status s = workspace(false, floats * sizeof(float), &part);
-        if (s != LPQ_OK) return s;
+        const lpq_status s = workspace(false, floats * sizeof(float), &part);
+        if (s == LPQ_ERR_BUFSIZE) range = (n + 63) / 64 * 64, splits = 1;      // no room for the splits' results: one split needs none
+        else if (s != LPQ_OK) return s;
     }
     return launch_attention_decode(qkv, st->k_cache, st->vt_cache, st->alibi_slopes, n_seqs, n, fresh, cfg->n_heads, cfg->head_dim, cfg->max_seq,
-                                   out, part, stream) == hipSuccess ? LPQ_OK : LPQ_ERR_DEVICE;
+                                   range, splits, out, part, stream) == hipSuccess ? LPQ_OK : LPQ_ERR_DEVICE;
 }
 
 }  // namespace
@@ -772,7 +793,7 @@ lpq_status lpq_variance_indicator(const void* w_fp16, int32_t K, int32_t N, cons
     if (K < 128 || K % 128 != 0 || N < 1 || M < 1) return LPQ_ERR_SHAPE;
     if (misaligned(w_fp16) || misaligned(x) || (reinterpret_cast<uintptr_t>(omega) & 7u)) return LPQ_ERR_ALIGN;
     float* ws = nullptr;
-    lpq_status st = workspace(false, indicator_workspace_bytes(), &ws);
+    lpq_status st = workspace(false, indicator_workspace_bytes(K, N, M), &ws);
     if (st != LPQ_OK) return st;
     return launch_indicator(w_fp16, K, N, x, M, stochastic != 0, omega, ws, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                ? LPQ_OK : LPQ_ERR_DEVICE;

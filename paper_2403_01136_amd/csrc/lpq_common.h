@@ -77,13 +77,51 @@ struct PrefillLin {
     int32_t token_groups;   // 1, 2, 4 or 8
     int32_t act;            // lpq_activation applied to acc + bias (before the residual)
     const uint16_t* residual;   // fp16 [M][N] added to the output before its one rounding, or null
-    // K split: with k_splits > 1 every tile is computed k_splits times over consecutive ranges of the
-    // 128-column steps, each workgroup leaving its fp32 sums in partial[split][M][N]; a second kernel adds
-    // the splits in order and applies bias, activation, residual and the one rounding.  An XCD's list of
-    // tiles is then walked k_splits times (split-major), so the launch has k_splits times the workgroups.
+    // K split, for linears with too few tiles to fill the chip (k_splits > 1): the first whole_tiles tiles are computed as
+    // they are, each of the others k_splits times over consecutive ranges of the 128-column steps, the workgroups leaving
+    // their fp32 sums in partial[split][M][split_cols(L)]; a second kernel adds the splits in order and applies bias,
+    // activation, residual and the one rounding.  Tiles are then numbered token block fastest and the work units (whole tiles; behind
+    // them (tile, split) pairs) are dealt out to the XCDs in eight equal contiguous shares, whatever the
+    // numbers of token and row blocks (prefill_split_unit); token_groups is not used.  With up to two token blocks a tile's splits
+    // are neighbours; with more, a split's tiles are, so that an XCD reads a range of K of the activations only (4-bit
+    // 28672 -> 7168 at 1191 rows 488 us against 526; 2048 -> 8192 at 200 rows 35 against 32).
     float* partial;
-    int32_t k_splits, pad;
+    int32_t k_splits, whole_tiles;
 };
+
+// first row block of W with a split tile, and the columns of y from there on
+__host__ __device__ inline int split_first_block(const PrefillLin& L, int m_blocks) { return L.whole_tiles / m_blocks; }
+__host__ __device__ inline int split_cols(const PrefillLin& L, int m_blocks) { return L.N - 256 * split_first_block(L, m_blocks); }
+
+// Workgroups of XCD x's share: `whole` whole tiles from tile whole0 on, then `units` split units from unit0 on.
+struct PrefillShare { int whole0, whole, unit0, units; };
+__host__ __device__ inline PrefillShare prefill_split_share(const PrefillLin& L, int m_blocks, int x)
+{
+    const int w = L.whole_tiles, u = (m_blocks * L.n_blocks - w) * L.k_splits;
+    PrefillShare s;
+    s.whole0 = (int)((long)w * x / 8);
+    s.whole = (int)((long)w * (x + 1) / 8) - s.whole0;
+    s.unit0 = (int)((long)u * x / 8);
+    s.units = (int)((long)u * (x + 1) / 8) - s.unit0;
+    return s;
+}
+
+// Work unit l of XCD x: its tile, and its split (-1: the whole tile); false past the end of the share.
+__host__ __device__ inline bool prefill_split_unit(const PrefillLin& L, int m_blocks, int x, int l, int* tile_m, int* tile_n, int* split)
+{
+    const PrefillShare s = prefill_split_share(L, m_blocks, x);
+    int tile = s.whole0 + l;
+    *split = -1;
+    if (l >= s.whole) {
+        if (l - s.whole >= s.units) return false;
+        const int u = s.unit0 + l - s.whole, rest = m_blocks * L.n_blocks - L.whole_tiles;
+        if (m_blocks > 2) *split = u / rest, tile = L.whole_tiles + u % rest;
+        else              *split = u % L.k_splits, tile = L.whole_tiles + u / L.k_splits;
+    }
+    *tile_m = tile % m_blocks;
+    *tile_n = tile / m_blocks;
+    return true;
+}
 
 // Token block and row block of tile l of XCD x; false if that XCD has fewer tiles.
 __host__ __device__ inline bool prefill_xcd_tile(int m_blocks, int n_blocks, int token_groups, int x, int l, int* tile_m, int* tile_n)
@@ -141,7 +179,7 @@ hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s);     // small 
 hipError_t launch_decode_mid(const DecodeArgs& a, hipStream_t s);      // small launches, M <= 64: aux = K splits, cum_weight = workgroups before
 hipError_t launch_prefill(int variant, const PrefillArgs& a, hipStream_t s);      // both kernels, if any linear is K-split
 // variance indicator (lpq_indicator.hip)
-size_t indicator_workspace_bytes();
+size_t indicator_workspace_bytes(int K, int N, int M);
 hipError_t launch_indicator(const void* w, int K, int N, const void* x, int M, int stochastic, double* omega, void* ws, hipStream_t s);
 // the rest of the decoder layer (lpq_layer.hip)
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, float eps, int M, int h, void* y, hipStream_t s);
@@ -151,7 +189,7 @@ hipError_t launch_kv_append(const void* qkv, void* kc, void* vtc, int n_seqs, in
 void attention_decode_plan(int n_seqs, int H, int n, int* range, int* splits);
 size_t attention_decode_workspace_floats(int n_seqs, int H, int d, int splits);
 hipError_t launch_attention_decode(const void* qkv, void* kc, void* vtc, const float* slopes, int n_seqs, int n, bool fresh, int H, int d, int S,
-                                   void* out, float* part, hipStream_t s);
+                                   int range, int splits, void* out, float* part, hipStream_t s);
 hipError_t launch_attention_prefill(const void* qkv, const void* kc, const void* vtc, const float* slopes, int n_seqs, int T, int pos0, int H, int d,
                                     int S, void* out, hipStream_t s);
 

@@ -160,15 +160,27 @@ __global__ __launch_bounds__(IND_THREADS) void indicator_finish_kernel(const Ind
 
 }  // namespace
 
-size_t indicator_workspace_bytes() { return 2 * IND_MAX_BLOCKS * sizeof(IndPart); }
+// Workgroups of W: a row per wave up to what the chip holds at once; of X: so that one reads about what a workgroup of W does.
+static void indicator_blocks(int K, int N, int M, int* wb, int* xb)
+{
+    const long n8 = (long)M * K / 8, w8 = (long)N * K / 8;
+    *wb = (int)std::min<long>(IND_MAX_BLOCKS, (N + IND_WAVES - 1) / IND_WAVES);
+    const long per = std::max<long>(IND_THREADS, (w8 + *wb - 1) / *wb);
+    *xb = (int)std::min<long>(IND_MAX_BLOCKS, std::max<long>(1, (n8 + per - 1) / per));
+}
+
+size_t indicator_workspace_bytes(int K, int N, int M)
+{
+    int wb, xb;
+    indicator_blocks(K, N, M, &wb, &xb);
+    return (size_t)(wb + xb) * sizeof(IndPart);
+}
 
 hipError_t launch_indicator(const void* w, int K, int N, const void* x, int M, int stochastic, double* omega, void* ws, hipStream_t s)
 {
-    // workgroups of W: a row per wave up to what the chip holds at once; of X: so that one reads about what a workgroup of W does
-    const long n8 = (long)M * K / 8, w8 = (long)N * K / 8;
-    const int wb = (int)std::min<long>(IND_MAX_BLOCKS, (N + IND_WAVES - 1) / IND_WAVES);
-    const long per = std::max<long>(IND_THREADS, (w8 + wb - 1) / wb);
-    const int xb = (int)std::min<long>(IND_MAX_BLOCKS, std::max<long>(1, (n8 + per - 1) / per));
+    int wb, xb;
+    indicator_blocks(K, N, M, &wb, &xb);
+    const long n8 = (long)M * K / 8;
     IndPart* part = static_cast<IndPart*>(ws);
     indicator_stats_kernel<<<(unsigned)(wb + xb), IND_THREADS, 0, s>>>(static_cast<const uint16_t*>(w), K, N, wb, static_cast<const uint16_t*>(x), n8, part);
     indicator_finish_kernel<<<1, IND_THREADS, 0, s>>>(part, wb, wb + xb, K, N, (double)M * (double)K, stochastic, omega);

@@ -593,12 +593,10 @@ void attention_decode_plan(int n_seqs, int H, int n, int* range, int* splits)
 size_t attention_decode_workspace_floats(int n_seqs, int H, int d, int splits) { return splits > 1 ? (size_t)n_seqs * H * splits * (d + 2) : 0; }
 
 hipError_t launch_attention_decode(const void* qkv, void* kc, void* vtc, const float* slopes, int n_seqs, int n, bool fresh, int H, int d, int S,
-                                   void* out, float* part, hipStream_t s)
+                                   int range, int splits, void* out, float* part, hipStream_t s)
 {
     const uint16_t* q = static_cast<const uint16_t*>(qkv);
     uint16_t *k = static_cast<uint16_t*>(kc), *v = static_cast<uint16_t*>(vtc), *o = static_cast<uint16_t*>(out);
-    int range, splits;
-    attention_decode_plan(n_seqs, H, n, &range, &splits);
     const dim3 grid((unsigned)(n_seqs * H), (unsigned)splits);
 #define LPQ_ATT(D, F) attention_decode_kernel<D, F><<<grid, 256, 0, s>>>(q, k, v, slopes, H, S, n, range, splits, o, part)
     if (d == 128) { if (fresh) LPQ_ATT(128, true); else LPQ_ATT(128, false); }

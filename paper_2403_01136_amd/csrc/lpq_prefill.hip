@@ -66,10 +66,10 @@ void prefill_kernel(const PrefillArgs a)
     // rectangle of token blocks x row blocks so that its L2 fetches those activations and weights once.
     const int tile = (int)blockIdx.x - L.tile_begin;
     const int m_blocks = (M + BM - 1) / BM;
-    const int per_xcd = SPLIT ? prefill_xcd_tiles(m_blocks, L.n_blocks, L.token_groups) : 0x7fffffff;
-    const int split = SPLIT ? (tile >> 3) / per_xcd : 0;         // 0 unless the linear is K-split
-    int tile_m, tile_n;
-    if (!prefill_xcd_tile(m_blocks, L.n_blocks, L.token_groups, tile & 7, SPLIT ? (tile >> 3) % per_xcd : (tile >> 3), &tile_m, &tile_n)) return;
+    int tile_m, tile_n, split = -1;                  // split -1: all of K
+    if (SPLIT && L.k_splits > 1) {
+        if (!prefill_split_unit(L, m_blocks, tile & 7, tile >> 3, &tile_m, &tile_n, &split)) return;
+    } else if (!prefill_xcd_tile(m_blocks, L.n_blocks, L.token_groups, tile & 7, tile >> 3, &tile_m, &tile_n)) return;
     constexpr int SCHEME = VInfo<V>::SCHEME;
     constexpr int NW = 4;                           // 16-row tiles per wave = one 64-row block
     constexpr int MTB = BM / 32;                    // 32-token tiles per block
@@ -84,9 +84,12 @@ void prefill_kernel(const PrefillArgs a)
     const int r = lane & 15;
     const int KT = K / 128;
     // this workgroup's 128-column steps: all of them, or the split's share (the first KT % k_splits splits take one more)
-    const int n_splits = SPLIT ? L.k_splits : 1;
-    const int kt_share = KT / n_splits, kt_extra = KT % n_splits;
-    const int kt_begin = split * kt_share + min(split, kt_extra), kt_end = kt_begin + kt_share + (split < kt_extra ? 1 : 0);
+    int kt_begin = 0, kt_end = KT;
+    if (SPLIT && split >= 0) {
+        const int share = KT / L.k_splits, extra = KT % L.k_splits;
+        kt_begin = split * share + min(split, extra);
+        kt_end = kt_begin + share + (split < extra ? 1 : 0);
+    }
     const long RB = N / 64;                          // 64-row blocks of W
     const int m0 = tile_m * BM;
     const long rb = (long)tile_n * 4 + wave;         // this wave's row block
@@ -324,8 +327,9 @@ void prefill_kernel(const PrefillArgs a)
         if constexpr (SCHEME == SCH_SYM) post[p] = (float)__builtin_bit_cast(_Float16, scales[nbase + p]);
         bs[p] = bias ? (float)__builtin_bit_cast(_Float16, bias[nbase + p]) : 0.0f;
     }
-    if (SPLIT && L.k_splits > 1) {                   // fp32 sums of this split; the reduce kernel finishes them
-        float* part = L.partial + (size_t)split * M * N;
+    if (SPLIT && split >= 0) {                       // fp32 sums of this split; the reduce kernel finishes them
+        const int cols = split_cols(L, m_blocks);
+        float* part = L.partial + (size_t)split * M * cols - 256 * split_first_block(L, m_blocks);
 #pragma unroll
         for (int mt = 0; mt < MTB; ++mt)
 #pragma unroll
@@ -333,7 +337,7 @@ void prefill_kernel(const PrefillArgs a)
                 const int tok = m0 + 32 * mt + 8 * (v / 4) + 4 * thalf + (v % 4);
                 if (tok >= M) continue;
                 const f2 o = {acc[0][mt][v] * post[0], acc[1][mt][v] * post[1]};
-                *reinterpret_cast<f2*>(part + (size_t)tok * N + nbase) = o;
+                *reinterpret_cast<f2*>(part + (size_t)tok * cols + nbase) = o;
             }
         return;
     }
@@ -406,10 +410,10 @@ void prefill_ring_kernel(const PrefillArgs a)
     constexpr int BM = 256;
     const int tile = (int)blockIdx.x - L.tile_begin;
     const int m_blocks = (M + BM - 1) / BM;
-    const int per_xcd = SPLIT ? prefill_xcd_tiles(m_blocks, L.n_blocks, L.token_groups) : 0x7fffffff;
-    const int split = SPLIT ? (tile >> 3) / per_xcd : 0;
-    int tile_m, tile_n;
-    if (!prefill_xcd_tile(m_blocks, L.n_blocks, L.token_groups, tile & 7, SPLIT ? (tile >> 3) % per_xcd : (tile >> 3), &tile_m, &tile_n)) return;
+    int tile_m, tile_n, split = -1;                  // split -1: all of K
+    if (SPLIT && L.k_splits > 1) {
+        if (!prefill_split_unit(L, m_blocks, tile & 7, tile >> 3, &tile_m, &tile_n, &split)) return;
+    } else if (!prefill_xcd_tile(m_blocks, L.n_blocks, L.token_groups, tile & 7, tile >> 3, &tile_m, &tile_n)) return;
     constexpr int SCHEME = VInfo<V>::SCHEME;
     constexpr bool DMA_W = (V == V_F16);             // weights go to LDS as they are
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
@@ -419,9 +423,12 @@ void prefill_ring_kernel(const PrefillArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int KT = K / 128;
-    const int n_splits = SPLIT ? L.k_splits : 1;
-    const int kt_share = KT / n_splits, kt_extra = KT % n_splits;
-    const int kt_begin = split * kt_share + min(split, kt_extra), kt_end = kt_begin + kt_share + (split < kt_extra ? 1 : 0);
+    int kt_begin = 0, kt_end = KT;
+    if (SPLIT && split >= 0) {
+        const int share = KT / L.k_splits, extra = KT % L.k_splits;
+        kt_begin = split * share + min(split, extra);
+        kt_end = kt_begin + share + (split < extra ? 1 : 0);
+    }
     const long RB = N / 64;
     const int m0 = tile_m * BM;
     const long rb = (long)tile_n * 4 + wn;           // the row block this wave multiplies
@@ -651,8 +658,9 @@ void prefill_ring_kernel(const PrefillArgs a)
         if constexpr (SCHEME == SCH_SYM) post[p] = (float)__builtin_bit_cast(_Float16, scales[nbase + p]);
         bs[p] = bias ? (float)__builtin_bit_cast(_Float16, bias[nbase + p]) : 0.0f;
     }
-    if (SPLIT && L.k_splits > 1) {
-        float* part = L.partial + (size_t)split * M * N;
+    if (SPLIT && split >= 0) {
+        const int cols = split_cols(L, m_blocks);
+        float* part = L.partial + (size_t)split * M * cols - 256 * split_first_block(L, m_blocks);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
@@ -660,7 +668,7 @@ void prefill_ring_kernel(const PrefillArgs a)
                 const int tok = m0 + 128 * wm + 32 * mt + 8 * (v / 4) + 4 * thalf + (v % 4);
                 if (tok >= M) continue;
                 const f2 o = {acc[0][mt][v] * post[0], acc[1][mt][v] * post[1]};
-                *reinterpret_cast<f2*>(part + (size_t)tok * N + nbase) = o;
+                *reinterpret_cast<f2*>(part + (size_t)tok * cols + nbase) = o;
             }
         return;
     }
@@ -682,20 +690,25 @@ void prefill_ring_kernel(const PrefillArgs a)
         }
 }
 
-// Second kernel of a K-split linear: y = round(act(sum over splits + bias) + residual), four consecutive
+// Second kernel of a K-split linear: y = round(act(sum over splits + bias) + residual) for its split tiles, four consecutive
 // output rows of one token per thread, splits added in order (deterministic).
 __global__ __launch_bounds__(256) void prefill_reduce_kernel(const PrefillArgs a, int li)
 {
     const PrefillLin& L = a.lin[li];
-    const size_t quads = (size_t)a.M * L.N / 4, plane = (size_t)a.M * L.N;
+    const int m_blocks = (a.M + a.tokens_per_tile - 1) / a.tokens_per_tile;
+    const int first = split_first_block(L, m_blocks), cols = split_cols(L, m_blocks);
+    const int m_split = L.whole_tiles - first * m_blocks;      // in row block `first`, the token blocks before this one are whole
+    const size_t quads = (size_t)a.M * cols / 4, plane = (size_t)a.M * cols;
     for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < quads; q += (size_t)gridDim.x * 256) {
         const size_t e = 4 * q;
-        const int n = (int)(e % L.N);
+        const int tok = (int)(e / cols), c = (int)(e % cols), n = 256 * first + c;
+        if (c < 256 && tok / a.tokens_per_tile < m_split) continue;
         f4 sum = *reinterpret_cast<const f4*>(L.partial + e);
         for (int sp = 1; sp < L.k_splits; ++sp) sum += *reinterpret_cast<const f4*>(L.partial + sp * plane + e);
         typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+        const size_t at = (size_t)tok * L.N + n;
         h4 res = {0, 0, 0, 0}, out;
-        if (L.residual) res = *reinterpret_cast<const h4*>(L.residual + e);
+        if (L.residual) res = *reinterpret_cast<const h4*>(L.residual + at);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             float val = sum[v] + (L.bias ? (float)__builtin_bit_cast(_Float16, L.bias[n + v]) : 0.0f);
@@ -703,7 +716,7 @@ __global__ __launch_bounds__(256) void prefill_reduce_kernel(const PrefillArgs a
             if (L.residual) val += (float)res[v];
             out[v] = (_Float16)val;
         }
-        *reinterpret_cast<h4*>(L.y + e) = out;
+        *reinterpret_cast<h4*>(L.y + at) = out;
     }
 }
 
@@ -759,7 +772,7 @@ hipError_t launch_tiles(const PrefillArgs& a, hipStream_t s)
     e = hipGetLastError();
     for (int li = 0; li < a.n_lin && e == hipSuccess; ++li) {
         if (a.lin[li].k_splits <= 1) continue;
-        const size_t quads = (size_t)a.M * a.lin[li].N / 4;
+        const size_t quads = (size_t)a.M * split_cols(a.lin[li], (a.M + BM - 1) / BM) / 4;
         const unsigned blocks = (unsigned)std::min<size_t>((quads + 255) / 256, 8192);
         prefill_reduce_kernel<<<blocks, 256, 0, s>>>(a, li);
         e = hipGetLastError();

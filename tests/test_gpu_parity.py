@@ -427,3 +427,27 @@ def test_decode_17_to_64_rows_stage_of_unlike_linears(orc, M):
         for i, (b, s) in enumerate([(3, 1), (8, 2)]):
             for n in shapes:
                 check_output(ys[i][n], orc.qlinear(xh[i][n], host[i][n], b, s), "stage layer %d %s route %d" % (i, n, route))
+
+
+@pytest.mark.parametrize("bits,scheme", [(4, 1), (8, 2), (16, 0)], ids=["w4", "i8", "f16"])
+@pytest.mark.parametrize("M,N,K", [(700, 23104, 2048), (1191, 14912, 2048), (40, 71744, 2048), (256, 320, 4224), (300, 1088, 3200)])
+def test_prefill_whole_and_split_tiles(orc, bits, scheme, M, N, K):
+    """Linears with more tiles than the chip has compute units but fewer than twice as many (full rounds of whole tiles, the rest split over
+    K: the border runs through a row block when the token blocks do not divide it), and with fewer (all split), N that is no multiple of
+    256 and ragged token blocks: every output written exactly once.  Every output against an fp32 product of the dequantised weights
+    (both sides round fp32 sums once: the file's tolerance), the rows around the border and the last ones against the oracle."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(N + bits)
+    w = (torch.randn((N, K), generator=gen, device="cuda") * 0.02).half()
+    x = torch.randn((M, K), generator=gen, device="cuda").half()
+    qw = lpq.lpq_quantize_pack(w, bits, scheme)
+    y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    lpq.lpq_qlinear_prefill(qw, x, y)
+    ref = x.float() @ lpq.lpq_unpack_dequant(qw).t()
+    d = (y.float() - ref).double()
+    assert torch.isfinite(y).all()
+    assert float(d.norm() / ref.double().norm()) <= 1e-3 and float(d.abs().max()) <= 1e-2 * float(ref.abs().max())
+    border = 256 * (256 // ((M + 255) // 256)) if M > 128 else 256 * 256
+    rows = sorted({min(max(r, 0), N - 64) // 64 * 64 for r in (0, border - 64, border, border + 256, N - 64)})
+    for r0 in rows:
+        check_output(y[:, r0:r0 + 64], orc.qlinear(x.cpu().numpy(), w[r0:r0 + 64].cpu().numpy(), bits, scheme), "rows %d.. of %d" % (r0, N))
