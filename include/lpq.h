@@ -174,7 +174,8 @@ lpq_status lpq_load_quantize_pack(const void *w_fp16_host, const lpq_qdesc *desc
                                   size_t staging_bytes, void *hip_stream);
 
 /* One quantised linear at a prefill micro-batch (Sec. 4.3: M = eta * s tokens): weight tiles
- * are dequantised in registers to fp16 and multiplied on the matrix cores.
+ * are dequantised in registers to fp16 and multiplied on the matrix cores (up to 64 rows most calls take the decode
+ * kernels, which are faster there).
  *   w: host struct with device buffers;  x: device fp16 [M][K];  y: device fp16 [M][N].
  * Correct for every M >= 1.  Errors: NULL, BITS, SCHEME, SHAPE (M < 1), ALIGN, DEVICE. */
 lpq_status lpq_qlinear_prefill(const lpq_qweight *w, const void *x, int32_t M, void *y, void *hip_stream);

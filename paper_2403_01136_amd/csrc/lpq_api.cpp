@@ -311,6 +311,17 @@ bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, i
     return load <= g_rows_max_mb.load() / 192.0;
 }
 
+// Whether a decode launch goes to the kernels for launches that stream little: up to 16 token rows by the bytes of its codes,
+// 17 to 64 by mid_route.
+bool small_launch(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
+{
+    if (M > 64) return false;
+    if (M > 16) return mid_route(calls, begin, end, M);
+    int64_t stream_bytes = 0;
+    for (size_t c = begin; c < end; ++c) stream_bytes += (int64_t)calls[c].w->d.K * calls[c].w->d.N * calls[c].w->d.bits / 8;
+    return stream_bytes <= (int64_t)g_rows_max_mb.load() << 20;
+}
+
 // Decode-phase dispatch of a list of independent linears: grouped launches of at most
 // MAX_LIN_PER_LAUNCH linears, 64 token rows per pass, each launch one round of equally loaded
 // workgroups (see lpq_decode.hip).
@@ -338,9 +349,15 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
             for (size_t c = c0; c < c1; ++c) b += prepared_bytes(calls[c].w->d, last_rows, in_place);
             sums_bytes = std::max(sums_bytes, b);
         }
+    // the even-share launches' space is asked for ahead of every launch; the others' (K splits, if any) is no more than that
+    bool any_even_share = false;
+    for (size_t li = 0; li < n_launch; ++li)
+        any_even_share = any_even_share || !small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M);
     float* ws = nullptr;
-    st = workspace(static_ws, partial_bytes + sums_bytes, &ws);
-    if (st != LPQ_OK) return st;
+    if (any_even_share) {
+        st = workspace(static_ws, partial_bytes + sums_bytes, &ws);
+        if (st != LPQ_OK) return st;
+    }
     for (size_t li = 0; li < n_launch; ++li) {
         DecodeArgs a;
         a.M = M;
@@ -352,7 +369,7 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         a.row_tiles = 4;
         a.pad = 0;
         a.partial = ws;
-        a.prep = sums_bytes ? reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(ws) + partial_bytes) : nullptr;
+        a.prep = ws && sums_bytes ? reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(ws) + partial_bytes) : nullptr;
         uint64_t total = 0;
         size_t sums_off16 = 0;               // in 16-byte units
         const bool in_place = reads_in_place(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M);
@@ -387,18 +404,13 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         // straight from L2 and streams from deeper rings -- except a single linear of 13 to 16 rows that the former
         // runs without splitting K (at 16 rows, 3 and 4 bit, us: 5120 -> 15360 15.8 against 13.7, 7168 -> 28672 31 / 26, 4096 -> 12288
         // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower).
-        const bool mid_load = M > 16 && M <= 64 && mid_route(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M);
-        const int64_t rows_max_bytes = (int64_t)g_rows_max_mb.load() << 20;
-        int64_t stream_bytes = 0;
-        for (size_t c = li * per_launch; c < std::min(n, (li + 1) * per_launch); ++c)
-            stream_bytes += (int64_t)calls[c].w->d.K * calls[c].w->d.N * calls[c].w->d.bits / 8;
-        if (mid_load || (M <= 16 && stream_bytes <= rows_max_bytes)) {
+        if (small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M)) {
             // longest K first: the last workgroups to start are then the shortest
             std::stable_sort(a.lin, a.lin + a.n_lin, [](const LinDesc& x, const LinDesc& y) { return x.kt > y.kt; });
             int cus = 0;
             st = device_cus(&cus);
             if (st != LPQ_OK) return st;
-            bool mid = mid_load;
+            bool mid = M > 16;
             if (mid || (M > 12 && a.n_lin == 1)) {
                 mid_plan(a, cus, partial_bytes / sizeof(float));
                 mid = mid || a.lin[0].aux == 1;
@@ -587,7 +599,7 @@ lpq_status run_prefill_rows(const std::vector<LinearCall>& calls, int32_t M, int
     return LPQ_OK;
 }
 
-// Tokens per tile.  256 as a rule: weights are fetched and unpacked once per token block.  A call of at most 128 rows
+// Prefill-phase dispatch.  Tokens per tile: 256 as a rule: weights are fetched and unpacked once per token block.  A call of at most 128 rows
 // has one block either way and takes 128-token tiles (half the matrix instructions per step).  A call of 1024 rows
 // or more whose last block of 256 would hold at most 128 rows pays a full tile of matrix instructions for that block
 // (1100 rows cost what 1280 do): there the tail runs as launches of its own with 128-token tiles -- measured on an
@@ -597,6 +609,14 @@ lpq_status run_prefill_rows(const std::vector<LinearCall>& calls, int32_t M, int
 lpq_status run_prefill(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false)
 {
     const int32_t tail = M % 256, body = M - tail;
+    // Up to 64 rows a 128-token tile is at least half empty, and the decode kernels for launches that stream little hold all
+    // rows at once: at 40 rows, 4 bit, 5120 -> 15360 23.5 us against 31.1, 8 bit 7168 -> 21504 38 against 81; at 9 rows 13 against
+    // 27 and 30 against 79.  Beyond the line between those and the even-share kernel, which needs tens of megabytes of workspace,
+    // a single linear of up to 16 rows goes there too.  (What the workspace or the descriptors do not hold stays here.)
+    if (M <= 64 && calls.size() <= MAX_LIN_PER_LAUNCH && (small_launch(calls, 0, calls.size(), M) || (M <= 16 && calls.size() == 1))) {
+        const lpq_status st = run_decode(calls, M, stream, static_ws);
+        if (st != LPQ_ERR_BUFSIZE && st != LPQ_ERR_UNSUPPORTED) return st;
+    }
     if (M <= 128) return run_prefill_rows(calls, M, 128, stream, static_ws);
     if (tail == 0 || tail > 128) return run_prefill_rows(calls, M, 256, stream, static_ws);
     if (M < 1024) return run_prefill_rows(calls, M, 256, stream, static_ws);
