@@ -403,7 +403,8 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         // them: from 17 token rows on the one that shares the activations through LDS; up to 16 the one that reads them
         // straight from L2 and streams from deeper rings -- except a single linear of 13 to 16 rows that the former
         // runs without splitting K (at 16 rows, 3 and 4 bit, us: 5120 -> 15360 15.8 against 13.7, 7168 -> 28672 31 / 26, 4096 -> 12288
-        // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower).
+        // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower, and where five tiles a workgroup fill the
+        // chip in one round the two are level alone but not in a layer: 5120 -> 20480, 4 bit, 18.8 against 20.3).
         if (small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M)) {
             // longest K first: the last workgroups to start are then the shortest
             std::stable_sort(a.lin, a.lin + a.n_lin, [](const LinDesc& x, const LinDesc& y) { return x.kt > y.kt; });
@@ -411,14 +412,14 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
             st = device_cus(&cus);
             if (st != LPQ_OK) return st;
             bool mid = M > 16;
-            if (mid || (M > 12 && a.n_lin == 1)) {
+            int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
+            if (!mid && a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
+            if (mid || (M > 12 && a.n_lin == 1 && tiles != 5)) {
                 mid_plan(a, cus, partial_bytes / sizeof(float));
                 mid = mid || a.lin[0].aux == 1;
             }
             const int forced = g_rows_tiles.load();
-            int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
             if (!mid) {
-                if (a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
                 if (forced >= 2 && forced <= 5 && forced != tiles) tiles = forced, splits1 = 0;
                 for (int i = 0; i < a.n_lin; ++i)
                     if ((a.lin[i].N / 16) % rows_group_tiles(a.lin[i].variant, tiles) != 0) tiles = 4, splits1 = 0;    // groups must tile every linear exactly

@@ -20,9 +20,9 @@
 // (sum over groups of zero * sum of x) once per unit from the activations' group sums, which decode_prepare_kernel
 // computes in front of the launch.
 //
-// A launch that streams little (a single linear of a decoder layer, up to 32 token rows per pass) takes a second
-// kernel, decode_rows_kernel further down: one workgroup per group of 16-row tiles whose waves split K, no LDS
-// staging, no fix-up pass.
+// A launch that streams little (a single linear of a decoder layer) takes other kernels, further down, without a fix-up
+// pass: up to 16 token rows decode_rows_kernel (one workgroup per group of 16-row tiles whose waves split K, no LDS
+// staging), from 17 to 64 decode_mid_kernel (a few row blocks per workgroup, all token rows at once, activations through LDS).
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -1078,7 +1078,7 @@ __global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode
     }
 }
 
-// ---- small launches of 17 to 64 token rows (MT = 2 .. 4 token tiles of 16) -------------------------------------
+// ---- small launches of 17 to 64 token rows (MT = 2 .. 4 token tiles of 16; MT = 1: some of 13 to 16) -----------
 // Bound by the vector and matrix work of a step (unpacking, two FMAs per output for scale and zero, 20 MT matrix
 // instructions: some 1400 cycles at MT = 2, 2400 at MT = 4), not by the 3-4 KB it streams.  What counts is that every SIMD
 // has two waves at work, that they all have the same share, and that the codes are unpacked once for all token rows.
