@@ -324,8 +324,9 @@ bool small_launch(const std::vector<LinearCall>& calls, size_t begin, size_t end
 
 // Decode-phase dispatch of a list of independent linears: grouped launches of at most
 // MAX_LIN_PER_LAUNCH linears, 64 token rows per pass, each launch one round of equally loaded
-// workgroups (see lpq_decode.hip).
-lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false)
+// workgroups (see lpq_decode.hip).  prefill: a prefill call's linears (M <= 64), for the kernels of small launches
+// whatever they stream, 8-bit symmetric codes without an offset.
+lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false, bool prefill = false)
 {
     const size_t n = calls.size();
     const size_t n_launch = (n + MAX_LIN_PER_LAUNCH - 1) / MAX_LIN_PER_LAUNCH;
@@ -352,7 +353,7 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
     // the even-share launches' space is asked for ahead of every launch; the others' (K splits, if any) is no more than that
     bool any_even_share = false;
     for (size_t li = 0; li < n_launch; ++li)
-        any_even_share = any_even_share || !small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M);
+        any_even_share = any_even_share || !(prefill || small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M));
     float* ws = nullptr;
     if (any_even_share) {
         st = workspace(static_ws, partial_bytes + sums_bytes, &ws);
@@ -405,7 +406,7 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         // runs without splitting K (at 16 rows, 3 and 4 bit, us: 5120 -> 15360 15.8 against 13.7, 7168 -> 28672 31 / 26, 4096 -> 12288
         // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower, and where five tiles a workgroup fill the
         // chip in one round the two are level alone but not in a layer: 5120 -> 20480, 4 bit, 18.8 against 20.3).
-        if (small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M)) {
+        if (prefill || small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M)) {
             // longest K first: the last workgroups to start are then the shortest
             std::stable_sort(a.lin, a.lin + a.n_lin, [](const LinDesc& x, const LinDesc& y) { return x.kt > y.kt; });
             int cus = 0;
@@ -450,6 +451,8 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
             if (!mid) {
                 a.row_tiles = tiles;
                 a.waves = blocks <= 64 ? 8 : 4;          // very few blocks: more waves per block keep more loads in flight
+                for (int i = 0; i < a.n_lin; ++i)
+                    if (prefill && a.lin[i].variant == 3) a.lin[i].variant = V_I8_SIGNED;
             }
             if ((mid ? launch_decode_mid(a, stream) : launch_decode_rows(a, stream)) != hipSuccess) return LPQ_ERR_DEVICE;
             continue;
@@ -612,10 +615,12 @@ lpq_status run_prefill(const std::vector<LinearCall>& calls, int32_t M, hipStrea
     const int32_t tail = M % 256, body = M - tail;
     // Up to 64 rows a 128-token tile is at least half empty, and the decode kernels for launches that stream little hold all
     // rows at once: at 40 rows, 4 bit, 5120 -> 15360 23.5 us against 31.1, 8 bit 7168 -> 21504 38 against 81; at 9 rows 13 against
-    // 27 and 30 against 79.  Beyond the line between those and the even-share kernel, which needs tens of megabytes of workspace,
-    // a single linear of up to 16 rows goes there too.  (What the workspace or the descriptors do not hold stays here.)
-    if (M <= 64 && calls.size() <= MAX_LIN_PER_LAUNCH && (small_launch(calls, 0, calls.size(), M) || (M <= 16 && calls.size() == 1))) {
-        const lpq_status st = run_decode(calls, M, stream, static_ws);
+    // 27 and 30 against 79.  A single linear of up to 16 rows goes there however large it is: not to the even-share kernel,
+    // whose offset 8-bit codes cost a prefill call precision.  (What the workspace or the descriptors do not hold stays here,
+    // and so does everything while lpq_set_decode_routing keeps launches away from those kernels.)
+    if (M <= 64 && calls.size() <= MAX_LIN_PER_LAUNCH &&
+        (small_launch(calls, 0, calls.size(), M) || (M <= 16 && calls.size() == 1 && g_rows_max_mb.load() > 0))) {
+        const lpq_status st = run_decode(calls, M, stream, static_ws, true);
         if (st != LPQ_ERR_BUFSIZE && st != LPQ_ERR_UNSUPPORTED) return st;
     }
     if (M <= 128) return run_prefill_rows(calls, M, 128, stream, static_ws);

@@ -11,9 +11,10 @@ namespace lpq {
 // WAVES row blocks a workgroup owns), each of weight `step_weight` (bytes streamed, scaled by a
 // per-variant cost factor); `cum_weight` is the total weight of the linears before it.
 // LinDesc::variant is the storage variant (0 .. 4: 3-, 4-, 8-bit grouped, 8-bit per row, fp16) -- or, in the descriptors
-// of a stage-wide decode launch only, this: 3-bit codes that the kernel masks where they lie, against activations scaled
-// for it beforehand (lpq_decode.hip); the host decides per launch.
-enum { V_W3_INPLACE = 5 };
+// of a stage-wide decode launch only, V_W3_INPLACE: 3-bit codes that the kernel masks where they lie, against activations scaled
+// for it beforehand (lpq_decode.hip); the host decides per launch.  V_I8_SIGNED, in a small launch of a prefill call: 8-bit per-row
+// codes multiplied as signed integers, not offset by 128.
+enum { V_W3_INPLACE = 5, V_I8_SIGNED = 6 };
 
 struct LinDesc {
     const uint8_t* codes;
@@ -29,7 +30,7 @@ struct LinDesc {
     int32_t aux;            // stage-wide kernel: offset of the linear's prepared activations in DecodeArgs::prep, in 16-byte units;
                             // small-launch kernel: number of K splits
     uint16_t kt;            // K / 128 (K < 2^23)
-    uint8_t variant;        // V_W3 .. V_F16, V_W3_INPLACE
+    uint8_t variant;        // V_W3 .. V_F16, V_W3_INPLACE, V_I8_SIGNED
     uint8_t act;            // lpq_activation applied to acc + bias (before the residual)
     __host__ __device__ int K() const { return (int)kt * 128; }
 };

@@ -78,6 +78,17 @@ template <int V, bool INPL> __device__ __forceinline__ h8 unpack_post(const WRaw
     else return unpack_subnormal_step<V>(w, j);
 }
 
+// The same for the kernels of small launches.  SIGNED: per-row 8-bit codes as the signed integers they are.  Offset by 128 and with
+// 128 * sum(x) taken off behind a wave's whole range of K, activations of one sign (a ReLU's output) make both sums hundreds of
+// times the result, and their roundings stay: 57344 -> 14336 with x ~ N(3, 1), error against 64 bits 1.3e-3, so 2.1e-4.  The packed
+// subtraction per pair costs 3-5 %; taking the offset off every few steps instead costs the same where it is as exact.  Decode launches
+// of up to 16 rows keep the offset.
+template <int V, bool SIGNED> __device__ __forceinline__ h8 unpack_small(const WRaw<V>& w, int j)
+{
+    if constexpr (V == V_I8 && SIGNED) return unpack_codes_step<V>(w, j);
+    else return unpack_subnormal_step<V>(w, j);
+}
+
 // A chunk: up to CHUNK consecutive 128-column steps of one (linear, row superblock) unit.
 struct Chunk {
     int sb, kt0, n;      // row superblock, first step, number of steps (0 = none)
@@ -898,7 +909,7 @@ __global__ __launch_bounds__(256) void decode_fixup_kernel(const DecodeArgs a)
 // for a small second kernel; otherwise there are no partial tiles and no second kernel.  rows_row_blocks(L, row_tiles) is the
 // linear's number of groups, a.lin[i].cum_weight the number of workgroups of the linears before i, a.n_blocks
 // their total.
-template <int V, int WAVES, int TILES>
+template <int V, int WAVES, int TILES, bool SIGNED = false>
 __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int split, float* __restrict__ partial, float* __restrict__ red)
 {
     constexpr int RT = (V == V_F16 && TILES > 2) ? 2 : TILES;      // 16-row tiles per workgroup; rb counts groups of RT tiles
@@ -909,7 +920,8 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
     constexpr int LOADS = RT * (VInfo<V>::TILE_BYTES >= 1024 ? VInfo<V>::TILE_BYTES / 1024 : 1) +
                           (SCHEME == SCH_ASYM ? (ALIGNED ? 2 : 4) : 0) + 4;
     static_assert((STAGES - 1) * LOADS < 64, "vmcnt is a 6-bit counter");
-    constexpr int NV = (RT + (SCHEME == SCH_SYM ? 1 : 0)) * 4;   // floats a lane hands to the reduction
+    constexpr bool OFFSET = SCHEME == SCH_SYM && !SIGNED;       // codes are multiplied as code + 128
+    constexpr int NV = (RT + (OFFSET ? 1 : 0)) * 4;   // floats a lane hands to the reduction
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // a scalar: the row block and the tile addresses derive from it
     const int r = lane & 15, kq = lane >> 4;
@@ -959,17 +971,17 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
             const f4 zero4 = {0, 0, 0, 0};
             f4 d[RT], xs;
 #pragma unroll
-            for (int t = 0; t < RT; ++t) wj[0][t] = unpack_subnormal_step<V>(b.w[t], 0);
+            for (int t = 0; t < RT; ++t) wj[0][t] = unpack_small<V, SIGNED>(b.w[t], 0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 // one scheduling group per tile: its matrix instructions of step j and the unpacking of the same tile
                 // for step j + 1, so that the vector work sits between matrix instructions, not in front of them
                 if constexpr (SCHEME == SCH_ASYM) xs = mfma16(b.a[j], ones, j == 0 ? zero4 : xs);
-                else                               xsum = mfma16(b.a[j], ones, xsum);
+                if constexpr (OFFSET)              xsum = mfma16(b.a[j], ones, xsum);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int t = 0; t < RT; ++t) {
-                    if (j < 3) wj[(j + 1) & 1][t] = unpack_subnormal_step<V>(b.w[t], j + 1);
+                    if (j < 3) wj[(j + 1) & 1][t] = unpack_small<V, SIGNED>(b.w[t], j + 1);
                     if constexpr (SCHEME == SCH_ASYM) d[t] = mfma16(b.a[j], wj[j & 1][t], j == 0 ? zero4 : d[t]);
                     else                               acc[t] = mfma16(b.a[j], wj[j & 1][t], acc[t]);
                     __builtin_amdgcn_sched_barrier(0);
@@ -1020,7 +1032,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
     for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int v = 0; v < 4; ++v) mine[(4 * t + v) * 64 + lane] = acc[t][v];
-    if constexpr (SCHEME == SCH_SYM) {
+    if constexpr (OFFSET) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) mine[(4 * RT + v) * 64 + lane] = xsum[v];
     }
@@ -1034,7 +1046,8 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) sum += red[((size_t)w * NV + 4 * t + v) * 64 + ln];
         const long row = ((g0 + t) >> 2) * 64 + 4 * rr + ((g0 + t) & 3);
-        if constexpr (SCHEME == SCH_SYM) {
+        if constexpr (SIGNED) sum *= (float)__builtin_bit_cast(_Float16, L.scales[row]);
+        if constexpr (OFFSET) {
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) xs += red[((size_t)w * NV + 4 * RT + v) * 64 + ln];
             sum = (sum * 16777216.0f - 128.0f * xs) * (float)__builtin_bit_cast(_Float16, L.scales[row]);   // undo 2^-24 and the +128 offset
@@ -1074,6 +1087,7 @@ __global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode
     case V_W4: run_rows<V_W4, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
     case V_W8: run_rows<V_W8, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
     case V_I8: run_rows<V_I8, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
+    case V_I8_SIGNED: run_rows<V_I8, WAVES, TILES, true>(L, a.M, rb, split, partial, red); break;
     default:   run_rows<V_F16, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
     }
 }
@@ -1147,13 +1161,11 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
             b.z = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(L.zeros) + row0 + soff);
         }
     };
-    f4 acc[4][MT], xsum[MT];
+    f4 acc[4][MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        xsum[m] = f4{0, 0, 0, 0};
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t][m] = f4{0, 0, 0, 0};
-    }
     auto compute = [&](const Stage& b, const uint16_t* xs) {
         const _Float16 one = (_Float16)1.0f;
         const h8 ones = {one, one, one, one, one, one, one, one};
@@ -1170,25 +1182,22 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
             f4 d[TG][MT];
             h8 wj[2][TG];
 #pragma unroll
-            for (int t = 0; t < TG; ++t) wj[0][t] = unpack_subnormal_step<V>(b.w[TG * hf + t], 0);
+            for (int t = 0; t < TG; ++t) wj[0][t] = unpack_small<V, true>(b.w[TG * hf + t], 0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0), ahead of the next reads: with global-to-LDS loads under way
                                                        // the compiler would wait for those too
                 if (j < 3) read_x(xa[(j + 1) & 1], j + 1);
                 else if (hf + 1 < 4 / TG) read_x(xa[0], 0);
-                if (hf == 0) {
+                if (SCHEME == SCH_ASYM && hf == 0) {
 #pragma unroll
-                    for (int m = 0; m < MT; ++m) {
-                        if constexpr (SCHEME == SCH_ASYM) xg[m] = mfma16(xa[j & 1][m], ones, j == 0 ? zero4 : xg[m]);
-                        if constexpr (SCHEME == SCH_SYM)  xsum[m] = mfma16(xa[j & 1][m], ones, xsum[m]);
-                    }
+                    for (int m = 0; m < MT; ++m) xg[m] = mfma16(xa[j & 1][m], ones, j == 0 ? zero4 : xg[m]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 // one scheduling group per tile: its matrix instructions and the unpacking of the same tile for step j + 1
 #pragma unroll
                 for (int t = 0; t < TG; ++t) {
-                    if (j < 3) wj[(j + 1) & 1][t] = unpack_subnormal_step<V>(b.w[TG * hf + t], j + 1);
+                    if (j < 3) wj[(j + 1) & 1][t] = unpack_small<V, true>(b.w[TG * hf + t], j + 1);
 #pragma unroll
                     for (int m = 0; m < MT; ++m) {
                         if constexpr (SCHEME == SCH_ASYM) d[t][m] = mfma16(xa[j & 1][m], wj[j & 1][t], j == 0 ? zero4 : d[t][m]);
@@ -1244,7 +1253,7 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
     // finishes items kw * OWN .. + OWN - 1 and hands the others over.
     wait_vmem_all_but<0>();                            // the last fill: the buffer is overwritten
     __syncthreads();
-    constexpr int OWN = 4 * MT < KW ? 1 : 4 * MT / KW, OTHERS = 4 * MT < KW ? 4 * MT : 4 * MT - OWN, FL = SCHEME == SCH_SYM ? 5 : 4;         // floats of an item: four rows, and the sum of x
+    constexpr int OWN = 4 * MT < KW ? 1 : 4 * MT / KW, OTHERS = 4 * MT < KW ? 4 * MT : 4 * MT - OWN, FL = 4;         // floats of an item: four rows
     static_assert((size_t)8 * OTHERS * FL * 256 <= MidCfg<MT, RB>::SMEM, "the hand-over fits the activations' buffers");
     float* const red = reinterpret_cast<float*>(smem);
     auto slot = [&](int k, int item, int i) -> float& {                      // what wave k of this row block hands over
@@ -1259,7 +1268,6 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
             if (item / OWN == kw) continue;
 #pragma unroll
             for (int t = 0; t < 4; ++t) slot(kw, item, t) = acc[t][m][v];
-            if constexpr (SCHEME == SCH_SYM) slot(kw, item, 4) = xsum[m][v];
         }
     __syncthreads();
     if (rb >= NB) return;
@@ -1275,7 +1283,6 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
             const int item = 4 * m + v, tok = 16 * m + 4 * kq + v;
             if (item / OWN != kw) continue;
             f4 o;
-            float xt = SCHEME == SCH_SYM ? xsum[m][v] : 0.0f;
 #pragma unroll
             for (int t = 0; t < 4; ++t) o[t] = acc[t][m][v];
 #pragma unroll
@@ -1283,11 +1290,10 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
                 const int other = (kw + k) % KW;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) o[t] += slot(other, item, t);
-                if constexpr (SCHEME == SCH_SYM) xt += slot(other, item, 4);
             }
-            if constexpr (SCHEME == SCH_SYM)           // undo 2^-24 and the +128 offset
+            if constexpr (SCHEME == SCH_SYM)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) o[t] = (o[t] * 16777216.0f - 128.0f * xt) * (float)sc[t];
+                for (int t = 0; t < 4; ++t) o[t] *= (float)sc[t];
             if (tok >= M) continue;
             const size_t at = (size_t)tok * L.N + row;
             if (splits > 1) {

@@ -451,3 +451,30 @@ def test_prefill_whole_and_split_tiles(orc, bits, scheme, M, N, K):
     rows = sorted({min(max(r, 0), N - 64) // 64 * 64 for r in (0, border - 64, border, border + 256, N - 64)})
     for r0 in rows:
         check_output(y[:, r0:r0 + 64], orc.qlinear(x.cpu().numpy(), w[r0:r0 + 64].cpu().numpy(), bits, scheme), "rows %d.. of %d" % (r0, N))
+
+
+@pytest.mark.parametrize("phase", [lpq.LPQ_PREFILL, lpq.LPQ_DECODE], ids=["prefill", "decode"])
+@pytest.mark.parametrize("K,N", [(20480, 5120), (57344, 14336)])
+def test_symmetric_weights_with_activations_of_one_sign(phase, K, N):
+    """The second feed-forward linear's input is a ReLU's output.  Per-row symmetric 8-bit codes are multiplied as signed integers by
+    every prefill call and from 17 decode rows on, so no sums cancel and the error against 64 bits is that of the one rounding to
+    fp16: uniform within half an ulp, an ulp between 2^-11 and 2^-10 of the value, so at most 2^-11 / sqrt(3) = 2.82e-4 in the 2-norm.
+    The 32-bit sums' share is under 1e-5: 3e-4.  Decode launches of up to 16 rows multiply offset codes and are not part of this."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    w = (torch.randn((N, K), generator=gen, device="cuda", dtype=torch.float16) * 0.02)
+    flat = w.view(-1)
+    flat[torch.randint(0, flat.numel(), (flat.numel() // 1000,), generator=gen, device="cuda")] *= 20.0
+    qw = lpq.lpq_quantize_pack(w, 8, lpq.LPQ_SYM_CHANNEL)
+    rows = torch.arange(0, N, 37, device="cuda")
+    scale = qw.scales[rows].double()[:, None]
+    deq = torch.clamp(torch.round(w[rows].float() / qw.scales[rows].float()[:, None]), -127, 127).double() * scale
+    for M in (9, 20, 40, 64):
+        if phase == lpq.LPQ_DECODE and M <= 16:
+            continue
+        z = torch.randn((M, K), generator=gen, device="cuda")
+        for name, x in (("relu", torch.relu(z).half()), ("shifted", (z + 3.0).half())):
+            y = lpq.lpq_qlinear_fused(qw, x, phase)[:, rows].double()
+            ref = x.double() @ deq.t()
+            rel = float((y - ref).norm() / ref.norm())
+            assert rel <= 3e-4, "%d rows, %s: %.2e" % (M, name, rel)
