@@ -894,6 +894,38 @@ __global__ __launch_bounds__(256) void decode_fixup_kernel(const DecodeArgs a)
     }
 }
 
+// Infinite activations in small launches.  Scale and zero applied behind the products (as the offset of 8-bit codes) turn an infinity
+// into Inf - Inf = NaN, where a product with the dequantised weights is infinite with the weight's sign.  A sum that
+// is not finite betrays them at no cost inside the loop; then, and only for the tokens concerned, a wave forms its sums
+// again, slowly, from weights dequantised to fp16.  tile: the tile's place in 64-row block rb; xlane: the lane's token row plus 8 * kq;
+// the wave's steps are step(0) .. step(n - 1), those from kt_end on left out.
+template <int V, typename Step>
+__device__ __forceinline__ f4 dequantised_sums(const LinDesc& L, long rb, int tile, const uint16_t* xlane, int n, int kt_end, Step step)
+{
+    constexpr int SCHEME = VInfo<V>::SCHEME, TILE = VInfo<V>::TILE_BYTES, LANE_BYTES = V == V_W3 ? 12 : 16;
+    const int lane = threadIdx.x & 63, r = lane & 15;
+    f4 sum = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+        const int kt = step(i);
+        if (kt >= kt_end) continue;
+        const WRaw<V> w = load_tile_at<V>(L.codes + ((size_t)rb * L.kt + kt) * (4 * (size_t)TILE) + tile * TILE + LANE_BYTES * lane);
+        h8 o[4];
+        unpack_codes<V>(w, o);
+        if constexpr (SCHEME == SCH_ASYM) {
+            const size_t at = (size_t)kt * L.N + rb * 64 + 4 * r + tile;
+            apply_scale_zero(o, __builtin_bit_cast(_Float16, L.scales[at]), __builtin_bit_cast(_Float16, L.zeros[at]));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum = mfma16(*reinterpret_cast<const h8*>(xlane + (size_t)kt * 128 + 32 * j), o[j], sum);
+    }
+    return sum;
+}
+__device__ __forceinline__ bool any_not_finite(const f4& v)
+{
+    return __any(!(__builtin_isfinite(v[0]) && __builtin_isfinite(v[1]) && __builtin_isfinite(v[2]) && __builtin_isfinite(v[3])));
+}
+
 // ---- small launches (one linear of a decoder layer, up to 16 token rows) ---------------
 // The even-share kernel above needs a launch with many steps to spread; a single linear has few, and cutting
 // its units into short ranges leaves each workgroup waiting on memory latency and pays a fix-up pass.  Here a
@@ -1023,6 +1055,23 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
                 compute(st[sidx]);
                 issue(st[sidx], i + STAGES);
             }
+        }
+    }
+
+    if constexpr (POST && !SIGNED) {
+        if (__builtin_expect(any_not_finite(acc[0]), 0)) {       // a token's sums are finite in all tiles or in none
+#pragma unroll 1
+            for (int t = 0; t < RT; ++t) {
+                const f4 sum = dequantised_sums<V>(L, (g0 + t) >> 2, (int)((g0 + t) & 3), xrow, n_w, kt1, [&](int i) { return kt0 + wave + i * WAVES; });
+#pragma unroll
+                for (int u = 0; u < RT; ++u)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (u == t && !__builtin_isfinite(acc[u][v])) acc[u][v] = SCHEME == SCH_SYM ? sum[v] / 16777216.0f : sum[v];
+            }
+            if constexpr (OFFSET)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) xsum[v] = __builtin_isfinite(xsum[v]) ? xsum[v] : 0.0f;
         }
     }
 
@@ -1246,6 +1295,23 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
             iteration(it, std::integral_constant<int, 0>());
             if (it + 1 >= n_it) break;
             iteration(it + 1, std::integral_constant<int, 1>());
+        }
+    }
+
+    if constexpr (SCHEME == SCH_ASYM) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            if (__builtin_expect(!any_not_finite(acc[0][m]), 1)) continue;
+            const uint16_t* xlane = L.x + (size_t)min(16 * m + r, M - 1) * K + 8 * kq;
+#pragma unroll 1
+            for (int t = 0; t < 4; ++t) {
+                const f4 sum = dequantised_sums<V>(L, rbc, t, xlane, n_it * C, kt1, [&](int i) { return kt0 + i / C * SLOTS + C * kw + i % C; });
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (u == t && !__builtin_isfinite(acc[u][m][v])) acc[u][m][v] = sum[v];
+            }
         }
     }
 

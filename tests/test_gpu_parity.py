@@ -478,3 +478,36 @@ def test_symmetric_weights_with_activations_of_one_sign(phase, K, N):
             ref = x.double() @ deq.t()
             rel = float((y - ref).norm() / ref.norm())
             assert rel <= 3e-4, "%d rows, %s: %.2e" % (M, name, rel)
+
+
+@pytest.mark.parametrize("bits,scheme", VARIANTS, ids=VARIANT_IDS)
+@pytest.mark.parametrize("phase,M", [(lpq.LPQ_PREFILL, 5), (lpq.LPQ_PREFILL, 16), (lpq.LPQ_PREFILL, 30), (lpq.LPQ_PREFILL, 64),
+                                     (lpq.LPQ_PREFILL, 100), (lpq.LPQ_DECODE, 40), (lpq.LPQ_DECODE, 64)])
+def test_infinite_activations(phase, M, bits, scheme):
+    """An infinite activation makes its token's outputs infinite with the dequantised weight's sign (NaN where infinities of both signs or
+    a zero weight meet), whichever kernel a prefill call takes, and in decode calls of 33 to 64 rows; the other tokens' outputs
+    are the same bits as without it.  Weights are kept away from zero, where rounding to fp16 would decide."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(M + bits)
+    N, K = 320, 2304
+    w = torch.randn((N, K), generator=gen, device="cuda") * 0.02
+    w = (w + 0.01 * torch.sign(w)).half()
+    qw = lpq.lpq_quantize_pack(w, bits, scheme)
+    x = torch.randn((M, K), generator=gen, device="cuda").half()
+    plain = lpq.lpq_qlinear_fused(qw, x, phase)
+    deq = lpq.lpq_unpack_dequant(qw)
+    inf = float("inf")
+    x[0, 1000] = inf
+    x[M - 1, 2303], x[M - 1, 0] = -inf, -inf
+    x[M // 2, 130] = float("nan")
+    y = lpq.lpq_qlinear_fused(qw, x, phase)
+    keep = torch.ones(M, dtype=torch.bool, device="cuda")
+    keep[[0, M // 2, M - 1]] = False
+    assert torch.equal(y[keep], plain[keep]), "a token without infinities changed"
+    assert torch.isnan(y[M // 2]).all()
+    sure = (deq[:, [0, 1000, 2303]].abs() > 1e-4).all(1)
+    assert int(sure.sum()) > N // 2
+    assert torch.equal(y[0, sure].float(), (torch.sign(deq[:, 1000]) * inf)[sure])
+    a, b = deq[sure, 0], deq[sure, 2303]
+    both = torch.where(torch.sign(a) == torch.sign(b), -torch.sign(a) * inf, torch.full_like(a, float("nan")))
+    assert torch.equal(torch.nan_to_num(y[M - 1, sure].float(), nan=3.0), torch.nan_to_num(both, nan=3.0))
