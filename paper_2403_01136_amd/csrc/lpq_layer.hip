@@ -5,8 +5,8 @@
 //
 // Cache layout per layer: K [B][H][S][d] (a position's d values contiguous) and V transposed,
 // VT [B][H][d][S] (a feature's positions contiguous).  With that, both contractions of attention read
-// their operands along the contracted index: q.K over d, p.V over positions -- as 16-byte loads, and in
-// the prefill kernel directly as MFMA B operands from global memory (no LDS staging, no transposes).
+// their operands along the contracted index: q.K over d, p.V over positions -- as 16-byte loads, which the
+// prefill kernel stages through LDS as MFMA A operands (no transposes).
 #include <algorithm>
 #include <type_traits>
 
@@ -362,6 +362,46 @@ __device__ __forceinline__ int swap_bits23(int x) { return (x & ~12) | ((x & 4) 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
+// One query at position p by one wave, on the vector units, over the keys it sees and no others: lanes along the keys for the scores, along
+// the features for p . V.  For queries whose sums came out not finite: a later token's infinite or NaN value row, at weight
+// zero, does that in the matrix product of a tile that both share.  (Same scaling, exponents and rounding of the weights.)
+template <int D>
+__device__ __forceinline__ void attention_one_query(const uint16_t* __restrict__ qp, const uint16_t* __restrict__ kbase, const uint16_t* __restrict__ vbase,
+                                                    int S, int p, float c, float slope, uint16_t* __restrict__ op)
+{
+    const int lane = threadIdx.x & 63;
+    float m = -INFINITY, l = 0.0f, acc[D / 64] = {};
+#pragma unroll 1
+    for (int j0 = 0; j0 <= p; j0 += 64) {
+        const int j = j0 + lane;                       // within the cache: it holds whole tiles of 64
+        float sc = 0.0f;
+#pragma unroll 1
+        for (int f = 0; f < D; f += 8) {
+            const h8 q = *reinterpret_cast<const h8*>(qp + f), k = *reinterpret_cast<const h8*>(kbase + (size_t)j * D + f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sc += (float)q[e] * (float)k[e];
+        }
+        sc = j <= p ? __builtin_fmaf(sc, c, slope * (float)(j - p)) : -INFINITY;
+        const float mn = fmaxf(m, group_reduce<64>(sc, OpMax())), alpha = __builtin_amdgcn_exp2f(m - mn);
+        const float w = j <= p ? __builtin_amdgcn_exp2f(sc - mn) : 0.0f;
+        m = mn;
+        l = l * alpha + w;
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) acc[i] *= alpha;
+        const int n = min(64, p + 1 - j0);
+#pragma unroll 1
+        for (int u = 0; u < n; ++u) {
+            const float wu = (float)(_Float16)__shfl(w, u);
+#pragma unroll
+            for (int i = 0; i < D / 64; ++i)
+                acc[i] = __builtin_fmaf(wu, (float)__builtin_bit_cast(_Float16, vbase[(size_t)(64 * i + lane) * S + j0 + u]), acc[i]);
+        }
+    }
+    l = group_reduce<64>(l, OpAdd());
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) op[64 * i + lane] = __builtin_bit_cast(uint16_t, (_Float16)(acc[i] / l));
+}
+
 template <int D, bool ALIBI>
 __global__ __launch_bounds__(256, 2) void attention_prefill_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ kc,
                                                                    const uint16_t* __restrict__ vtc, const float* __restrict__ slopes,
@@ -533,6 +573,14 @@ __global__ __launch_bounds__(256, 2) void attention_prefill_kernel(const uint16_
     l = l2[0] + l2[1];
     // the lane holds features 32 d + 8 a + 4 half + 0 .. 3 of its query; the halves trade so that each stores 16 bytes
     const float inv = 1.0f / l;
+    float total[4] = {0.0f, 0.0f, 0.0f, 0.0f};         // finite if all the lane's sums are
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) total[v % 4] += o[d][v];
+    uint64_t again = __ballot(!__builtin_isfinite((total[0] + total[1]) + (total[2] + total[3])) && t0 + col < T);
+    again = (again | again >> 32) & 0xffffffffu;       // queries to be done again: a bit per column, of either half
+    const bool store = t0 + col < T && !(again >> col & 1);
     uint16_t* op = out + ((size_t)b * T + t0 + col) * h + head * D + 8 * half;
 #pragma unroll
     for (int d = 0; d < DT; ++d)
@@ -547,8 +595,14 @@ __global__ __launch_bounds__(256, 2) void attention_prefill_kernel(const uint16_
                 w[i] = t[0];
                 w[2 + i] = t[1];
             }
-            if (t0 + col < T) *reinterpret_cast<u32x4*>(op + 32 * d + 8 * a) = w;
+            if (store) *reinterpret_cast<u32x4*>(op + 32 * d + 8 * a) = w;
         }
+    while (__builtin_expect(again != 0, 0)) {
+        const int t = t0 + __builtin_ctzll(again);
+        again &= again - 1;
+        const size_t row = (size_t)b * T + t;
+        attention_one_query<D>(qkv + row * 3 * h + head * D, kbase, vbase, S, pos0 + t, c, slope, out + row * h + head * D);
+    }
 }
 
 }  // namespace

@@ -317,3 +317,40 @@ def test_variance_indicator_block_edges(N, K, M):
         ref = OI.indicator(w, x, stochastic)
         for i, key in enumerate(OI.ORDER):
             assert abs(got[i] - ref[key]) <= 1e-5 * abs(ref[key]) + 1e-300, (key, got[i], ref[key])
+
+
+@pytest.mark.parametrize("d,T,pos0,bad", [(128, 100, 1, 70), (64, 300, 0, 130), (128, 40, 30, 39), (64, 33, 64, 32), (128, 260, 5, 0)])
+@pytest.mark.parametrize("alibi", [False, True])
+def test_non_finite_values_of_a_later_token(d, T, pos0, bad, alibi):
+    """Infinities and NaN in the value row of one prompt token reach the queries at and behind it, not the ones before: those are what they are
+    without it, up to the order of 32-bit sums (tolerance: the file's); the other head is the same bits."""
+    import torch
+    B, H, S = 1, 2, (pos0 + T + 63) // 64 * 64
+    st, _, slopes = make_state(B, H, d, S, T, alibi)
+    r = rng("nonfinite", d, T, pos0)
+    h = H * d
+    qkv = f16(r.standard_normal((B * T, 3 * h)))
+    k, vt = f16(r.standard_normal((B, H, S, d))), f16(r.standard_normal((B, H, d, S)))
+    outs = []
+    for value in (None, np.inf, np.nan):
+        q = qkv.copy()
+        if value is not None:
+            q[bad, 2 * h:2 * h + d:3] = value                # every third feature of head 0
+            q[bad, 2 * h + 1] = -value
+        st.k_cache.copy_(to_dev(k)), st.vt_cache.copy_(to_dev(vt))
+        lpq.lpq_kv_append(to_dev(q), st, B, T, pos0)
+        outs.append(lpq.lpq_attention(to_dev(q), st, B, T, pos0).double().cpu().numpy())
+    clean, inf, nan = outs
+    for got in (inf, nan):
+        assert np.all(np.isfinite(got[:bad, :d])), "queries before the token"
+        if bad:
+            assert np.linalg.norm(got[:bad] - clean[:bad]) <= 1e-3 * np.linalg.norm(clean[:bad])
+        assert np.array_equal(got[:, d:], clean[:, d:])
+    # the queries that see it: +-inf or NaN in its features (its weight may round to zero), the others unharmed
+    hit = np.zeros(d, dtype=bool)
+    hit[0::3], hit[1] = True, True
+    assert not np.any(np.isfinite(inf[bad:, :d][:, hit])) and not np.any(np.isfinite(nan[bad:, :d][:, hit]))
+    seen = inf[bad, :d]
+    assert np.all(seen[0::3] == np.inf) and seen[1] == -np.inf
+    rest = inf[bad:, :d][:, ~hit]
+    assert np.linalg.norm(rest - clean[bad:, :d][:, ~hit]) <= 1e-3 * np.linalg.norm(clean[bad:, :d][:, ~hit])
