@@ -161,15 +161,6 @@ std::atomic<int32_t> g_rows_tiles{0};        // 2..5: force that many 16-row til
 // The workgroups per launch are what the chip holds at once.
 int decode_waves(int /*M*/) { return 8; }
 
-lpq_status decode_block_count(int waves, int* out)
-{
-    int cus = 0;
-    lpq_status st = device_cus(&cus);
-    if (st != LPQ_OK) return st;
-    *out = cus * (8 / waves);
-    return LPQ_OK;
-}
-
 // relative cost of streaming one byte of each variant (x16), used to weight the even-share split
 uint32_t variant_cost_x16(int variant)
 {
@@ -322,155 +313,167 @@ bool small_launch(const std::vector<LinearCall>& calls, size_t begin, size_t end
     return stream_bytes <= (int64_t)g_rows_max_mb.load() << 20;
 }
 
+// One grouped decode launch: its arguments (without the workspace's addresses), the kernel it takes and the bytes of
+// workspace it needs.
+enum DecodeKernel { DECODE_EVEN_SHARE = 0, DECODE_ROWS = 1, DECODE_MID = 2 };
+struct DecodeLaunch {
+    DecodeArgs a;
+    DecodeKernel kernel;
+    size_t partial_bytes, workspace_bytes;       // of them partial sums; all
+};
+
+// Plans the launch of linears [begin, end) on a device of `cus` compute units; a function of its arguments and the
+// routing settings alone.  prefill: a prefill call's linears (M <= 64), for the kernels of small launches whatever they stream, 8-bit
+// symmetric codes without an offset.
+lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M, int cus, bool prefill, DecodeLaunch* out)
+{
+    DecodeArgs& a = out->a;
+    const int waves = decode_waves(M);
+    const int n_blocks = cus * (8 / waves);
+    const int tok_rows = std::min(64, (M + 15) / 16 * 16);
+    a.M = M;
+    a.m0 = 0;
+    a.n_lin = 0;
+    a.waves = waves;
+    a.n_blocks = n_blocks;
+    a.slot_floats = tok_rows * waves * 64;
+    a.row_tiles = 4;
+    a.pad = 0;
+    a.partial = nullptr;
+    a.prep = nullptr;
+    const size_t partial_bytes = ((size_t)2 * n_blocks * a.slot_floats * sizeof(float) + 255) & ~(size_t)255;
+    // after the partial tiles: what decode_prepare_kernel leaves for a launch whose last pass has up to 32 token rows
+    const int last_rows = (M - 1) % 64 + 1;
+    const bool in_place = reads_in_place(calls, begin, end, M);
+    uint64_t total = 0;
+    size_t sums_off16 = 0;                       // in 16-byte units
+    for (size_t c = begin; c < end; ++c) {
+        const lpq_qweight& w = *calls[c].w;
+        LinDesc& L = a.lin[a.n_lin++];
+        L.codes = static_cast<const uint8_t*>(w.codes);
+        L.scales = static_cast<const uint16_t*>(w.scales);
+        L.zeros = static_cast<const uint16_t*>(w.zeros);
+        L.x = static_cast<const uint16_t*>(calls[c].x);
+        L.y = static_cast<uint16_t*>(calls[c].y);
+        L.bias = static_cast<const uint16_t*>(w.bias);
+        L.residual = static_cast<const uint16_t*>(calls[c].residual);
+        L.act = (uint8_t)calls[c].act;
+        L.aux = (int32_t)sums_off16;
+        sums_off16 += prepared_bytes(w.d, last_rows, in_place) / 16;
+        if (w.d.K / 128 > 0xffff) return LPQ_ERR_UNSUPPORTED;          // the descriptor keeps K / 128 in 16 bits
+        L.kt = (uint16_t)(w.d.K / 128);
+        L.N = w.d.N;
+        L.variant = (uint8_t)variant_of(w.d);
+        const int rows = decode_rows_per_wave(L.variant);
+        const uint32_t step_bytes = (uint32_t)(waves * rows) * (128u * (uint32_t)w.d.bits / 8u + (w.d.scheme == LPQ_ASYM_GROUP ? 4u : 0u));
+        L.step_weight = step_bytes * variant_cost_x16(L.variant);
+        L.cum_weight = total;
+        total += (uint64_t)L.step_weight * (uint64_t)lin_row_superblocks(L, waves) * (uint64_t)L.kt;
+    }
+    if (total >= ((uint64_t)1 << 50)) return LPQ_ERR_UNSUPPORTED;
+    a.total_weight = total;
+    // A launch that streams little (a single linear of a decoder layer) has too few steps to spread evenly and pays the
+    // fix-up pass: it goes to the kernels whose workgroups take a few tiles of W over K (no pieces to add).  Which of
+    // them: from 17 token rows on the one that shares the activations through LDS; up to 16 the one that reads them
+    // straight from L2 and streams from deeper rings -- except a single linear of 13 to 16 rows that the former
+    // runs without splitting K (at 16 rows, 3 and 4 bit, us: 5120 -> 15360 15.8 against 13.7, 7168 -> 28672 31 / 26, 4096 -> 12288
+    // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower, and where five tiles a workgroup fill the
+    // chip in one round the two are level alone but not in a layer: 5120 -> 20480, 4 bit, 18.8 against 20.3).
+    if (prefill || small_launch(calls, begin, end, M)) {
+        // longest K first: the last workgroups to start are then the shortest
+        std::stable_sort(a.lin, a.lin + a.n_lin, [](const LinDesc& x, const LinDesc& y) { return x.kt > y.kt; });
+        bool mid = M > 16;
+        int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
+        if (!mid && a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
+        if (mid || (M > 12 && a.n_lin == 1 && tiles != 5)) {
+            mid_plan(a, cus, partial_bytes / sizeof(float));
+            mid = mid || a.lin[0].aux == 1;
+        }
+        const int forced = g_rows_tiles.load();
+        if (!mid) {
+            if (forced >= 2 && forced <= 5 && forced != tiles) tiles = forced, splits1 = 0;
+            for (int i = 0; i < a.n_lin; ++i)
+                if ((a.lin[i].N / 16) % rows_group_tiles(a.lin[i].variant, tiles) != 0) tiles = 4, splits1 = 0;    // groups must tile every linear exactly
+        }
+        int64_t blocks = 0, row_blocks = 0, partial_floats = 0;
+        for (int i = 0; i < a.n_lin; ++i) row_blocks += a.lin[i].N / 16 / rows_group_tiles(a.lin[i].variant, tiles);
+        for (int i = 0; i < a.n_lin; ++i) {
+            LinDesc& L = a.lin[i];
+            if (!mid) {
+                // K splits (L.aux) of a launch of several linears: only if it leaves most compute units without a
+                // workgroup, and only down to 32 steps per workgroup
+                const int KT = L.kt;
+                const int want = (int)std::max<int64_t>(1, 320 / std::max<int64_t>(1, row_blocks));
+                L.aux = splits1 > 0 ? splits1 : std::max(1, std::min(std::min(want, KT / 32), 8));
+            }
+            L.step_weight = (uint32_t)partial_floats;                 // float offset of this linear's partial sums
+            if (L.aux > 1) partial_floats += (int64_t)L.aux * M * L.N;
+            L.cum_weight = (uint64_t)blocks;
+            blocks += (int64_t)(mid ? mid_superblocks(L, a.row_tiles) : rows_row_blocks(L, tiles)) * L.aux;
+            if (!mid && prefill && L.variant == 3) L.variant = V_I8_SIGNED;
+        }
+        if (blocks > 0x7fffffffLL || partial_floats > 0x7fffffffLL) return LPQ_ERR_UNSUPPORTED;
+        a.n_blocks = (int32_t)blocks;
+        if (!mid) {
+            a.row_tiles = tiles;
+            a.waves = blocks <= 64 ? 8 : 4;          // very few blocks: more waves per block keep more loads in flight
+        }
+        out->kernel = mid ? DECODE_MID : DECODE_ROWS;
+        out->partial_bytes = out->workspace_bytes = (size_t)partial_floats * sizeof(float);
+        return LPQ_OK;
+    }
+    // A small launch (one linear of a decoder layer) is not cut into more ranges than it has chunks of
+    // steps: thinner ranges stream no faster and only multiply the pieces the fix-up pass has to add.
+    const int min_steps = M <= 16 ? 16 : 8;              // a 64-token step is 3x as long
+    int64_t steps = 0;
+    for (int i = 0; i < a.n_lin; ++i) steps += (int64_t)lin_row_superblocks(a.lin[i], waves) * a.lin[i].kt;
+    a.n_blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(n_blocks, steps / min_steps));
+    a.range_q = a.total_weight / (uint64_t)a.n_blocks;
+    a.range_rem = (uint32_t)(a.total_weight % (uint64_t)a.n_blocks);
+    if (in_place)
+        for (int i = 0; i < a.n_lin; ++i)
+            if (a.lin[i].variant == 0) a.lin[i].variant = V_W3_INPLACE;
+    out->kernel = DECODE_EVEN_SHARE;
+    out->partial_bytes = partial_bytes;
+    out->workspace_bytes = partial_bytes + (last_rows <= 32 ? sums_off16 * 16 : 0);
+    return LPQ_OK;
+}
+
 // Decode-phase dispatch of a list of independent linears: grouped launches of at most
 // MAX_LIN_PER_LAUNCH linears, 64 token rows per pass, each launch one round of equally loaded
-// workgroups (see lpq_decode.hip).  prefill: a prefill call's linears (M <= 64), for the kernels of small launches
-// whatever they stream, 8-bit symmetric codes without an offset.
+// workgroups (see lpq_decode.hip).  Every launch is planned, and the workspace of the largest asked for, ahead of the first
+// one: launches and passes run one after the other on the stream and share the space.
 lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false, bool prefill = false)
 {
     const size_t n = calls.size();
     const size_t n_launch = (n + MAX_LIN_PER_LAUNCH - 1) / MAX_LIN_PER_LAUNCH;
     const size_t per_launch = (n + n_launch - 1) / n_launch;
-    const int waves = decode_waves(M);
-    int n_blocks = 0;
-    lpq_status st = decode_block_count(waves, &n_blocks);
+    int cus = 0;
+    lpq_status st = device_cus(&cus);
     if (st != LPQ_OK) return st;
-    const int tok_rows = std::min(64, (M + 15) / 16 * 16);
-    const int slot_floats = tok_rows * waves * 64;
-    // after the partial tiles: what decode_prepare_kernel leaves for one launch whose last pass has up to 32 token
-    // rows; launches and passes run one after the other on the stream and share the space
-    const size_t partial_bytes = ((size_t)2 * n_blocks * slot_floats * sizeof(float) + 255) & ~(size_t)255;
-    const int last_rows = (M - 1) % 64 + 1;
-    size_t sums_bytes = 0;
-    if (last_rows <= 32)
-        for (size_t li = 0; li < n_launch; ++li) {
-            size_t b = 0;
-            const size_t c0 = li * per_launch, c1 = std::min(n, (li + 1) * per_launch);
-            const bool in_place = reads_in_place(calls, c0, c1, M);
-            for (size_t c = c0; c < c1; ++c) b += prepared_bytes(calls[c].w->d, last_rows, in_place);
-            sums_bytes = std::max(sums_bytes, b);
-        }
-    // the even-share launches' space is asked for ahead of every launch; the others' (K splits, if any) is no more than that
-    bool any_even_share = false;
-    for (size_t li = 0; li < n_launch; ++li)
-        any_even_share = any_even_share || !(prefill || small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M));
+    std::vector<DecodeLaunch> plan(n_launch);
+    size_t need = 0;
+    for (size_t li = 0; li < n_launch; ++li) {
+        st = plan_decode(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M, cus, prefill, &plan[li]);
+        if (st != LPQ_OK) return st;
+        need = std::max(need, plan[li].workspace_bytes);
+    }
     float* ws = nullptr;
-    if (any_even_share) {
-        st = workspace(static_ws, partial_bytes + sums_bytes, &ws);
+    if (need) {
+        st = workspace(static_ws, need, &ws);
         if (st != LPQ_OK) return st;
     }
-    for (size_t li = 0; li < n_launch; ++li) {
-        DecodeArgs a;
-        a.M = M;
-        a.m0 = 0;
-        a.n_lin = 0;
-        a.waves = waves;
-        a.n_blocks = n_blocks;
-        a.slot_floats = slot_floats;
-        a.row_tiles = 4;
-        a.pad = 0;
-        a.partial = ws;
-        a.prep = ws && sums_bytes ? reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(ws) + partial_bytes) : nullptr;
-        uint64_t total = 0;
-        size_t sums_off16 = 0;               // in 16-byte units
-        const bool in_place = reads_in_place(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M);
-        for (size_t c = li * per_launch; c < std::min(n, (li + 1) * per_launch); ++c) {
-            const lpq_qweight& w = *calls[c].w;
-            LinDesc& L = a.lin[a.n_lin++];
-            L.codes = static_cast<const uint8_t*>(w.codes);
-            L.scales = static_cast<const uint16_t*>(w.scales);
-            L.zeros = static_cast<const uint16_t*>(w.zeros);
-            L.x = static_cast<const uint16_t*>(calls[c].x);
-            L.y = static_cast<uint16_t*>(calls[c].y);
-            L.bias = static_cast<const uint16_t*>(w.bias);
-            L.residual = static_cast<const uint16_t*>(calls[c].residual);
-            L.act = (uint8_t)calls[c].act;
-            L.aux = (int32_t)sums_off16;
-            sums_off16 += prepared_bytes(w.d, last_rows, in_place) / 16;
-            if (w.d.K / 128 > 0xffff) return LPQ_ERR_UNSUPPORTED;          // the descriptor keeps K / 128 in 16 bits
-            L.kt = (uint16_t)(w.d.K / 128);
-            L.N = w.d.N;
-            L.variant = (uint8_t)variant_of(w.d);
-            const int rows = decode_rows_per_wave(L.variant);
-            const uint32_t step_bytes = (uint32_t)(waves * rows) * (128u * (uint32_t)w.d.bits / 8u + (w.d.scheme == LPQ_ASYM_GROUP ? 4u : 0u));
-            L.step_weight = step_bytes * variant_cost_x16(L.variant);
-            L.cum_weight = total;
-            total += (uint64_t)L.step_weight * (uint64_t)lin_row_superblocks(L, waves) * (uint64_t)L.kt;
-        }
-        if (total >= ((uint64_t)1 << 50)) return LPQ_ERR_UNSUPPORTED;
-        a.total_weight = total;
-        // A launch that streams little (a single linear of a decoder layer) has too few steps to spread evenly and pays the
-        // fix-up pass: it goes to the kernels whose workgroups take a few tiles of W over K (no pieces to add).  Which of
-        // them: from 17 token rows on the one that shares the activations through LDS; up to 16 the one that reads them
-        // straight from L2 and streams from deeper rings -- except a single linear of 13 to 16 rows that the former
-        // runs without splitting K (at 16 rows, 3 and 4 bit, us: 5120 -> 15360 15.8 against 13.7, 7168 -> 28672 31 / 26, 4096 -> 12288
-        // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower, and where five tiles a workgroup fill the
-        // chip in one round the two are level alone but not in a layer: 5120 -> 20480, 4 bit, 18.8 against 20.3).
-        if (prefill || small_launch(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M)) {
-            // longest K first: the last workgroups to start are then the shortest
-            std::stable_sort(a.lin, a.lin + a.n_lin, [](const LinDesc& x, const LinDesc& y) { return x.kt > y.kt; });
-            int cus = 0;
-            st = device_cus(&cus);
-            if (st != LPQ_OK) return st;
-            bool mid = M > 16;
-            int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
-            if (!mid && a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
-            if (mid || (M > 12 && a.n_lin == 1 && tiles != 5)) {
-                mid_plan(a, cus, partial_bytes / sizeof(float));
-                mid = mid || a.lin[0].aux == 1;
-            }
-            const int forced = g_rows_tiles.load();
-            if (!mid) {
-                if (forced >= 2 && forced <= 5 && forced != tiles) tiles = forced, splits1 = 0;
-                for (int i = 0; i < a.n_lin; ++i)
-                    if ((a.lin[i].N / 16) % rows_group_tiles(a.lin[i].variant, tiles) != 0) tiles = 4, splits1 = 0;    // groups must tile every linear exactly
-            }
-            int64_t blocks = 0, row_blocks = 0, partial_floats = 0;
-            for (int i = 0; i < a.n_lin; ++i) row_blocks += a.lin[i].N / 16 / rows_group_tiles(a.lin[i].variant, tiles);
-            for (int i = 0; i < a.n_lin; ++i) {
-                LinDesc& L = a.lin[i];
-                if (!mid) {
-                    // K splits (L.aux) of a launch of several linears: only if it leaves most compute units without a
-                    // workgroup, and only down to 32 steps per workgroup
-                    const int KT = L.kt;
-                    const int want = (int)std::max<int64_t>(1, 320 / std::max<int64_t>(1, row_blocks));
-                    L.aux = splits1 > 0 ? splits1 : std::max(1, std::min(std::min(want, KT / 32), 8));
-                }
-                L.step_weight = (uint32_t)partial_floats;                 // float offset of this linear's partial sums
-                if (L.aux > 1) partial_floats += (int64_t)L.aux * M * L.N;
-                L.cum_weight = (uint64_t)blocks;
-                blocks += (int64_t)(mid ? mid_superblocks(L, a.row_tiles) : rows_row_blocks(L, tiles)) * L.aux;
-            }
-            if (blocks > 0x7fffffffLL || partial_floats > 0x7fffffffLL) return LPQ_ERR_UNSUPPORTED;
-            if (partial_floats) {
-                st = workspace(static_ws, (size_t)partial_floats * sizeof(float), &ws);
-                if (st != LPQ_OK) return st;
-            }
-            a.partial = ws;
-            a.n_blocks = (int32_t)blocks;
-            if (!mid) {
-                a.row_tiles = tiles;
-                a.waves = blocks <= 64 ? 8 : 4;          // very few blocks: more waves per block keep more loads in flight
-                for (int i = 0; i < a.n_lin; ++i)
-                    if (prefill && a.lin[i].variant == 3) a.lin[i].variant = V_I8_SIGNED;
-            }
-            if ((mid ? launch_decode_mid(a, stream) : launch_decode_rows(a, stream)) != hipSuccess) return LPQ_ERR_DEVICE;
+    for (DecodeLaunch& p : plan) {
+        p.a.partial = ws;
+        if (p.workspace_bytes > p.partial_bytes)
+            p.a.prep = reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(ws) + p.partial_bytes);
+        if (p.kernel != DECODE_EVEN_SHARE) {
+            if ((p.kernel == DECODE_MID ? launch_decode_mid(p.a, stream) : launch_decode_rows(p.a, stream)) != hipSuccess) return LPQ_ERR_DEVICE;
             continue;
         }
-        // A small launch (one linear of a decoder layer) is not cut into more ranges than it has chunks of
-        // steps: thinner ranges stream no faster and only multiply the pieces the fix-up pass has to add.
-        const int min_steps = M <= 16 ? 16 : 8;              // a 64-token step is 3x as long
-        int64_t steps = 0;
-        for (int i = 0; i < a.n_lin; ++i) steps += (int64_t)lin_row_superblocks(a.lin[i], waves) * a.lin[i].kt;
-        a.n_blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(n_blocks, steps / min_steps));
-        a.range_q = a.total_weight / (uint64_t)a.n_blocks;
-        a.range_rem = (uint32_t)(a.total_weight % (uint64_t)a.n_blocks);
-        if (in_place)
-            for (int i = 0; i < a.n_lin; ++i)
-                if (a.lin[i].variant == 0) a.lin[i].variant = V_W3_INPLACE;
         for (int m0 = 0; m0 < M; m0 += 64) {
-            a.m0 = m0;
-            if (launch_decode(a, stream) != hipSuccess) return LPQ_ERR_DEVICE;
+            p.a.m0 = m0;
+            if (launch_decode(p.a, stream) != hipSuccess) return LPQ_ERR_DEVICE;
         }
     }
     return LPQ_OK;

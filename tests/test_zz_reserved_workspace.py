@@ -1,6 +1,6 @@
 """A workspace reservation that is too small for the splits' partial results (in a process of its own: a reservation holds until the
 process ends): prefill linears and decode attention run unsplit with the same results, a call that cannot do without it
-returns LPQ_ERR_BUFSIZE."""
+returns LPQ_ERR_BUFSIZE and launches nothing, also where only its second launch needs the space."""
 import os
 import subprocess
 import sys
@@ -37,8 +37,41 @@ print("reserved ok")
 """
 
 
+# Two launches of 26 linears: the first needs no workspace, the second (K = 8192 on few rows) splits K and does.
+CHILD_REFUSED = r"""
+import torch
+import paper_2403_01136_amd as lpq
+lpq.lpq_workspace_reserve(256)
+dev = torch.device("cuda")
+def weight(K): return lpq.lpq_quantize_pack(torch.randn((64, K), device=dev).half(), 4, 1)
+small, large = weight(128), weight(8192)
+layers = [{n: small if i < 7 else large for n in lpq.LINEARS} for i in range(13)]
+for M in (8, 20):
+    x = {K: torch.randn((M, K), device=dev).half() for K in (128, 8192)}
+    xs = [{n: x[layer[n].K] for n in lpq.LINEARS} for layer in layers]
+    ys = [{n: torch.full((M, 64), float("nan"), dtype=torch.float16, device=dev) for n in lpq.LINEARS} for _ in layers]
+    try:
+        lpq.lpq_stage_linears(lpq.Stage(layers, xs, ys), lpq.LPQ_DECODE)
+        raise SystemExit("%d rows ran without their workspace" % M)
+    except lpq.LpqError as e:
+        assert e.status == 6, e
+    torch.cuda.synchronize()
+    assert all(bool(torch.isnan(y).all()) for d in ys for y in d.values()), "%d rows: a refused call wrote outputs" % M
+print("reserved ok")
+"""
+
+
+def run_child(code):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "reserved ok" in r.stdout, r.stdout + r.stderr
+
+
 @pytest.mark.gpu
 def test_small_reservation_runs_unsplit():
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    r = subprocess.run([sys.executable, "-c", CHILD], cwd=root, capture_output=True, text=True, timeout=100)
-    assert r.returncode == 0 and "reserved ok" in r.stdout, r.stdout + r.stderr
+    run_child(CHILD)
+
+
+@pytest.mark.gpu
+def test_small_reservation_refuses_before_the_first_launch():
+    run_child(CHILD_REFUSED)
