@@ -383,6 +383,21 @@ size_t lpq_workspace_bytes(void);
  * Errors: SHAPE. */
 lpq_status lpq_set_decode_routing(int32_t rows_max_mib, int32_t rows_tiles);
 
+/* The kernels that a call of the linears `descs` takes under those settings, as one grouped launch (n <= 48), on a device of
+ * compute_units units with room for its workspace: a pure function (host only, touches no device), for tests that must
+ * reach a certain kernel.  Errors: NULL, BITS, SCHEME, SHAPE, UNSUPPORTED (as the call). */
+enum { LPQ_ROUTE_EVEN_SHARE = 0,     /* decode: even shares of the streamed bytes                            */
+       LPQ_ROUTE_ROWS = 1,           /* small launches, up to 16 rows                                        */
+       LPQ_ROUTE_MID = 2,            /* small launches, 13 to 64 rows                                        */
+       LPQ_ROUTE_PREFILL = 3 };
+typedef struct {
+    int32_t kernel;                  /* LPQ_ROUTE_*                                                          */
+    int32_t tiles;                   /* ROWS: 16-row tiles, MID: 64-row blocks per workgroup; PREFILL, n = 1: tokens per tile */
+    int32_t splits;                  /* the most K splits of a linear (1: none; PREFILL: for n = 1)          */
+    int32_t whole_tiles;             /* PREFILL, n = 1: tiles that are not split                             */
+} lpq_route;
+lpq_status lpq_route_of(const lpq_qdesc *descs, int32_t n, lpq_phase phase, int32_t M, int32_t compute_units, lpq_route *out);
+
 /* Test helper, not on the hot path: w_fp32[n][k] = scale * code + zero (fp32 multiply, then
  * fp32 add; the fp16 weight itself for LPQ_FP16) read back from the packed buffers.
  *   w_fp32: device float [N][K].  Errors: NULL, BITS, SCHEME, SHAPE, ALIGN, DEVICE. */

@@ -315,7 +315,7 @@ bool small_launch(const std::vector<LinearCall>& calls, size_t begin, size_t end
 
 // One grouped decode launch: its arguments (without the workspace's addresses), the kernel it takes and the bytes of
 // workspace it needs.
-enum DecodeKernel { DECODE_EVEN_SHARE = 0, DECODE_ROWS = 1, DECODE_MID = 2 };
+enum DecodeKernel { DECODE_EVEN_SHARE = LPQ_ROUTE_EVEN_SHARE, DECODE_ROWS = LPQ_ROUTE_ROWS, DECODE_MID = LPQ_ROUTE_MID };
 struct DecodeLaunch {
     DecodeArgs a;
     DecodeKernel kernel;
@@ -385,11 +385,11 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
         bool mid = M > 16;
         int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
         if (!mid && a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
-        if (mid || (M > 12 && a.n_lin == 1 && tiles != 5)) {
+        const int forced = g_rows_tiles.load();
+        if (mid || (M > 12 && a.n_lin == 1 && tiles != 5 && forced == 0)) {
             mid_plan(a, cus, partial_bytes / sizeof(float));
             mid = mid || a.lin[0].aux == 1;
         }
-        const int forced = g_rows_tiles.load();
         if (!mid) {
             if (forced >= 2 && forced <= 5 && forced != tiles) tiles = forced, splits1 = 0;
             for (int i = 0; i < a.n_lin; ++i)
@@ -606,6 +606,17 @@ lpq_status run_prefill_rows(const std::vector<LinearCall>& calls, int32_t M, int
     return LPQ_OK;
 }
 
+// Whether a prefill call goes to the decode kernels for small launches.  Up to 64 rows a 128-token tile is at least half empty, and
+// those kernels hold all rows at once: at 40 rows, 4 bit, 5120 -> 15360 23.5 us against 31.1, 8 bit 7168 -> 21504 38 against 81; at
+// 9 rows 13 against 27 and 30 against 79.  A single linear of up to 16 rows goes there however large it is: not to the
+// even-share kernel, whose offset 8-bit codes cost a prefill call precision.  (What the workspace or the descriptors do not
+// hold takes the prefill kernels, and so does everything while lpq_set_decode_routing keeps launches away from those kernels.)
+bool prefill_takes_decode(const std::vector<LinearCall>& calls, int32_t M)
+{
+    return M <= 64 && calls.size() <= MAX_LIN_PER_LAUNCH &&
+           (small_launch(calls, 0, calls.size(), M) || (M <= 16 && calls.size() == 1 && g_rows_max_mb.load() > 0));
+}
+
 // Prefill-phase dispatch.  Tokens per tile: 256 as a rule: weights are fetched and unpacked once per token block.  A call of at most 128 rows
 // has one block either way and takes 128-token tiles (half the matrix instructions per step).  A call of 1024 rows
 // or more whose last block of 256 would hold at most 128 rows pays a full tile of matrix instructions for that block
@@ -616,13 +627,7 @@ lpq_status run_prefill_rows(const std::vector<LinearCall>& calls, int32_t M, int
 lpq_status run_prefill(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false)
 {
     const int32_t tail = M % 256, body = M - tail;
-    // Up to 64 rows a 128-token tile is at least half empty, and the decode kernels for launches that stream little hold all
-    // rows at once: at 40 rows, 4 bit, 5120 -> 15360 23.5 us against 31.1, 8 bit 7168 -> 21504 38 against 81; at 9 rows 13 against
-    // 27 and 30 against 79.  A single linear of up to 16 rows goes there however large it is: not to the even-share kernel,
-    // whose offset 8-bit codes cost a prefill call precision.  (What the workspace or the descriptors do not hold stays here,
-    // and so does everything while lpq_set_decode_routing keeps launches away from those kernels.)
-    if (M <= 64 && calls.size() <= MAX_LIN_PER_LAUNCH &&
-        (small_launch(calls, 0, calls.size(), M) || (M <= 16 && calls.size() == 1 && g_rows_max_mb.load() > 0))) {
+    if (prefill_takes_decode(calls, M)) {
         const lpq_status st = run_decode(calls, M, stream, static_ws, true);
         if (st != LPQ_ERR_BUFSIZE && st != LPQ_ERR_UNSUPPORTED) return st;
     }
@@ -939,6 +944,39 @@ lpq_status lpq_set_decode_routing(int32_t rows_max_mib, int32_t rows_tiles)
     if (rows_max_mib > 4096 || (rows_tiles > 0 && (rows_tiles < 2 || rows_tiles > 5))) return LPQ_ERR_SHAPE;
     g_rows_max_mb.store(rows_max_mib < 0 ? 192 : rows_max_mib);
     g_rows_tiles.store(rows_tiles < 0 ? 0 : rows_tiles);
+    return LPQ_OK;
+}
+
+lpq_status lpq_route_of(const lpq_qdesc* descs, int32_t n, lpq_phase phase, int32_t M, int32_t compute_units, lpq_route* out)
+{
+    if (!descs || !out) return LPQ_ERR_NULL;
+    if (n < 1 || n > MAX_LIN_PER_LAUNCH || M < 1 || compute_units < 1 || (phase != LPQ_DECODE && phase != LPQ_PREFILL)) return LPQ_ERR_SHAPE;
+    std::vector<lpq_qweight> w((size_t)n);
+    std::vector<LinearCall> calls((size_t)n);
+    for (int i = 0; i < n; ++i) {
+        const lpq_status st = check_desc(&descs[i]);
+        if (st != LPQ_OK) return st;
+        w[i] = lpq_qweight{descs[i], nullptr, nullptr, nullptr, nullptr};
+        calls[i] = LinearCall{&w[i], nullptr, nullptr};
+    }
+    *out = lpq_route{LPQ_ROUTE_PREFILL, 0, 1, 0};
+    if (phase == LPQ_PREFILL && !prefill_takes_decode(calls, M)) {
+        if (n > 1) return LPQ_OK;
+        const int bm = M <= 128 ? 128 : 256;                             // of the body, where a tail is launched apart
+        const int32_t rows = M >= 1024 && M % 256 <= 128 ? M - M % 256 : M;
+        const int tiles = (rows + bm - 1) / bm * ((descs[0].N + 255) / 256);
+        out->tiles = bm;
+        prefill_k_splits(variant_of(descs[0]), tiles, descs[0].K / 128, rows, descs[0].N, compute_units, true, &out->whole_tiles, &out->splits);
+        if (out->splits == 1) out->whole_tiles = tiles;
+        return LPQ_OK;
+    }
+    std::vector<DecodeLaunch> plan(1);
+    const lpq_status st = plan_decode(calls, 0, calls.size(), M, compute_units, phase == LPQ_PREFILL, &plan[0]);
+    if (st != LPQ_OK) return st;
+    out->kernel = plan[0].kernel;
+    if (plan[0].kernel == DECODE_EVEN_SHARE) return LPQ_OK;
+    out->tiles = plan[0].a.row_tiles;
+    for (int i = 0; i < n; ++i) out->splits = std::max(out->splits, plan[0].a.lin[i].aux);
     return LPQ_OK;
 }
 

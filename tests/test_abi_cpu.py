@@ -182,3 +182,51 @@ def test_decode_routing_arguments():
     for mib, tiles in ((5000, 0), (192, 1), (192, 6)):
         assert lib.lpq_set_decode_routing(mib, tiles) == 4
     assert lib.lpq_set_decode_routing(-1, -1) == 0
+
+
+ROUTE_SHAPES = [(K, N) for K in (128, 384, 640, 768, 2048, 5120, 20480, 57344) for N in (64, 320, 768, 2304, 5120, 15360, 36864)]
+
+
+def test_a_forced_group_size_holds_up_to_16_rows():
+    """lpq_set_decode_routing(-1, T): every small launch of up to 16 rows takes the kernel for those rows with T tiles per workgroup (4 where T
+    does not divide the linear's tiles, fp16 weights at most 2), also at 13 to 16 rows, where the library may choose otherwise."""
+    try:
+        for T in (2, 3, 4, 5):
+            lpq.lpq_set_decode_routing(-1, T)
+            for bits, scheme in ((3, 1), (4, 1), (8, 1), (8, 2), (16, 0)):
+                for K, N in ROUTE_SHAPES:
+                    if K * N * bits // 8 > 192 << 20:
+                        continue
+                    rt = 2 if bits == 16 and T > 2 else T
+                    want = T if N // 16 % rt == 0 else 4
+                    for M in (1, 12, 13, 16):
+                        kernel, tiles, _, _ = lpq.lpq_route_of([(bits, scheme, K, N)], lpq.LPQ_DECODE, M)
+                        assert (kernel, tiles) == (lpq.LPQ_ROUTE_ROWS, want), (T, bits, scheme, K, N, M)
+    finally:
+        lpq.lpq_set_decode_routing(-1, -1)
+
+
+def test_routes():
+    """The families a call can take, by phase, rows and size, and what lpq_set_decode_routing(0, 0) does to them."""
+    small, large = [(4, 1, 5120, 15360)], [(4, 1, 14336, 57344)] * 4
+    kernel = lambda d, phase, M: lpq.lpq_route_of(d, phase, M)[0]
+    for M in (1, 8, 12):
+        assert kernel(small, lpq.LPQ_DECODE, M) == kernel(small, lpq.LPQ_PREFILL, M) == lpq.LPQ_ROUTE_ROWS
+    for M in (17, 32, 33, 64):
+        assert kernel(small, lpq.LPQ_DECODE, M) == kernel(small, lpq.LPQ_PREFILL, M) == lpq.LPQ_ROUTE_MID
+    assert kernel(small, lpq.LPQ_DECODE, 65) == lpq.LPQ_ROUTE_EVEN_SHARE and kernel(small, lpq.LPQ_PREFILL, 65) == lpq.LPQ_ROUTE_PREFILL
+    for M in (1, 16, 17, 64):
+        assert kernel(large, lpq.LPQ_DECODE, M) == lpq.LPQ_ROUTE_EVEN_SHARE and kernel(large, lpq.LPQ_PREFILL, M) == lpq.LPQ_ROUTE_PREFILL
+    assert kernel(large[:1], lpq.LPQ_PREFILL, 12) == lpq.LPQ_ROUTE_ROWS              # a single linear, however large
+    try:
+        lpq.lpq_set_decode_routing(0, 0)
+        for M in (1, 16, 17, 64):
+            assert kernel(small, lpq.LPQ_DECODE, M) == lpq.LPQ_ROUTE_EVEN_SHARE and kernel(small, lpq.LPQ_PREFILL, M) == lpq.LPQ_ROUTE_PREFILL
+    finally:
+        lpq.lpq_set_decode_routing(-1, -1)
+    lib, r, d = lpq.load_library(), lpq.lpq_route(), lpq.make_desc(4, 1, 128, 64)
+    assert lib.lpq_route_of(None, 1, 1, 1, 256, ctypes.byref(r)) == 1 and lib.lpq_route_of(ctypes.byref(d), 1, 1, 1, 256, None) == 1
+    for n, phase, M, cus in ((0, 1, 1, 256), (49, 1, 1, 256), (1, 1, 0, 256), (1, 1, 1, 0), (1, 2, 1, 256)):
+        assert lib.lpq_route_of(ctypes.byref(d), n, phase, M, cus, ctypes.byref(r)) == 4
+    d = lpq.make_desc(4, 1, 65536 * 128, 64)
+    assert lib.lpq_route_of(ctypes.byref(d), 1, 1, 1, 256, ctypes.byref(r)) == 8
