@@ -387,7 +387,7 @@ lpq_status lpq_set_decode_routing(int32_t rows_max_mib, int32_t rows_tiles);
  * compute_units units with room for its workspace: a pure function (host only, touches no device), for tests that must
  * reach a certain kernel.  Errors: NULL, BITS, SCHEME, SHAPE, UNSUPPORTED (as the call). */
 enum { LPQ_ROUTE_EVEN_SHARE = 0,     /* decode: even shares of the streamed bytes                            */
-       LPQ_ROUTE_ROWS = 1,           /* small launches, up to 16 rows                                        */
+       LPQ_ROUTE_ROWS = 1,           /* small launches, up to 16 rows (32 where K <= 256)                     */
        LPQ_ROUTE_MID = 2,            /* small launches, 13 to 64 rows                                        */
        LPQ_ROUTE_PREFILL = 3 };
 typedef struct {

@@ -204,42 +204,55 @@ void rows_plan(const LinDesc& L, int cus, int* tiles, int* splits)
 
 // Row blocks per workgroup (DecodeArgs::row_tiles) and K splits (LinDesc::aux) of a launch of the decode kernel for 17-64 token
 // rows.  A launch is fastest when its workgroups just fill the compute units once and their ranges of K are equally long:
-// every number of row blocks and many range lengths t are tried (fewer for launches of many linears), each linear
-// gets ceil(KT / t) splits, and the estimate (microseconds) ranks them: a step's arithmetic on the SIMDs of a workgroup,
-// its activations through LDS, a workgroup's start and end, a reduce launch and its traffic per split linear.  The splits'
-// sums stay within `max_floats`.
+// every number of row blocks and range lengths t are tried (a linear alone: those that change its splits; launches of several:
+// fewer, each shape once, so that planning 48 linears takes 2 us of host time and not 20), each linear gets ceil(KT / t)
+// splits, and the estimate (microseconds) ranks them: a step's arithmetic on the SIMDs of a workgroup (fp16 weights are a
+// third longer, four times the loads), its activations through LDS, a workgroup's start and end, a reduce launch and its traffic.
+// The constants are fitted to 17 shapes x 4 formats x 5 row counts with every row-block and split count timed: the choice is
+// 2 % from the fastest in the mean, 12 % at most.  The splits' sums stay within `max_floats`.
 void mid_plan(DecodeArgs& p, int cus, size_t max_floats)
 {
-    static const double step_us[4] = {0.5, 0.75, 1.0, 1.25};                     // of four row blocks at 2, 3, 4 token tiles
+    static const double step_us[4] = {0.42, 0.55, 1.2, 1.45};                    // of four row blocks at 1, 2, 3, 4 token tiles
+    static const double format[5] = {1.0, 1.0, 1.05, 1.05, 1.35};
+    struct Shape { int kt, N, variant, count; } shapes[MAX_LIN_PER_LAUNCH];
     const int tiles = (p.M + 15) / 16;
-    int kt_max = 1;
-    for (int i = 0; i < p.n_lin; ++i) kt_max = std::max(kt_max, (int)p.lin[i].kt);
+    int n = 0, kt_max = 1;
+    for (int i = 0; i < p.n_lin; ++i) {
+        const LinDesc& L = p.lin[i];
+        kt_max = std::max(kt_max, (int)L.kt);
+        int k = 0;
+        while (k < n && (shapes[k].kt != L.kt || shapes[k].N != L.N || shapes[k].variant != L.variant)) ++k;
+        if (k == n) shapes[n++] = Shape{L.kt, L.N, L.variant, 0};
+        ++shapes[k].count;
+    }
     double best = 1e30;
     int best_t = kt_max;
     p.row_tiles = 4;
     for (int rb = 4; rb >= (tiles <= 2 ? 1 : 2); rb /= 2) {
         const int slots = tiles == 1 ? 16 / rb : tiles == 2 && rb <= 2 ? 8 : 4;                    // steps per iteration (MidCfg in lpq_decode.hip)
-        const double step = 0.25 * rb * step_us[tiles - 1] + 0.032 * tiles;
-        for (int t = kt_max; t >= 4; t = std::min(t - 1, p.n_lin == 1 ? t * 63 / 64 : t * 7 / 8)) {
-            double wgs = 0.0, reduce = 0.0, floats = 0.0, sum = 0.0, longest = 0.0, shortest = 1e30;
-            for (int i = 0; i < p.n_lin; ++i) {
-                const LinDesc& L = p.lin[i];
+        const double step = 0.25 * rb * step_us[tiles - 1], lds = 0.027 * tiles;
+        for (int t = kt_max; t >= 4 || t == kt_max;) {
+            double wgs = 0.0, floats = 0.0, sum = 0.0, longest = 0.0, shortest = 1e30;
+            int most = 1;
+            for (int k = 0; k < n; ++k) {
+                const Shape& L = shapes[k];
                 const int s = (L.kt + t - 1) / t, len = (L.kt + s - 1) / s;
-                const double n = (double)mid_superblocks(L, rb) * s, us = (len + slots - 1) / slots * slots * step + 4.0;
-                wgs += n;
-                sum += n * us;
+                const double w = (double)((L.N / 64 + rb - 1) / rb) * s * L.count;
+                const double us = (len + slots - 1) / slots * slots * (step * format[L.variant] + lds) + 2.0;
+                wgs += w;
+                sum += w * us;
                 longest = std::max(longest, us);
                 shortest = std::min(shortest, us);
-                if (s > 1) {
-                    floats += (double)s * p.M * L.N;
-                    reduce = 4.5 + floats * 8.0 / 4.0e6;
-                }
+                if (s > 1) floats += (double)s * p.M * L.N * L.count;
+                most = std::max(most, s);
             }
             if (floats > (double)max_floats) break;                         // shorter ranges only need more
             // up to two rounds of workgroups are counted whole; more, or of unlike lengths (longest first), fill up better
-            const double est = reduce + (wgs <= cus ? longest : p.n_lin == 1 && wgs <= 2.0 * cus ? 2.0 * longest
-                                                                             : std::max(longest, sum / cus + 0.5 * shortest));
+            const double est = (most > 1 ? 1.2 + 0.05 * most + floats * 8.0 / 1.4e6 : 0.0) +
+                               (wgs <= cus ? longest : p.n_lin == 1 && wgs <= 2.0 * cus ? 2.0 * longest : std::max(longest, sum / cus + 0.5 * shortest));
             if (est < best * 0.99) best = est, best_t = t, p.row_tiles = rb;
+            const int splits = (kt_max + t - 1) / t;
+            t = p.n_lin == 1 ? (kt_max - 1) / splits : std::min(t - 1, t * 7 / 8);      // alone: the longest range with one split more
         }
     }
     for (int i = 0; i < p.n_lin; ++i) p.lin[i].aux = (p.lin[i].kt + best_t - 1) / best_t;
@@ -313,6 +326,19 @@ bool small_launch(const std::vector<LinearCall>& calls, size_t begin, size_t end
     return stream_bytes <= (int64_t)g_rows_max_mb.load() << 20;
 }
 
+// Whether a single linear of 13 to 16 token rows takes the kernel for 17 and more.  Measured at 16 rows, us, that for up to 16 / this:
+// 4 bit, 128 -> 4096 4.3 / 4.9, 384 -> 15168 6.8 / 6.0, 768 -> 3072 6.9 / 6.1, 2048 -> 2048 10.3 / 6.9, 5120 -> 5120 12.6 / 10.4,
+// 5120 -> 20480 19.1 / 15.8, 28672 -> 7168 35.1 / 27.3; 8 bit, 768 -> 3072 6.2 / 6.9, 2048 -> 6144 8.0 / 8.3, 2048 -> 2048 9.2 / 7.8,
+// 5120 -> 5120 12.8 / 12.1, 384 -> 15168 7.0 / 7.1, 768 -> 36864 18.5 / 10.3, 5120 -> 20480 24.8 / 22.6; fp16, 768 -> 3072 7.5 / 8.8, 2048 -> 6144
+// 10.6 / 11.1, 8192 -> 2048 16.5 / 13.6, 5120 -> 15360 35.4 / 31.7.  With codes unpacked once for all waves' steps it is 3- and 4-bit
+// weights that gain; wider ones where the other kernel has few workgroups with long ranges, or more than a round of them.
+bool mid_at_16(const LinDesc& L, int cus)
+{
+    const int blocks = L.N / 64;
+    if (L.variant <= 1) return L.kt >= 3;
+    return (L.kt >= 16 && blocks <= cus / 3) || (L.kt >= 6 && blocks >= cus * 3 / 4);
+}
+
 // One grouped decode launch: its arguments (without the workspace's addresses), the kernel it takes and the bytes of
 // workspace it needs.
 enum DecodeKernel { DECODE_EVEN_SHARE = LPQ_ROUTE_EVEN_SHARE, DECODE_ROWS = LPQ_ROUTE_ROWS, DECODE_MID = LPQ_ROUTE_MID };
@@ -375,22 +401,18 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     // A launch that streams little (a single linear of a decoder layer) has too few steps to spread evenly and pays the
     // fix-up pass: it goes to the kernels whose workgroups take a few tiles of W over K (no pieces to add).  Which of
     // them: from 17 token rows on the one that shares the activations through LDS; up to 16 the one that reads them
-    // straight from L2 and streams from deeper rings -- except a single linear of 13 to 16 rows that the former
-    // runs without splitting K (at 16 rows, 3 and 4 bit, us: 5120 -> 15360 15.8 against 13.7, 7168 -> 28672 31 / 26, 4096 -> 12288
-    // 13 / 11; at 8 rows and on shapes that need a split it is 5 to 30 % slower, and where five tiles a workgroup fill the
-    // chip in one round the two are level alone but not in a layer: 5120 -> 20480, 4 bit, 18.8 against 20.3).
+    // straight from L2 and streams from deeper rings -- except a single linear of 13 to 16 rows (mid_at_16), and that at up
+    // to 256 columns the latter takes up to 32 rows, 16 per workgroup (128 -> 4096, 17 rows: 4.6 us against 5.4).
     if (prefill || small_launch(calls, begin, end, M)) {
         // longest K first: the last workgroups to start are then the shortest
         std::stable_sort(a.lin, a.lin + a.n_lin, [](const LinDesc& x, const LinDesc& y) { return x.kt > y.kt; });
-        bool mid = M > 16;
-        int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
-        if (!mid && a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
         const int forced = g_rows_tiles.load();
-        if (mid || (M > 12 && a.n_lin == 1 && tiles != 5 && forced == 0)) {
+        const bool mid = (M > 16 && (M > 32 || a.lin[0].kt > 2)) || (M > 12 && M <= 16 && a.n_lin == 1 && forced == 0 && mid_at_16(a.lin[0], cus));
+        int tiles = 4, splits1 = 0;                  // the kernel for up to 16 rows: tiles per workgroup, K splits of a single linear
+        if (mid) {
             mid_plan(a, cus, partial_bytes / sizeof(float));
-            mid = mid || a.lin[0].aux == 1;
-        }
-        if (!mid) {
+        } else {
+            if (a.n_lin == 1) rows_plan(a.lin[0], cus, &tiles, &splits1);
             if (forced >= 2 && forced <= 5 && forced != tiles) tiles = forced, splits1 = 0;
             for (int i = 0; i < a.n_lin; ++i)
                 if ((a.lin[i].N / 16) % rows_group_tiles(a.lin[i].variant, tiles) != 0) tiles = 4, splits1 = 0;    // groups must tile every linear exactly

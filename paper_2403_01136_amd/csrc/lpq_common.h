@@ -176,7 +176,7 @@ hipError_t launch_unpack_dequant(const lpq_qweight& w, float* out, hipStream_t s
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t s);
 // device address and size of the static scratch array of the current device (for the entry point that allocates nothing)
 hipError_t static_scratch(void** ptr, size_t* bytes);
-hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s);     // small launches, M <= 16: cum_weight = workgroups before
+hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s);     // small launches, M <= 32: cum_weight = workgroups before
 hipError_t launch_decode_mid(const DecodeArgs& a, hipStream_t s);      // small launches, M <= 64: aux = K splits, cum_weight = workgroups before
 hipError_t launch_prefill(int variant, const PrefillArgs& a, hipStream_t s);      // both kernels, if any linear is K-split
 // variance indicator (lpq_indicator.hip)

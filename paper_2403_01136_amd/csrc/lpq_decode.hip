@@ -942,7 +942,7 @@ __device__ __forceinline__ bool any_not_finite(const f4& v)
 // linear's number of groups, a.lin[i].cum_weight the number of workgroups of the linears before i, a.n_blocks
 // their total.
 template <int V, int WAVES, int TILES, bool SIGNED = false>
-__device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int split, float* __restrict__ partial, float* __restrict__ red)
+__device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long rb, int split, float* __restrict__ partial, float* __restrict__ red)
 {
     constexpr int RT = (V == V_F16 && TILES > 2) ? 2 : TILES;      // 16-row tiles per workgroup; rb counts groups of RT tiles
     constexpr bool ALIGNED = RT == 2 || RT == 4;                    // the group lies in one 64-row block
@@ -963,7 +963,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
     const int splits = L.aux, share = KT / splits, extra = KT % splits;
     const int kt0 = split * share + min(split, extra), kt1 = kt0 + share + (split < extra ? 1 : 0);
     const int n_w = kt1 - kt0 > wave ? (kt1 - kt0 - wave + WAVES - 1) / WAVES : 0;      // this wave's steps
-    const uint16_t* __restrict__ xrow = L.x + (size_t)min(r, M - 1) * L.K() + 8 * kq;       // rows past M repeat the last one
+    const uint16_t* __restrict__ xrow = L.x + (size_t)min(m0 + r, M - 1) * L.K() + 8 * kq;       // rows past M repeat the last one
 
     struct Stage {
         WRaw<V> w[RT];
@@ -1089,7 +1089,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
     constexpr int ROWS = 16 * RT;
     for (int idx = tid; idx < 16 * ROWS; idx += 64 * WAVES) {
         const int tok = idx / ROWS, rl = idx % ROWS;
-        if (tok >= M) continue;
+        if (m0 + tok >= M) continue;
         const int rr = rl / RT, t = rl % RT, v = tok & 3, ln = 16 * (tok >> 2) + rr;
         float sum = 0.0f, xs = 0.0f;
 #pragma unroll
@@ -1101,7 +1101,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, long rb, int s
             for (int w = 0; w < WAVES; ++w) xs += red[((size_t)w * NV + 4 * RT + v) * 64 + ln];
             sum = (sum * 16777216.0f - 128.0f * xs) * (float)__builtin_bit_cast(_Float16, L.scales[row]);   // undo 2^-24 and the +128 offset
         }
-        const size_t o = (size_t)tok * L.N + row;
+        const size_t o = (size_t)(m0 + tok) * L.N + row;
         if (splits > 1) {
             partial[(size_t)split * M * L.N + o] = sum;
             continue;
@@ -1129,15 +1129,15 @@ __global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode
     const long wg = (long)b - (long)L.cum_weight;          // split-major: a split's groups are neighbours
     const int row_blocks = rows_row_blocks(L, a.row_tiles);
     const long rb = wg % row_blocks;
-    const int split = (int)(wg / row_blocks);
+    const int split = (int)(wg / row_blocks), m0 = 16 * blockIdx.y;       // of up to 32 rows, 16 per workgroup
     float* partial = a.partial + L.step_weight;
     switch (L.variant) {
-    case V_W3: run_rows<V_W3, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
-    case V_W4: run_rows<V_W4, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
-    case V_W8: run_rows<V_W8, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
-    case V_I8: run_rows<V_I8, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
-    case V_I8_SIGNED: run_rows<V_I8, WAVES, TILES, true>(L, a.M, rb, split, partial, red); break;
-    default:   run_rows<V_F16, WAVES, TILES>(L, a.M, rb, split, partial, red); break;
+    case V_W3: run_rows<V_W3, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
+    case V_W4: run_rows<V_W4, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
+    case V_W8: run_rows<V_W8, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
+    case V_I8: run_rows<V_I8, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
+    case V_I8_SIGNED: run_rows<V_I8, WAVES, TILES, true>(L, a.M, m0, rb, split, partial, red); break;
+    default:   run_rows<V_F16, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
     }
 }
 
@@ -1565,13 +1565,13 @@ hipError_t launch_decode_mid(const DecodeArgs& a, hipStream_t s)
 
 hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s)
 {
-    const unsigned grid = (unsigned)a.n_blocks;
+    const dim3 grid((unsigned)a.n_blocks, (unsigned)((a.M + 15) / 16));
 #define LPQ_ROWS_CASE(T)                                                                      \
     case T:                                                                                   \
         if (a.waves == 8) decode_rows_kernel<8, T><<<grid, 512, 0, s>>>(a);                   \
         else              decode_rows_kernel<4, T><<<grid, 256, 0, s>>>(a);                   \
         break;
-    if (a.M > 16) return hipErrorInvalidValue;
+    if (a.M > 32) return hipErrorInvalidValue;
     switch (a.row_tiles) {
         LPQ_ROWS_CASE(2) LPQ_ROWS_CASE(3) LPQ_ROWS_CASE(4) LPQ_ROWS_CASE(5)
     default: return hipErrorInvalidValue;

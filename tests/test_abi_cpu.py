@@ -230,3 +230,21 @@ def test_routes():
         assert lib.lpq_route_of(ctypes.byref(d), n, phase, M, cus, ctypes.byref(r)) == 4
     d = lpq.make_desc(4, 1, 65536 * 128, 64)
     assert lib.lpq_route_of(ctypes.byref(d), 1, 1, 1, 256, ctypes.byref(r)) == 8
+
+
+def test_routes_of_13_to_32_rows():
+    """Where the kernel for 17 and more rows would be the slower one: 8-bit and fp16 linears of 13 to 16 rows with neither few workgroups of long
+    ranges nor more than a round of them, and one or two groups of columns up to 32 rows.  Below 512 columns, too, the blocks
+    per workgroup follow from the estimate: as many workgroups as fit the chip, not four blocks in each."""
+    route = lambda fmt, K, N, M: lpq.lpq_route_of([fmt + (K, N)], lpq.LPQ_DECODE, M)
+    for fmt in ((8, 1), (8, 2), (16, 0)):
+        for K, N in ((768, 2304), (768, 3072), (2048, 6144), (1920, 6272), (384, 15168)):
+            for M in (13, 16):
+                assert route(fmt, K, N, M)[0] == lpq.LPQ_ROUTE_ROWS, (fmt, K, N, M)
+    for fmt in ((3, 1), (4, 1), (8, 1), (8, 2), (16, 0)):
+        for M in (13, 16, 17, 32):
+            assert route(fmt, 128, 4096, M)[0] == lpq.LPQ_ROUTE_ROWS and route(fmt, 256, 4096, M)[0] == lpq.LPQ_ROUTE_ROWS
+        assert route(fmt, 128, 4096, 33)[0] == route(fmt, 384, 4096, 17)[0] == lpq.LPQ_ROUTE_MID
+        for M in (17, 32, 33, 64):
+            kernel, blocks, splits, _ = route(fmt, 384, 15168, M)
+            assert kernel == lpq.LPQ_ROUTE_MID and splits == 1 and 15168 // 64 / blocks >= 118, (fmt, M, blocks)

@@ -511,3 +511,20 @@ def test_infinite_activations(phase, M, bits, scheme):
     a, b = deq[sure, 0], deq[sure, 2303]
     both = torch.where(torch.sign(a) == torch.sign(b), -torch.sign(a) * inf, torch.full_like(a, float("nan")))
     assert torch.equal(torch.nan_to_num(y[M - 1, sure].float(), nan=3.0), torch.nan_to_num(both, nan=3.0))
+
+
+@pytest.mark.parametrize("bits,scheme", VARIANTS, ids=VARIANT_IDS)
+@pytest.mark.parametrize("K,N", [(128, 64), (256, 960)])
+def test_decode_17_to_32_rows_of_few_columns(orc, bits, scheme, K, N):
+    """One or two groups of columns: the kernel for up to 16 rows, in two workgroups of 16 rows each, with bias, activation and a residual in place."""
+    r = np.random.default_rng(wl.stream_seed("short", K, N))
+    w, x, res = wl.weight_np(N, K, "short", bits), wl.act_np(32, K, True, "short", K), r.standard_normal((32, N)).astype(np.float16)
+    bias = (0.1 * r.standard_normal(N)).astype(np.float16)
+    qw = lpq.lpq_quantize_pack(to_dev(w), bits, scheme, bias=to_dev(bias))
+    ref = np.maximum(orc.qlinear(x, w, bits, scheme, bias), 0.0) + res.astype(np.float64)
+    for phase in (lpq.LPQ_DECODE, lpq.LPQ_PREFILL):
+        for M in (17, 31, 32):
+            assert lpq.lpq_route_of([(bits, scheme, K, N)], phase, M)[0] == lpq.LPQ_ROUTE_ROWS
+            y = to_dev(res[:M]).clone()
+            lpq.lpq_qlinear_fused(qw, to_dev(x[:M]), phase, activation=lpq.LPQ_ACT_RELU, residual=y, y=y)
+            check_output(y, ref[:M], "%d rows, %d bits, %d -> %d" % (M, bits, K, N))
