@@ -364,7 +364,7 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     a.n_blocks = n_blocks;
     a.slot_floats = tok_rows * waves * 64;
     a.row_tiles = 4;
-    a.pad = 0;
+    a.prefill = prefill;
     a.partial = nullptr;
     a.prep = nullptr;
     const size_t partial_bytes = ((size_t)2 * n_blocks * a.slot_floats * sizeof(float) + 255) & ~(size_t)255;
@@ -432,7 +432,6 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
             if (L.aux > 1) partial_floats += (int64_t)L.aux * M * L.N;
             L.cum_weight = (uint64_t)blocks;
             blocks += (int64_t)(mid ? mid_superblocks(L, a.row_tiles) : rows_row_blocks(L, tiles)) * L.aux;
-            if (!mid && prefill && L.variant == 3) L.variant = V_I8_SIGNED;
         }
         if (blocks > 0x7fffffffLL || partial_floats > 0x7fffffffLL) return LPQ_ERR_UNSUPPORTED;
         a.n_blocks = (int32_t)blocks;

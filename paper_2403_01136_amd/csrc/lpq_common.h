@@ -12,9 +12,8 @@ namespace lpq {
 // per-variant cost factor); `cum_weight` is the total weight of the linears before it.
 // LinDesc::variant is the storage variant (0 .. 4: 3-, 4-, 8-bit grouped, 8-bit per row, fp16) -- or, in the descriptors
 // of a stage-wide decode launch only, V_W3_INPLACE: 3-bit codes that the kernel masks where they lie, against activations scaled
-// for it beforehand (lpq_decode.hip); the host decides per launch.  V_I8_SIGNED, in a small launch of a prefill call: 8-bit per-row
-// codes multiplied as signed integers, not offset by 128.
-enum { V_W3_INPLACE = 5, V_I8_SIGNED = 6 };
+// for it beforehand (lpq_decode.hip); the host decides per launch.
+enum { V_W3_INPLACE = 5 };
 
 struct LinDesc {
     const uint8_t* codes;
@@ -30,7 +29,7 @@ struct LinDesc {
     int32_t aux;            // stage-wide kernel: offset of the linear's prepared activations in DecodeArgs::prep, in 16-byte units;
                             // small-launch kernel: number of K splits
     uint16_t kt;            // K / 128 (K < 2^23)
-    uint8_t variant;        // V_W3 .. V_F16, V_W3_INPLACE, V_I8_SIGNED
+    uint8_t variant;        // V_W3 .. V_F16, V_W3_INPLACE
     uint8_t act;            // lpq_activation applied to acc + bias (before the residual)
     __host__ __device__ int K() const { return (int)kt * 128; }
 };
@@ -45,8 +44,9 @@ enum { MAX_LIN_PER_LAUNCH = 48 };   // keeps DecodeArgs under 4 KB of kernel arg
 struct DecodeArgs {
     int32_t n_lin, M, m0, waves;         // m0: first token row of this pass (M > 64 is run 64 rows at a time)
     int32_t n_blocks, slot_floats;       // slot_floats: floats per partial tile = 64 tokens x rows per workgroup
-    int32_t row_tiles, pad;              // small-launch kernels: 16-row tiles per workgroup (2 .. 5; fp16 weights: at most 2);
-                                         // from 17 token rows on: 64-row blocks per workgroup (1, 2 or 4)
+    int32_t row_tiles, prefill;          // small-launch kernels: 16-row tiles per workgroup (2 .. 5; fp16 weights: at most 2);
+                                         // from 17 token rows on: 64-row blocks per workgroup (1, 2 or 4).  prefill: 1 for a
+                                         // prefill call's linears
     uint64_t total_weight;
     uint64_t range_q;                    // total_weight / n_blocks and
     uint32_t range_rem, pad2;            // total_weight % n_blocks: range b begins at range_q * b + range_rem * b / n_blocks

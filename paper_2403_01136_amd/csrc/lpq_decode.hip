@@ -82,7 +82,7 @@ template <int V, bool INPL> __device__ __forceinline__ h8 unpack_post(const WRaw
 // 128 * sum(x) taken off behind a wave's whole range of K, activations of one sign (a ReLU's output) make both sums hundreds of
 // times the result, and their roundings stay: 57344 -> 14336 with x ~ N(3, 1), error against 64 bits 1.3e-3, so 2.1e-4.  The packed
 // subtraction per pair costs 3-5 %; taking the offset off every few steps instead costs the same where it is as exact.  Decode launches
-// of up to 16 rows keep the offset.
+// of the kernel for up to 16 rows keep the offset.
 template <int V, bool SIGNED> __device__ __forceinline__ h8 unpack_small(const WRaw<V>& w, int j)
 {
     if constexpr (V == V_I8 && SIGNED) return unpack_codes_step<V>(w, j);
@@ -941,7 +941,7 @@ __device__ __forceinline__ bool any_not_finite(const f4& v)
 // for a small second kernel; otherwise there are no partial tiles and no second kernel.  rows_row_blocks(L, row_tiles) is the
 // linear's number of groups, a.lin[i].cum_weight the number of workgroups of the linears before i, a.n_blocks
 // their total.
-template <int V, int WAVES, int TILES, bool SIGNED = false>
+template <int V, int WAVES, int TILES, bool PREFILL>
 __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long rb, int split, float* __restrict__ partial, float* __restrict__ red)
 {
     constexpr int RT = (V == V_F16 && TILES > 2) ? 2 : TILES;      // 16-row tiles per workgroup; rb counts groups of RT tiles
@@ -952,7 +952,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
     constexpr int LOADS = RT * (VInfo<V>::TILE_BYTES >= 1024 ? VInfo<V>::TILE_BYTES / 1024 : 1) +
                           (SCHEME == SCH_ASYM ? (ALIGNED ? 2 : 4) : 0) + 4;
     static_assert((STAGES - 1) * LOADS < 64, "vmcnt is a 6-bit counter");
-    constexpr bool OFFSET = SCHEME == SCH_SYM && !SIGNED;       // codes are multiplied as code + 128
+    constexpr bool OFFSET = SCHEME == SCH_SYM && !PREFILL;      // codes are multiplied as code + 128
     constexpr int NV = (RT + (OFFSET ? 1 : 0)) * 4;   // floats a lane hands to the reduction
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // a scalar: the row block and the tile addresses derive from it
@@ -1003,7 +1003,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
             const f4 zero4 = {0, 0, 0, 0};
             f4 d[RT], xs;
 #pragma unroll
-            for (int t = 0; t < RT; ++t) wj[0][t] = unpack_small<V, SIGNED>(b.w[t], 0);
+            for (int t = 0; t < RT; ++t) wj[0][t] = unpack_small<V, PREFILL>(b.w[t], 0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 // one scheduling group per tile: its matrix instructions of step j and the unpacking of the same tile
@@ -1013,7 +1013,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int t = 0; t < RT; ++t) {
-                    if (j < 3) wj[(j + 1) & 1][t] = unpack_small<V, SIGNED>(b.w[t], j + 1);
+                    if (j < 3) wj[(j + 1) & 1][t] = unpack_small<V, PREFILL>(b.w[t], j + 1);
                     if constexpr (SCHEME == SCH_ASYM) d[t] = mfma16(b.a[j], wj[j & 1][t], j == 0 ? zero4 : d[t]);
                     else                               acc[t] = mfma16(b.a[j], wj[j & 1][t], acc[t]);
                     __builtin_amdgcn_sched_barrier(0);
@@ -1058,7 +1058,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
         }
     }
 
-    if constexpr (POST && !SIGNED) {
+    if constexpr (PREFILL && SCHEME == SCH_ASYM) {
         if (__builtin_expect(any_not_finite(acc[0]), 0)) {       // a token's sums are finite in all tiles or in none
 #pragma unroll 1
             for (int t = 0; t < RT; ++t) {
@@ -1067,11 +1067,8 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
                 for (int u = 0; u < RT; ++u)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (u == t && !__builtin_isfinite(acc[u][v])) acc[u][v] = SCHEME == SCH_SYM ? sum[v] / 16777216.0f : sum[v];
+                        if (u == t && !__builtin_isfinite(acc[u][v])) acc[u][v] = sum[v];
             }
-            if constexpr (OFFSET)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) xsum[v] = __builtin_isfinite(xsum[v]) ? xsum[v] : 0.0f;
         }
     }
 
@@ -1095,7 +1092,7 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) sum += red[((size_t)w * NV + 4 * t + v) * 64 + ln];
         const long row = ((g0 + t) >> 2) * 64 + 4 * rr + ((g0 + t) & 3);
-        if constexpr (SIGNED) sum *= (float)__builtin_bit_cast(_Float16, L.scales[row]);
+        if constexpr (SCHEME == SCH_SYM && PREFILL) sum *= (float)__builtin_bit_cast(_Float16, L.scales[row]);
         if constexpr (OFFSET) {
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) xs += red[((size_t)w * NV + 4 * RT + v) * 64 + ln];
@@ -1115,7 +1112,8 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
 
 // Two workgroups of four waves per compute unit; five tiles of W fill the 256 registers of that occupancy: that
 // kernel takes up to 512 registers per lane and one four-wave workgroup per unit.
-template <int WAVES, int TILES>
+// PREFILL: for a prefill call (a.prefill), which keeps what the prefill kernels give it: exact 8-bit codes, infinities.
+template <int WAVES, int TILES, bool PREFILL>
 __global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode_rows_kernel(const DecodeArgs a)
 {
     __shared__ float red[WAVES * (TILES + 1) * 4 * 64];
@@ -1132,12 +1130,11 @@ __global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode
     const int split = (int)(wg / row_blocks), m0 = 16 * blockIdx.y;       // of up to 32 rows, 16 per workgroup
     float* partial = a.partial + L.step_weight;
     switch (L.variant) {
-    case V_W3: run_rows<V_W3, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
-    case V_W4: run_rows<V_W4, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
-    case V_W8: run_rows<V_W8, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
-    case V_I8: run_rows<V_I8, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
-    case V_I8_SIGNED: run_rows<V_I8, WAVES, TILES, true>(L, a.M, m0, rb, split, partial, red); break;
-    default:   run_rows<V_F16, WAVES, TILES>(L, a.M, m0, rb, split, partial, red); break;
+    case V_W3: run_rows<V_W3, WAVES, TILES, PREFILL>(L, a.M, m0, rb, split, partial, red); break;
+    case V_W4: run_rows<V_W4, WAVES, TILES, PREFILL>(L, a.M, m0, rb, split, partial, red); break;
+    case V_W8: run_rows<V_W8, WAVES, TILES, PREFILL>(L, a.M, m0, rb, split, partial, red); break;
+    case V_I8: run_rows<V_I8, WAVES, TILES, PREFILL>(L, a.M, m0, rb, split, partial, red); break;
+    default:   run_rows<V_F16, WAVES, TILES, PREFILL>(L, a.M, m0, rb, split, partial, red); break;
     }
 }
 
@@ -1568,8 +1565,13 @@ hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s)
     const dim3 grid((unsigned)a.n_blocks, (unsigned)((a.M + 15) / 16));
 #define LPQ_ROWS_CASE(T)                                                                      \
     case T:                                                                                   \
-        if (a.waves == 8) decode_rows_kernel<8, T><<<grid, 512, 0, s>>>(a);                   \
-        else              decode_rows_kernel<4, T><<<grid, 256, 0, s>>>(a);                   \
+        if (a.prefill) {                                                                      \
+            if (a.waves == 8) decode_rows_kernel<8, T, true><<<grid, 512, 0, s>>>(a);         \
+            else              decode_rows_kernel<4, T, true><<<grid, 256, 0, s>>>(a);         \
+        } else {                                                                              \
+            if (a.waves == 8) decode_rows_kernel<8, T, false><<<grid, 512, 0, s>>>(a);        \
+            else              decode_rows_kernel<4, T, false><<<grid, 256, 0, s>>>(a);        \
+        }                                                                                     \
         break;
     if (a.M > 32) return hipErrorInvalidValue;
     switch (a.row_tiles) {
