@@ -83,9 +83,10 @@ struct PrefillLin {
     // their fp32 sums in partial[split][M][split_cols(L)]; a second kernel adds the splits in order and applies bias,
     // activation, residual and the one rounding.  Tiles are then numbered token block fastest and the work units (whole tiles; behind
     // them (tile, split) pairs) are dealt out to the XCDs in eight equal contiguous shares, whatever the
-    // numbers of token and row blocks (prefill_split_unit); token_groups is not used.  With up to two token blocks a tile's splits
-    // are neighbours; with more, a split's tiles are, so that an XCD reads a range of K of the activations only (4-bit
-    // 28672 -> 7168 at 1191 rows 488 us against 526; 2048 -> 8192 at 200 rows 35 against 32).
+    // numbers of token and row blocks (prefill_split_unit); token_groups is not used.  Where an XCD's L2 (4 MB) holds the activations, a
+    // tile's splits are neighbours; where it does not, a split's tiles are, so that an XCD reads a range of K of the activations
+    // only.  Neighbouring splits / tiles, us: 2.9 MB, 4 bit, 2048 -> 6144 at 700 rows 38.1 / 39.9, fp16, 2048 -> 2048 at 700 30.1 / 32.3; 3.7 MB,
+    // 4 bit, 28672 -> 7168 at 65 63.4 / 65.3; 4.3 MB, 7168 -> 21504 at 300 155.6 / 151.3; 17 MB, 28672 -> 7168 at 300 186.1 / 181.0, 8 bit 201.5 / 197.8.
     float* partial;
     int32_t k_splits, whole_tiles;
 };
@@ -108,7 +109,7 @@ __host__ __device__ inline PrefillShare prefill_split_share(const PrefillLin& L,
 }
 
 // Work unit l of XCD x: its tile, and its split (-1: the whole tile); false past the end of the share.
-__host__ __device__ inline bool prefill_split_unit(const PrefillLin& L, int m_blocks, int x, int l, int* tile_m, int* tile_n, int* split)
+__host__ __device__ inline bool prefill_split_unit(const PrefillLin& L, int M, int m_blocks, int x, int l, int* tile_m, int* tile_n, int* split)
 {
     const PrefillShare s = prefill_split_share(L, m_blocks, x);
     int tile = s.whole0 + l;
@@ -116,8 +117,8 @@ __host__ __device__ inline bool prefill_split_unit(const PrefillLin& L, int m_bl
     if (l >= s.whole) {
         if (l - s.whole >= s.units) return false;
         const int u = s.unit0 + l - s.whole, rest = m_blocks * L.n_blocks - L.whole_tiles;
-        if (m_blocks > 2) *split = u / rest, tile = L.whole_tiles + u % rest;
-        else              *split = u % L.k_splits, tile = L.whole_tiles + u / L.k_splits;
+        if ((long)M * L.K * 2 > (4L << 20)) *split = u / rest, tile = L.whole_tiles + u % rest;
+        else                                *split = u % L.k_splits, tile = L.whole_tiles + u / L.k_splits;
     }
     *tile_m = tile % m_blocks;
     *tile_n = tile / m_blocks;

@@ -68,7 +68,7 @@ void prefill_kernel(const PrefillArgs a)
     const int m_blocks = (M + BM - 1) / BM;
     int tile_m, tile_n, split = -1;                  // split -1: all of K
     if (SPLIT && L.k_splits > 1) {
-        if (!prefill_split_unit(L, m_blocks, tile & 7, tile >> 3, &tile_m, &tile_n, &split)) return;
+        if (!prefill_split_unit(L, M, m_blocks, tile & 7, tile >> 3, &tile_m, &tile_n, &split)) return;
     } else if (!prefill_xcd_tile(m_blocks, L.n_blocks, L.token_groups, tile & 7, tile >> 3, &tile_m, &tile_n)) return;
     constexpr int SCHEME = VInfo<V>::SCHEME;
     constexpr int NW = 4;                           // 16-row tiles per wave = one 64-row block
@@ -412,7 +412,7 @@ void prefill_ring_kernel(const PrefillArgs a)
     const int m_blocks = (M + BM - 1) / BM;
     int tile_m, tile_n, split = -1;                  // split -1: all of K
     if (SPLIT && L.k_splits > 1) {
-        if (!prefill_split_unit(L, m_blocks, tile & 7, tile >> 3, &tile_m, &tile_n, &split)) return;
+        if (!prefill_split_unit(L, M, m_blocks, tile & 7, tile >> 3, &tile_m, &tile_n, &split)) return;
     } else if (!prefill_xcd_tile(m_blocks, L.n_blocks, L.token_groups, tile & 7, tile >> 3, &tile_m, &tile_n)) return;
     constexpr int SCHEME = VInfo<V>::SCHEME;
     constexpr bool DMA_W = (V == V_F16);             // weights go to LDS as they are
@@ -698,10 +698,12 @@ __global__ __launch_bounds__(256) void prefill_reduce_kernel(const PrefillArgs a
     const int m_blocks = (a.M + a.tokens_per_tile - 1) / a.tokens_per_tile;
     const int first = split_first_block(L, m_blocks), cols = split_cols(L, m_blocks);
     const int m_split = L.whole_tiles - first * m_blocks;      // in row block `first`, the token blocks before this one are whole
-    const size_t quads = (size_t)a.M * cols / 4, plane = (size_t)a.M * cols;
-    for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < quads; q += (size_t)gridDim.x * 256) {
-        const size_t e = 4 * q;
-        const int tok = (int)(e / cols), c = (int)(e % cols), n = 256 * first + c;
+    const size_t plane = (size_t)a.M * cols;
+    // fewer than two rounds of tiles are split (prefill_k_splits): 32 bits hold every index
+    const uint32_t row = (uint32_t)cols / 4, quads = (uint32_t)a.M * row;
+    for (uint32_t q = blockIdx.x * 256 + threadIdx.x; q < quads; q += gridDim.x * 256) {
+        const uint32_t e = 4 * q;
+        const int tok = (int)(q / row), c = 4 * (int)(q % row), n = 256 * first + c;
         if (c < 256 && tok / a.tokens_per_tile < m_split) continue;
         f4 sum = *reinterpret_cast<const f4*>(L.partial + e);
         for (int sp = 1; sp < L.k_splits; ++sp) sum += *reinterpret_cast<const f4*>(L.partial + sp * plane + e);
