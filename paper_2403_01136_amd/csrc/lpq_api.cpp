@@ -521,14 +521,13 @@ int prefill_token_groups(int m_blocks, int n_blocks)
 }
 
 // K splits of one prefill linear that is launched with too few tiles to fill the chip (a single linear of a decoder layer at a
-// small micro-batch): *whole tiles are computed as they are -- full rounds of the compute units, if the launch has this
-// linear only --, the rest in *splits ranges of K.  Estimated time in units of one 128-column step of a tile (about 4.1 us):
+// small micro-batch): *whole tiles are computed as they are -- full rounds of the compute units --, the rest in *splits ranges of K.  Estimated time in units of one 128-column step of a tile (about 4.1 us):
 // rounds of workgroups times steps per workgroup, a round that is not full at 0.85 + 0.15 of its share (the chip is
 // power-limited: fewer busy units run faster), plus the fp32 partial sums written and read (8 bytes per element and split,
 // 8 TB/s, most of it served by the caches) and the second kernel's launch.  4 bit, us before (all tiles split alike, an XCD's share
 // a rectangle of tiles, so shares up to a fifth out of balance) and now: 5120 -> 15360 at 1191 rows 280 / 209, 20480 -> 5120 at 1191
 // 320 / 250 and at 700 244 / 150, 5120 -> 5120 at 700 86 / 56, 7168 -> 21504 at 200 129 / 86.
-void prefill_k_splits(int variant, int tiles, int KT, int32_t M, int32_t N, int cus, bool alone, int* whole, int* splits)
+void prefill_k_splits(int variant, int tiles, int KT, int32_t M, int32_t N, int cus, int* whole, int* splits)
 {
     *whole = 0;
     *splits = 1;
@@ -540,13 +539,43 @@ void prefill_k_splits(int variant, int tiles, int KT, int32_t M, int32_t N, int 
     // a split must pay clearly in the eight-wave kernel (160 tiles of 40 steps: 3 and 4 bit 4 % faster split, 8 bit and fp16 slower)
     double best = rounds(tiles) * KT * (variant <= 1 ? 1.0 : 0.97);
     const double tile_elements = (double)M * N / tiles;
-    for (int w = 0; w < tiles && (w == 0 || alone); w += cus)
+    for (int w = 0; w < tiles; w += cus)
         for (int s = 2; s <= 8 && KT / s >= 8; ++s) {                      // keep the pipeline's fill and drain small
             const int rest = tiles - w;
             const double cost = (double)(w / cus) * KT + rounds((double)rest * s) * ((KT + s - 1) / s) + 1.5 +
                                 8.0 * s * tile_elements * rest / 8.0e12 / 4.1e-6;
             if (cost < best) best = cost, *whole = w, *splits = s;
         }
+}
+
+// Splits of a linear of KT steps at about t steps each: at most 8, of at least 8 steps (the pipeline's fill and drain stay small).
+int prefill_range_splits(int KT, int t) { return std::max(1, std::min(std::min((KT + t - 1) / t, 8), KT / 8)); }
+
+// Steps of K per work unit in a launch of several linears with too few tiles: every linear is cut in ceil(KT / t) splits.  Estimated
+// as above: the longest unit, or the launch's steps dealt out over the units of the chip with half a unit left over at the end,
+// plus each split linear's traffic and reduce launch.  (Each linear judged by itself against the launch's rounds cut a 5120-wide
+// layer's second feed-forward linear in 7 at 500 rows, and the others in 2: 1538 us for a layer each of 3, 8, 8 and 16 bit, 1441 cut
+// in 2 all of them, 1313 now; 2048-wide at 100 rows 170, 249 cut in 3 and 2, 160 now; 2048-wide, four layers of 4 bit at 100 rows 131, now 92.)
+int prefill_range(const std::vector<const LinearCall*>& mine, size_t first, size_t last, int m_blocks, int32_t M, int cus)
+{
+    int kt_max = 1, best_t = 0;
+    for (size_t i = first; i < last; ++i) kt_max = std::max(kt_max, mine[i]->w->d.K / 128);
+    double best = 1e30;
+    for (int t = kt_max; t >= 8; t = std::min(t - 1, t * 7 / 8)) {
+        double units = 0.0, steps = 0.0, longest = 0.0, extra = 0.0;
+        for (size_t i = first; i < last; ++i) {
+            const lpq_qdesc& d = mine[i]->w->d;
+            const int KT = d.K / 128, s = prefill_range_splits(KT, t);
+            const double n = (double)m_blocks * ((d.N + 255) / 256);
+            units += n * s;
+            steps += n * KT;
+            longest = std::max(longest, (double)((KT + s - 1) / s));
+            if (s > 1) extra += 1.5 + 8.0 * s * (double)M * d.N / 8.0e12 / 4.1e-6;
+        }
+        const double est = (units <= cus ? longest : std::max(longest, steps / cus + 0.5 * longest)) + extra;
+        if (est < best * 0.97) best = est, best_t = t;
+    }
+    return std::max(best_t, 8);
 }
 
 // Prefill-phase dispatch of a list of independent linears: one grouped launch per storage variant
@@ -572,9 +601,11 @@ lpq_status run_prefill_rows(const std::vector<LinearCall>& calls, int32_t M, int
                 a.tokens_per_tile = BM;
                 long tiles = 0, launch_tiles = 0;
                 size_t partial_floats = 0;
-                for (size_t i = first; i < std::min(mine.size(), first + (size_t)MAX_PREFILL_LIN); ++i)
-                    launch_tiles += (long)m_blocks * ((mine[i]->w->d.N + 255) / 256);
-                for (size_t i = first; i < std::min(mine.size(), first + (size_t)MAX_PREFILL_LIN); ++i) {
+                const size_t last = std::min(mine.size(), first + (size_t)MAX_PREFILL_LIN);
+                for (size_t i = first; i < last; ++i) launch_tiles += (long)m_blocks * ((mine[i]->w->d.N + 255) / 256);
+                const bool few = split && launch_tiles < 2L * cus;
+                const int range = few && last - first > 1 ? prefill_range(mine, first, last, m_blocks, M, cus) : 0;
+                for (size_t i = first; i < last; ++i) {
                     const lpq_qweight& w = *mine[i]->w;
                     PrefillLin& L = a.lin[a.n_lin++];
                     L.codes = static_cast<const uint8_t*>(w.codes);
@@ -593,8 +624,8 @@ lpq_status run_prefill_rows(const std::vector<LinearCall>& calls, int32_t M, int
                     // splitting is judged per launch: a launch with many tiles fills the chip whatever its linears' shapes
                     L.whole_tiles = 0;
                     L.k_splits = 1;
-                    if (split && launch_tiles < 2L * cus)
-                        prefill_k_splits(variant, (int)launch_tiles, w.d.K / 128, M, w.d.N, cus, mine.size() == 1, &L.whole_tiles, &L.k_splits);
+                    if (range) L.k_splits = prefill_range_splits(w.d.K / 128, range);
+                    else if (few) prefill_k_splits(variant, (int)launch_tiles, w.d.K / 128, M, w.d.N, cus, &L.whole_tiles, &L.k_splits);
                     L.partial = nullptr;
                     if (L.k_splits > 1) {
                         partial_floats += (size_t)L.k_splits * M * split_cols(L, m_blocks);
@@ -987,7 +1018,7 @@ lpq_status lpq_route_of(const lpq_qdesc* descs, int32_t n, lpq_phase phase, int3
         const int32_t rows = M >= 1024 && M % 256 <= 128 ? M - M % 256 : M;
         const int tiles = (rows + bm - 1) / bm * ((descs[0].N + 255) / 256);
         out->tiles = bm;
-        prefill_k_splits(variant_of(descs[0]), tiles, descs[0].K / 128, rows, descs[0].N, compute_units, true, &out->whole_tiles, &out->splits);
+        prefill_k_splits(variant_of(descs[0]), tiles, descs[0].K / 128, rows, descs[0].N, compute_units, &out->whole_tiles, &out->splits);
         if (out->splits == 1) out->whole_tiles = tiles;
         return LPQ_OK;
     }

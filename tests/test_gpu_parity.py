@@ -528,3 +528,29 @@ def test_decode_17_to_32_rows_of_few_columns(orc, bits, scheme, K, N):
             y = to_dev(res[:M]).clone()
             lpq.lpq_qlinear_fused(qw, to_dev(x[:M]), phase, activation=lpq.LPQ_ACT_RELU, residual=y, y=y)
             check_output(y, ref[:M], "%d rows, %d bits, %d -> %d" % (M, bits, K, N))
+
+
+def _prefill_reference(qw, x, bias):
+    """The dequantised weights times x, in 64 bits on the GPU."""
+    return (x.double() @ lpq.lpq_unpack_dequant(qw).double().t() + bias.double()).cpu().numpy()
+
+
+@pytest.mark.parametrize("bits,scheme", VARIANTS, ids=VARIANT_IDS)
+@pytest.mark.parametrize("M", [100, 300])
+def test_prefill_layer_split_over_k(bits, scheme, M):
+    """The four linears of a layer in one launch of few tiles: ranges of K of about one length for all, the long second feed-forward linear
+    in several, the others in one or two."""
+    import torch
+    h, f = 1088, 4352                                     # no multiples of 256
+    gen = torch.Generator(device="cuda").manual_seed(M + bits)
+    shapes = {"qkv": (1152, 3 * h), "out": (1152, h), "fc1": (1152, f), "fc2": (f, h)}
+    layer, xs, ys, ref = {}, {}, {}, {}
+    for n, (K, N) in shapes.items():
+        bias = torch.randn((N,), generator=gen, device="cuda").half()
+        layer[n] = lpq.lpq_quantize_pack((torch.randn((N, K), generator=gen, device="cuda") * 0.02).half(), bits, scheme, bias=bias)
+        xs[n] = torch.randn((M, K), generator=gen, device="cuda").half()
+        ys[n] = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+        ref[n] = _prefill_reference(layer[n], xs[n], bias)
+    lpq.lpq_stage_linears(lpq.Stage([layer], [xs], [ys]), lpq.LPQ_PREFILL)
+    for n in shapes:
+        check_output(ys[n], ref[n], "%s, %d rows" % (n, M))
