@@ -430,13 +430,16 @@ def test_decode_17_to_64_rows_stage_of_unlike_linears(orc, M):
 
 
 @pytest.mark.parametrize("bits,scheme", [(4, 1), (8, 2), (16, 0)], ids=["w4", "i8", "f16"])
-@pytest.mark.parametrize("M,N,K", [(700, 23104, 2048), (1191, 14912, 2048), (40, 71744, 2048), (256, 320, 4224), (300, 1088, 3200)])
+@pytest.mark.parametrize("M,N,K", [(700, 23104, 2048), (1191, 14912, 2048), (100, 71744, 2048), (256, 320, 4224), (300, 1088, 3200), (300, 1088, 8192), (700, 1088, 4096)])
 def test_prefill_whole_and_split_tiles(orc, bits, scheme, M, N, K):
     """Linears with more tiles than the chip has compute units but fewer than twice as many (full rounds of whole tiles, the rest split over
     K: the border runs through a row block when the token blocks do not divide it), and with fewer (all split), N that is no multiple of
-    256 and ragged token blocks: every output written exactly once.  Every output against an fp32 product of the dequantised weights
+    256 and ragged token blocks: every output written exactly once; 256 tokens to a tile, and 128 (100 rows).  Activations below and above 4 MB, where the order of
+    the work units changes, with up to two token blocks and more.  Every output against an fp32 product of the dequantised weights
     (both sides round fp32 sums once: the file's tolerance), the rows around the border and the last ones against the oracle."""
     import torch
+    kernel, tile, splits, whole = lpq.lpq_route_of([(bits, scheme, K, N)], lpq.LPQ_PREFILL, M)
+    assert kernel == lpq.LPQ_ROUTE_PREFILL and tile == (128 if M <= 128 else 256) and splits > 1 and (whole > 0) == (N > 10000)
     gen = torch.Generator(device="cuda").manual_seed(N + bits)
     w = (torch.randn((N, K), generator=gen, device="cuda") * 0.02).half()
     x = torch.randn((M, K), generator=gen, device="cuda").half()
@@ -536,6 +539,38 @@ def _prefill_reference(qw, x, bias):
 
 
 @pytest.mark.parametrize("bits,scheme", VARIANTS, ids=VARIANT_IDS)
+@pytest.mark.parametrize("M", [65, 100, 127])
+@pytest.mark.parametrize("N,K", [(320, 640), (320, 8192), (320, 4224)])
+def test_prefill_128_token_tiles(orc, bits, scheme, M, N, K):
+    """65 to 127 rows, the ragged 128-token tile: whole, split over K (two numbers of steps, one that no split count divides), a bias added once."""
+    kernel, tile, splits, _ = lpq.lpq_route_of([(bits, scheme, K, N)], lpq.LPQ_PREFILL, M)
+    assert (kernel, tile) == (lpq.LPQ_ROUTE_PREFILL, 128) and (splits > 1) == (K > 2048)
+    w, x = wl.weight_np(N, K, "pre128", bits, scheme), wl.act_np(M, K, True, "pre128", M)
+    bias = (np.arange(N) % 5 - 2).astype(np.float16)
+    y = lpq.lpq_qlinear_prefill(lpq.lpq_quantize_pack(to_dev(w), bits, scheme, bias=to_dev(bias)), to_dev(x))
+    check_output(y, orc.qlinear(x, w, bits, scheme, bias), "prefill %d rows" % M)
+
+
+@pytest.mark.parametrize("bits,scheme", VARIANTS, ids=VARIANT_IDS)
+@pytest.mark.parametrize("M,N,K", [(1, 320, 640), (7, 320, 8192), (24, 320, 640), (40, 192, 4224), (64, 320, 640)])
+def test_prefill_kernels_up_to_64_rows(orc, bits, scheme, M, N, K):
+    """Calls of few rows that keep the prefill kernels (launches past the line of the decode kernels, longer lists of linears, no workspace):
+    reached by turning those kernels off.  Activations from 2^-12 to 2^5."""
+    w = wl.weight_np(N, K, "pre64", bits, scheme)
+    bias = (np.arange(N) % 5 - 2).astype(np.float16)
+    qw = lpq.lpq_quantize_pack(to_dev(w), bits, scheme, bias=to_dev(bias))
+    lpq.lpq_set_decode_routing(0, 0)
+    try:
+        assert lpq.lpq_route_of([(bits, scheme, K, N)], lpq.LPQ_PREFILL, M)[0] == lpq.LPQ_ROUTE_PREFILL
+        for mag in (2.0 ** -12, 1.0, 2.0 ** 5):
+            x = (wl.act_np(M, K, False, "pre64", M).astype(np.float32) * mag).astype(np.float16)
+            y = lpq.lpq_qlinear_prefill(qw, to_dev(x))
+            check_output(y, orc.qlinear(x, w, bits, scheme, bias), "prefill %d rows x*%g" % (M, mag))
+    finally:
+        lpq.lpq_set_decode_routing(-1, -1)
+
+
+@pytest.mark.parametrize("bits,scheme", VARIANTS, ids=VARIANT_IDS)
 @pytest.mark.parametrize("M", [100, 300])
 def test_prefill_layer_split_over_k(bits, scheme, M):
     """The four linears of a layer in one launch of few tiles: ranges of K of about one length for all, the long second feed-forward linear
@@ -554,3 +589,31 @@ def test_prefill_layer_split_over_k(bits, scheme, M):
     lpq.lpq_stage_linears(lpq.Stage([layer], [xs], [ys]), lpq.LPQ_PREFILL)
     for n in shapes:
         check_output(ys[n], ref[n], "%s, %d rows" % (n, M))
+
+
+MID_FORMS = [(16, 1, False, 1408, 2496), (16, 1, True, 2432, 3200), (16, 2, False, 1152, 16448), (16, 2, True, 2432, 448), (16, 4, False, 1152, 32832),
+             (16, 4, True, 2432, 64), (24, 1, False, 1152, 2496), (24, 1, True, 1152, 64), (24, 2, False, 1152, 16448), (24, 2, True, 14464, 6208),
+             (24, 4, False, 1152, 32832), (24, 4, True, 9344, 16448), (40, 2, False, 1152, 8256), (40, 2, True, 1152, 64), (40, 4, False, 1152, 32832),
+             (40, 4, True, 9344, 16448), (60, 2, False, 1152, 8256), (60, 2, True, 1152, 64), (60, 4, False, 1152, 32832), (60, 4, True, 9344, 16448)]
+
+
+@pytest.mark.parametrize("M,blocks,split,K,N", MID_FORMS, ids=["M%d_rb%d_%s" % (c[0], c[1], "split" if c[2] else "whole") for c in MID_FORMS])
+@pytest.mark.parametrize("bits,scheme", [(3, 1), (4, 1), (8, 2), (16, 0)], ids=["w3", "w4", "i8", "fp16"])
+def test_decode_mid_kernel_forms(bits, scheme, M, blocks, split, K, N):
+    """Every form of the kernel for 17-64 rows (13-16 too): 1, 2 and 4 row blocks per workgroup at 1 to 4 token tiles, with and without K splits,
+    over several iterations of its loop with a ragged last one, and row blocks that do not fill the last workgroup; bias, activation
+    and a residual in place.  Against the dequantised weights in 64 bits."""
+    import torch
+    kernel, got_blocks, splits, _ = lpq.lpq_route_of([(bits, scheme, K, N)], lpq.LPQ_DECODE, M)
+    if M == 16 and kernel != lpq.LPQ_ROUTE_MID:
+        pytest.skip("this format stays with the kernel for up to 16 rows here")
+    assert kernel == lpq.LPQ_ROUTE_MID and (got_blocks, splits > 1) == (blocks, split)
+    gen = torch.Generator(device="cuda").manual_seed(K + N + bits)
+    w = (torch.randn((N, K), generator=gen, device="cuda", dtype=torch.float16) * 0.02)
+    bias = torch.randn((N,), generator=gen, device="cuda").half()
+    x, res = torch.randn((M, K), generator=gen, device="cuda").half(), torch.randn((M, N), generator=gen, device="cuda").half()
+    qw = lpq.lpq_quantize_pack(w, bits, scheme, bias=bias)
+    ref = np.maximum(_prefill_reference(qw, x, bias), 0.0) + res.double().cpu().numpy()
+    y = res.clone()
+    lpq.lpq_qlinear_fused(qw, x, lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU, residual=y, y=y)
+    check_output(y, ref, "%d rows, %d -> %d" % (M, K, N))

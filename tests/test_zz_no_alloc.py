@@ -71,21 +71,18 @@ def test_noalloc_matches_stage_linears_twice_in_a_row(orc, case, even_share):
 
 
 def test_noalloc_prefill_and_many_rows(orc):
-    """A stage-wide prefill launch needs no partial sums and runs (one that the library splits over K may be refused);
-    a decode call of 300 rows runs in passes of 64 rows, whose partial tiles the static array holds."""
+    """A stage-wide prefill call, whose K splits' sums the static array holds; a decode call of 300 rows runs in passes of 64 rows,
+    whose partial tiles it holds."""
     import torch
     h, f, specs, M = 256, 1024, [(4, 1), (16, 0)], 300
     layers, xs, host, outputs = _stage("noalloc_pre", h, f, 3 * h, specs, M)
     ys = outputs()
-    try:
-        lpq.lpq_stage_linears_noalloc(lpq.Stage(layers, xs, ys), lpq.LPQ_PREFILL)
-        torch.cuda.synchronize()
-        for li, (bits, scheme) in enumerate(specs):
-            for name in wl.LINEARS:
-                w, x = host[li][name]
-                check_output(ys[li][name], orc.qlinear(x, w, bits, scheme), "prefill layer %d %s" % (li, name))
-    except lpq.LpqError as e:            # a K-split launch: legitimately refused, never allocated
-        assert e.status == 6
+    lpq.lpq_stage_linears_noalloc(lpq.Stage(layers, xs, ys), lpq.LPQ_PREFILL)
+    torch.cuda.synchronize()
+    for li, (bits, scheme) in enumerate(specs):
+        for name in wl.LINEARS:
+            w, x = host[li][name]
+            check_output(ys[li][name], orc.qlinear(x, w, bits, scheme), "prefill layer %d %s" % (li, name))
     lpq.lpq_set_decode_routing(0, 0)
     try:
         ys = outputs()
@@ -97,6 +94,28 @@ def test_noalloc_prefill_and_many_rows(orc):
                 check_output(ys[li][name], orc.qlinear(x, w, bits, scheme), "decode 300 rows, layer %d %s" % (li, name))
     finally:
         lpq.lpq_set_decode_routing(-1, -1)
+
+
+def test_noalloc_prefill_runs_unsplit_where_the_sums_do_not_fit():
+    """A prefill linear whose K splits' partial sums exceed the static array (128 MiB) runs without the splits."""
+    import torch
+    lpq.load_library()
+    M, K, N = 512, 16384, 17408
+    kernel, _, splits, whole = lpq.lpq_route_of([(4, 1, K, N)], lpq.LPQ_PREFILL, M)
+    assert kernel == lpq.LPQ_ROUTE_PREFILL and whole == 0 and splits * M * N * 4 > 128 << 20
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    normal = lambda *shape: torch.randn(shape, generator=gen, device="cuda", dtype=torch.float16)
+    shapes = {"qkv": (128, 64), "out": (128, 64), "fc1": (K, N), "fc2": (128, 64)}
+    layer = {n: lpq.lpq_quantize_pack(normal(n_, k) * 0.02, *((4, 1) if n == "fc1" else (16, 0))) for n, (k, n_) in shapes.items()}
+    xs = {n: normal(M, k) for n, (k, n_) in shapes.items()}
+    ys = {n: torch.full((M, n_), float("nan"), dtype=torch.float16, device="cuda") for n, (k, n_) in shapes.items()}
+    lpq.lpq_stage_linears_noalloc(lpq.Stage([layer], [xs], [ys]), lpq.LPQ_PREFILL)
+    for n in shapes:
+        ref = torch.empty((M, shapes[n][1]), dtype=torch.float64, device="cuda")
+        deq = lpq.lpq_unpack_dequant(layer[n])
+        for r in range(0, shapes[n][1], 4096):
+            ref[:, r:r + 4096] = xs[n].double() @ deq[r:r + 4096].double().t()
+        check_output(ys[n], ref.cpu().numpy(), "prefill %s" % n)
 
 
 def test_noalloc_size_limit():
