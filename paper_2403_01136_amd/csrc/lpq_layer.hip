@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256, 4) void attention_decode_kernel(const uint16_t
     if constexpr (FRESH) {
         // Behind the tiles, by the wave with the fewest of them: ahead of them its loads and scattered stores hold the
         // stream back (43 sequences of 56 heads at 1338 positions: 314 us; so: 305; kv_append and this kernel without it: 11.8 + 287,
-        // 16 of 40 at 563: 6 + 36 against 37).
+        // 16 of 40 at 563: 6 + 36 against 37; the host takes two launches where the caches are large).
         if (split == 0 && wave == 3) {
             const h8 k = *reinterpret_cast<const h8*>(qrow + h + 8 * (lane % LPK));
             uint16_t v[LOADS];

@@ -354,3 +354,27 @@ def test_non_finite_values_of_a_later_token(d, T, pos0, bad, alibi):
     assert np.all(seen[0::3] == np.inf) and seen[1] == -np.inf
     rest = inf[bad:, :d][:, ~hit]
     assert np.linalg.norm(rest - clean[bad:, :d][:, ~hit]) <= 1e-3 * np.linalg.norm(clean[bad:, :d][:, ~hit])
+
+
+def test_decode_layer_of_large_caches_appends_ahead():
+    """A decode step over more than 1 GB of cache appends in a launch of its own: the same bits as the operators one by one, in the outputs too."""
+    import torch
+    B, H, d, f, pos0 = 34, 16, 64, 256, 8001
+    h, S, dev = H * d, (pos0 + 64) // 64 * 64, torch.device("cuda")
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    normal = lambda *shape: torch.randn(shape, generator=gen, device="cuda", dtype=torch.float16)
+    ln = [(1.0 + 0.1 * normal(h), 0.1 * normal(h)) for _ in range(2)]
+    st = lpq.LayerState(H, d, S, B, dev, *ln)
+    st.k_cache.normal_(generator=gen), st.vt_cache.normal_(generator=gen)
+    layer = {n: lpq.lpq_quantize_pack(normal(N, K) * 0.03, 4, 1) for n, (K, N) in {"qkv": (h, 3 * h), "out": (h, h), "fc1": (h, f), "fc2": (f, h)}.items()}
+    x = normal(B, h)
+    k0, v0 = st.k_cache.clone(), st.vt_cache.clone()
+    y, _ = lpq.lpq_decoder_layer(layer, st, lpq.LPQ_DECODE, B, 1, pos0, x)
+    k1, v1 = st.k_cache.clone(), st.vt_cache.clone()
+    st.k_cache.copy_(k0), st.vt_cache.copy_(v0)
+    qkv = lpq.lpq_qlinear_decode(layer["qkv"], lpq.lpq_layernorm(x, *st.ln1, 1e-5))
+    lpq.lpq_kv_append(qkv, st, B, 1, pos0)
+    assert torch.equal(k1, st.k_cache) and torch.equal(v1, st.vt_cache)
+    x1 = lpq.lpq_qlinear_fused(layer["out"], lpq.lpq_attention(qkv, st, B, 1, pos0), lpq.LPQ_DECODE, residual=x)
+    ff = lpq.lpq_qlinear_fused(layer["fc1"], lpq.lpq_layernorm(x1, *st.ln2, 1e-5), lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU)
+    assert torch.equal(y, lpq.lpq_qlinear_fused(layer["fc2"], ff, lpq.LPQ_DECODE, residual=x1))
