@@ -714,8 +714,10 @@ lpq_status run_attention(const void* qkv, const lpq_layer_cfg* cfg, const lpq_la
         return launch_attention_prefill(qkv, st->k_cache, st->vt_cache, st->alibi_slopes, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim,
                                         cfg->max_seq, out, stream) == hipSuccess ? LPQ_OK : LPQ_ERR_DEVICE;
     const int n = fresh ? pos0 : pos0 + 1;
-    int range = 0, splits = 0;
-    attention_decode_plan(n_seqs, cfg->n_heads, n, &range, &splits);
+    int range = 0, splits = 0, cus = 0;
+    const lpq_status cst = device_cus(&cus);
+    if (cst != LPQ_OK) return cst;
+    attention_decode_plan(n_seqs, cfg->n_heads, n, cus, &range, &splits);
     const size_t floats = attention_decode_workspace_floats(n_seqs, cfg->n_heads, cfg->head_dim, splits);
     float* part = nullptr;
     if (floats) {

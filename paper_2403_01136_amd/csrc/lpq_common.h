@@ -188,7 +188,7 @@ hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, 
 int layernorm_max_hidden();
 hipError_t launch_kv_append(const void* qkv, void* kc, void* vtc, int n_seqs, int T, int pos0, int H, int d, int S, hipStream_t s);
 // decode attention over n cached positions; fresh: the new token (position n) is read from qkv and written to the caches
-void attention_decode_plan(int n_seqs, int H, int n, int* range, int* splits);
+void attention_decode_plan(int n_seqs, int H, int n, int cus, int* range, int* splits);
 size_t attention_decode_workspace_floats(int n_seqs, int H, int d, int splits);
 hipError_t launch_attention_decode(const void* qkv, void* kc, void* vtc, const float* slopes, int n_seqs, int n, bool fresh, int H, int d, int S,
                                    int range, int splits, void* out, float* part, hipStream_t s);

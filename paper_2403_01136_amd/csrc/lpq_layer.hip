@@ -630,7 +630,7 @@ hipError_t launch_kv_append(const void* qkv, void* kc, void* vtc, int n_seqs, in
 // workgroup takes its tiles four at a time and about three tiles' time to start and to end; up to four workgroups share a
 // compute unit, more are dealt out as others end; a split costs the combining kernel, about four tiles' time.
 // (3 sequences of 56 heads at 6002 positions: three splits, 80 us; 43 at 1338: one, 253 us on its own.)
-void attention_decode_plan(int n_seqs, int H, int n, int* range, int* splits)
+void attention_decode_plan(int n_seqs, int H, int n, int cus, int* range, int* splits)
 {
     const long bh = (long)n_seqs * H, tiles = std::max(1, (n + 63) / 64);
     double best = 1e30;
@@ -638,7 +638,7 @@ void attention_decode_plan(int n_seqs, int H, int n, int* range, int* splits)
     *splits = 1;
     for (long sp = 1; sp <= std::min<long>(64, (tiles + 3) / 4); ++sp) {
         const long per = (tiles + sp - 1) / sp, used = (tiles + per - 1) / per, wgs = bh * used;     // splits that have any
-        const double rounds = wgs <= 1024 ? (double)((wgs + 255) / 256) : (double)wgs / 256.0 + 1.0;
+        const double rounds = wgs <= 4L * cus ? (double)((wgs + cus - 1) / cus) : (double)wgs / cus + 1.0;
         const double est = rounds * (double)((per + 3) / 4 * 4 + 3) + (used > 1 ? 4.0 : 0.0);
         if (est < best * 0.99) best = est, *range = (int)per * 64, *splits = (int)used;
     }
