@@ -142,6 +142,11 @@ struct OpMax { __device__ __forceinline__ float operator()(float a, float b) con
 
 constexpr float LOG2E = 1.4426950408889634f;
 
+// A lane's byte offset into eight feature rows of the transposed V cache: 32 bits where 14 * max_seq + 126 fits them, so that a load takes a
+// scalar base and a 32-bit offset as they are; LONG: 64 bits.
+template <bool LONG> using VOffset = typename std::conditional<LONG, uint64_t, uint32_t>::type;
+bool long_rows(int S) { return S > (1 << 28); }
+
 // ---- decode attention: one new token per sequence over the cached positions --------------------
 // HBM-bound on the cache: 2 * n * d * 2 bytes per (sequence, head).  Grid (sequences * heads, splits); a
 // workgroup takes a contiguous range of positions, its four waves take the range's tiles of 64 positions in
@@ -155,7 +160,7 @@ constexpr float LOG2E = 1.4426950408889634f;
 // caches (kv_append in the same launch).  `n`: cached positions that are read (without the new token if FRESH).
 // With several splits the unnormalised partial outputs and their (max, sum) go to a workspace and a second
 // kernel combines them.
-template <int D, bool FRESH>
+template <int D, bool FRESH, bool LONG>
 __global__ __launch_bounds__(256, 4) void attention_decode_kernel(const uint16_t* __restrict__ qkv, uint16_t* kc, uint16_t* vtc,
                                                                   const float* __restrict__ slopes, int H, int S, int n, int range, int splits,
                                                                   uint16_t* __restrict__ out, float* __restrict__ part)
@@ -195,7 +200,7 @@ __global__ __launch_bounds__(256, 4) void attention_decode_kernel(const uint16_t
     // a load's address is a scalar base and a 32-bit lane offset in bytes: key LOADS * (lane / LPK) + u of the tile;
     // feature 8 u + lane / 8, positions 8 (lane % 8) ..
     uint32_t koff = (uint32_t)((lane / LPK) * LOADS * D + 8 * (lane % LPK)) * 2u;
-    uint32_t voff = ((uint32_t)(lane / 8) * (uint32_t)S + 8u * (uint32_t)(lane % 8)) * 2u;
+    VOffset<LONG> voff = ((VOffset<LONG>)(lane / 8) * (uint32_t)S + 8u * (uint32_t)(lane % 8)) * 2u;
     auto load_k = [&](int t, int x) {
         const uint8_t* base = reinterpret_cast<const uint8_t*>(kbase + (size_t)64 * t * D);
         asm volatile("" : "+v"(koff));                 // keeps the widening to 64 bits next to the loads
@@ -402,7 +407,7 @@ __device__ __forceinline__ void attention_one_query(const uint16_t* __restrict__
     for (int i = 0; i < D / 64; ++i) op[64 * i + lane] = __builtin_bit_cast(uint16_t, (_Float16)(acc[i] / l));
 }
 
-template <int D, bool ALIBI>
+template <int D, bool ALIBI, bool LONG>
 __global__ __launch_bounds__(256, 2) void attention_prefill_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ kc,
                                                                    const uint16_t* __restrict__ vtc, const float* __restrict__ slopes,
                                                                    int BH, int H, int S, int T, int pos0, int q_blocks, uint16_t* __restrict__ out)
@@ -435,7 +440,7 @@ __global__ __launch_bounds__(256, 2) void attention_prefill_kernel(const uint16_
     // wave-uniform, r0; the swizzle's share of r0 is XOR-ed into the chunk.  V: r0 is a multiple of 8 and has no share.
     constexpr int ROWS = 512 / D;                      // keys per load
     const uint32_t kl = (uint32_t)((lane / CH) * D + 8 * ((lane % CH) ^ (swap_bits23(lane / CH) & (CH - 1)))) * 2u;
-    uint32_t vl = ((uint32_t)(lane / 8) * (uint32_t)S + 8u * (uint32_t)((lane % 8) ^ (lane / 8))) * 2u;
+    VOffset<LONG> vl = ((VOffset<LONG>)(lane / 8) * (uint32_t)S + 8u * (uint32_t)((lane % 8) ^ (lane / 8))) * 2u;
     auto fill = [&](int j, int buf) {
         const uint8_t* kb = reinterpret_cast<const uint8_t*>(kbase + (size_t)64 * j * D);
         const uint8_t* vb = reinterpret_cast<const uint8_t*>(vbase + 64 * j);
@@ -652,7 +657,11 @@ hipError_t launch_attention_decode(const void* qkv, void* kc, void* vtc, const f
     const uint16_t* q = static_cast<const uint16_t*>(qkv);
     uint16_t *k = static_cast<uint16_t*>(kc), *v = static_cast<uint16_t*>(vtc), *o = static_cast<uint16_t*>(out);
     const dim3 grid((unsigned)(n_seqs * H), (unsigned)splits);
-#define LPQ_ATT(D, F) attention_decode_kernel<D, F><<<grid, 256, 0, s>>>(q, k, v, slopes, H, S, n, range, splits, o, part)
+#define LPQ_ATT(D, F)                                                                                                        \
+    do {                                                                                                                     \
+        if (long_rows(S)) attention_decode_kernel<D, F, true><<<grid, 256, 0, s>>>(q, k, v, slopes, H, S, n, range, splits, o, part); \
+        else              attention_decode_kernel<D, F, false><<<grid, 256, 0, s>>>(q, k, v, slopes, H, S, n, range, splits, o, part); \
+    } while (0)
     if (d == 128) { if (fresh) LPQ_ATT(128, true); else LPQ_ATT(128, false); }
     else          { if (fresh) LPQ_ATT(64, true); else LPQ_ATT(64, false); }
 #undef LPQ_ATT
@@ -670,7 +679,12 @@ hipError_t launch_attention_prefill(const void* qkv, const void* kc, const void*
     uint16_t* o = static_cast<uint16_t*>(out);
     const int bh = n_seqs * H, q_blocks = (T + 127) / 128;
     const unsigned grid = 8u * (unsigned)((bh + 7) / 8) * (unsigned)q_blocks;
-#define LPQ_ATT(D, A) attention_prefill_kernel<D, A><<<grid, 256, 2 * 2 * 64 * D * 2, s>>>(q, k, v, slopes, bh, H, S, T, pos0, q_blocks, o)
+#define LPQ_ATT(D, A)                                                                                                        \
+    do {                                                                                                                     \
+        constexpr size_t smem = 2 * 2 * 64 * D * 2;                                                                          \
+        if (long_rows(S)) attention_prefill_kernel<D, A, true><<<grid, 256, smem, s>>>(q, k, v, slopes, bh, H, S, T, pos0, q_blocks, o); \
+        else              attention_prefill_kernel<D, A, false><<<grid, 256, smem, s>>>(q, k, v, slopes, bh, H, S, T, pos0, q_blocks, o); \
+    } while (0)
     if (d == 128) { if (slopes) LPQ_ATT(128, true); else LPQ_ATT(128, false); }
     else          { if (slopes) LPQ_ATT(64, true); else LPQ_ATT(64, false); }
 #undef LPQ_ATT

@@ -378,3 +378,35 @@ def test_decode_layer_of_large_caches_appends_ahead():
     x1 = lpq.lpq_qlinear_fused(layer["out"], lpq.lpq_attention(qkv, st, B, 1, pos0), lpq.LPQ_DECODE, residual=x)
     ff = lpq.lpq_qlinear_fused(layer["fc1"], lpq.lpq_layernorm(x1, *st.ln2, 1e-5), lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU)
     assert torch.equal(y, lpq.lpq_qlinear_fused(layer["fc2"], ff, lpq.LPQ_DECODE, residual=x1))
+
+
+def test_attention_over_very_long_rows():
+    """max_seq beyond 2^32 / 14: a lane's offset into eight rows of the transposed V cache no longer fits 32 bits."""
+    import torch
+    H, d, S = 1, 64, 306_783_424
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("two caches of 39 GB")
+    dev = torch.device("cuda")
+    one = torch.ones(d, dtype=torch.float16, device=dev)
+    st = lpq.LayerState(H, d, 64, 1, dev, (one, one), (one, one))
+    st.cfg.max_seq = S
+    st.k_cache = torch.empty((1, H, S, d), dtype=torch.float16, device=dev)
+    st.vt_cache = torch.empty((1, H, d, S), dtype=torch.float16, device=dev)
+    try:
+        gen = torch.Generator(device="cuda").manual_seed(2)
+        pos0, T = 100, 5
+        qkv = torch.randn((T, 3 * d), generator=gen, device=dev).half()
+        st.k_cache[0, 0, :pos0].normal_(generator=gen)
+        st.vt_cache[0, 0, :, :pos0] = torch.randn((d, pos0), generator=gen, device=dev).half()
+        for rows in (1, T):                                       # the decode kernel, the prefill kernel
+            x = qkv[:rows].contiguous()
+            lpq.lpq_kv_append(x, st, 1, rows, pos0)
+            out = lpq.lpq_attention(x, st, 1, rows, pos0).double()
+            k, v = st.k_cache[0, 0, :pos0 + rows].double(), st.vt_cache[0, 0, :, :pos0 + rows].double()
+            sc = x[:, :d].double() @ k.t() / d ** 0.5
+            sc = sc.masked_fill(torch.arange(pos0 + rows, device=dev)[None, :] > torch.arange(pos0, pos0 + rows, device=dev)[:, None], float("-inf"))
+            ref = torch.softmax(sc, 1) @ v.t()
+            assert float((out - ref).norm() / ref.norm()) <= 1e-3, rows
+    finally:
+        st.k_cache = st.vt_cache = None
+        torch.cuda.empty_cache()
