@@ -697,14 +697,14 @@ __global__ __launch_bounds__(256) void prefill_reduce_kernel(const PrefillArgs a
     const PrefillLin& L = a.lin[li];
     const int m_blocks = (a.M + a.tokens_per_tile - 1) / a.tokens_per_tile;
     const int first = split_first_block(L, m_blocks), cols = split_cols(L, m_blocks);
-    const int m_split = L.whole_tiles - first * m_blocks;      // in row block `first`, the token blocks before this one are whole
+    const int m_split = (L.whole_tiles - first * m_blocks) * a.tokens_per_tile;      // in row block `first`, the tokens before this one are in whole tiles
     const size_t plane = (size_t)a.M * cols;
     // fewer than two rounds of tiles are split (prefill_k_splits): 32 bits hold every index
     const uint32_t row = (uint32_t)cols / 4, quads = (uint32_t)a.M * row;
     for (uint32_t q = blockIdx.x * 256 + threadIdx.x; q < quads; q += gridDim.x * 256) {
         const uint32_t e = 4 * q;
         const int tok = (int)(q / row), c = 4 * (int)(q % row), n = 256 * first + c;
-        if (c < 256 && tok / a.tokens_per_tile < m_split) continue;
+        if (c < 256 && tok < m_split) continue;
         f4 sum = *reinterpret_cast<const f4*>(L.partial + e);
         for (int sp = 1; sp < L.k_splits; ++sp) sum += *reinterpret_cast<const f4*>(L.partial + sp * plane + e);
         typedef _Float16 h4 __attribute__((ext_vector_type(4)));
