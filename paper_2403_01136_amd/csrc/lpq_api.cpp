@@ -298,10 +298,10 @@ bool reads_in_place(const std::vector<LinearCall>& calls, size_t begin, size_t e
 // kernel.  That one has some 30 us of preparation, fix-up pass and partial tiles, this one a higher cost per 3- or 4-bit weight
 // (both tiles' FMAs against the zero term outside the loop; at 33-64 rows a product per group against weights
 // dequantised once), so the line lies at a number of weights; 8- and 16-bit codes cost about the same in both.  Measured, us,
-// even-share / this, at 32, 48 and 64 rows: a 4-bit layer of 5120 (315 M weights) 79 / 46, 88 / 55, 93 / 66; a 3- and a 4-bit layer
-// of 5120 (629 M) 107 / 88, 131 / 119, 138 / 139; a 3- and a 4-bit layer of 7168 (1.2 G) 163 / 156, 216 / 201, 226 / 244; a 3-bit layer of
-// 14336 (2.7 G) 250 / 305, 375 / 379, 389 / 459; 8 bit, 7168 -> 28672 77 / 42, 98 / 54, 99 / 60; an 8-bit layer of 9216 (0.85 G) 223 / 198,
-// 239 / 197, 244 / 212; fp16, 7168 -> 28672 96 / 66, 101 / 73, 106 / 75.
+// even-share / this, at 32, 48 and 64 rows: a 4-bit layer of 5120 (315 M weights) 81 / 46, 90 / 55, 93 / 65; a 3- and a 4-bit layer
+// of 5120 (629 M) 107 / 83, 131 / 109, 138 / 130; three 4-bit layers of 5120 (944 M) 143 / 128, 173 / 162, 182 / 198; a 3- and a 4-bit layer of 7168
+// (1.2 G) 165 / 149, 222 / 200, 226 / 238; a 3-bit layer of 14336 (2.5 G) 259 / 290, 381 / 370, 393 / 455; 8 bit, 7168 -> 28672 93 / 42, 110 / 48, 119 / 56;
+// an 8-bit layer of 9216 (1.0 G) 227 / 193, 244 / 220, 252 / 252; fp16, 7168 -> 28672 114 / 66, 120 / 71, 129 / 73.
 // rows_max_mib of lpq_set_decode_routing (default 192) moves the line in proportion.
 bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
 {

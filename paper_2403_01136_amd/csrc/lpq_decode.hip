@@ -1149,7 +1149,7 @@ __global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode
 // picks RB and splits K over workgroups so that these just fill the chip (mid_plan in lpq_api.cpp): RB = 4 reads the activations
 // least, RB = 1 needs no split (and no reduce kernel) where W has about as many row blocks as the chip has compute units.
 // Before, two token tiles per wave in the kernel above, and two passes of it from 33 rows on.  One linear, 3 bit, us before and
-// now: 7168 -> 21504 at 32 rows 50 / 31, at 43 rows 75 / 35, at 64 rows 97 / 43; 5120 -> 5120 at 43 rows 28 / 18.
+// now: 7168 -> 21504 at 32 rows 48 / 25, at 64 rows 95 / 40; 5120 -> 5120 at 64 rows 36 / 18.
 template <int MT, int RB> struct MidCfg {
     enum { KW = 8 / RB, C = MT == 1 ? 2 : MT == 2 ? (RB == 1 ? 1 : 2) : (RB == 4 ? 2 : 1), SLOTS = KW * C };     // SLOTS * MT <= 16: 128 KB of LDS
     static constexpr size_t SMEM = (size_t)2 * SLOTS * 16 * MT * 256;

@@ -139,7 +139,7 @@ def test_other_configs_whole_stage(orc, ci):
 @pytest.mark.parametrize("bits,scheme", [(3, 1), (4, 1), (8, 1), (8, 2), (16, 0)], ids=["w3", "w4", "w8", "i8", "f16"])
 def test_single_linear_launches_at_layer_shapes(orc, bits, scheme):
     """One linear per launch, as a decoder layer issues them (OPT-13B shapes): the decode phase then runs in the
-    small-launch kernel (a workgroup per group of 2-5 tiles, one or two token tiles; FC2 K-split with its reduce kernel), the prefill phase K-splits
+    small-launch kernels (2-5 tiles of W per workgroup, or a few row blocks; K splits with their reduce kernel), the prefill phase K-splits
     the launches with few tiles.  Sampled bands and tokens against the oracle, one projection over every column."""
     import torch
     cfg = wl.CONFIGS[1]
