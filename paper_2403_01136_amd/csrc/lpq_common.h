@@ -83,10 +83,11 @@ struct PrefillLin {
     // their fp32 sums in partial[split][M][split_cols(L)]; a second kernel adds the splits in order and applies bias,
     // activation, residual and the one rounding.  Tiles are then numbered token block fastest and the work units (whole tiles; behind
     // them (tile, split) pairs) are dealt out to the XCDs in eight equal contiguous shares, whatever the
-    // numbers of token and row blocks (prefill_split_unit); token_groups is not used.  Where an XCD's L2 (4 MB) holds the activations, a
-    // tile's splits are neighbours; where it does not, a split's tiles are, so that an XCD reads a range of K of the activations
-    // only.  Neighbouring splits / tiles, us: 2.9 MB, 4 bit, 2048 -> 6144 at 700 rows 38.1 / 39.9, fp16, 2048 -> 2048 at 700 30.1 / 32.3; 3.7 MB,
-    // 4 bit, 28672 -> 7168 at 65 63.4 / 65.3; 4.3 MB, 7168 -> 21504 at 300 155.6 / 151.3; 17 MB, 28672 -> 7168 at 300 186.1 / 181.0, 8 bit 201.5 / 197.8.
+    // numbers of token and row blocks (prefill_split_unit); token_groups is not used.  A tile's splits are neighbours; but where an
+    // XCD's L2 (4 MB) does not hold the activations, and a split has tiles for the 32 compute units of an XCD, a split's tiles are, so that
+    // an XCD reads a range of K of the activations only.  Neighbouring splits / tiles, us: 2.9 MB, 4 bit, 2048 -> 6144 at 700 rows 38.1 /
+    // 39.9, fp16, 2048 -> 2048 at 700 30.1 / 32.3; 4.3 MB, 4 bit, 7168 -> 21504 at 300 155.6 / 151.3; 17 MB, 28672 -> 7168 at 300 186.1 / 181.0, 8 bit
+    // 201.5 / 197.8; with 16 and 20 tiles: 4.9 MB, 4 bit, 8192 -> 2048 at 300 34.8 / 38.6; 8.2 MB, 8 bit, 20480 -> 5120 at 200 76.7 / 78.9.
     float* partial;
     int32_t k_splits, whole_tiles;
 };
@@ -117,8 +118,8 @@ __host__ __device__ inline bool prefill_split_unit(const PrefillLin& L, int M, i
     if (l >= s.whole) {
         if (l - s.whole >= s.units) return false;
         const int u = s.unit0 + l - s.whole, rest = m_blocks * L.n_blocks - L.whole_tiles;
-        if ((long)M * L.K * 2 > (4L << 20)) *split = u / rest, tile = L.whole_tiles + u % rest;
-        else                                *split = u % L.k_splits, tile = L.whole_tiles + u / L.k_splits;
+        if (rest >= 32 && (long)M * L.K * 2 > (4L << 20)) *split = u / rest, tile = L.whole_tiles + u % rest;
+        else *split = u % L.k_splits, tile = L.whole_tiles + u / L.k_splits;
     }
     *tile_m = tile % m_blocks;
     *tile_n = tile / m_blocks;

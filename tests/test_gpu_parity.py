@@ -430,12 +430,12 @@ def test_decode_17_to_64_rows_stage_of_unlike_linears(orc, M):
 
 
 @pytest.mark.parametrize("bits,scheme", [(4, 1), (8, 2), (16, 0)], ids=["w4", "i8", "f16"])
-@pytest.mark.parametrize("M,N,K", [(700, 23104, 2048), (1191, 14912, 2048), (100, 71744, 2048), (256, 320, 4224), (300, 1088, 3200), (300, 1088, 8192), (700, 1088, 4096)])
+@pytest.mark.parametrize("M,N,K", [(700, 23104, 2048), (1191, 14912, 2048), (100, 71744, 2048), (256, 320, 4224), (300, 1088, 3200), (300, 1088, 8192), (300, 4160, 8192), (700, 2880, 4096)])
 def test_prefill_whole_and_split_tiles(orc, bits, scheme, M, N, K):
     """Linears with more tiles than the chip has compute units but fewer than twice as many (full rounds of whole tiles, the rest split over
     K: the border runs through a row block when the token blocks do not divide it), and with fewer (all split), N that is no multiple of
-    256 and ragged token blocks: every output written exactly once; 256 tokens to a tile, and 128 (100 rows).  Activations below and above 4 MB, where the order of
-    the work units changes, with up to two token blocks and more.  Every output against an fp32 product of the dequantised weights
+    256 and ragged token blocks: every output written exactly once; 256 tokens to a tile, and 128 (100 rows).  Activations below and above 4 MB, fewer and more than 32
+    tiles, where the order of the work units changes, with up to two token blocks and more.  Every output against an fp32 product of the dequantised weights
     (both sides round fp32 sums once: the file's tolerance), the rows around the border and the last ones against the oracle."""
     import torch
     kernel, tile, splits, whole = lpq.lpq_route_of([(bits, scheme, K, N)], lpq.LPQ_PREFILL, M)
