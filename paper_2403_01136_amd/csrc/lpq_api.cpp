@@ -475,7 +475,9 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
     int cus = 0;
     lpq_status st = device_cus(&cus);
     if (st != LPQ_OK) return st;
-    std::vector<DecodeLaunch> plan(n_launch);
+    DecodeLaunch one;                            // the usual call is a single launch: no allocation, no clearing of 4 KB
+    std::vector<DecodeLaunch> several(n_launch > 1 ? n_launch : 0);
+    DecodeLaunch* const plan = n_launch > 1 ? several.data() : &one;
     size_t need = 0;
     for (size_t li = 0; li < n_launch; ++li) {
         st = plan_decode(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M, cus, prefill, &plan[li]);
@@ -487,7 +489,8 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         st = workspace(static_ws, need, &ws);
         if (st != LPQ_OK) return st;
     }
-    for (DecodeLaunch& p : plan) {
+    for (size_t li = 0; li < n_launch; ++li) {
+        DecodeLaunch& p = plan[li];
         p.a.partial = ws;
         if (p.workspace_bytes > p.partial_bytes)
             p.a.prep = reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(ws) + p.partial_bytes);
