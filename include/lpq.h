@@ -37,8 +37,8 @@
  *     aligned; y is overwritten.  A linear computes y[m][n] = sum_k x[m][k] * w~[n][k]
  *     (+ bias[n]) with fp32 accumulation and one final round-to-nearest-even to fp16.
  *     An infinite x[m][k] gives what the weights rounded to fp16 give: an infinity of the weight's sign,
- *     NaN where infinities of both signs or a zero weight meet.  In decode calls of up to 32 rows it may
- *     give NaN instead.
+ *     NaN where infinities of both signs or a zero weight meet.  In decode calls of up to 32 rows, and in
+ *     the last up to 32 rows of one of more than 64 (which runs 64 at a time), it may give NaN instead.
  *
  * Storage format of a quantised weight W [N][K] (K contiguous); N % 64 == 0, K % 128 == 0
  *   A block is 64 rows x 128 columns (one quantisation group per row); blocks are stored in
