@@ -57,7 +57,6 @@ template <int TOK, int WAVES, int CAP> struct DecodeSmem { uint16_t x[2][TOK][Pi
 // Halves per token row of a linear's group sums (see decode_prepare_kernel).
 __device__ __host__ __forceinline__ int group_sums_stride(int K) { return 2 * ((K / 128 + 15) & ~15) + 8; }
 
-typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // s_waitcnt vmcnt(N): all but the wave's newest N vector-memory operations have completed.  Also a
@@ -66,6 +65,17 @@ template <int N> __device__ __forceinline__ void wait_vmem_all_but()
 {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// A workgroup barrier that leaves global loads under way (ahead of __syncthreads' fence the compiler waits for all of them): LDS
+// operations are complete, and no memory operation moves across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // The codes of one MFMA step as fp16 subnormals, for the kernel that applies scale and zero after the matrix cores:
@@ -323,21 +333,27 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     };
 
     // INPLACE: rows 0 .. of this pass of the activations that decode_prepare_kernel scaled, behind the linear's 32 rows of group sums
-    const uint16_t* xrows = INPLACE ? prep + (size_t)L.aux * 8 + (size_t)32 * group_sums_stride(L.K()) : L.x;
-    const int xrow0 = INPLACE ? 0 : m0, xrow_last = INPLACE ? min(TOK, M - m0) - 1 : M - 1;
+    const uint16_t* xrows = INPLACE ? prep + (size_t)L.aux * 8 + (size_t)32 * group_sums_stride(L.K()) : L.x + (size_t)m0 * L.K();
+    const int x_rows = min(TOK, M - m0);
     // ---- activation staging: the x columns of one chunk, shared by the workgroup through LDS.
-    // Global-to-LDS loads, 1 KB per wave and instruction (four 256-byte row segments); a lane fetches
-    // the column group that belongs in its 16-byte slot after swizzling.  Token rows past M and steps
+    // Buffer loads to LDS, 1 KB per wave and instruction (four 256-byte row segments, at most 64 rows of 2^24 bytes); a lane fetches
+    // the column group that belongs in its 16-byte slot after swizzling.  (With global_load_lds under way the compiler takes loads for
+    // unordered and waits for all of them ahead of a weight stage's first use.  That, and the fence of __syncthreads, emptied
+    // the weight pipeline once per chunk.  Buffer loads issued in the block that uses the stages, and lds_barrier, us per pass before and now:
+    // 14336-wide layers, 3 bit, 24 rows 907 / 848, 40 1429 / 1361, 64 1455 / 1400; 7168-wide, 4 bit, 32 rows 813 / 773, 64 1217 / 1150;
+    // 5120-wide, 3 to 16 bit, 16 rows 366 / 362, 32 418 / 407.)  Token rows past M and steps
     // past the end of a short chunk are clamped to valid ones: they feed nothing that is stored.
     // The loads are asynchronous: wait on vmcnt before the barrier that publishes the buffer.
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(xrows), (short)0,
+                                                                          (int)(2u * (uint32_t)x_rows * (uint32_t)L.K()), 0x00020000);
     auto fill_x_chunk = [&](const Chunk& c, int buf) {
 #pragma unroll
         for (int i = 0; i < XQ; ++i) {
             const int q = XQ * wave + i;
             const int u = 4 * q + (lane >> 4), row = u / CHUNK, seg = min(u % CHUNK, c.n - 1);
             const int c16 = (lane & 15) ^ (row & 15);
-            const uint16_t* g = xrows + (size_t)min(xrow0 + row, xrow_last) * L.K() + (size_t)(c.kt0 + seg) * 128 + c16 * 8;
-            __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)(&sm.x[buf][0][0] + 512 * q), 16, 0, 0);
+            const uint32_t off = ((uint32_t)min(row, x_rows - 1) * (uint32_t)L.K() + (uint32_t)(seg * 128 + c16 * 8)) * 2u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, (lptr_t)(&sm.x[buf][0][0] + 512 * q), 16, (int)off, 256 * c.kt0, 0, 0);
         }
         asm volatile("" ::: "memory");      // weight loads issued later stay later: vmcnt counts in issue order
     };
@@ -509,16 +525,16 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     for (int i = 0; i < STAGES; ++i)
         if (i < cur.n) issue(st[i], cur.sb, cur.kt0 + i, oc);      // slots past a short chunk stay empty
     wait_vmem_all_but<0>();
-    __syncthreads();
+    lds_barrier();
     int buf = 0;
     while (cur.n > 0) {
-        if (nxt.n > 0) fill_x_chunk(nxt, buf ^ 1);
         const bool active = row_block(cur.sb) < row_blocks;
         // steady state: a chunk of N steps (a full one; in the 16-step form also a linear's remainder of exactly 8)
         // followed by enough steps to refill every slot -- no per-step conditions, so the whole chunk is one
         // schedulable block
         auto steady_chunk = [&](auto n_steps) {
             constexpr int N = decltype(n_steps)::value;
+            fill_x_chunk(nxt, buf ^ 1);                 // in this block, where the compiler can count the fill ahead of the stages' uses
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 compute(st[i % STAGES], buf, i);
@@ -535,6 +551,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
         } else if (CHUNK == 16 && cur.n == 8 && active && nxt.n >= STAGES) {
             steady_chunk(std::integral_constant<int, CHUNK == 16 ? 8 : CHUNK>());
         } else {
+            if (nxt.n > 0) fill_x_chunk(nxt, buf ^ 1);
 #pragma unroll
             for (int i = 0; i < CHUNK; ++i) {
                 if (i < cur.n && active) compute(st[i % STAGES], buf, i);
@@ -550,7 +567,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             const bool whole = u0 >= s_begin && u0 + KT <= s_end;
             finish_unit(cur.sb, whole ? nullptr : (u0 < s_begin ? slot_first : slot_last));
         }
-        __syncthreads();
+        lds_barrier();
         buf ^= 1;
         cur = nxt;
         nxt = next_chunk(nxt);
