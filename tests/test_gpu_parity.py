@@ -617,3 +617,70 @@ def test_decode_mid_kernel_forms(bits, scheme, M, blocks, split, K, N):
     y = res.clone()
     lpq.lpq_qlinear_fused(qw, x, lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU, residual=y, y=y)
     check_output(y, ref, "%d rows, %d -> %d" % (M, K, N))
+
+
+@pytest.fixture
+def even_share():
+    """Launches that stream little go to the even-share kernel too."""
+    lpq.lpq_set_decode_routing(0, 0)
+    yield
+    lpq.lpq_set_decode_routing(-1, -1)
+
+
+@pytest.mark.parametrize("bits", [3, 4], ids=["w3", "w4"])
+@pytest.mark.parametrize("K,N", [(128, 64), (384, 320), (4736, 192), (1152, 1088), (2048 * 128 + 1152, 64)])
+def test_decode_33_to_64_rows_in_digits(bits, K, N, even_share):
+    """The even-share kernel of fp6 codes and activations in three fp6 digits (33 to 64 rows, 3- and 4-bit weights), at the edges of its token
+    tiles, with waves without a row block, chunks of one to four steps and rows longer than the preparing kernel keeps sums of;
+    rows of unlike magnitude, rows of zeros and of the smallest fp16 numbers, elements thirty and a thousand times their neighbours,
+    bias, activation and a residual in place.  Against 64 bits, row by row: the rounding of the output (2.1e-4 of it), plus digits that
+    are exact to 2^-15 of a block's largest element -- a thousand times the others, 2^-15 * 1000 / sqrt(3) of each of those 31 --
+    against a result that this largest element dominates: within 1e-4 of it; 4e-4 leaves a quarter for sums in 32 bits."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(K + N + bits)
+    w = (torch.randn((N, K), generator=gen, device="cuda") * 0.02).half()
+    bias = (0.1 * torch.randn(N, generator=gen, device="cuda")).half()
+    qw = lpq.lpq_quantize_pack(w, bits, lpq.LPQ_ASYM_GROUP, bias=bias)
+    deq = lpq.lpq_unpack_dequant(qw).double()
+    x = torch.randn((64, K), generator=gen, device="cuda")
+    x[:, torch.randperm(K, generator=gen, device="cuda")[:3]] *= 30.0
+    x[1, 5] *= 1000.0
+    scale = torch.tensor([1.0, 2.0 ** -11, 2.0 ** 5], device="cuda")[torch.arange(64, device="cuda") % 3]
+    x = (x * scale[:, None]).half()
+    x[2] = 0.0
+    x[3] = 2.0 ** -24
+    acc = x.double() @ deq.t()
+    for M in (33, 47, 48, 49, 63, 64):
+        y = lpq.lpq_qlinear_fused(qw, x[:M], lpq.LPQ_DECODE).double()
+        ref = acc[:M] + bias.double()
+        err = (y - ref).norm(dim=1) / ref.norm(dim=1)
+        assert float(err.max()) <= 4e-4, "%d rows: row %d off by %.2e" % (M, int(err.argmax()), float(err.max()))
+        res = torch.randn((M, N), generator=gen, device="cuda").half()
+        z = res.clone()
+        lpq.lpq_qlinear_fused(qw, x[:M], lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU, residual=z, y=z)
+        check_output(z, (torch.relu(ref) + res.double()).cpu().numpy(), "digits %d rows" % M)
+
+
+@pytest.mark.parametrize("M", [40, 64])
+@pytest.mark.parametrize("bits", [3, 4], ids=["w3", "w4"])
+def test_infinite_activations_in_digits(bits, M, even_share):
+    test_infinite_activations(lpq.LPQ_DECODE, M, bits, lpq.LPQ_ASYM_GROUP)
+
+
+@pytest.mark.parametrize("M", [40, 64])
+def test_decode_digits_without_room(M, even_share):
+    """A launch whose digits do not fit the static scratch array (128 MiB) runs without them, as before there were any."""
+    import torch
+    layer = {n: lpq.lpq_quantize_pack((torch.randn((N, K), device="cuda") * 0.02).half(), 3, lpq.LPQ_ASYM_GROUP)
+             for n, (K, N) in {"qkv": (65536, 64), "out": (65536, 64), "fc1": (65536, 64), "fc2": (65536, 64)}.items()}
+    n = 10                                                  # 40 linears of 65536 columns: 315 MB of digits at 40 rows beside 64 MiB of partial tiles
+    xs = [{k: torch.randn((M, 65536), device="cuda").half() for k in layer}] * n
+    out = []
+    for static in (False, True):
+        ys = [{k: torch.empty((M, 64), dtype=torch.float16, device="cuda") for k in layer} for _ in range(n)]
+        (lpq.lpq_stage_linears_noalloc if static else lpq.lpq_stage_linears)(lpq.Stage([layer] * n, xs, ys), lpq.LPQ_DECODE)
+        out.append(ys)
+    for name in layer:
+        ref = xs[0][name].double() @ lpq.lpq_unpack_dequant(layer[name]).double().t()
+        for ys in out:
+            check_output(ys[n - 1][name], ref.cpu().numpy(), "%s, %d rows" % (name, M))
