@@ -398,6 +398,8 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     a.prefill = prefill;
     a.partial = nullptr;
     a.prep = nullptr;
+    a.ln_gamma = a.ln_beta = nullptr;
+    a.ln_eps = 0.0f;
     const size_t partial_bytes = ((size_t)2 * n_blocks * a.slot_floats * sizeof(float) + 255) & ~(size_t)255;
     // after the partial tiles: what decode_prepare_kernel leaves for a launch whose last pass has up to 32 token rows
     const int last_rows = (M - 1) % 64 + 1;
@@ -493,11 +495,29 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     return LPQ_OK;
 }
 
+// The layer norm in front of a decoder layer's linear: rows [M][h] of x, normalised into the linear's x if not by its kernel.
+struct NormBefore {
+    const void *x, *gamma, *beta;
+    float eps;
+    void* y;
+};
+
+// Whether a decode linear's kernel normalises its M rows of K columns itself (every workgroup all of them) rather than a launch in front of it.  Whole
+// layers, us, apart / so: 768 wide, 4 bit, 1 row 35.0 / 30.5, 4 rows 38.1 / 30.8, 12 rows 43.7 / 42.0; 2048, 8 bit, 1 row 47.1 / 41.0, 8 rows 52.5 / 50.0;
+// 4096, 4 bit, 1 row 59.7 / 54.5, 4 rows 61.9 / 58.6; 5120, 4 bit, 1 row 70.4 / 66.0, 2 rows 71.2 / 67.4, 3 rows 71.5 / 71.5; 7168, 4 bit, 1 row
+// 101.7 / 103.0.
+bool norm_in_linear(int32_t M, int32_t K)
+{
+    return M <= 16 && K <= LN_LINEAR_MAX_K && (int64_t)M * K <= (K <= 4096 ? 16384 : 10240);
+}
+
 // Decode-phase dispatch of a list of independent linears: grouped launches of at most
 // MAX_LIN_PER_LAUNCH linears, 64 token rows per pass, each launch one round of equally loaded
 // workgroups (see lpq_decode.hip).  Every launch is planned, and the workspace of the largest asked for, ahead of the first
 // one: launches and passes run one after the other on the stream and share the space.
-lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false, bool prefill = false)
+// norm (a single linear): its activations' layer norm comes first, in the linear's own launch where that takes few enough of them.
+lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false, bool prefill = false,
+                      const NormBefore* norm = nullptr)
 {
     const size_t n = calls.size();
     const size_t n_launch = (n + MAX_LIN_PER_LAUNCH - 1) / MAX_LIN_PER_LAUNCH;
@@ -520,6 +540,18 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         if (need) st = workspace(static_ws, need, &ws);
         if (st == LPQ_OK) break;
         if (st != LPQ_ERR_BUFSIZE || !room) return st;
+    }
+    if (norm) {
+        DecodeArgs& a = plan[0].a;
+        const int64_t K = a.lin[0].K();
+        if (plan[0].kernel == DECODE_ROWS && a.waves == 4 && norm_in_linear(M, (int32_t)K)) {
+            a.lin[0].x = static_cast<const uint16_t*>(norm->x);
+            a.ln_gamma = static_cast<const uint16_t*>(norm->gamma);
+            a.ln_beta = static_cast<const uint16_t*>(norm->beta);
+            a.ln_eps = norm->eps;
+        } else if (launch_layernorm(norm->x, norm->gamma, norm->beta, norm->eps, M, (int)K, norm->y, stream) != hipSuccess) {
+            return LPQ_ERR_DEVICE;
+        }
     }
     for (size_t li = 0; li < n_launch; ++li) {
         DecodeLaunch& p = plan[li];
@@ -900,8 +932,16 @@ lpq_status lpq_decoder_layer(const lpq_layer* layer, const lpq_layer_cfg* cfg, c
         std::vector<LinearCall> calls(1, LinearCall{wt, in, out, residual, act});
         return phase == LPQ_PREFILL ? run_prefill(calls, (int32_t)M, stream) : run_decode(calls, (int32_t)M, stream);
     };
-    if (launch_layernorm(x, st->ln1_gamma, st->ln1_beta, cfg->ln_eps, (int)M, (int)h, h1, stream) != hipSuccess) return LPQ_ERR_DEVICE;
-    if ((s = linear(&layer->qkv, h1, qkv, nullptr, LPQ_ACT_NONE)) != LPQ_OK) return s;
+    auto norm_linear = [&](const void* in, const void* gamma, const void* beta, const lpq_qweight* wt, void* out, int act) {
+        if (phase == LPQ_DECODE) {
+            const NormBefore norm = {in, gamma, beta, cfg->ln_eps, h1};
+            std::vector<LinearCall> calls(1, LinearCall{wt, h1, out, nullptr, act});
+            return run_decode(calls, (int32_t)M, stream, false, false, &norm);
+        }
+        if (launch_layernorm(in, gamma, beta, cfg->ln_eps, (int)M, (int)h, h1, stream) != hipSuccess) return LPQ_ERR_DEVICE;
+        return linear(wt, h1, out, nullptr, act);
+    };
+    if ((s = norm_linear(x, st->ln1_gamma, st->ln1_beta, &layer->qkv, qkv, LPQ_ACT_NONE)) != LPQ_OK) return s;
     // One new token per sequence: the attention kernel writes it to the caches itself, a launch less -- unless it streams long enough for
     // the scattered stores to cost more than that.  Whole layer, us, in one launch / two, by the megabytes of cache it reads: 1 (12
     // heads) 28.7 / 30.4, 184 (16 sequences of 40) 85.8 / 91.4, 655 175.8 / 176.5, 1376 332.7 / 330.2, 1648 (43 of 56) 378.9 / 370.5, 2455 537 / 521,
@@ -911,8 +951,7 @@ lpq_status lpq_decoder_layer(const lpq_layer* layer, const lpq_layer_cfg* cfg, c
         return LPQ_ERR_DEVICE;
     if ((s = run_attention(qkv, cfg, st, n_seqs, T, pos0, fresh, att, stream)) != LPQ_OK) return s;
     if ((s = linear(&layer->out, att, y, x, LPQ_ACT_NONE)) != LPQ_OK) return s;                    // y = x + out-projection
-    if (launch_layernorm(y, st->ln2_gamma, st->ln2_beta, cfg->ln_eps, (int)M, (int)h, h1, stream) != hipSuccess) return LPQ_ERR_DEVICE;
-    if ((s = linear(&layer->fc1, h1, ff, nullptr, cfg->activation)) != LPQ_OK) return s;
+    if ((s = norm_linear(y, st->ln2_gamma, st->ln2_beta, &layer->fc1, ff, cfg->activation)) != LPQ_OK) return s;
     return linear(&layer->fc2, ff, y, y, LPQ_ACT_NONE);                                           // y += feed-forward
 }
 

@@ -56,8 +56,12 @@ struct DecodeArgs {
     float* partial;
     const uint16_t* prep;                // stage-wide kernel: what the preparing kernel leaves (the activations' group sums at up to 32
                                          // token rows per pass, for 3-bit weights the activations, scaled; or sums and fp6 digits)
+    const uint16_t *ln_gamma, *ln_beta;  // a single linear of up to 16 rows whose rows x the kernel layer-normalises first, or null
+    float ln_eps;
+    int32_t pad3;
     LinDesc lin[MAX_LIN_PER_LAUNCH];
 };
+enum { LN_LINEAR_MAX_K = 5120 };         // columns up to which a decode linear's kernel can normalise its rows itself
 static_assert(sizeof(DecodeArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
 // One linear of a grouped prefill launch: its output is cut into tiles of BM tokens x 256 rows of W.

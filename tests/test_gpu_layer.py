@@ -410,3 +410,40 @@ def test_attention_over_very_long_rows():
     finally:
         st.k_cache = st.vt_cache = None
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("bits,scheme", [(3, 1), (4, 1), (8, 1), (8, 2), (16, 0)], ids=["w3", "w4", "w8", "i8", "f16"])
+@pytest.mark.parametrize("heads,d,seqs", [(9, 128, 1), (9, 128, 5), (12, 64, 2), (12, 64, 3), (12, 64, 16), (32, 128, 4), (40, 128, 1), (40, 128, 2), (42, 64, 6)])
+def test_decode_layer_normalises_in_the_linears(bits, scheme, heads, d, seqs):
+    """Decode layers of few rows, whose QKV and FC1 kernels normalise their rows themselves (one, two or more rows to a wave, rows that fill no
+    whole number of 512 columns, up to the longest that do), against the same layer of single calls.  Both round to fp16 at the same places;
+    statistics added in another order move an element by one such rounding now and then: the layer's 2e-3 as in this file."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(heads * d + seqs)
+    h, pos = heads * d, 70
+
+    def rand(*shape, std=1.0):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).half()
+
+    shapes = {"qkv": (h, 3 * h), "out": (h, h), "fc1": (h, 4 * h), "fc2": (4 * h, h)}
+    layer = {n: lpq.lpq_quantize_pack(rand(N, K, std=0.02), bits, scheme, bias=rand(N, std=0.05)) for n, (K, N) in shapes.items()}
+    norms = [((1 + 0.1 * torch.randn(h, generator=gen, device="cuda")).half(), rand(h, std=0.1)) for _ in range(2)]
+    st = lpq.LayerState(heads, d, 128, seqs, torch.device("cuda"), norms[0], norms[1])
+    st.k_cache[:, :, :pos] = rand(seqs, heads, pos, d)
+    st.vt_cache[:, :, :, :pos] = rand(seqs, heads, d, pos)
+    k0, v0 = st.k_cache.clone(), st.vt_cache.clone()
+    x = rand(seqs, h, std=2.0)
+    x[:, 5] *= 30
+    x += 0.5
+    y, _ = lpq.lpq_decoder_layer(layer, st, lpq.LPQ_DECODE, seqs, 1, pos, x)
+    k1, v1 = st.k_cache.clone(), st.vt_cache.clone()
+    st.k_cache.copy_(k0)
+    st.vt_cache.copy_(v0)
+    qkv = lpq.lpq_qlinear_decode(layer["qkv"], lpq.lpq_layernorm(x, *norms[0], 1e-5))
+    lpq.lpq_kv_append(qkv, st, seqs, 1, pos)
+    att = lpq.lpq_attention(qkv, st, seqs, 1, pos)
+    z = lpq.lpq_qlinear_fused(layer["out"], att, lpq.LPQ_DECODE, residual=x)
+    ff = lpq.lpq_qlinear_fused(layer["fc1"], lpq.lpq_layernorm(z, *norms[1], 1e-5), lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU)
+    z = lpq.lpq_qlinear_fused(layer["fc2"], ff, lpq.LPQ_DECODE, residual=z)
+    for a, b in ((y, z), (k1, st.k_cache), (v1, st.vt_cache)):
+        assert float((a.double() - b.double()).norm() / b.double().norm()) <= 2e-3
