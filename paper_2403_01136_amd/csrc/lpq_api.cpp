@@ -398,7 +398,8 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     a.prefill = prefill;
     a.partial = nullptr;
     a.prep = nullptr;
-    a.ln_gamma = a.ln_beta = nullptr;
+    a.ln_gamma = a.ln_beta = a.after_gamma = a.after_beta = nullptr;
+    a.after_y = nullptr;
     a.ln_eps = 0.0f;
     const size_t partial_bytes = ((size_t)2 * n_blocks * a.slot_floats * sizeof(float) + 255) & ~(size_t)255;
     // after the partial tiles: what decode_prepare_kernel leaves for a launch whose last pass has up to 32 token rows
@@ -495,11 +496,17 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     return LPQ_OK;
 }
 
-// The layer norm in front of a decoder layer's linear: rows [M][h] of x, normalised into the linear's x if not by its kernel.
+// A layer norm in front of a decoder layer's linear, rows [M][h] of x, normalised into the linear's x if not by its kernel; or behind one, rows of its y.
 struct NormBefore {
     const void *x, *gamma, *beta;
     float eps;
     void* y;
+};
+struct NormAfter {
+    const void *gamma, *beta;
+    float eps;
+    void* y;
+    bool done;              // out: the linear's launches have done it
 };
 
 // Whether a decode linear's kernel normalises its M rows of K columns itself (every workgroup all of them) rather than a launch in front of it.  Whole
@@ -515,9 +522,10 @@ bool norm_in_linear(int32_t M, int32_t K)
 // MAX_LIN_PER_LAUNCH linears, 64 token rows per pass, each launch one round of equally loaded
 // workgroups (see lpq_decode.hip).  Every launch is planned, and the workspace of the largest asked for, ahead of the first
 // one: launches and passes run one after the other on the stream and share the space.
-// norm (a single linear): its activations' layer norm comes first, in the linear's own launch where that takes few enough of them.
+// norm (a single linear): its activations' layer norm comes first, in the linear's own launch where that takes few enough of them.  after (a single
+// linear): a layer norm of its output, done if its K splits are added by a kernel of their own, which then does both.
 lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream_t stream, bool static_ws = false, bool prefill = false,
-                      const NormBefore* norm = nullptr)
+                      const NormBefore* norm = nullptr, NormAfter* after = nullptr)
 {
     const size_t n = calls.size();
     const size_t n_launch = (n + MAX_LIN_PER_LAUNCH - 1) / MAX_LIN_PER_LAUNCH;
@@ -552,6 +560,14 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
         } else if (launch_layernorm(norm->x, norm->gamma, norm->beta, norm->eps, M, (int)K, norm->y, stream) != hipSuccess) {
             return LPQ_ERR_DEVICE;
         }
+    }
+    if (after && plan[0].kernel != DECODE_EVEN_SHARE && plan[0].a.lin[0].aux > 1) {
+        DecodeArgs& a = plan[0].a;
+        a.after_gamma = static_cast<const uint16_t*>(after->gamma);
+        a.after_beta = static_cast<const uint16_t*>(after->beta);
+        a.after_y = static_cast<uint16_t*>(after->y);
+        a.ln_eps = after->eps;
+        after->done = true;
     }
     for (size_t li = 0; li < n_launch; ++li) {
         DecodeLaunch& p = plan[li];
@@ -950,8 +966,18 @@ lpq_status lpq_decoder_layer(const lpq_layer* layer, const lpq_layer_cfg* cfg, c
     if (!fresh && launch_kv_append(qkv, st->k_cache, st->vt_cache, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim, cfg->max_seq, stream) != hipSuccess)
         return LPQ_ERR_DEVICE;
     if ((s = run_attention(qkv, cfg, st, n_seqs, T, pos0, fresh, att, stream)) != LPQ_OK) return s;
-    if ((s = linear(&layer->out, att, y, x, LPQ_ACT_NONE)) != LPQ_OK) return s;                    // y = x + out-projection
-    if ((s = norm_linear(y, st->ln2_gamma, st->ln2_beta, &layer->fc1, ff, cfg->activation)) != LPQ_OK) return s;
+    // y = x + out-projection, then feed-forward of its norm
+    NormAfter ln2 = {st->ln2_gamma, st->ln2_beta, cfg->ln_eps, h1, false};
+    if (phase == LPQ_DECODE) {
+        std::vector<LinearCall> calls(1, LinearCall{&layer->out, att, y, x, LPQ_ACT_NONE});
+        s = run_decode(calls, (int32_t)M, stream, false, false, nullptr, &ln2);
+    } else {
+        s = linear(&layer->out, att, y, x, LPQ_ACT_NONE);
+    }
+    if (s != LPQ_OK) return s;
+    s = ln2.done ? linear(&layer->fc1, h1, ff, nullptr, cfg->activation)
+                 : norm_linear(y, st->ln2_gamma, st->ln2_beta, &layer->fc1, ff, cfg->activation);
+    if (s != LPQ_OK) return s;
     return linear(&layer->fc2, ff, y, y, LPQ_ACT_NONE);                                           // y += feed-forward
 }
 

@@ -57,6 +57,8 @@ struct DecodeArgs {
     const uint16_t* prep;                // stage-wide kernel: what the preparing kernel leaves (the activations' group sums at up to 32
                                          // token rows per pass, for 3-bit weights the activations, scaled; or sums and fp6 digits)
     const uint16_t *ln_gamma, *ln_beta;  // a single linear of up to 16 rows whose rows x the kernel layer-normalises first, or null
+    const uint16_t *after_gamma, *after_beta;          // a single K-split linear of up to 16384 columns of y: the kernel that adds its splits also
+    uint16_t* after_y;                                 // layer-normalises its rows into after_y; or null
     float ln_eps;
     int32_t pad3;
     LinDesc lin[MAX_LIN_PER_LAUNCH];

@@ -447,3 +447,10 @@ def test_decode_layer_normalises_in_the_linears(bits, scheme, heads, d, seqs):
     z = lpq.lpq_qlinear_fused(layer["fc2"], ff, lpq.LPQ_DECODE, residual=z)
     for a, b in ((y, z), (k1, st.k_cache), (v1, st.vt_cache)):
         assert float((a.double() - b.double()).norm() / b.double().norm()) <= 2e-3
+
+
+@pytest.mark.parametrize("heads,d,seqs", [(40, 128, 16), (20, 128, 33), (64, 128, 2), (128, 128, 20), (17, 128, 50)])
+def test_decode_layer_norm_behind_split_sums(heads, d, seqs):
+    """Decode layers whose out-projection is split over K: the kernel that adds the splits also forms the second norm (rows of up to 16384 columns,
+    that fill its threads or not).  Against the same layer of single calls, as above."""
+    test_decode_layer_normalises_in_the_linears(4, 1, heads, d, seqs)
