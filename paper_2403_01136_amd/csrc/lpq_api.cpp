@@ -958,11 +958,12 @@ lpq_status lpq_decoder_layer(const lpq_layer* layer, const lpq_layer_cfg* cfg, c
         return linear(wt, h1, out, nullptr, act);
     };
     if ((s = norm_linear(x, st->ln1_gamma, st->ln1_beta, &layer->qkv, qkv, LPQ_ACT_NONE)) != LPQ_OK) return s;
-    // One new token per sequence: the attention kernel writes it to the caches itself, a launch less -- unless it streams long enough for
-    // the scattered stores to cost more than that.  Whole layer, us, in one launch / two, by the megabytes of cache it reads: 1 (12
-    // heads) 28.7 / 30.4, 184 (16 sequences of 40) 85.8 / 91.4, 655 175.8 / 176.5, 1376 332.7 / 330.2, 1648 (43 of 56) 378.9 / 370.5, 2455 537 / 521,
-    // 5243 937 / 881.
-    const bool fresh = T == 1 && 4.0 * n_seqs * (double)h * pos0 <= 1.0e9;
+    // One new token per sequence: the attention kernel writes it to the caches itself, a launch less -- while the cache it reads is small: its stores of two
+    // bytes then cost less than kv_append's launch.  Whole layer, 4 bit, us, in one launch / two, by the megabytes of cache: 8 (2 sequences, 2048 wide) 41.2 /
+    // 41.9, 20 (4, 4096) 61.3 / 62.9, 49 (8, 5120) 86.8 / 88.9, 66 (16, 5120) 90.3 / 88.8, 184 (16, 5120) 107.4 / 105.9, 246 (8, 5120) 121.4 / 115.2, 344
+    // (40, 7168) 212.9 / 199.5, 1648 (43, 7168) 436.5 / 395.2.  At the first position of a tile of 64 it also saves the reading of that tile: 1174 (64, 7168,
+    // position 640) 375 / 386.
+    const bool fresh = T == 1 && (4.0 * n_seqs * (double)h * pos0 <= 6.0e7 || pos0 % 64 == 0);
     if (!fresh && launch_kv_append(qkv, st->k_cache, st->vt_cache, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim, cfg->max_seq, stream) != hipSuccess)
         return LPQ_ERR_DEVICE;
     if ((s = run_attention(qkv, cfg, st, n_seqs, T, pos0, fresh, att, stream)) != LPQ_OK) return s;

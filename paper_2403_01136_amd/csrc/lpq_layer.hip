@@ -147,6 +147,38 @@ struct OpMax { __device__ __forceinline__ float operator()(float a, float b) con
 
 constexpr float LOG2E = 1.4426950408889634f;
 
+// KV append of one token per sequence: a workgroup per (sequence, head).  In the transposed V cache the token is one value in each feature row.  Stored by
+// itself it is two bytes of a line that the memory has to read, change and write back, which goes on behind the kernel and holds the attention's reads
+// up; so 64 aligned bytes (32 positions; four lanes of 16 bytes) are read, changed and stored as a whole.  kv_append and attention, us, with stores of two
+// bytes / 16 / 64 / 128: 43 sequences of 56 heads at 1338 positions 290.9 / 265.8 / 264.4 / 274.3 (attention alone 241), 64 of 40 at 601 164.7 / 148.0 /
+// 147.1 / 156.0, 16 of 40 at 563 41.4 / 36.8 / 36.1 / 36.9.
+template <int D>
+__global__ __launch_bounds__(256) void kv_append_token_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ kc, uint16_t* __restrict__ vtc,
+                                                              int pos, int H, int S)
+{
+    constexpr int ROUNDS = D / 64;                     // 64 feature rows at a time
+    const int bh = blockIdx.x, b = bh / H, head = bh % H, h = H * D, tid = threadIdx.x;
+    const uint16_t* src = qkv + (size_t)b * 3 * h + head * D;
+    uint16_t* at = vtc + ((size_t)bh * D + tid / 4) * S + (pos & ~31) + 8 * (tid % 4);
+    u32x4 chunk[ROUNDS];
+    uint16_t v[ROUNDS];
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        chunk[i] = *reinterpret_cast<const u32x4*>(at + (size_t)64 * i * S);
+        v[i] = src[2 * h + 64 * i + tid / 4];
+    }
+    if (tid < D / 8) *reinterpret_cast<h8*>(kc + ((size_t)bh * S + pos) * D + 8 * tid) = *reinterpret_cast<const h8*>(src + h + 8 * tid);
+    const bool mine = tid % 4 == (pos % 32) / 8;       // the lane whose chunk the position lies in
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if (mine && (pos & 7) >> 1 == w)
+                chunk[i][w] = (pos & 1) ? (chunk[i][w] & 0xffffu) | (uint32_t)v[i] << 16 : (chunk[i][w] & 0xffff0000u) | v[i];
+        *reinterpret_cast<u32x4*>(at + (size_t)64 * i * S) = chunk[i];
+    }
+}
+
 // A lane's byte offset into eight feature rows of the transposed V cache: 32 bits where 14 * max_seq + 126 fits them, so that a load takes a
 // scalar base and a 32-bit offset as they are; LONG: 64 bits.
 template <bool LONG> using VOffset = typename std::conditional<LONG, uint64_t, uint32_t>::type;
@@ -283,8 +315,8 @@ __global__ __launch_bounds__(256, 4) void attention_decode_kernel(const uint16_t
     }
     if constexpr (FRESH) {
         // Behind the tiles, by the wave with the fewest of them: ahead of them its loads and scattered stores hold the
-        // stream back (43 sequences of 56 heads at 1338 positions: 314 us; so: 305; kv_append and this kernel without it: 11.8 + 287,
-        // 16 of 40 at 563: 6 + 36 against 37; the host takes two launches where the caches are large).
+        // stream back (43 sequences of 56 heads at 1338 positions: 314 us; so: 305; kv_append and this kernel without it: 264; the host takes two
+        // launches where the caches are not small.  64 aligned bytes read, changed and stored per feature row, as kv_append does it, are slower here.)
         if (split == 0 && wave == 3) {
             const h8 k = *reinterpret_cast<const h8*>(qrow + h + 8 * (lane % LPK));
             uint16_t v[LOADS];
@@ -633,6 +665,12 @@ hipError_t launch_kv_append(const void* qkv, void* kc, void* vtc, int n_seqs, in
 {
     const dim3 grid((unsigned)(n_seqs * H), (unsigned)((T + 63) / 64));
     const uint16_t* q = static_cast<const uint16_t*>(qkv);
+    if (T == 1) {
+        uint16_t *k = static_cast<uint16_t*>(kc), *v = static_cast<uint16_t*>(vtc);
+        if (d == 128) kv_append_token_kernel<128><<<(unsigned)(n_seqs * H), 256, 0, s>>>(q, k, v, pos0, H, S);
+        else          kv_append_token_kernel<64><<<(unsigned)(n_seqs * H), 256, 0, s>>>(q, k, v, pos0, H, S);
+        return hipGetLastError();
+    }
     if (d == 128) kv_append_kernel<128><<<grid, 256, 0, s>>>(q, static_cast<uint16_t*>(kc), static_cast<uint16_t*>(vtc), T, pos0, H, S);
     else          kv_append_kernel<64><<<grid, 256, 0, s>>>(q, static_cast<uint16_t*>(kc), static_cast<uint16_t*>(vtc), T, pos0, H, S);
     return hipGetLastError();

@@ -454,3 +454,20 @@ def test_decode_layer_norm_behind_split_sums(heads, d, seqs):
     """Decode layers whose out-projection is split over K: the kernel that adds the splits also forms the second norm (rows of up to 16384 columns,
     that fill its threads or not).  Against the same layer of single calls, as above."""
     test_decode_layer_normalises_in_the_linears(4, 1, heads, d, seqs)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("pos0", [0, 1, 30, 31, 32, 63, 64, 127])
+def test_kv_append_of_one_token(d, pos0):
+    """One token per sequence, at every place of a 16-byte chunk's halves and at the edges of the 32 positions that are stored together: its K and V
+    and nothing else change, beside positions that hold NaN and infinities."""
+    B, H, S = 3, 5, 128
+    st, _, _ = make_state(B, H, d, S, d)
+    r = rng("kv1", d, pos0)
+    qkv = f16(r.standard_normal((B, 3 * H * d)))
+    k0, v0 = f16(r.standard_normal((B, H, S, d))), f16(r.standard_normal((B, H, d, S)))
+    v0[:, :, :, pos0:], v0[:, 0, :, ::3] = np.nan, np.inf
+    st.k_cache.copy_(to_dev(k0)), st.vt_cache.copy_(to_dev(v0))
+    lpq.lpq_kv_append(to_dev(qkv), st, B, 1, pos0)
+    OL.kv_append(k0, v0, qkv, B, 1, pos0, H)
+    assert np.array_equal(u16(st.k_cache), k0.view(np.uint16)) and np.array_equal(u16(st.vt_cache), v0.view(np.uint16))
