@@ -25,10 +25,11 @@ __device__ __forceinline__ float wave_sum(float v)
 }
 
 // ---- layer normalisation: one workgroup per row, the row held in registers -------------------
-// HBM-bound at many rows (2 bytes read + 2 bytes written per element), a chain of latencies at few: so a thread takes one 16-byte chunk (two of rows
-// beyond 8192), and asks for its part of gamma and beta together with it, ahead of the sums.  5120 columns, 16 rows: 5.1 us with 256 threads of up to eight
-// chunks, gamma and beta behind the sums, so 4.3; 1191 rows 11.0 / 10.9 (a wave per row: 12).
-constexpr int LN_MAX_CHUNKS = 2, LN_MAX_THREADS = 1024;       // rows up to 16384
+// HBM-bound at many rows (2 bytes read + 2 bytes written per element), a chain of latencies at few: so a thread of few rows takes one 16-byte chunk (two
+// beyond 8192 columns), and asks for its part of gamma and beta together with it, ahead of the sums.  Cold rows, us, 256 threads of up to eight chunks with
+// gamma and beta behind the sums / so: 5120 columns, 16 rows 5.4 / 4.8, 400 rows 6.3 / 5.4, 1191 rows 12.1 / 9.6 (with 640 threads 10.9, a wave per row 12); 14336
+// columns, 16 rows 8.9 / 4.9, 2048 rows 35.8 / 31.5.
+constexpr int LN_MAX_HIDDEN = 16384, LN_MAX_THREADS = 1024;
 
 template <int CHUNKS>
 __global__ __launch_bounds__(LN_MAX_THREADS) void layernorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma,
@@ -651,15 +652,17 @@ __global__ __launch_bounds__(256, 2) void attention_prefill_kernel(const uint16_
 
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, float eps, int M, int h, void* y, hipStream_t s)
 {
-    const int chunks = h / 8, threads = std::min(LN_MAX_THREADS, (chunks + 63) / 64 * 64);
+    // many rows: 256 threads of up to four chunks, more rows at work at a time
+    const int chunks = h / 8, threads = std::min(M > 512 && chunks <= 1024 ? 256 : LN_MAX_THREADS, (chunks + 63) / 64 * 64);
     const uint16_t *xs = static_cast<const uint16_t*>(x), *g = static_cast<const uint16_t*>(gamma), *b = static_cast<const uint16_t*>(beta);
     uint16_t* out = static_cast<uint16_t*>(y);
-    if (chunks <= threads) layernorm_kernel<1><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
-    else                   layernorm_kernel<2><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
+    if (chunks <= threads)          layernorm_kernel<1><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
+    else if (chunks <= 2 * threads) layernorm_kernel<2><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
+    else                            layernorm_kernel<4><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
     return hipGetLastError();
 }
 
-int layernorm_max_hidden() { return LN_MAX_THREADS * 8 * LN_MAX_CHUNKS; }
+int layernorm_max_hidden() { return LN_MAX_HIDDEN; }
 
 hipError_t launch_kv_append(const void* qkv, void* kc, void* vtc, int n_seqs, int T, int pos0, int H, int d, int S, hipStream_t s)
 {
