@@ -313,14 +313,16 @@ bool reads_in_place(const std::vector<LinearCall>& calls, size_t begin, size_t e
 bool takes_digits(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
 {
     if (M <= 32 || M > 64) return false;
-    double w3 = 0.0, all = 0.0;
+    double w3 = 0.0, all = 0.0, columns = 0.0;
     for (size_t c = begin; c < end; ++c) {
         const lpq_qdesc& d = calls[c].w->d;
         if (variant_of(d) > 1) return false;
+        columns += d.K;
         const double weights = (double)d.K * (double)d.N;
         all += weights;
         if (variant_of(d) == 0) w3 += weights;
     }
+    if (columns > 5.0e7) return false;               // 8 GB of digits at 64 rows (a stage of ten 14336-wide layers: 1 million columns)
     const double line = g_rows_max_mb.load() / 192.0;
     return M <= 48 ? all >= 1.2e9 * line : w3 >= 0.5 * all && all >= 3.0e9 * line;
 }
