@@ -335,6 +335,8 @@ bool takes_digits(const std::vector<LinearCall>& calls, size_t begin, size_t end
 // of 5120 (629 M) 107 / 83, 131 / 109, 138 / 130; three 4-bit layers of 5120 (944 M) 143 / 128, 173 / 162, 182 / 198; a 3- and a 4-bit layer of 7168
 // (1.2 G) 165 / 149, 222 / 200, 226 / 238; a 3-bit layer of 14336 (2.5 G) 259 / 290, 381 / 370, 393 / 455; 8 bit, 7168 -> 28672 93 / 42, 110 / 48, 119 / 56;
 // an 8-bit layer of 9216 (1.0 G) 227 / 193, 244 / 220, 252 / 252; fp16, 7168 -> 28672 114 / 66, 120 / 71, 129 / 73.
+// With the weight pipeline of the even-share kernel kept full across its chunks: three 4-bit layers of 5120 125 / 108 at 17 rows, 134 / 128 at 32, 182 / 198
+// at 64; a 3- and a 4-bit layer of 7168 (1.2 G) 143 / 139, 157 / 151, 240 / 244; three of them (1.85 G) 190 / 199, 203 / 212, 309 / 342.
 // rows_max_mib of lpq_set_decode_routing (default 192) moves the line in proportion.
 bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
 {
