@@ -212,9 +212,7 @@ lpq_status lpq_stage_linears(const lpq_layer *layers, int32_t n_layers, lpq_phas
  * (one copy per device, held until the process ends) instead of the growing workspace, and the call never allocates or
  * frees.  That array covers a decode-phase call of any number of rows (64 MiB of partial tiles per pass of 64 rows; up to
  * 16 rows 16 MiB and, for 3-bit linears, 2 bytes per token row and column of the launch's activations: ten
- * BLOOM-176B-shaped layers at 16 rows take 31 MiB; a large launch of 33 to 64 rows of 3- and 4-bit linears takes 2.5 bytes per
- * row, in whole tiles of 16, and column for activations in fp6 digits, and runs on weights dequantised to fp16, with other roundings,
- * where that does not fit), and a prefill-phase call (a launch whose K splits' partial sums do
+ * BLOOM-176B-shaped layers at 16 rows take 31 MiB), and a prefill-phase call (a launch whose K splits' partial sums do
  * not fit runs without the splits); a call that would need more returns LPQ_ERR_BUFSIZE and launches nothing
  * further.  All calls on a device share the array, which keeps the last call's contents (nothing in it has to
  * start at zero: every partial tile read was written by the same call); calls that overlap on one device race.

@@ -261,17 +261,12 @@ void mid_plan(DecodeArgs& p, int cus, size_t max_floats)
     for (int i = 0; i < p.n_lin; ++i) p.lin[i].aux = (p.lin[i].kt + best_t - 1) / best_t;
 }
 
-// Bytes that the preparing kernel leaves for a linear in a stage-wide decode launch of up to 32 token rows per pass, or in digits.  The group
+// Bytes that decode_prepare_kernel leaves for a linear in a decode launch of up to 32 token rows per pass.  The group
 // sums: per token row (32 of them) an fp16 pair per 128-column group, groups padded to a multiple of 16, and 16 bytes
 // for the row's factors; behind them, for 3-bit weights that the launch reads in place, `rows` rows of scaled
 // activations.
-size_t prepared_bytes(const lpq_qdesc& d, int rows, bool in_place, bool digits)
+size_t prepared_bytes(const lpq_qdesc& d, int rows, bool in_place)
 {
-    if (digits) {                                    // sums of whole tiles of 16 rows, and the digits
-        const size_t kt = (size_t)d.K / 128, tiles = ((size_t)rows + 15) / 16;
-        return 16 * tiles * (4 * ((kt + 15) & ~(size_t)15) + 16) + kt * tiles * DIGIT_TILE;
-    }
-    if (rows > 32) return 0;
     const size_t sums = (size_t)32 * (4 * (((size_t)d.K / 128 + 15) & ~(size_t)15) + 16);
     return sums + (in_place && variant_of(d) == 0 ? (size_t)rows * (size_t)d.K * 2 : 0);
 }
@@ -300,31 +295,6 @@ bool reads_in_place(const std::vector<LinearCall>& calls, size_t begin, size_t e
         if (variant_of(d) == 0) w3 += bytes;
     }
     return w3 >= 0.25 * all;
-}
-
-// Whether a stage-wide decode launch takes its codes as fp6 numbers, against activations cut into fp6 digits (lpq_decode.hip): 33 to 64 rows of
-// 3- and 4-bit linears only, where the weights would otherwise be dequantised to fp16 one by one and 33 rows cost what 64 do.  Cutting the
-// activations, and the zero term behind the product, cost about 20 us more per launch, so the line lies at a number of weights.  Measured, us,
-// dequantised / digits: 3 bit, 0.9 G weights, 48 rows 170 / 177; 3 and 4 bit, 1.2 G 33 rows 205 / 197, 48 210 / 205, 64 218 / 238; 1.85 G 48 rows
-// 290 / 262, 64 301 / 307; 2.5 G 33 rows 365 / 302, 64 385 / 390; 3 bit, 3.1 G 64 rows 470 / 460; 3.7 G (14336-wide) 48 rows 1393 / 1081, 64 1381 /
-// 1335; 4 bit, 7.4 G 48 rows 1136 / 971, 64 1163 / 1163.  Up to 32 rows scale and zero are applied after the product either way: 3 bit 3-8 % faster
-// in digits, 4 bit 4-6 % slower, and the results a little less exact, so not.  Error against 64 bits at 33 rows and more: 2.2e-4 to 2.4e-4, dequantised 2.7e-4.
-// rows_max_mib of lpq_set_decode_routing (default 192) moves the lines in proportion.
-bool takes_digits(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
-{
-    if (M <= 32 || M > 64) return false;
-    double w3 = 0.0, all = 0.0, columns = 0.0;
-    for (size_t c = begin; c < end; ++c) {
-        const lpq_qdesc& d = calls[c].w->d;
-        if (variant_of(d) > 1) return false;
-        columns += d.K;
-        const double weights = (double)d.K * (double)d.N;
-        all += weights;
-        if (variant_of(d) == 0) w3 += weights;
-    }
-    if (columns > 5.0e7) return false;               // 8 GB of digits at 64 rows (a stage of ten 14336-wide layers: 1 million columns)
-    const double line = g_rows_max_mb.load() / 192.0;
-    return M <= 48 ? all >= 1.2e9 * line : w3 >= 0.5 * all && all >= 3.0e9 * line;
 }
 
 // Whether a decode launch of 17 to 64 token rows goes to the kernel of few row blocks per workgroup instead of the even-share
@@ -385,8 +355,8 @@ struct DecodeLaunch {
 
 // Plans the launch of linears [begin, end) on a device of `cus` compute units; a function of its arguments and the
 // routing settings alone.  prefill: a prefill call's linears (M <= 64), for the kernels of small launches whatever they stream, 8-bit
-// symmetric codes without an offset.  room: whether there is workspace for the activations' digits.
-lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M, int cus, bool prefill, bool room, DecodeLaunch* out)
+// symmetric codes without an offset.
+lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M, int cus, bool prefill, DecodeLaunch* out)
 {
     DecodeArgs& a = out->a;
     const int waves = decode_waves(M);
@@ -408,7 +378,7 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     const size_t partial_bytes = ((size_t)2 * n_blocks * a.slot_floats * sizeof(float) + 255) & ~(size_t)255;
     // after the partial tiles: what decode_prepare_kernel leaves for a launch whose last pass has up to 32 token rows
     const int last_rows = (M - 1) % 64 + 1;
-    const bool in_place = reads_in_place(calls, begin, end, M), digits = room && takes_digits(calls, begin, end, M);
+    const bool in_place = reads_in_place(calls, begin, end, M);
     uint64_t total = 0;
     size_t sums_off16 = 0;                       // in 16-byte units
     for (size_t c = begin; c < end; ++c) {
@@ -423,7 +393,7 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
         L.residual = static_cast<const uint16_t*>(calls[c].residual);
         L.act = (uint8_t)calls[c].act;
         L.aux = (int32_t)sums_off16;
-        sums_off16 += prepared_bytes(w.d, last_rows, in_place, digits) / 16;
+        sums_off16 += prepared_bytes(w.d, last_rows, in_place) / 16;
         if (w.d.K / 128 > 0xffff) return LPQ_ERR_UNSUPPORTED;          // the descriptor keeps K / 128 in 16 bits
         L.kt = (uint16_t)(w.d.K / 128);
         L.N = w.d.N;
@@ -492,11 +462,9 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
     if (in_place)
         for (int i = 0; i < a.n_lin; ++i)
             if (a.lin[i].variant == 0) a.lin[i].variant = V_W3_INPLACE;
-    if (digits)
-        for (int i = 0; i < a.n_lin; ++i) a.lin[i].variant = (uint8_t)(a.lin[i].variant == 0 ? V_W3_DIGITS : V_W4_DIGITS);
     out->kernel = DECODE_EVEN_SHARE;
     out->partial_bytes = partial_bytes;
-    out->workspace_bytes = partial_bytes + sums_off16 * 16;
+    out->workspace_bytes = partial_bytes + (last_rows <= 32 ? sums_off16 * 16 : 0);
     return LPQ_OK;
 }
 
@@ -540,18 +508,16 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
     DecodeLaunch one;                            // the usual call is a single launch: no allocation, no clearing of 4 KB
     std::vector<DecodeLaunch> several(n_launch > 1 ? n_launch : 0);
     DecodeLaunch* const plan = n_launch > 1 ? several.data() : &one;
+    size_t need = 0;
+    for (size_t li = 0; li < n_launch; ++li) {
+        st = plan_decode(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M, cus, prefill, &plan[li]);
+        if (st != LPQ_OK) return st;
+        need = std::max(need, plan[li].workspace_bytes);
+    }
     float* ws = nullptr;
-    // a second time, without digits, if there is no room for them (a reservation, the static scratch array)
-    for (bool room : {true, false}) {
-        size_t need = 0;
-        for (size_t li = 0; li < n_launch; ++li) {
-            st = plan_decode(calls, li * per_launch, std::min(n, (li + 1) * per_launch), M, cus, prefill, room, &plan[li]);
-            if (st != LPQ_OK) return st;
-            need = std::max(need, plan[li].workspace_bytes);
-        }
-        if (need) st = workspace(static_ws, need, &ws);
-        if (st == LPQ_OK) break;
-        if (st != LPQ_ERR_BUFSIZE || !room) return st;
+    if (need) {
+        st = workspace(static_ws, need, &ws);
+        if (st != LPQ_OK) return st;
     }
     if (norm) {
         DecodeArgs& a = plan[0].a;
@@ -1137,7 +1103,7 @@ lpq_status lpq_route_of(const lpq_qdesc* descs, int32_t n, lpq_phase phase, int3
         return LPQ_OK;
     }
     std::vector<DecodeLaunch> plan(1);
-    const lpq_status st = plan_decode(calls, 0, calls.size(), M, compute_units, phase == LPQ_PREFILL, true, &plan[0]);
+    const lpq_status st = plan_decode(calls, 0, calls.size(), M, compute_units, phase == LPQ_PREFILL, &plan[0]);
     if (st != LPQ_OK) return st;
     out->kernel = plan[0].kernel;
     if (plan[0].kernel == DECODE_EVEN_SHARE) return LPQ_OK;

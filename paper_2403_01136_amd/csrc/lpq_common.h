@@ -12,11 +12,8 @@ namespace lpq {
 // per-variant cost factor); `cum_weight` is the total weight of the linears before it.
 // LinDesc::variant is the storage variant (0 .. 4: 3-, 4-, 8-bit grouped, 8-bit per row, fp16) -- or, in the descriptors
 // of a stage-wide decode launch only, V_W3_INPLACE: 3-bit codes that the kernel masks where they lie, against activations scaled
-// for it beforehand (lpq_decode.hip), or V_W3_DIGITS / V_W4_DIGITS: codes taken as fp6 numbers, against activations cut into fp6 digits; the
-// host decides per launch.
-enum { V_W3_INPLACE = 5, V_W3_DIGITS = 6, V_W4_DIGITS = 7 };
-// Activations in fp6 digits: bytes of a 128-column step of a tile of 16 token rows, five 16-byte pieces per lane
-enum { DIGIT_TILE = 5 * 1024 };
+// for it beforehand (lpq_decode.hip); the host decides per launch.
+enum { V_W3_INPLACE = 5 };
 
 struct LinDesc {
     const uint8_t* codes;
@@ -54,8 +51,8 @@ struct DecodeArgs {
     uint64_t range_q;                    // total_weight / n_blocks and
     uint32_t range_rem, pad2;            // total_weight % n_blocks: range b begins at range_q * b + range_rem * b / n_blocks
     float* partial;
-    const uint16_t* prep;                // stage-wide kernel: what the preparing kernel leaves (the activations' group sums at up to 32
-                                         // token rows per pass, for 3-bit weights the activations, scaled; or sums and fp6 digits)
+    const uint16_t* prep;                // stage-wide kernel, up to 32 token rows per pass: what decode_prepare_kernel leaves
+                                         // (the activations' group sums; for 3-bit weights the activations, scaled)
     const uint16_t *ln_gamma, *ln_beta;  // a single linear of up to 16 rows whose rows x the kernel layer-normalises first, or null
     const uint16_t *after_gamma, *after_beta;          // a single K-split linear of up to 16384 columns of y: the kernel that adds its splits also
     uint16_t* after_y;                                 // layer-normalises its rows into after_y; or null

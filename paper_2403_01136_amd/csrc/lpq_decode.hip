@@ -18,8 +18,7 @@
 //
 // Up to 32 token rows per pass the scale is applied after the matrix cores, per 128-column group, and the zero term
 // (sum over groups of zero * sum of x) once per unit from the activations' group sums, which decode_prepare_kernel
-// computes in front of the launch.  So they are in large launches of 33 to 64 rows of 3- and 4-bit weights, whose codes are multiplied as fp6
-// numbers with activations that decode_digits_kernel has cut into three fp6 digits; other launches of 33 to 64 rows dequantise to fp16.
+// computes in front of the launch.
 //
 // A launch that streams little (a single linear of a decoder layer) takes other kernels, further down, without a fix-up
 // pass: up to 16 token rows decode_rows_kernel (one workgroup per group of 16-row tiles whose waves split K, no LDS
@@ -54,15 +53,6 @@ template <int TOK, int WAVES, int CAP> struct PipeCfg {
 // c16 ^ (row % 16) of that step: rows are a multiple of 256 bytes apart, and the swizzle makes the
 // 16-byte operand reads of 16 consecutive rows hit 16 different bank groups.
 template <int TOK, int WAVES, int CAP> struct DecodeSmem { uint16_t x[2][TOK][PipeCfg<TOK, WAVES, CAP>::ROW_HALVES]; };
-
-// Launches of fp6 digits (TOK = 48 or 64): MT tiles of 16 token rows, two buffers of four steps of DIGIT_TILE bytes per tile, in the order
-// the lanes take them: 160 KB of LDS at four tiles.
-template <int TOK> struct DigitCfg { enum { MT = TOK / 16, CHUNK = 4, PIECES = CHUNK * MT * 5 }; };       // 1 KB pieces of a chunk
-template <int TOK, int WAVES, int CAP, bool DIGITS> constexpr size_t decode_smem_bytes()
-{
-    if constexpr (DIGITS) return (size_t)2 * DigitCfg<TOK>::PIECES * 1024;
-    else return sizeof(DecodeSmem<TOK, WAVES, CAP>);
-}
 
 // Halves per token row of a linear's group sums (see decode_prepare_kernel).
 __device__ __host__ __forceinline__ int group_sums_stride(int K) { return 2 * ((K / 128 + 15) & ~15) + 8; }
@@ -109,38 +99,6 @@ template <int V, bool SIGNED> __device__ __forceinline__ h8 unpack_small(const W
     else return unpack_subnormal_step<V>(w, j);
 }
 
-// Infinite activations in small launches and those of fp6 digits.  Scale and zero applied behind the products (as the offset of 8-bit codes) turn an infinity
-// into Inf - Inf = NaN, where a product with the dequantised weights is infinite with the weight's sign.  A sum that
-// is not finite betrays them at no cost inside the loop; then, and only for the tokens concerned, a wave forms its sums
-// again, slowly, from weights dequantised to fp16.  tile: the tile's place in 64-row block rb; xlane: the lane's token row plus 8 * kq;
-// the wave's steps are step(0) .. step(n - 1), those from kt_end on left out.
-template <int V, typename Step>
-__device__ __forceinline__ f4 dequantised_sums(const LinDesc& L, long rb, int tile, const uint16_t* xlane, int n, int kt_end, Step step)
-{
-    constexpr int SCHEME = VInfo<V>::SCHEME, TILE = VInfo<V>::TILE_BYTES, LANE_BYTES = V == V_W3 ? 12 : 16;
-    const int lane = threadIdx.x & 63, r = lane & 15;
-    f4 sum = {0, 0, 0, 0};
-#pragma unroll 1
-    for (int i = 0; i < n; ++i) {
-        const int kt = step(i);
-        if (kt >= kt_end) continue;
-        const WRaw<V> w = load_tile_at<V>(L.codes + ((size_t)rb * L.kt + kt) * (4 * (size_t)TILE) + tile * TILE + LANE_BYTES * lane);
-        h8 o[4];
-        unpack_codes<V>(w, o);
-        if constexpr (SCHEME == SCH_ASYM) {
-            const size_t at = (size_t)kt * L.N + rb * 64 + 4 * r + tile;
-            apply_scale_zero(o, __builtin_bit_cast(_Float16, L.scales[at]), __builtin_bit_cast(_Float16, L.zeros[at]));
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sum = mfma16(*reinterpret_cast<const h8*>(xlane + (size_t)kt * 128 + 32 * j), o[j], sum);
-    }
-    return sum;
-}
-__device__ __forceinline__ bool any_not_finite(const f4& v)
-{
-    return __any(!(__builtin_isfinite(v[0]) && __builtin_isfinite(v[1]) && __builtin_isfinite(v[2]) && __builtin_isfinite(v[3])));
-}
-
 // A chunk: up to CHUNK consecutive 128-column steps of one (linear, row superblock) unit.
 struct Chunk {
     int sb, kt0, n;      // row superblock, first step, number of steps (0 = none)
@@ -151,25 +109,22 @@ struct Chunk {
 // the end of a unit the accumulators are stored -- as fp16 if the unit's whole K range lay inside
 // [s_begin, s_end), else as an fp32 partial tile in slot_first (the unit this range entered mid-way)
 // or slot_last (the unit it leaves mid-way) -- and cleared.
-// DIGITS (3 and 4 bit, TOK 48 and 64): fp6 codes against activations in three fp6 digits.
-template <int V, int TOK, int WAVES, int CAP, bool INPL = false, bool DIGITS = false>
+template <int V, int TOK, int WAVES, int CAP, bool INPL = false>
 __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long s_begin, long s_end, const uint16_t* __restrict__ prep,
-                                          float* __restrict__ slot_first, float* __restrict__ slot_last, uint8_t* __restrict__ smem)
+                                          float* __restrict__ slot_first, float* __restrict__ slot_last, DecodeSmem<TOK, WAVES, CAP>& sm)
 {
     constexpr int RT = DecodeCfg<V>::RT;
     constexpr int SCHEME = VInfo<V>::SCHEME;
-    constexpr bool WIDE = TOK > 32 && !DIGITS;      // 32x32x16 path
-    constexpr int MT = WIDE ? 1 : TOK / 16;         // narrow path and digits: 16-token tiles
+    constexpr bool WIDE = TOK > 32;                 // 32x32x16 path
+    constexpr int MT = WIDE ? 1 : TOK / 16;         // narrow path: 16-token tiles
     constexpr int NP = RT / 2, MT2 = WIDE ? TOK / 32 : 1;      // wide path: tile pairs and 32-token tiles
-    constexpr int CHUNK = DIGITS ? (int)DigitCfg<TOK>::CHUNK : (int)PipeCfg<TOK, WAVES, CAP>::CHUNK, XQ = PipeCfg<TOK, WAVES, CAP>::XQ;
-    DecodeSmem<TOK, WAVES, CAP>& sm = *reinterpret_cast<DecodeSmem<TOK, WAVES, CAP>*>(smem);
-    // 32-token launches keep two steps in flight per wave: their second token tile needs the registers; so do four tiles of digits (four
-    // steps spill into the loop: 14336-wide layers, 3 bit, 64 rows 1455 us, so 1334)
-    constexpr int WANT = TOK == 32 || (DIGITS && MT == 4) ? 2 : (int)DecodeCfg<V>::DEPTH;
+    constexpr int CHUNK = PipeCfg<TOK, WAVES, CAP>::CHUNK, XQ = PipeCfg<TOK, WAVES, CAP>::XQ;
+    // 32-token launches keep two steps in flight per wave: their second token tile needs the registers
+    constexpr int WANT = TOK == 32 ? 2 : (int)DecodeCfg<V>::DEPTH;
     constexpr int STAGES = WANT < CHUNK ? WANT : CHUNK;
     // vector-memory loads of one Stage: the tiles (one load per KB, the 768-byte 3-bit tile included) and scale + zero
-    constexpr bool POST = DIGITS || (TOK <= 32 && V != V_F16);   // scale and zero folded in after the matrix cores (see compute below)
-    constexpr bool INPLACE = POST && !DIGITS && V == V_W3 && INPL;   // 3-bit codes masked where they lie, against activations scaled for it
+    constexpr bool POST = TOK <= 32 && V != V_F16;   // scale and zero folded in after the matrix cores (see compute below)
+    constexpr bool INPLACE = POST && V == V_W3 && INPL;   // 3-bit codes masked where they lie, against activations scaled for it
     constexpr int STAGE_LOADS = RT * (VInfo<V>::TILE_BYTES >= 1024 ? VInfo<V>::TILE_BYTES / 1024 : 1) + (SCHEME == SCH_ASYM ? (POST ? 1 : 2) : 0);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 15, kq = lane >> 4;
@@ -312,46 +267,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             }
             return;
         }
-        if constexpr (DIGITS) {
-            // A token tile's operands are read while the tile before is multiplied, and its group products are scaled and added
-            // while the next one is: the wait for a batch of reads stands ahead of the next batch's issue.
-            const uint8_t* xs = smem + ((size_t)buf * DigitCfg<TOK>::PIECES + (size_t)step * MT * 5) * 1024 + 16 * lane;
-            u32x4 a[2][5];
-            auto read_x = [&](u32x4 (&o)[5], int m) {
-#pragma unroll
-                for (int i = 0; i < 5; ++i) o[i] = *reinterpret_cast<const u32x4*>(xs + (5 * m + i) * 1024);
-            };
-            read_x(a[0], 0);
-            uint32_t wb[RT][6];
-#pragma unroll
-            for (int t = 0; t < RT; ++t) unpack_digits<V>(b.w[t], wb[t]);
-            f4 d[2][RT];
-            auto add_products = [&](int m) {
-#pragma unroll
-                for (int t = 0; t < RT; ++t) {
-                    const float sf = (float)as_h2(b.s[t >> 1])[t & 1];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[t][m][v] = __builtin_fmaf(sf, d[m & 1][t][v], acc[t][m][v]);
-                }
-            };
-            const f4 zero4 = {0, 0, 0, 0};
-#pragma unroll
-            for (int m = 0; m < MT; ++m) {
-                __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0)
-                if (m + 1 < MT) read_x(a[(m + 1) & 1], m + 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t = 0; t < RT; ++t) d[m & 1][t] = mfma_digit<2>(a[m & 1], wb[t], zero4);
-                if (m > 0) add_products(m - 1);
-#pragma unroll
-                for (int t = 0; t < RT; ++t) d[m & 1][t] = mfma_digit<1>(a[m & 1], wb[t], d[m & 1][t]);
-#pragma unroll
-                for (int t = 0; t < RT; ++t) d[m & 1][t] = mfma_digit<0>(a[m & 1], wb[t], d[m & 1][t]);
-            }
-            add_products(MT - 1);
-            return;
-        }
-        if constexpr (POST && !DIGITS) {
+        if constexpr (POST && !WIDE) {
             // In-order issue: vector work in front of a run of matrix instructions is not hidden by
             // them, vector work between them is.  So the codes of MFMA step j + 1 are unpacked in the
             // same scheduling group as the matrix instructions of step j.
@@ -431,21 +347,6 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(xrows), (short)0,
                                                                           (int)(2u * (uint32_t)x_rows * (uint32_t)L.K()), 0x00020000);
     auto fill_x_chunk = [&](const Chunk& c, int buf) {
-        if constexpr (DIGITS) {
-            // a chunk's pieces are consecutive; buffer loads, which the compiler counts together with the weight loads
-            constexpr int PIECES = DigitCfg<TOK>::PIECES;
-            const int w = __builtin_amdgcn_readfirstlane(wave);
-            const uint8_t* digits = reinterpret_cast<const uint8_t*>(prep) + (size_t)L.aux * 16 + (size_t)TOK * group_sums_stride(L.K()) * 2;
-            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(digits), (short)0, KT * MT * DIGIT_TILE, 0x00020000);
-#pragma unroll
-            for (int i = 0; i < (PIECES + WAVES - 1) / WAVES; ++i) {
-                const int q = min(w + WAVES * i, PIECES - 1);          // three tiles: some waves repeat the last piece
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)(smem + ((size_t)buf * PIECES + q) * 1024), 16, 16 * lane,
-                                                         (c.kt0 * MT * 5 + min(q, c.n * MT * 5 - 1)) * 1024, 0, 0);
-            }
-            asm volatile("" ::: "memory");
-            return;
-        }
 #pragma unroll
         for (int i = 0; i < XQ; ++i) {
             const int q = XQ * wave + i;
@@ -573,26 +474,6 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
                     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) acc[t][mt][v] *= undo[mt][v];
-                if constexpr (DIGITS) {
-                    // infinite activations, as from weights dequantised ahead of the product
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        f4 seen = acc[0][mt];          // rows past the call's hold anything
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) seen[v] = m0 + 16 * mt + 4 * kq + v < M ? seen[v] : 0.0f;
-                        if (__builtin_expect(!any_not_finite(seen), 1)) continue;
-                        const uint16_t* xlane = L.x + (size_t)min(m0 + 16 * mt + r, M - 1) * L.K() + 8 * kq;
-#pragma unroll 1
-                        for (int t = 0; t < RT; ++t) {
-                            const f4 sum = dequantised_sums<V>(L, rb, t, xlane, g_hi - g_lo, g_hi, [&](int i) { return g_lo + i; });
-#pragma unroll
-                            for (int u = 0; u < RT; ++u)
-#pragma unroll
-                                for (int v = 0; v < 4; ++v)
-                                    if (u == t && !__builtin_isfinite(acc[u][mt][v])) acc[u][mt][v] = sum[v];
-                        }
-                    }
-                }
             }
             float post[RT], bias[RT];
 #pragma unroll
@@ -660,7 +541,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
                 const int q = i + STAGES;                   // slot to refill
                 if (q < N) issue(st[i % STAGES], cur.sb, cur.kt0 + q, oc);
                 else       issue(st[i % STAGES], nxt.sb, nxt.kt0 + (q - N), on);
-                if constexpr (WIDE || DIGITS) __builtin_amdgcn_sched_barrier(0);      // keeps a step's operand reads out of earlier steps (register pressure)
+                if constexpr (WIDE) __builtin_amdgcn_sched_barrier(0);      // keeps a step's operand reads out of earlier steps (register pressure)
             }
             // the next chunk's activations were requested before this chunk's last STAGES refills, which stay in flight
             wait_vmem_all_but<STAGES * STAGE_LOADS>();
@@ -752,22 +633,6 @@ __device__ __forceinline__ uint64_t range_begin(const DecodeArgs& a, int b)
 // the sums in registers for the second use; a longer row is read twice.
 constexpr int GS_THREADS = 1024, GS_ROUNDS = 8, GS_LANES = 16, GS_GROUPS = GS_THREADS / GS_LANES;
 
-// the power of two that brings m into [2^(top-1), 2^top); 1 for a row of zeros (or one that holds an infinity)
-__device__ __forceinline__ float power_for(float m, int top)
-{
-    if (!(m > 0.0f && m < __builtin_inff())) return 1.0f;
-    int ex;
-    (void)frexpf(m, &ex);                             // m = f * 2^ex, f in [0.5, 1)
-    return ldexpf(1.0f, max(-40, min(40, top - ex)));
-}
-
-// A group's pair of a row's sums (see above)
-__device__ __forceinline__ uint32_t sum_pair(float scaled)
-{
-    const _Float16 hi = (_Float16)scaled, lo = (_Float16)(scaled - (float)hi);
-    return (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
-}
-
 template <bool ANY_INPLACE>
 __global__ __launch_bounds__(GS_THREADS) void decode_prepare_kernel(const DecodeArgs a, uint16_t* __restrict__ prep)
 {
@@ -828,10 +693,21 @@ __global__ __launch_bounds__(GS_THREADS) void decode_prepare_kernel(const Decode
     big = xbig = 0.0f;
 #pragma unroll
     for (int w = 0; w < GS_THREADS / 64; ++w) { big = fmaxf(big, wmax[0][w]); xbig = fmaxf(xbig, wmax[1][w]); }
+    // the power of two that brings m into [2^(top-1), 2^top); 1 for a row of zeros (or one that holds an infinity)
+    auto power_for = [](float m, int top) {
+        if (!(m > 0.0f && m < __builtin_inff())) return 1.0f;
+        int ex;
+        (void)frexpf(m, &ex);                         // m = f * 2^ex, f in [0.5, 1)
+        return ldexpf(1.0f, max(-40, min(40, top - ex)));
+    };
     const float scale = power_for(big, 14);
     const float xscale = scaled ? power_for(xbig, 15) : 1.0f;
     auto store_sum = [&](int g, float sum) {
-        if (l16 == 0 && g < GP) reinterpret_cast<uint32_t*>(dst)[g] = sum_pair(sum * scale);
+        const float sc = sum * scale;
+        const _Float16 hi = (_Float16)sc;
+        const _Float16 lo = (_Float16)(sc - (float)hi);
+        if (l16 == 0 && g < GP)
+            reinterpret_cast<uint32_t*>(dst)[g] = (uint32_t)__builtin_bit_cast(uint16_t, hi) | ((uint32_t)__builtin_bit_cast(uint16_t, lo) << 16);
     };
     // the lane's eight columns are columns 8 * (l16 % 4) .. + 7 of MFMA step l16 / 4: output registers k = 0 .. 3 of that step
     float mult[4];
@@ -867,144 +743,11 @@ __global__ __launch_bounds__(GS_THREADS) void decode_prepare_kernel(const Decode
     }
 }
 
-// The same for 3- and 4-bit weights taken as fp6 codes: the group sums, and the activations as three fp6 digits.  Four threads per group,
-// each the 32 columns 32 j + 8 kq + e that an operand lane holds, as one block: scaled by a power of two 2^-e to a largest
-// |x| in [2, 4), x = d0 + d1 / 32 + d2 / 1024 with every digit the nearest fp6 number to what is left: a digit keeps at least four
-// bits and leaves at most half of its last one, so an element is exact to 2^-14 of a number in [2, 4) -- all of its 11 bits
-// from a 64th of the block's largest element up; what is smaller carries an absolute error of 2^-15 of that element.  The group sums are those of the
-// numbers the digits stand for, so that this error meets the weights w~ and not the codes (several times larger): with the sums of x itself the error
-// against 64 bits was 3.8e-4 to 4.5e-4 with a few channels thirty times larger, so 2.2e-4 to 2.4e-4.
-// The digits' scales 2^e, 2^(e-5), 2^(e-10) go along as exponent bytes for the matrix instruction.  Order of a tile: DIGIT_TILE bytes per (step, tile of 16 rows), piece i of lane 16 kq + row % 16 at
-// 1024 i + 16 lane.
-template <int V>
-__device__ __forceinline__ void prepare_digits(const DecodeArgs& a, const LinDesc& L, int row, float* wmax, uint16_t* __restrict__ prep)
-{
-    typedef _Float16 h32 __attribute__((ext_vector_type(32)));
-    constexpr int GROUPS = GS_THREADS / 4;
-    const int rows = min(64, a.M - a.m0), tiles = (rows + 15) >> 4;
-    const int KT = L.kt, GP = (KT + 15) & ~15, rounds = (GP + GROUPS - 1) / GROUPS;
-    uint16_t* base = prep + (size_t)L.aux * 8;
-    uint16_t* dst = base + (size_t)row * group_sums_stride(L.K());
-    uint8_t* digits = reinterpret_cast<uint8_t*>(base + (size_t)16 * tiles * group_sums_stride(L.K()));
-    const int kq = threadIdx.x & 3, g0 = threadIdx.x >> 2;
-    const uint16_t* src = L.x + (size_t)(a.m0 + row) * L.K() + 8 * kq;
-    struct Block { h8 v[4]; };
-    auto load = [&](int g) {
-        Block b;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) b.v[j] = *reinterpret_cast<const h8*>(src + (size_t)min(g, KT - 1) * 128 + 32 * j);
-        return b;
-    };
-    auto group_sum = [&](const Block& b, float left, bool valid) {
-        float sum = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            sum += (((float)b.v[j][0] + (float)b.v[j][1]) + ((float)b.v[j][2] + (float)b.v[j][3])) +
-                   (((float)b.v[j][4] + (float)b.v[j][5]) + ((float)b.v[j][6] + (float)b.v[j][7]));
-        sum = valid ? sum - left : 0.0f;
-        sum += __shfl_xor(sum, 1, 4);
-        return sum + __shfl_xor(sum, 2, 4);
-    };
-    // stores the digits (if `store`); returns the sum of what they leave of the 32 elements
-    auto cut = [&](int g, const Block& b, bool store) {
-        float big = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) big = fmaxf(big, fabsf((float)b.v[j][e]));
-        // exponent byte of the first digit's scale: big * 2^-e in [2, 4).  fp16 numbers are no smaller than 2^-24
-        const int eb = max((int)(__builtin_bit_cast(uint32_t, big) >> 23), 127 - 24) - 1;
-        const float f = __builtin_bit_cast(float, (uint32_t)(254 - eb) << 23);
-        h32 x;
-#pragma unroll
-        for (int s = 0; s < 32; ++s) {
-            const int c = digits_code<V>(s);
-            x[s] = (_Float16)((float)b.v[c / 8][c % 8] * (digits_class<V>(s) ? 0.5f * f : f));
-        }
-        uint32_t o[20];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const auto q = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(x, 1.0f);
-#pragma unroll
-            for (int i = 0; i < 6; ++i) o[6 * d + i] = q[i];
-            x = (x - __builtin_amdgcn_cvt_scalef32_pk32_f16_fp6(q, 1.0f)) * (_Float16)32.0f;       // exact
-        }
-        float left = 0.0f;
-#pragma unroll
-        for (int s = 0; s < 32; ++s) left += (float)x[s] * (digits_class<V>(s) ? 2.0f : 1.0f);
-        left *= __builtin_bit_cast(float, (uint32_t)(eb - 15) << 23);
-        o[18] = (uint32_t)eb | (uint32_t)(eb - 5) << 8 | (uint32_t)(eb - 10) << 16;
-        o[19] = 0;
-        uint8_t* to = digits + ((size_t)g * tiles + (row >> 4)) * DIGIT_TILE + 16 * (16 * kq + (row & 15));
-        if (store)
-#pragma unroll
-            for (int i = 0; i < 5; ++i) *reinterpret_cast<u32x4*>(to + 1024 * i) = u32x4{o[4 * i], o[4 * i + 1], o[4 * i + 2], o[4 * i + 3]};
-        return left;
-    };
-    float sums[GS_ROUNDS], big = 0.0f;
-    const bool fits = rounds <= GS_ROUNDS;
-    if (fits) {
-#pragma unroll
-        for (int i = 0; i < GS_ROUNDS; ++i) {
-            sums[i] = 0.0f;
-            if (i < rounds) {
-                const int g = g0 + GROUPS * i;
-                const Block b = load(g);
-                sums[i] = group_sum(b, cut(g, b, g < KT), g < KT);
-                big = fmaxf(big, fabsf(sums[i]));
-            }
-        }
-    } else {
-        for (int g = g0; g < GP; g += GROUPS) {
-            const Block b = load(g);
-            big = fmaxf(big, fabsf(group_sum(b, cut(g, b, g < KT), g < KT)));
-        }
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) big = fmaxf(big, __shfl_xor(big, o, 64));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = big;
-    __syncthreads();
-    big = 0.0f;
-#pragma unroll
-    for (int w = 0; w < GS_THREADS / 64; ++w) big = fmaxf(big, wmax[w]);
-    const float scale = power_for(big, 14);
-    auto store_sum = [&](int g, float sum) {
-        if (kq == 0 && g < GP) reinterpret_cast<uint32_t*>(dst)[g] = sum_pair(sum * scale);
-    };
-    if (fits) {
-#pragma unroll
-        for (int i = 0; i < GS_ROUNDS; ++i)
-            if (i < rounds) store_sum(g0 + GROUPS * i, sums[i]);
-    } else {
-        for (int g = g0; g < GP; g += GROUPS) {
-            const Block b = load(g);
-            store_sum(g, group_sum(b, cut(g, b, false), g < KT));
-        }
-    }
-    if (threadIdx.x == 0) {
-        float* f = reinterpret_cast<float*>(dst + 2 * GP);
-        f[0] = scale * 8.0f;                           // an fp6 code is code / 8
-        f[1] = 1.0f / scale;
-    }
-}
-
-// Workgroups: (linear, tile of 16 token rows) items go round-robin over the XCDs and an item's rows to workgroups of one XCD, whose L2 puts their
-// 16-byte pieces of a line together.
-__global__ __launch_bounds__(GS_THREADS) void decode_digits_kernel(const DecodeArgs a, uint16_t* __restrict__ prep)
-{
-    __shared__ float wmax[GS_THREADS / 64];
-    const int slot = (int)(blockIdx.x >> 3), tiles = (min(64, a.M - a.m0) + 15) >> 4;
-    const int item = slot / 16 * 8 + (int)(blockIdx.x & 7), li = item / tiles, row = item % tiles * 16 + slot % 16;
-    if (li >= a.n_lin || a.m0 + row >= a.M) return;
-    const LinDesc& L = a.lin[li];
-    if (L.variant == V_W3_DIGITS) prepare_digits<V_W3>(a, L, row, wmax, prep);
-    else                          prepare_digits<V_W4>(a, L, row, wmax, prep);
-}
-
-template <int TOK, int WAVES, int CAP, bool DIGITS>
+template <int TOK, int WAVES, int CAP>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void decode_kernel(const DecodeArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) uint8_t sm[];
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
+    DecodeSmem<TOK, WAVES, CAP>& sm = *reinterpret_cast<DecodeSmem<TOK, WAVES, CAP>*>(smem_raw);
     // Workgroup ids go round-robin over the 8 XCDs, each with its own L2.  XCD x takes the x-th eighth of the
     // ranges, so that a linear's activations are fetched into one or two L2s instead of all eight.
     const int b = (a.n_blocks & 7) == 0 ? (int)(blockIdx.x & 7) * (a.n_blocks >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
@@ -1020,20 +763,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void decode_kernel(const Dec
         if (start >= hi) break;
         const long budget = (long)((hi - start + L.step_weight - 1) / L.step_weight);      // steps of this range from here
         const long s_end = min(steps, c.step + budget);
-        if constexpr (DIGITS) {
-            if (L.variant == V_W3_DIGITS) run_range<V_W3, TOK, WAVES, CAP, false, true>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm);
-            else                          run_range<V_W4, TOK, WAVES, CAP, false, true>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm);
-        } else {
-            switch (L.variant) {
-            case V_W3: run_range<V_W3, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
-            case V_W3_INPLACE:
-                if constexpr (TOK <= 16) run_range<V_W3, TOK, WAVES, CAP, true>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm);
-                break;
-            case V_W4: run_range<V_W4, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
-            case V_W8: run_range<V_W8, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
-            case V_I8: run_range<V_I8, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
-            default:   run_range<V_F16, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
-            }
+        switch (L.variant) {
+        case V_W3: run_range<V_W3, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
+        case V_W3_INPLACE:
+            if constexpr (TOK <= 16) run_range<V_W3, TOK, WAVES, CAP, true>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm);
+            break;
+        case V_W4: run_range<V_W4, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
+        case V_W8: run_range<V_W8, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
+        case V_I8: run_range<V_I8, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
+        default:   run_range<V_F16, TOK, WAVES, CAP>(L, a.M, a.m0, c.step, s_end, a.prep, slot_first, slot_last, sm); break;
         }
         c.step = s_end;
     }
@@ -1171,6 +909,38 @@ __global__ __launch_bounds__(256) void decode_fixup_kernel(const DecodeArgs a)
                    fetch(base + 256 * q + threadIdx.x));
         }
     }
+}
+
+// Infinite activations in small launches.  Scale and zero applied behind the products (as the offset of 8-bit codes) turn an infinity
+// into Inf - Inf = NaN, where a product with the dequantised weights is infinite with the weight's sign.  A sum that
+// is not finite betrays them at no cost inside the loop; then, and only for the tokens concerned, a wave forms its sums
+// again, slowly, from weights dequantised to fp16.  tile: the tile's place in 64-row block rb; xlane: the lane's token row plus 8 * kq;
+// the wave's steps are step(0) .. step(n - 1), those from kt_end on left out.
+template <int V, typename Step>
+__device__ __forceinline__ f4 dequantised_sums(const LinDesc& L, long rb, int tile, const uint16_t* xlane, int n, int kt_end, Step step)
+{
+    constexpr int SCHEME = VInfo<V>::SCHEME, TILE = VInfo<V>::TILE_BYTES, LANE_BYTES = V == V_W3 ? 12 : 16;
+    const int lane = threadIdx.x & 63, r = lane & 15;
+    f4 sum = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+        const int kt = step(i);
+        if (kt >= kt_end) continue;
+        const WRaw<V> w = load_tile_at<V>(L.codes + ((size_t)rb * L.kt + kt) * (4 * (size_t)TILE) + tile * TILE + LANE_BYTES * lane);
+        h8 o[4];
+        unpack_codes<V>(w, o);
+        if constexpr (SCHEME == SCH_ASYM) {
+            const size_t at = (size_t)kt * L.N + rb * 64 + 4 * r + tile;
+            apply_scale_zero(o, __builtin_bit_cast(_Float16, L.scales[at]), __builtin_bit_cast(_Float16, L.zeros[at]));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum = mfma16(*reinterpret_cast<const h8*>(xlane + (size_t)kt * 128 + 32 * j), o[j], sum);
+    }
+    return sum;
+}
+__device__ __forceinline__ bool any_not_finite(const f4& v)
+{
+    return __any(!(__builtin_isfinite(v[0]) && __builtin_isfinite(v[1]) && __builtin_isfinite(v[2]) && __builtin_isfinite(v[3])));
 }
 
 __device__ __forceinline__ float wave_sum(float v)
@@ -1880,8 +1650,7 @@ __global__ __launch_bounds__(1024) void decode_reduce_norm_kernel(const DecodeAr
 // 128 MiB per device, held until the process ends.  A decode launch of up to 32 token rows takes 32 MiB of partial
 // tiles (2 slots x 256 workgroups x 32 rows x 512 columns x 4 bytes), group sums (48 linears of K = 57344: 2.7 MiB)
 // and, at up to 16 rows, 2 bytes per token row and column of scaled activations for 3-bit linears read in place (ten
-// BLOOM-176B-shaped layers at 16 rows: 31 MiB); passes of 64 rows take 64 MiB of partial tiles, and launches in fp6 digits 2.5 bytes per
-// row (whole tiles of 16) and column, which run without digits where that does not fit.  Nothing in it has to
+// BLOOM-176B-shaped layers at 16 rows: 31 MiB); passes of 64 rows take 64 MiB of partial tiles.  Nothing in it has to
 // start at zero:
 // whatever is read was written earlier in the same call.
 constexpr size_t LPQ_SCRATCH_BYTES = (size_t)128 << 20;
@@ -1912,7 +1681,7 @@ hipError_t static_scratch(void** ptr, size_t* bytes)
     return hipSuccess;
 }
 
-template <int TOK, int WAVES, int CAP, bool DIGITS = false>
+template <int TOK, int WAVES, int CAP>
 static hipError_t launch_tok(const DecodeArgs& a, hipStream_t s)
 {
     // the slab may exceed the 64 KB that needs no opt-in: raise the kernel's limit once per device
@@ -1923,11 +1692,11 @@ static hipError_t launch_tok(const DecodeArgs& a, hipStream_t s)
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     std::call_once(flags[dev], [&] {
-        results[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<TOK, WAVES, CAP, DIGITS>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)decode_smem_bytes<TOK, WAVES, CAP, DIGITS>());
+        results[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<TOK, WAVES, CAP>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(DecodeSmem<TOK, WAVES, CAP>));
     });
     if (results[dev] != hipSuccess) return results[dev];
-    decode_kernel<TOK, WAVES, CAP, DIGITS><<<(unsigned)a.n_blocks, 64 * WAVES, decode_smem_bytes<TOK, WAVES, CAP, DIGITS>(), s>>>(a);
+    decode_kernel<TOK, WAVES, CAP><<<(unsigned)a.n_blocks, 64 * WAVES, sizeof(DecodeSmem<TOK, WAVES, CAP>), s>>>(a);
     return hipGetLastError();
 }
 
@@ -2041,14 +1810,6 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t s)
 {
     if (a.waves != 8) return hipErrorInvalidValue;
     const int rows = a.M - a.m0;
-    const bool digits = a.lin[0].variant == V_W3_DIGITS || a.lin[0].variant == V_W4_DIGITS;         // all of the launch's linears, or none
-    if (digits) {
-        if (!a.prep || rows <= 32 || rows > 64) return hipErrorInvalidValue;
-        const unsigned items = (unsigned)(a.n_lin * ((rows + 15) / 16));
-        decode_digits_kernel<<<(items + 7) / 8 * 128, GS_THREADS, 0, s>>>(a, const_cast<uint16_t*>(a.prep));
-        const hipError_t e0 = hipGetLastError();
-        if (e0 != hipSuccess) return e0;
-    }
     if (rows <= 32) {       // the kernels for up to 32 token rows take the zero term from the activations' group sums
         bool any = false;
         for (int li = 0; li < a.n_lin; ++li) any = any || a.lin[li].variant != V_F16;
@@ -2063,7 +1824,7 @@ hipError_t launch_decode(const DecodeArgs& a, hipStream_t s)
             if (e0 != hipSuccess) return e0;
         }
     }
-    hipError_t e = !digits ? launch_waves<8>(a, s) : rows > 48 ? launch_tok<64, 8, 8, true>(a, s) : launch_tok<48, 8, 8, true>(a, s);
+    hipError_t e = launch_waves<8>(a, s);
     if (e != hipSuccess) return e;
     if (a.n_blocks > 1) {
         const int m_cnt = std::min(64, a.M - a.m0);

@@ -428,84 +428,4 @@ __device__ __forceinline__ void pair_tiles_for_mfma32(h8& a, h8& b)
     b = __builtin_bit_cast(h8, ub);
 }
 
-// ---- 3- and 4-bit codes as fp6 numbers ------------------------------------------------------
-// In the fp6 format E2M3 (sign, 2 exponent bits, 3 mantissa bits) the encodings 0 .. 15 are the numbers 0/8 .. 15/8: a code
-// zero-extended to six bits IS the number code / 8, and a 3-bit code one bit further up is code / 4.  v_mfma_scale_f32_16x16x128_f8f6f4
-// multiplies fp6 operands at four times the rate of fp16 ones, so activations cut into three fp6 digits (decode_prepare_kernel) cost
-// three quarters of the matrix time of fp16 ones, and a tile's 32 codes per lane take 19 (3 bit) or 21 (4 bit) vector instructions instead of
-// 33 or 28: masks that pick the fields that lie right already, five at a time.  A lane's operand is 32 slots of six bits in six
-// registers, slot s at bit 6 s; which of the lane's 32 codes (c = 8 j + e: column 32 j + 8 kq + e) a slot holds is free, as long as the
-// activations are laid out alike: digits_code.  digits_class is 1 where a 3-bit code lies one bit up: those activations are halved.
-template <int V> __device__ __host__ constexpr int digits_code(int s)
-{
-    static_assert(V == V_W3 || V == V_W4, "3- and 4-bit codes");
-    if (V == V_W3) {
-        // fields of a word, as (pair field f, half): E = f0 f2 f4 of the low half, f1 f3 of the high one; O = the others.  Words 0 .. 5 of
-        // the operand hold E(0) O(0) O(1) E(1) O(2) E(2); slots 5 and 21, which cross words, the codes spread over the bits 15 and 31
-        constexpr int field[2][5] = {{0, 2, 4, 1, 3}, {1, 3, 0, 2, 4}}, high[2][5] = {{0, 0, 0, 1, 1}, {0, 0, 1, 1, 1}};
-        constexpr int odd[6] = {0, 1, 1, 0, 1, 0}, word[6] = {0, 0, 1, 1, 2, 2};
-        if (s == 5) return 31;
-        if (s == 21) return 30;
-        const int h = s / 16, i = s % 16, o = 3 * h + (i < 5 ? 0 : i < 11 ? 1 : 2), k = i < 5 ? i : i < 11 ? i - 6 : i - 11;
-        return 2 * (5 * word[o] + field[odd[o]][k]) + high[odd[o]][k];
-    }
-    // (word, nibble) of each slot; nibble n of a word is its code e = 2 n (n < 4) or 2 (n - 4) + 1
-    constexpr int at[32] = {000, 002, 003, 005, 006, 037, 001, 012, 004, 015, 007, 011, 022, 014, 025, 017,
-                            010, 032, 013, 035, 016, 030, 021, 033, 024, 036, 027, 020, 031, 023, 034, 026};     // octal: word * 8 + nibble
-    const int n = at[s] % 8;
-    return 8 * (at[s] / 8) + (n < 4 ? 2 * n : 2 * (n - 4) + 1);
-}
-template <int V> __device__ __host__ constexpr int digits_class(int s)
-{
-    if (V != V_W3) return 0;
-    if (s == 5 || s == 21) return 1;
-    const int h = s / 16, i = s % 16, w = i < 5 ? 0 : i < 11 ? 1 : 2, k = i < 5 ? i : i < 11 ? i - 6 : i - 11;
-    const int odd = w == 0 ? 0 : w == 1 ? 1 : (h == 0 ? 1 : 0);                // words 0 .. 5: E O O E O E
-    return k >= (odd ? 2 : 3);
-}
-
-__device__ __forceinline__ uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
-
-template <int V>
-__device__ __forceinline__ void unpack_digits(const WRaw<V>& w, uint32_t o[6])
-{
-    static_assert(V == V_W3 || V == V_W4, "3- and 4-bit codes");
-    if constexpr (V == V_W3) {
-        const uint32_t a = w.q[0], b = w.q[1], c = w.q[2];
-        constexpr uint32_t E = 7u | 7u << 6 | 7u << 12 | 7u << 19 | 7u << 25, O = 7u << 3 | 7u << 9 | 7u << 16 | 7u << 22 | 7u << 28;
-        o[0] = a & (E | 1u << 31);                                             // and bit 0 of the code in the bits 31: slot 5, one bit up
-        o[1] = ((a << 1) & (O << 1)) | bit_select(1u, b >> 31, c >> 30);       // and its bits 1 and 2
-        o[2] = (b >> 1) & (O >> 1);
-        o[3] = ((a << 16) & 0x80000000u) | (b & E);                            // and the code in the bits 15: slot 21, one bit up
-        o[4] = ((c << 1) & (O << 1)) | (bit_select(1u, b >> 15, c >> 14) & 3u);
-        o[5] = (c << 2) & (E << 2);
-    } else {
-        constexpr uint32_t T0 = 15u | 15u << 12 | 15u << 24, T4 = T0 << 4, T2 = T0 << 2;      // three nibbles twelve bits apart, from bit 0, 4, 2
-        constexpr uint32_t P8 = 15u << 8 | 15u << 20, P6 = P8 >> 2, P10 = P8 << 2;            // two, from bit 8, 6, 10
-        const uint32_t a = w.q[0], b = w.q[1], c = w.q[2], d = w.q[3], a2 = a >> 2, d2 = d >> 2;
-        o[0] = ((a & T0) | (a2 & P6)) | ((d << 2) & 0xc0000000u);              // and the low half of d's top nibble: slot 5
-        o[1] = __builtin_amdgcn_alignbit((b & P8) | (a2 & T2), d, 30);         // and its high half
-        o[2] = (c & P8) | ((b >> 2) & T2);
-        o[3] = ((b & T0) | (d2 & P6)) | (d << 30);                             // and the low half of d's lowest nibble: slot 21
-        o[4] = (c & T4) | (d2 & (P10 | 3u));                                   // and its high half
-        o[5] = ((c << 2) & T2) | ((d << 4) & P8);
-    }
-}
-
-// One matrix instruction over 128 columns: digit DIGIT of the activations (a: a lane's 18 registers of digits, then its three scales as
-// exponent bytes) against fp6 codes.
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-template <int DIGIT>
-__device__ __forceinline__ f4 mfma_digit(const u32x4 (&a)[5], const uint32_t (&b)[6], f4 c)
-{
-    i32x8 av = {0, 0, 0, 0, 0, 0, 0, 0}, bv = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        av[i] = (int)a[(6 * DIGIT + i) / 4][(6 * DIGIT + i) % 4];
-        bv[i] = (int)b[i];
-    }
-    // formats 2 and 2: fp6 E2M3 both; scale byte DIGIT of the lane's word; the codes' scale is 2^0
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, c, 2, 2, DIGIT, (int)a[4][2], 0, 127);
-}
-
 }  // namespace lpq

@@ -628,14 +628,38 @@ def even_share():
 
 
 @pytest.mark.parametrize("bits", [3, 4], ids=["w3", "w4"])
+@pytest.mark.parametrize("size", [300.0, 1000.0, 10000.0, 60000.0])
+def test_decode_beside_large_activations(bits, size, even_share):
+    """Activations are read as they are, whatever stands next to them: one element of each row is up to 60000 times the others, in a column whose
+    weights are zero in W and in W~, so that the outputs are made of the others alone.  Against 64 bits, row by row: the rounding of the output (2.1e-4 of
+    it) and, in calls of 33 rows and more, that of the weights to fp16 (1.7e-4), 2.7e-4 together; 4e-4 leaves room for sums of 1152 terms in 32 bits."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(bits)
+    K, N = 1152, 1088
+    col = torch.arange(64, device="cuda") * 17 % K                                        # every place of a lane's 32 columns
+    w = (torch.randn((N, K), generator=gen, device="cuda") * 0.02).abs().half()           # a group's least weight is the 0 there
+    w[:, col] = 0.0
+    qw = lpq.lpq_quantize_pack(w, bits, lpq.LPQ_ASYM_GROUP)
+    deq = lpq.lpq_unpack_dequant(qw).double()
+    assert float(deq[:, col].abs().max()) == 0.0
+    x = torch.randn((64, K), generator=gen, device="cuda").half()
+    x[torch.arange(64, device="cuda"), col] = size
+    ref = x.double() @ deq.t()
+    for M in (8, 24, 33, 48, 64):
+        assert lpq.lpq_route_of([(bits, lpq.LPQ_ASYM_GROUP, K, N)], lpq.LPQ_DECODE, M)[0] == lpq.LPQ_ROUTE_EVEN_SHARE
+        y = lpq.lpq_qlinear_decode(qw, x[:M]).double()
+        err = (y - ref[:M]).norm(dim=1) / ref[:M].norm(dim=1)
+        assert float(err.max()) <= 4e-4, "%d rows: row %d off by %.2e" % (M, int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("bits", [3, 4], ids=["w3", "w4"])
 @pytest.mark.parametrize("K,N", [(128, 64), (384, 320), (4736, 192), (1152, 1088), (2048 * 128 + 1152, 64)])
-def test_decode_33_to_64_rows_in_digits(bits, K, N, even_share):
-    """The even-share kernel of fp6 codes and activations in three fp6 digits (33 to 64 rows, 3- and 4-bit weights), at the edges of its token
-    tiles, with waves without a row block, chunks of one to four steps and rows longer than the preparing kernel keeps sums of;
+def test_decode_33_to_64_rows_even_share(bits, K, N, even_share):
+    """The even-share kernel of 33 to 64 rows, 3- and 4-bit weights, at the edges of its token
+    tiles, with waves without a row block, chunks of one step to a whole one and rows of up to 263296 columns;
     rows of unlike magnitude, rows of zeros and of the smallest fp16 numbers, elements thirty and a thousand times their neighbours,
-    bias, activation and a residual in place.  Against 64 bits, row by row: the rounding of the output (2.1e-4 of it), plus digits that
-    are exact to 2^-15 of a block's largest element -- a thousand times the others, 2^-15 * 1000 / sqrt(3) of each of those 31 --
-    against a result that this largest element dominates: within 1e-4 of it; 4e-4 leaves a quarter for sums in 32 bits."""
+    bias, activation and a residual in place.  Against 64 bits, row by row: the roundings of the output and of the weights to fp16
+    (2.1e-4 and 1.7e-4 of it, 2.7e-4 together); 4e-4 leaves room for sums in 32 bits."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(K + N + bits)
     w = (torch.randn((N, K), generator=gen, device="cuda") * 0.02).half()
@@ -651,6 +675,7 @@ def test_decode_33_to_64_rows_in_digits(bits, K, N, even_share):
     x[3] = 2.0 ** -24
     acc = x.double() @ deq.t()
     for M in (33, 47, 48, 49, 63, 64):
+        assert lpq.lpq_route_of([(bits, lpq.LPQ_ASYM_GROUP, K, N)], lpq.LPQ_DECODE, M)[0] == lpq.LPQ_ROUTE_EVEN_SHARE
         y = lpq.lpq_qlinear_fused(qw, x[:M], lpq.LPQ_DECODE).double()
         ref = acc[:M] + bias.double()
         err = (y - ref).norm(dim=1) / ref.norm(dim=1)
@@ -658,22 +683,23 @@ def test_decode_33_to_64_rows_in_digits(bits, K, N, even_share):
         res = torch.randn((M, N), generator=gen, device="cuda").half()
         z = res.clone()
         lpq.lpq_qlinear_fused(qw, x[:M], lpq.LPQ_DECODE, activation=lpq.LPQ_ACT_RELU, residual=z, y=z)
-        check_output(z, (torch.relu(ref) + res.double()).cpu().numpy(), "digits %d rows" % M)
+        check_output(z, (torch.relu(ref) + res.double()).cpu().numpy(), "even share, %d rows" % M)
 
 
 @pytest.mark.parametrize("M", [40, 64])
 @pytest.mark.parametrize("bits", [3, 4], ids=["w3", "w4"])
-def test_infinite_activations_in_digits(bits, M, even_share):
+def test_infinite_activations_even_share(bits, M, even_share):
+    assert lpq.lpq_route_of([(bits, lpq.LPQ_ASYM_GROUP, 2304, 320)], lpq.LPQ_DECODE, M)[0] == lpq.LPQ_ROUTE_EVEN_SHARE
     test_infinite_activations(lpq.LPQ_DECODE, M, bits, lpq.LPQ_ASYM_GROUP)
 
 
 @pytest.mark.parametrize("M", [40, 64])
-def test_decode_digits_without_room(M, even_share):
-    """A launch whose digits do not fit the static scratch array (128 MiB) runs without them, as before there were any."""
+def test_decode_of_long_rows_without_allocation(M, even_share):
+    """A launch of 40 linears of 65536 columns, on the workspace and on the static scratch array (128 MiB): the same bits, right ones."""
     import torch
     layer = {n: lpq.lpq_quantize_pack((torch.randn((N, K), device="cuda") * 0.02).half(), 3, lpq.LPQ_ASYM_GROUP)
              for n, (K, N) in {"qkv": (65536, 64), "out": (65536, 64), "fc1": (65536, 64), "fc2": (65536, 64)}.items()}
-    n = 10                                                  # 40 linears of 65536 columns: 315 MB of digits at 40 rows beside 64 MiB of partial tiles
+    n = 10
     xs = [{k: torch.randn((M, 65536), device="cuda").half() for k in layer}] * n
     out = []
     for static in (False, True):
@@ -681,6 +707,7 @@ def test_decode_digits_without_room(M, even_share):
         (lpq.lpq_stage_linears_noalloc if static else lpq.lpq_stage_linears)(lpq.Stage([layer] * n, xs, ys), lpq.LPQ_DECODE)
         out.append(ys)
     for name in layer:
+        assert all(torch.equal(a[name], b[name]) for a, b in zip(*out)), "%s, %d rows: other bits" % (name, M)
         ref = xs[0][name].double() @ lpq.lpq_unpack_dequant(layer[name]).double().t()
         for ys in out:
             check_output(ys[n - 1][name], ref.cpu().numpy(), "%s, %d rows" % (name, M))
