@@ -249,8 +249,6 @@ lpq_status lpq_layernorm(const void *x, const void *gamma, const void *beta, flo
 
 /* Copy the K and V parts of qkv (device fp16 [n_seqs * T][3 * hidden]; per token q | k | v, heads of
  * head_dim each) into the caches at positions pos0 .. pos0 + T - 1 of sequences 0 .. n_seqs - 1.
- * T = 1 reads the 32 positions around pos0 (from a multiple of 32 on) of each feature row of V and stores them again with
- * the new one: calls that write the same rows of one cache are ordered, as on one stream.
  * Errors: NULL, SHAPE (head_dim, max_seq, pos0 + T > max_seq, counts < 1), ALIGN, DEVICE. */
 lpq_status lpq_kv_append(const void *qkv, const lpq_layer_cfg *cfg, const lpq_layer_state *st, int32_t n_seqs, int32_t T,
                          int32_t pos0, void *hip_stream);

@@ -148,35 +148,33 @@ struct OpMax { __device__ __forceinline__ float operator()(float a, float b) con
 
 constexpr float LOG2E = 1.4426950408889634f;
 
-// KV append of one token per sequence: a workgroup per (sequence, head).  In the transposed V cache the token is one value in each feature row.  Stored by
-// itself it is two bytes of a line that the memory has to read, change and write back, which goes on behind the kernel and holds the attention's reads
-// up; so 64 aligned bytes (32 positions; four lanes of 16 bytes) are read, changed and stored as a whole.  kv_append and attention, us, with stores of two
-// bytes / 16 / 64 / 128: 43 sequences of 56 heads at 1338 positions 290.9 / 265.8 / 264.4 / 274.3 (attention alone 241), 64 of 40 at 601 164.7 / 148.0 /
-// 147.1 / 156.0, 16 of 40 at 563 41.4 / 36.8 / 36.1 / 36.9.
+// KV append of one token per sequence: a workgroup per (sequence, head).  In the transposed V cache the token is one value in each feature row, two
+// bytes of a line.  Stored by themselves they miss the L2, and the memory reads, changes and writes the line behind the kernel, which holds the
+// attention's reads up.  So the line is read first and the store hits it; only the two bytes are stored (the other positions may be another
+// stream's to write: what is read of them is not used).  kv_append and attention, us, with the store alone / behind the read: 43 sequences of 56 heads at
+// 1338 positions 292.3 / 262.2 (attention alone 241), 64 of 56 at 1339 428.5 / 395.8, 64 of 40 at 601 161.8 / 142.3, 16 of 40 at 563 40.8 / 36.6; with 64 of
+// the 128 bytes read 266.3, 403.7, 142.5, 36.5.
 template <int D>
-__global__ __launch_bounds__(256) void kv_append_token_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ kc, uint16_t* __restrict__ vtc,
-                                                              int pos, int H, int S)
+__global__ __launch_bounds__(256) void kv_append_token_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ kc, uint16_t* vtc, int pos, int H, int S)
 {
-    constexpr int ROUNDS = D / 64;                     // 64 feature rows at a time
+    constexpr int ROUNDS = D / 64;                     // 64 feature rows at a time, four lanes a row
     const int bh = blockIdx.x, b = bh / H, head = bh % H, h = H * D, tid = threadIdx.x;
     const uint16_t* src = qkv + (size_t)b * 3 * h + head * D;
-    uint16_t* at = vtc + ((size_t)bh * D + tid / 4) * S + (pos & ~31) + 8 * (tid % 4);
-    u32x4 chunk[ROUNDS];
+    uint16_t* row = vtc + ((size_t)bh * D + tid / 4) * S;
+    const uint16_t* line = row + (pos & ~63) + 16 * (tid % 4);         // S is a multiple of 64
+    u32x4 seen[ROUNDS];
     uint16_t v[ROUNDS];
 #pragma unroll
     for (int i = 0; i < ROUNDS; ++i) {
-        chunk[i] = *reinterpret_cast<const u32x4*>(at + (size_t)64 * i * S);
+        seen[i] = *reinterpret_cast<const u32x4*>(line + (size_t)64 * i * S);
         v[i] = src[2 * h + 64 * i + tid / 4];
     }
     if (tid < D / 8) *reinterpret_cast<h8*>(kc + ((size_t)bh * S + pos) * D + 8 * tid) = *reinterpret_cast<const h8*>(src + h + 8 * tid);
-    const bool mine = tid % 4 == (pos % 32) / 8;       // the lane whose chunk the position lies in
 #pragma unroll
     for (int i = 0; i < ROUNDS; ++i) {
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            if (mine && (pos & 7) >> 1 == w)
-                chunk[i][w] = (pos & 1) ? (chunk[i][w] & 0xffffu) | (uint32_t)v[i] << 16 : (chunk[i][w] & 0xffff0000u) | v[i];
-        *reinterpret_cast<u32x4*>(at + (size_t)64 * i * S) = chunk[i];
+        const u32x4 rest = *reinterpret_cast<const u32x4*>(line + (size_t)64 * i * S + 8);
+        asm volatile("" ::"v"(seen[i]), "v"(rest) : "memory");                  // the reads are waited for ahead of the store
+        if (tid % 4 == 0) row[(size_t)64 * i * S + pos] = v[i];
     }
 }
 

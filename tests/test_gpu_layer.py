@@ -471,3 +471,25 @@ def test_kv_append_of_one_token(d, pos0):
     lpq.lpq_kv_append(to_dev(qkv), st, B, 1, pos0)
     OL.kv_append(k0, v0, qkv, B, 1, pos0, H)
     assert np.array_equal(u16(st.k_cache), k0.view(np.uint16)) and np.array_equal(u16(st.vt_cache), v0.view(np.uint16))
+
+
+@pytest.mark.parametrize("T", [1, 3])
+def test_kv_append_beside_another_writer(T):
+    """Other positions of the same V rows, in the same 32, are another stream's to write at the same time: both writers' values are there afterwards."""
+    import torch
+    B, H, d, S, pos0 = 8, 16, 128, 128, 69
+    st, _, _ = make_state(B, H, d, S, 5)
+    r = rng("kv2", T)
+    qkv, other = to_dev(f16(r.standard_normal((B * T, 3 * H * d)))), to_dev(f16(r.standard_normal((2, B, H, d, S))))
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for i in range(40):
+        with torch.cuda.stream(side):
+            st.vt_cache[:, :, :, 64:pos0].copy_(other[i % 2][:, :, :, 64:pos0])
+            st.vt_cache[:, :, :, pos0 + T:96].copy_(other[i % 2][:, :, :, pos0 + T:96])
+        for _ in range(3):
+            lpq.lpq_kv_append(qkv, st, B, T, pos0)
+        torch.cuda.synchronize()
+        want = other[i % 2].clone()
+        want[:, :, :, pos0:pos0 + T] = qkv.view(B, T, 3, H, d)[:, :, 2].permute(0, 2, 3, 1)
+        assert torch.equal(st.vt_cache[:, :, :, 64:96], want[:, :, :, 64:96]), "turn %d" % i
