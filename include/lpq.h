@@ -398,6 +398,18 @@ typedef struct {
 } lpq_route;
 lpq_status lpq_route_of(const lpq_qdesc *descs, int32_t n, lpq_phase phase, int32_t M, int32_t compute_units, lpq_route *out);
 
+/* What a decode-phase lpq_decoder_layer of linears `descs` (qkv, out, fc1, fc2) does with its layer norms and with the new token of each of
+ * n_seqs sequences at position pos0 (T = 1), under the same settings: a pure function, as lpq_route_of.
+ * Errors: NULL, BITS, SCHEME, SHAPE, UNSUPPORTED. */
+enum { LPQ_NORM_LAUNCH = 0,          /* a launch of its own                                                  */
+       LPQ_NORM_IN_LINEAR = 1,       /* in the kernel of the linear behind it                                */
+       LPQ_NORM_BEHIND_SPLITS = 2 }; /* in the kernel that adds the K splits of the linear in front of it    */
+typedef struct {
+    int32_t norm1, norm2;            /* LPQ_NORM_*                                                           */
+    int32_t append;                  /* 1: the attention kernel writes the caches, 0: a launch of its own    */
+} lpq_layer_route;
+lpq_status lpq_layer_route_of(const lpq_qdesc *descs, int32_t n_seqs, int32_t pos0, int32_t compute_units, lpq_layer_route *out);
+
 /* Test helper, not on the hot path: w_fp32[n][k] = scale * code + zero (fp32 multiply, then
  * fp32 add; the fp16 weight itself for LPQ_FP16) read back from the packed buffers.
  *   w_fp32: device float [N][K].  Errors: NULL, BITS, SCHEME, SHAPE, ALIGN, DEVICE. */

@@ -20,7 +20,7 @@ EXPORTS = ("lpq_packed_sizes", "lpq_quantize_pack", "lpq_quantize_pack_rows", "l
            "lpq_kv_append", "lpq_attention", "lpq_decoder_layer_workspace", "lpq_decoder_layer", "lpq_variance_indicator",
            "lpq_mem_embedding_bytes", "lpq_mem_layer_bytes", "lpq_mem_kv_bytes", "lpq_latency_fit", "lpq_latency_predict",
            "lpq_plan_objective", "lpq_plan_adabits", "lpq_plan_bitwidth_transfer",
-           "lpq_workspace_policy", "lpq_workspace_reserve", "lpq_workspace_bytes", "lpq_set_decode_routing", "lpq_route_of",
+           "lpq_workspace_policy", "lpq_workspace_reserve", "lpq_workspace_bytes", "lpq_set_decode_routing", "lpq_route_of", "lpq_layer_route_of",
            "lpq_unpack_dequant",
            "lpq_status_str")
 LPQ_ACT_NONE, LPQ_ACT_RELU, LPQ_ACT_GELU_TANH = 0, 1, 2
@@ -68,6 +68,11 @@ class lpq_route(ctypes.Structure):
     _fields_ = [("kernel", ctypes.c_int32), ("tiles", ctypes.c_int32), ("splits", ctypes.c_int32), ("whole_tiles", ctypes.c_int32)]
 
 
+class lpq_layer_route(ctypes.Structure):
+    _fields_ = [("norm1", ctypes.c_int32), ("norm2", ctypes.c_int32), ("append", ctypes.c_int32)]
+
+
+LPQ_NORM_LAUNCH, LPQ_NORM_IN_LINEAR, LPQ_NORM_BEHIND_SPLITS = 0, 1, 2
 LPQ_ROUTE_EVEN_SHARE, LPQ_ROUTE_ROWS, LPQ_ROUTE_MID, LPQ_ROUTE_PREFILL = 0, 1, 2, 3
 _dp, _ip = ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int32)
 
@@ -129,6 +134,7 @@ def load_library():
         L.lpq_workspace_bytes.argtypes = []
         L.lpq_set_decode_routing.argtypes = [i32, i32]
         L.lpq_route_of.argtypes = [ctypes.POINTER(lpq_qdesc), i32, ctypes.c_int, i32, i32, ctypes.POINTER(lpq_route)]
+        L.lpq_layer_route_of.argtypes = [ctypes.POINTER(lpq_qdesc), i32, i32, i32, ctypes.POINTER(lpq_layer_route)]
         L.lpq_status_str.argtypes = [ctypes.c_int]
         L.lpq_status_str.restype = ctypes.c_char_p
         other = {"lpq_decoder_layer_workspace": ctypes.c_size_t, "lpq_workspace_bytes": ctypes.c_size_t, "lpq_mem_embedding_bytes": ctypes.c_double,
@@ -514,6 +520,14 @@ def lpq_route_of(linears, phase, M, compute_units=256):
     r = lpq_route()
     _check(load_library().lpq_route_of(descs, len(linears), int(phase), int(M), int(compute_units), ctypes.byref(r)), "lpq_route_of")
     return r.kernel, r.tiles, r.splits, r.whole_tiles
+
+
+def lpq_layer_route_of(linears, n_seqs, pos0, compute_units=256):
+    """linears: [(bits, scheme, K, N)] of qkv, out, fc1 and fc2 -> (norm1, norm2, append) of a decode step as in lpq.h; host-only."""
+    descs = (lpq_qdesc * 4)(*[make_desc(*d) for d in linears])
+    r = lpq_layer_route()
+    _check(load_library().lpq_layer_route_of(descs, int(n_seqs), int(pos0), int(compute_units), ctypes.byref(r)), "lpq_layer_route_of")
+    return r.norm1, r.norm2, r.append
 
 
 def lpq_unpack_dequant(qw, stream=None):

@@ -490,6 +490,17 @@ bool norm_in_linear(int32_t M, int32_t K)
     return M <= 16 && K <= LN_LINEAR_MAX_K && (int64_t)M * K <= (K <= 4096 ? 16384 : 10240);
 }
 
+bool norm_inside(const DecodeLaunch& p) { return p.kernel == DECODE_ROWS && p.a.waves == 4 && norm_in_linear(p.a.M, (int32_t)p.a.lin[0].K()); }
+// Whether a launch of a single linear adds K splits in a kernel of their own, which can form a norm of the sums
+bool norm_behind(const DecodeLaunch& p) { return p.kernel != DECODE_EVEN_SHARE && p.a.lin[0].aux > 1; }
+
+// One new token per sequence: whether the attention kernel writes it to the caches itself, a launch less -- while the cache it reads is small: its stores of two
+// bytes then cost less than kv_append's launch.  Whole layer, 4 bit, us, in one launch / two, by the megabytes of cache: 8 (2 sequences, 2048 wide) 41.2 /
+// 41.9, 20 (4, 4096) 61.3 / 62.9, 49 (8, 5120) 86.8 / 88.9, 66 (16, 5120) 90.3 / 88.8, 184 (16, 5120) 107.4 / 105.9, 246 (8, 5120) 121.4 / 115.2, 344
+// (40, 7168) 212.9 / 199.5, 1648 (43, 7168) 436.5 / 395.2.  At the first position of a tile of 64 it also saves the reading of that tile: 1174 (64, 7168,
+// position 640) 375 / 386.
+bool append_in_attention(int32_t n_seqs, int64_t h, int32_t pos0) { return 4.0 * n_seqs * (double)h * pos0 <= 6.0e7 || pos0 % 64 == 0; }
+
 // Decode-phase dispatch of a list of independent linears: grouped launches of at most
 // MAX_LIN_PER_LAUNCH linears, 64 token rows per pass, each launch one round of equally loaded
 // workgroups (see lpq_decode.hip).  Every launch is planned, and the workspace of the largest asked for, ahead of the first
@@ -522,7 +533,7 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
     if (norm) {
         DecodeArgs& a = plan[0].a;
         const int64_t K = a.lin[0].K();
-        if (plan[0].kernel == DECODE_ROWS && a.waves == 4 && norm_in_linear(M, (int32_t)K)) {
+        if (norm_inside(plan[0])) {
             a.lin[0].x = static_cast<const uint16_t*>(norm->x);
             a.ln_gamma = static_cast<const uint16_t*>(norm->gamma);
             a.ln_beta = static_cast<const uint16_t*>(norm->beta);
@@ -531,7 +542,7 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
             return LPQ_ERR_DEVICE;
         }
     }
-    if (after && plan[0].kernel != DECODE_EVEN_SHARE && plan[0].a.lin[0].aux > 1) {
+    if (after && norm_behind(plan[0])) {
         DecodeArgs& a = plan[0].a;
         a.after_gamma = static_cast<const uint16_t*>(after->gamma);
         a.after_beta = static_cast<const uint16_t*>(after->beta);
@@ -928,12 +939,7 @@ lpq_status lpq_decoder_layer(const lpq_layer* layer, const lpq_layer_cfg* cfg, c
         return linear(wt, h1, out, nullptr, act);
     };
     if ((s = norm_linear(x, st->ln1_gamma, st->ln1_beta, &layer->qkv, qkv, LPQ_ACT_NONE)) != LPQ_OK) return s;
-    // One new token per sequence: the attention kernel writes it to the caches itself, a launch less -- while the cache it reads is small: its stores of two
-    // bytes then cost less than kv_append's launch.  Whole layer, 4 bit, us, in one launch / two, by the megabytes of cache: 8 (2 sequences, 2048 wide) 41.2 /
-    // 41.9, 20 (4, 4096) 61.3 / 62.9, 49 (8, 5120) 86.8 / 88.9, 66 (16, 5120) 90.3 / 88.8, 184 (16, 5120) 107.4 / 105.9, 246 (8, 5120) 121.4 / 115.2, 344
-    // (40, 7168) 212.9 / 199.5, 1648 (43, 7168) 436.5 / 395.2.  At the first position of a tile of 64 it also saves the reading of that tile: 1174 (64, 7168,
-    // position 640) 375 / 386.
-    const bool fresh = T == 1 && (4.0 * n_seqs * (double)h * pos0 <= 6.0e7 || pos0 % 64 == 0);
+    const bool fresh = T == 1 && append_in_attention(n_seqs, h, pos0);
     if (!fresh && launch_kv_append(qkv, st->k_cache, st->vt_cache, n_seqs, T, pos0, cfg->n_heads, cfg->head_dim, cfg->max_seq, stream) != hipSuccess)
         return LPQ_ERR_DEVICE;
     if ((s = run_attention(qkv, cfg, st, n_seqs, T, pos0, fresh, att, stream)) != LPQ_OK) return s;
@@ -1109,6 +1115,27 @@ lpq_status lpq_route_of(const lpq_qdesc* descs, int32_t n, lpq_phase phase, int3
     if (plan[0].kernel == DECODE_EVEN_SHARE) return LPQ_OK;
     out->tiles = plan[0].a.row_tiles;
     for (int i = 0; i < n; ++i) out->splits = std::max(out->splits, plan[0].a.lin[i].aux);
+    return LPQ_OK;
+}
+
+lpq_status lpq_layer_route_of(const lpq_qdesc* descs, int32_t n_seqs, int32_t pos0, int32_t compute_units, lpq_layer_route* out)
+{
+    if (!descs || !out) return LPQ_ERR_NULL;
+    if (n_seqs < 1 || pos0 < 0 || compute_units < 1) return LPQ_ERR_SHAPE;
+    for (int i = 0; i < 4; ++i) {
+        const lpq_status st = check_desc(&descs[i]);
+        if (st != LPQ_OK) return st;
+    }
+    std::vector<DecodeLaunch> plan(3);                                   // QKV, out-projection, FC1
+    for (int i = 0; i < 3; ++i) {
+        const lpq_qweight w = lpq_qweight{descs[i], nullptr, nullptr, nullptr, nullptr};
+        const std::vector<LinearCall> calls(1, LinearCall{&w, nullptr, nullptr});
+        const lpq_status st = plan_decode(calls, 0, 1, n_seqs, compute_units, false, &plan[i]);
+        if (st != LPQ_OK) return st;
+    }
+    out->norm1 = norm_inside(plan[0]) ? LPQ_NORM_IN_LINEAR : LPQ_NORM_LAUNCH;
+    out->norm2 = norm_behind(plan[1]) ? LPQ_NORM_BEHIND_SPLITS : norm_inside(plan[2]) ? LPQ_NORM_IN_LINEAR : LPQ_NORM_LAUNCH;
+    out->append = append_in_attention(n_seqs, descs[0].K, pos0);
     return LPQ_OK;
 }
 

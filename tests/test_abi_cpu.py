@@ -232,6 +232,25 @@ def test_routes():
     assert lib.lpq_route_of(ctypes.byref(d), 1, 1, 1, 256, ctypes.byref(r)) == 8
 
 
+def layer_route(fmt, h, n_seqs, pos0=70):
+    return lpq.lpq_layer_route_of([fmt + kn for kn in ((h, 3 * h), (h, h), (h, 4 * h), (4 * h, h))], n_seqs, pos0)
+
+
+def test_layer_routes():
+    """Where a decode layer forms its norms: inside the linears of few rows, behind the sums of a split out-projection, else in launches of their own."""
+    for fmt in ((3, 1), (4, 1), (8, 1), (8, 2), (16, 0)):
+        for h, B in ((768, 1), (768, 8), (2048, 8), (4096, 4)):
+            assert layer_route(fmt, h, B)[:2] == (lpq.LPQ_NORM_IN_LINEAR, lpq.LPQ_NORM_IN_LINEAR), (fmt, h, B)
+        for h, B in ((5248, 1), (7168, 1), (4096, 5)):
+            assert layer_route(fmt, h, B)[:2] == (lpq.LPQ_NORM_LAUNCH, lpq.LPQ_NORM_LAUNCH), (fmt, h, B)
+        for h, B in ((2560, 16), (5120, 16), (7168, 43), (16384, 64)):
+            assert layer_route(fmt, h, B)[:2] == (lpq.LPQ_NORM_LAUNCH, lpq.LPQ_NORM_BEHIND_SPLITS), (fmt, h, B)
+    lib, r, d = lpq.load_library(), lpq.lpq_layer_route(), (lpq.lpq_qdesc * 4)(*[lpq.make_desc(4, 1, 128, 64)] * 4)
+    assert lib.lpq_layer_route_of(None, 1, 0, 256, ctypes.byref(r)) == 1 and lib.lpq_layer_route_of(d, 1, 0, 256, None) == 1
+    for n_seqs, pos0, cus in ((0, 0, 256), (1, -1, 256), (1, 0, 0)):
+        assert lib.lpq_layer_route_of(d, n_seqs, pos0, cus, ctypes.byref(r)) == 4
+
+
 def test_routes_of_13_to_32_rows():
     """Where the kernel for 17 and more rows would be the slower one: 8-bit and fp16 linears of 13 to 16 rows with neither few workgroups of long
     ranges nor more than a round of them, and one or two groups of columns up to 32 rows.  Below 512 columns, too, the blocks

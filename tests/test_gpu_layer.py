@@ -31,6 +31,11 @@ def rng(*key):
     return np.random.default_rng(wl.stream_seed("layer", *key))
 
 
+def layer_shapes(h):
+    """(K, N) of a decoder layer's linears."""
+    return {"qkv": (h, 3 * h), "out": (h, h), "fc1": (h, 4 * h), "fc2": (4 * h, h)}
+
+
 @pytest.mark.parametrize("M,h", [(1, 64), (5, 768), (33, 5120), (3, 14336)])
 def test_layernorm(M, h):
     r = rng("ln", M, h)
@@ -414,7 +419,7 @@ def test_attention_over_very_long_rows():
 
 @pytest.mark.parametrize("bits,scheme", [(3, 1), (4, 1), (8, 1), (8, 2), (16, 0)], ids=["w3", "w4", "w8", "i8", "f16"])
 @pytest.mark.parametrize("heads,d,seqs", [(9, 128, 1), (9, 128, 5), (12, 64, 2), (12, 64, 3), (12, 64, 16), (32, 128, 4), (40, 128, 1), (40, 128, 2), (42, 64, 6)])
-def test_decode_layer_normalises_in_the_linears(bits, scheme, heads, d, seqs):
+def test_decode_layer_normalises_in_the_linears(bits, scheme, heads, d, seqs, norm_behind=False):
     """Decode layers of few rows, whose QKV and FC1 kernels normalise their rows themselves (one, two or more rows to a wave, rows that fill no
     whole number of 512 columns, up to the longest that do), against the same layer of single calls.  Both round to fp16 at the same places;
     statistics added in another order move an element by one such rounding now and then: the layer's 2e-3 as in this file."""
@@ -425,7 +430,12 @@ def test_decode_layer_normalises_in_the_linears(bits, scheme, heads, d, seqs):
     def rand(*shape, std=1.0):
         return (torch.randn(shape, generator=gen, device="cuda") * std).half()
 
-    shapes = {"qkv": (h, 3 * h), "out": (h, h), "fc1": (h, 4 * h), "fc2": (4 * h, h)}
+    shapes = layer_shapes(h)
+    norm1, norm2, _ = lpq.lpq_layer_route_of([(bits, scheme) + shapes[n] for n in lpq.LINEARS], seqs, pos)
+    if norm_behind:
+        assert norm2 == lpq.LPQ_NORM_BEHIND_SPLITS
+    elif seqs <= 12 or bits >= 8:                         # 3- and 4-bit linears of 13 to 16 rows go to the kernel for 17 and more
+        assert norm1 == lpq.LPQ_NORM_IN_LINEAR and (norm2 == norm1 or bits == 16)      # a fp16 FC1 of 200 MB is no small launch
     layer = {n: lpq.lpq_quantize_pack(rand(N, K, std=0.02), bits, scheme, bias=rand(N, std=0.05)) for n, (K, N) in shapes.items()}
     norms = [((1 + 0.1 * torch.randn(h, generator=gen, device="cuda")).half(), rand(h, std=0.1)) for _ in range(2)]
     st = lpq.LayerState(heads, d, 128, seqs, torch.device("cuda"), norms[0], norms[1])
@@ -449,11 +459,60 @@ def test_decode_layer_normalises_in_the_linears(bits, scheme, heads, d, seqs):
         assert float((a.double() - b.double()).norm() / b.double().norm()) <= 2e-3
 
 
-@pytest.mark.parametrize("heads,d,seqs", [(40, 128, 16), (20, 128, 33), (64, 128, 2), (128, 128, 20), (17, 128, 50)])
+@pytest.mark.parametrize("heads,d,seqs", [(40, 128, 16), (20, 128, 33), (64, 128, 20), (128, 128, 33), (17, 128, 50)])
 def test_decode_layer_norm_behind_split_sums(heads, d, seqs):
     """Decode layers whose out-projection is split over K: the kernel that adds the splits also forms the second norm (rows of up to 16384 columns,
     that fill its threads or not).  Against the same layer of single calls, as above."""
-    test_decode_layer_normalises_in_the_linears(4, 1, heads, d, seqs)
+    test_decode_layer_normalises_in_the_linears(4, 1, heads, d, seqs, norm_behind=True)
+
+
+@pytest.mark.parametrize("bits,scheme,heads,d,seqs", [(3, 1, 12, 64, 1), (4, 1, 9, 128, 5), (8, 2, 16, 128, 8), (16, 0, 42, 64, 6), (4, 1, 40, 128, 2),
+                                                      (3, 1, 17, 128, 50), (4, 1, 40, 128, 16), (8, 1, 64, 128, 33), (4, 1, 112, 128, 64)])
+def test_decode_layer_norms_against_64_bits(bits, scheme, heads, d, seqs):
+    """Norms inside the linears and behind split sums against 64 bits, every operator's output rounded to fp16: K and V of the new token (the first norm and
+    QKV alone) and y, with rows of small numbers beside outlier channels, so that y is what the layer adds to them.  K and V: the rounding of the norm
+    (2.1e-4), of the output (2.1e-4) and of the weights (1.7e-4), 3.5e-4 together, 1e-3 as for single operators; y: 2e-3 as in this file."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(heads * d + seqs)
+    h, pos, shapes = heads * d, 70, layer_shapes(heads * d)
+
+    def rand(*shape, std=1.0):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).half()
+
+    norm1, norm2, _ = lpq.lpq_layer_route_of([(bits, scheme) + shapes[n] for n in lpq.LINEARS], seqs, pos)
+    assert norm1 == norm2 == lpq.LPQ_NORM_IN_LINEAR if seqs <= 8 else norm2 == lpq.LPQ_NORM_BEHIND_SPLITS
+    layer = {n: lpq.lpq_quantize_pack(rand(N, K, std=0.02), bits, scheme, bias=rand(N, std=0.05)) for n, (K, N) in shapes.items()}
+    norms = [((1 + 0.1 * torch.randn(h, generator=gen, device="cuda")).half(), rand(h, std=0.1)) for _ in range(2)]
+    st = lpq.LayerState(heads, d, 128, seqs, torch.device("cuda"), norms[0], norms[1])
+    st.k_cache[:, :, :pos] = rand(seqs, heads, pos, d)
+    st.vt_cache[:, :, :, :pos] = rand(seqs, heads, d, pos)
+    x = rand(seqs, h, std=0.05)
+    x[:, 5] *= 30
+    x += 0.02
+    y, _ = lpq.lpq_decoder_layer(layer, st, lpq.LPQ_DECODE, seqs, 1, pos, x)
+
+    def rounded(a):
+        return a.half().double()
+
+    def norm(a, p):
+        m, v = a.mean(1, keepdim=True), a.var(1, unbiased=False, keepdim=True)
+        return rounded((a - m) / (v + 1e-5).sqrt() * p[0].double() + p[1].double())
+
+    def linear(name, a):
+        return a @ lpq.lpq_unpack_dequant(layer[name]).double().t() + layer[name].bias.double()
+
+    def off(a, ref):
+        return float((a.double() - ref).norm() / ref.norm())
+
+    qkv = rounded(linear("qkv", norm(x.double(), norms[0]))).view(seqs, 3, heads, d)
+    k, v = st.k_cache[:, :, pos], st.vt_cache[:, :, :, pos]
+    assert off(k, qkv[:, 1]) <= 1e-3 and off(v, qkv[:, 2]) <= 1e-3
+    keys, values = st.k_cache[:, :, :pos + 1].double(), st.vt_cache[:, :, :, :pos + 1].double()
+    p = torch.softmax((qkv[:, 0, :, None] * keys).sum(-1) / d ** 0.5, -1)
+    att = rounded((p[:, :, None] * values).sum(-1).view(seqs, h))
+    z = rounded(x.double() + linear("out", att))
+    ff = rounded(torch.relu(linear("fc1", norm(z, norms[1]))))
+    assert off(y, rounded(z + linear("fc2", ff))) <= 2e-3
 
 
 @pytest.mark.parametrize("d", [64, 128])
