@@ -25,43 +25,59 @@ __device__ __forceinline__ float wave_sum(float v)
 }
 
 // ---- layer normalisation: one workgroup per row, the row held in registers -------------------
-// HBM-bound at many rows (2 bytes read + 2 bytes written per element), a chain of latencies at few: so a thread of few rows takes one 16-byte chunk (two
-// beyond 8192 columns), and asks for its part of gamma and beta together with it, ahead of the sums.  Cold rows, us, 256 threads of up to eight chunks with
-// gamma and beta behind the sums / so: 5120 columns, 16 rows 5.4 / 4.8, 400 rows 6.3 / 5.4, 1191 rows 12.1 / 9.6 (with 640 threads 10.9, a wave per row 12); 14336
-// columns, 16 rows 8.9 / 4.9, 2048 rows 35.8 / 31.5.
-constexpr int LN_MAX_HIDDEN = 16384, LN_MAX_THREADS = 1024;
+// HBM-bound at many rows (2 bytes read + 2 bytes written per element), a chain of latencies at few.  Two forms.  AHEAD asks for a thread's part of gamma and
+// beta together with the row and keeps all of it as fp16; the other keeps the row as fp32, converted once, and reads gamma and beta behind the sums.
+// launch_layernorm has the lines between them and the figures.
+constexpr int LN_MAX_HIDDEN = 16384;
 
-template <int CHUNKS>
-__global__ __launch_bounds__(LN_MAX_THREADS) void layernorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma,
-                                                                   const uint16_t* __restrict__ beta, float eps, int h, uint16_t* __restrict__ y)
+// THREADS: of a workgroup; of a single chunk a thread, the most there may be.
+template <int THREADS, int CHUNKS, bool AHEAD>
+__global__ __launch_bounds__(THREADS) void layernorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
+                                                            float eps, int h, uint16_t* __restrict__ y)
 {
-    __shared__ float red[2][LN_MAX_THREADS / 64];
+    constexpr int MAX_WAVES = THREADS / 64;
+    __shared__ __attribute__((aligned(16))) float red[2][MAX_WAVES];
     const size_t row = blockIdx.x;
-    const int nch = h / 8, threads = blockDim.x, waves = threads / 64;       // 16-byte chunks in a row
-    h8 t[CHUNKS], g[CHUNKS], b[CHUNKS];
+    const int nch = h / 8, threads = CHUNKS == 1 ? (int)blockDim.x : THREADS, waves = threads / 64;       // 16-byte chunks in a row
+    typedef float f8 __attribute__((ext_vector_type(8)));
+    typename std::conditional<AHEAD, h8, f8>::type t[CHUNKS];
+    h8 g[CHUNKS], b[CHUNKS];
+    float s = 0.0f;
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
         const int ch = threadIdx.x + threads * c;
         if (ch < nch) {
-            t[c] = *reinterpret_cast<const h8*>(x + row * h + 8 * ch);
-            g[c] = *reinterpret_cast<const h8*>(gamma + 8 * ch);
-            b[c] = *reinterpret_cast<const h8*>(beta + 8 * ch);
+            const h8 v = *reinterpret_cast<const h8*>(x + row * h + 8 * ch);
+            if constexpr (AHEAD) {
+                t[c] = v;
+                g[c] = *reinterpret_cast<const h8*>(gamma + 8 * ch);
+                b[c] = *reinterpret_cast<const h8*>(beta + 8 * ch);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { t[c][e] = (float)v[e]; s += t[c][e]; }
+            }
         }
     }
+    // all of the waves' sums at once, absent waves' as zeros; the first four add up as (0 + 1) + (2 + 3)
     auto row_sum = [&](float v, float* r) {
         v = wave_sum(v);
         if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = v;
+        else if ((int)threadIdx.x > waves && threadIdx.x <= MAX_WAVES) r[threadIdx.x - 1] = 0.0f;
         __syncthreads();
         float sum = 0.0f;
-        for (int w = 0; w < waves; ++w) sum += r[w];
+#pragma unroll
+        for (int w = 0; w < MAX_WAVES; w += 4) {
+            const f4 p = *reinterpret_cast<const f4*>(r + w);
+            sum += (p[0] + p[1]) + (p[2] + p[3]);
+        }
         return sum;
     };
-    float s = 0.0f;
+    if constexpr (AHEAD)
 #pragma unroll
-    for (int c = 0; c < CHUNKS; ++c)
-        if ((int)threadIdx.x + threads * c < nch)
+        for (int c = 0; c < CHUNKS; ++c)
+            if ((int)threadIdx.x + threads * c < nch)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s += (float)t[c][e];
+                for (int e = 0; e < 8; ++e) s += (float)t[c][e];
     const float mean = row_sum(s, red[0]) / (float)h;
     float q = 0.0f;
 #pragma unroll
@@ -74,6 +90,10 @@ __global__ __launch_bounds__(LN_MAX_THREADS) void layernorm_kernel(const uint16_
     for (int c = 0; c < CHUNKS; ++c) {
         const int ch = threadIdx.x + threads * c;
         if (ch < nch) {
+            if constexpr (!AHEAD) {
+                g[c] = *reinterpret_cast<const h8*>(gamma + 8 * ch);
+                b[c] = *reinterpret_cast<const h8*>(beta + 8 * ch);
+            }
             h8 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = (_Float16)(((float)t[c][e] - mean) * rstd * (float)g[c][e] + (float)b[c][e]);
@@ -650,13 +670,30 @@ __global__ __launch_bounds__(256, 2) void attention_prefill_kernel(const uint16_
 
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, float eps, int M, int h, void* y, hipStream_t s)
 {
-    // many rows: 256 threads of up to four chunks, more rows at work at a time
-    const int chunks = h / 8, threads = std::min(M > 512 && chunks <= 1024 ? 256 : LN_MAX_THREADS, (chunks + 63) / 64 * 64);
+    // Threads of a row's workgroup and 16-byte chunks of a thread.  Rows not in any cache, us:
+    //   up to 512 rows: 512 threads, or as many as there are chunks (7168 columns: 1024 threads / so, 16 rows 3.7 / 3.1, 512 rows 6.3 / 5.4).
+    //   more, up to 8192 columns: 256 threads, up to four chunks, AHEAD (5120 columns: 512 threads / so, 1191 rows 8.3 / 7.2; 7168 columns: not AHEAD / so,
+    //   4000 rows 23.2 / 21.0).
+    //   more, beyond: four chunks at 512 threads (9216 columns: 1024 threads / so, 4000 rows 31.3 / 27.0; 16384 columns, 600 rows 10.6 / 9.9).  About 1000 rows
+    //   are four to a compute unit: six chunks at 256 threads up to 12288 columns (9216, 1000 rows: 512 threads / so 9.5 / 9.2).  Beyond 12288 columns and 1100
+    //   rows two chunks at 1024 threads, AHEAD (16384, 2000 rows: 512 threads / so 26.0 / 23.1).
+    const int chunks = h / 8, all = (chunks + 63) / 64 * 64;
     const uint16_t *xs = static_cast<const uint16_t*>(x), *g = static_cast<const uint16_t*>(gamma), *b = static_cast<const uint16_t*>(beta);
     uint16_t* out = static_cast<uint16_t*>(y);
-    if (chunks <= threads)          layernorm_kernel<1><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
-    else if (chunks <= 2 * threads) layernorm_kernel<2><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
-    else                            layernorm_kernel<4><<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out);
+    auto run = [&](auto kernel, int threads) { kernel<<<(unsigned)M, threads, 0, s>>>(xs, g, b, eps, h, out); };
+    if (M > 512 && chunks <= 1024) {
+        if (chunks <= 256)      run(layernorm_kernel<256, 1, true>, all);
+        else if (chunks <= 512) run(layernorm_kernel<256, 2, true>, 256);
+        else                    run(layernorm_kernel<256, 4, true>, 256);
+    } else if (M > 1100 && chunks > 1536) {
+        run(layernorm_kernel<1024, 2, true>, 1024);
+    } else if (M > 700 && M <= 1100 && chunks > 1024 && chunks <= 1536) {
+        run(layernorm_kernel<256, 6, false>, 256);
+    } else {
+        if (chunks <= 512)       run(layernorm_kernel<512, 1, false>, all);
+        else if (chunks <= 1024) run(layernorm_kernel<512, 2, false>, 512);
+        else                     run(layernorm_kernel<512, 4, false>, 512);
+    }
     return hipGetLastError();
 }
 

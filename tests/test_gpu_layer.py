@@ -46,6 +46,21 @@ def test_layernorm(M, h):
     check_output(y, OL.layernorm(x, g, b, 1e-5), "layernorm %dx%d" % (M, h))
 
 
+@pytest.mark.parametrize("M", [1, 512, 513, 701, 1100, 1101])
+@pytest.mark.parametrize("h", [8, 520, 2048, 2056, 4096, 4104, 8192, 8200, 12288, 12296, 16384])
+def test_layernorm_kernel_forms(M, h):
+    """Every number of threads and of chunks a thread that a launch takes, at its edges: waves of few chunks, an odd number of waves, the longest rows."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(M + h)
+    x = (torch.randn((M, h), generator=gen, device="cuda") * 2 + 0.5).half()
+    x[:, :3] *= 30
+    g, b = ((a + 0.1 * torch.randn(h, generator=gen, device="cuda")).half() for a in (1.0, 0.0))
+    y = lpq.lpq_layernorm(x, g, b, 1e-5)
+    d = x.double()
+    ref = (d - d.mean(1, keepdim=True)) / (d.var(1, unbiased=False, keepdim=True) + 1e-5).sqrt() * g.double() + b.double()
+    check_output(y, ref.cpu().numpy(), "layernorm %dx%d" % (M, h))
+
+
 @pytest.mark.parametrize("act", [lpq.LPQ_ACT_RELU, lpq.LPQ_ACT_GELU_TANH, lpq.LPQ_ACT_NONE], ids=["relu", "gelu", "none"])
 @pytest.mark.parametrize("phase,M", [(lpq.LPQ_DECODE, 7), (lpq.LPQ_DECODE, 40), (lpq.LPQ_PREFILL, 70)], ids=["dec7", "dec40", "pre70"])
 def test_fused_epilogue(orc, act, phase, M):
