@@ -943,13 +943,6 @@ __device__ __forceinline__ bool any_not_finite(const f4& v)
     return __any(!(__builtin_isfinite(v[0]) && __builtin_isfinite(v[1]) && __builtin_isfinite(v[2]) && __builtin_isfinite(v[3])));
 }
 
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
 // A row ahead of its layer norm, 16-byte chunk lane + 64 c of it (rows of up to LN_ROW_CHUNKS * 512 columns)
 enum { LN_ROW_CHUNKS = LN_LINEAR_MAX_K / 512 };
 __device__ __forceinline__ void load_norm_row(const LinDesc& L, int m, h8 (&v)[LN_ROW_CHUNKS])
@@ -1010,9 +1003,7 @@ __device__ __forceinline__ void normalise_rows(const LinDesc& L, int M, const No
         float q = 0.0f;
 #pragma unroll
         for (int c = 0; c < LN_ROW_CHUNKS; ++c)
-            if (lane + 64 * c < nch)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { const float d = (float)v[c][e] - mean; q += d * d; }
+            if (lane + 64 * c < nch) q = norm_squares(v[c], mean, q, c == 0);
         const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)K + ln.eps);
 #pragma unroll
         for (int c = 0; c < LN_ROW_CHUNKS; ++c) {
@@ -1021,7 +1012,7 @@ __device__ __forceinline__ void normalise_rows(const LinDesc& L, int M, const No
                 const h8 g = *reinterpret_cast<const h8*>(ln.gamma + 8 * ch), b = *reinterpret_cast<const h8*>(ln.beta + 8 * ch);
                 h8 o;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (_Float16)(((float)v[c][e] - mean) * rstd * (float)g[e] + (float)b[e]);
+                for (int e = 0; e < 8; ++e) o[e] = norm_element((float)v[c][e], mean, rstd, g[e], b[e]);
                 *reinterpret_cast<h8*>(xs + (size_t)m * (K + LN_PAD) + 8 * ch) = o;
             }
         }
@@ -1573,9 +1564,9 @@ __global__ __launch_bounds__(256) void decode_rows_reduce_kernel(const DecodeArg
 __global__ __launch_bounds__(1024) void decode_reduce_norm_kernel(const DecodeArgs a)
 {
     constexpr int CHUNKS = 2;                          // of eight columns per thread
-    __shared__ float red[2][16];
+    __shared__ __attribute__((aligned(16))) float red[2][16];
     const LinDesc& L = a.lin[0];
-    const int N = L.N, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int N = L.N;
     const size_t plane = (size_t)a.M * N, at = (size_t)blockIdx.x * N;
     const float* __restrict__ partial = a.partial + L.step_weight + at;
     h8 bias[CHUNKS], res[CHUNKS];
@@ -1612,23 +1603,12 @@ __global__ __launch_bounds__(1024) void decode_reduce_norm_kernel(const DecodeAr
         }
         *reinterpret_cast<h8*>(L.y + at + n) = o;
     }
-    auto row_sum = [&](float x, float (&r)[16]) {
-        x = wave_sum(x);
-        if (lane == 0) r[wave] = x;
-        __syncthreads();
-        float t = 0.0f;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) t += r[w];
-        return t;
-    };
-    const float mean = row_sum(total, red[0]) / (float)N;
+    const float mean = row_sum<16>(total, 16, red[0]) / (float)N;
     float q = 0.0f;
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c)
-        if (8 * ((int)threadIdx.x + 1024 * c) < N)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { const float d = v[c][e] - mean; q += d * d; }
-    const float rstd = 1.0f / sqrtf(row_sum(q, red[1]) / (float)N + a.ln_eps);
+        if (8 * ((int)threadIdx.x + 1024 * c) < N) q = norm_squares(v[c], mean, q, c == 0);
+    const float rstd = 1.0f / sqrtf(row_sum<16>(q, 16, red[1]) / (float)N + a.ln_eps);
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
         const int n = 8 * ((int)threadIdx.x + 1024 * c);
@@ -1636,7 +1616,7 @@ __global__ __launch_bounds__(1024) void decode_reduce_norm_kernel(const DecodeAr
         const h8 g = *reinterpret_cast<const h8*>(a.after_gamma + n), b = *reinterpret_cast<const h8*>(a.after_beta + n);
         h8 o;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = (_Float16)((v[c][e] - mean) * rstd * (float)g[e] + (float)b[e]);
+        for (int e = 0; e < 8; ++e) o[e] = norm_element(v[c][e], mean, rstd, g[e], b[e]);
         *reinterpret_cast<h8*>(a.after_y + at + n) = o;
     }
 }

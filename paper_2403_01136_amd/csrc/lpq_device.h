@@ -428,4 +428,45 @@ __device__ __forceinline__ void pair_tiles_for_mfma32(h8& a, h8& b)
     b = __builtin_bit_cast(h8, ub);
 }
 
+// ---- layer normalisation: what the kernels that form one share ------------------------------
+__device__ __forceinline__ float wave_sum(float v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+// The sum over a workgroup of up to WAVES waves; r: WAVES floats of LDS, used once.  All of the waves' sums are read at once, absent waves' as zeros; the
+// first four add up as (0 + 1) + (2 + 3).
+template <int WAVES> __device__ __forceinline__ float row_sum(float v, int waves, float* r)
+{
+    static_assert(WAVES % 4 == 0, "read by fours");
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = v;
+    else if ((int)threadIdx.x > waves && threadIdx.x <= WAVES) r[threadIdx.x - 1] = 0.0f;
+    __syncthreads();
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < WAVES; w += 4) {
+        const f4 p = *reinterpret_cast<const f4*>(r + w);
+        sum += (p[0] + p[1]) + (p[2] + p[3]);
+    }
+    return sum;
+}
+// The part of eight elements in the variance, added to q (a thread's first eight: to nothing), and an element itself, fused alike wherever they are compiled
+template <typename T> __device__ __forceinline__ float norm_squares(const T& v, float mean, float q, bool first)
+{
+    const float d0 = (float)v[0] - mean, d1 = (float)v[1] - mean;
+    q = first ? __builtin_fmaf(d0, d0, d1 * d1) : __builtin_fmaf(d1, d1, __builtin_fmaf(d0, d0, q));
+#pragma unroll
+    for (int e = 2; e < 8; ++e) {
+        const float d = (float)v[e] - mean;
+        q = __builtin_fmaf(d, d, q);
+    }
+    return q;
+}
+__device__ __forceinline__ _Float16 norm_element(float v, float mean, float rstd, _Float16 gamma, _Float16 beta)
+{
+    return (_Float16)__builtin_fmaf((v - mean) * rstd, (float)gamma, (float)beta);
+}
+
 }  // namespace lpq

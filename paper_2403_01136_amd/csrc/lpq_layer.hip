@@ -17,22 +17,15 @@ namespace lpq {
 
 namespace {
 
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
 // ---- layer normalisation: one workgroup per row, the row held in registers -------------------
 // HBM-bound at many rows (2 bytes read + 2 bytes written per element), a chain of latencies at few.  Two forms.  AHEAD asks for a thread's part of gamma and
 // beta together with the row and keeps all of it as fp16; the other keeps the row as fp32, converted once, and reads gamma and beta behind the sums.
 // launch_layernorm has the lines between them and the figures.
 constexpr int LN_MAX_HIDDEN = 16384;
 
-// THREADS: of a workgroup; of a single chunk a thread, the most there may be.
+// THREADS: of a workgroup; of a single chunk a thread, the most there may be.  512: no more than 64 registers, for four workgroups on a compute unit.
 template <int THREADS, int CHUNKS, bool AHEAD>
-__global__ __launch_bounds__(THREADS) void layernorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
+__global__ __launch_bounds__(THREADS, THREADS == 512 ? 8 : 4) void layernorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
                                                             float eps, int h, uint16_t* __restrict__ y)
 {
     constexpr int MAX_WAVES = THREADS / 64;
@@ -58,34 +51,18 @@ __global__ __launch_bounds__(THREADS) void layernorm_kernel(const uint16_t* __re
             }
         }
     }
-    // all of the waves' sums at once, absent waves' as zeros; the first four add up as (0 + 1) + (2 + 3)
-    auto row_sum = [&](float v, float* r) {
-        v = wave_sum(v);
-        if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = v;
-        else if ((int)threadIdx.x > waves && threadIdx.x <= MAX_WAVES) r[threadIdx.x - 1] = 0.0f;
-        __syncthreads();
-        float sum = 0.0f;
-#pragma unroll
-        for (int w = 0; w < MAX_WAVES; w += 4) {
-            const f4 p = *reinterpret_cast<const f4*>(r + w);
-            sum += (p[0] + p[1]) + (p[2] + p[3]);
-        }
-        return sum;
-    };
     if constexpr (AHEAD)
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c)
             if ((int)threadIdx.x + threads * c < nch)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) s += (float)t[c][e];
-    const float mean = row_sum(s, red[0]) / (float)h;
+    const float mean = row_sum<MAX_WAVES>(s, waves, red[0]) / (float)h;
     float q = 0.0f;
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c)
-        if ((int)threadIdx.x + threads * c < nch)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { const float d = (float)t[c][e] - mean; q += d * d; }
-    const float rstd = 1.0f / sqrtf(row_sum(q, red[1]) / (float)h + eps);
+        if ((int)threadIdx.x + threads * c < nch) q = norm_squares(t[c], mean, q, c == 0);
+    const float rstd = 1.0f / sqrtf(row_sum<MAX_WAVES>(q, waves, red[1]) / (float)h + eps);
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
         const int ch = threadIdx.x + threads * c;
@@ -96,7 +73,7 @@ __global__ __launch_bounds__(THREADS) void layernorm_kernel(const uint16_t* __re
             }
             h8 o;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (_Float16)(((float)t[c][e] - mean) * rstd * (float)g[c][e] + (float)b[c][e]);
+            for (int e = 0; e < 8; ++e) o[e] = norm_element((float)t[c][e], mean, rstd, g[c][e], b[c][e]);
             *reinterpret_cast<h8*>(y + row * h + 8 * ch) = o;
         }
     }
