@@ -481,13 +481,13 @@ struct NormAfter {
     bool done;              // out: the linear's launches have done it
 };
 
-// Whether a decode linear's kernel normalises its M rows of K columns itself (every workgroup all of them) rather than a launch in front of it.  Whole
-// layers, us, apart / so: 768 wide, 4 bit, 1 row 35.0 / 30.5, 4 rows 38.1 / 30.8, 12 rows 43.7 / 42.0; 2048, 8 bit, 1 row 47.1 / 41.0, 8 rows 52.5 / 50.0;
-// 4096, 4 bit, 1 row 59.7 / 54.5, 4 rows 61.9 / 58.6; 5120, 4 bit, 1 row 70.4 / 66.0, 2 rows 71.2 / 67.4, 3 rows 71.5 / 71.5; 7168, 4 bit, 1 row
-// 101.7 / 103.0.
+// Whether a decode linear's kernel normalises its M rows of K columns itself (every workgroup all of them) rather than a launch in front of it: where a
+// wave has one row, and of short rows two.  Whole layers, us, what it takes longer so (4-bit, symmetric 8-bit, fp16): 768 wide, 1 row -3.2, -3.2, -3.7; 4 rows -4.0, -3.5, -4.5; 8
+// rows -2.0, -1.5, -2.1; 9 rows 0.0, 1.2, 0.3; 16 rows -0.4, 2.9, 2.0.  2048, 8 rows -2.0, -0.3, -1.5; 9 rows 1.1, 2.6, 1.7.  2560, 4 rows -3.4, -1.5, -2.1; 8
+// rows -0.8, 0.5, 2.0.  4096, 4 rows -1.8, -1.1, 0.2; 5 rows 3.1, 2.4, 8.3.  5120, 4 rows -2.8, -1.8, -0.9.
 bool norm_in_linear(int32_t M, int32_t K)
 {
-    return M <= 16 && K <= LN_LINEAR_MAX_K && (int64_t)M * K <= (K <= 4096 ? 16384 : 10240);
+    return K <= LN_LINEAR_MAX_K && (M <= 4 || (M <= 8 && K <= 2048));
 }
 
 bool norm_inside(const DecodeLaunch& p) { return p.kernel == DECODE_ROWS && p.a.waves == 4 && norm_in_linear(p.a.M, (int32_t)p.a.lin[0].K()); }

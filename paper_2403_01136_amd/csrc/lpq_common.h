@@ -53,7 +53,7 @@ struct DecodeArgs {
     float* partial;
     const uint16_t* prep;                // stage-wide kernel, up to 32 token rows per pass: what decode_prepare_kernel leaves
                                          // (the activations' group sums; for 3-bit weights the activations, scaled)
-    const uint16_t *ln_gamma, *ln_beta;  // a single linear of up to 16 rows whose rows x the kernel layer-normalises first, or null
+    const uint16_t *ln_gamma, *ln_beta;  // a single linear of up to 8 rows whose rows x the kernel layer-normalises first, or null
     const uint16_t *after_gamma, *after_beta;          // a single K-split linear of up to 16384 columns of y: the kernel that adds its splits also
     uint16_t* after_y;                                 // layer-normalises its rows into after_y; or null
     float ln_eps;

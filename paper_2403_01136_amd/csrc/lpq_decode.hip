@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(64 * WAVES, TILES == 5 ? 1 : 8 / WAVES) void decode
     }
 }
 
-// The same with the layer norm of the activations in front: one linear, up to 16 rows
+// The same with the layer norm of the activations in front: one linear, up to eight rows
 template <int TILES>
 __global__ __launch_bounds__(256, TILES >= 4 ? 1 : 2) void decode_rows_norm_kernel(const DecodeArgs a)
 {
@@ -1764,7 +1764,7 @@ hipError_t launch_decode_rows(const DecodeArgs& a, hipStream_t s)
     if (a.M > 32) return hipErrorInvalidValue;
     if (a.ln_gamma) {
         const int K = a.lin[0].K();
-        if (a.n_lin != 1 || a.M > 16 || a.waves != 4 || K > LN_LINEAR_MAX_K) return hipErrorInvalidValue;
+        if (a.n_lin != 1 || a.M > 8 || a.waves != 4 || K > LN_LINEAR_MAX_K) return hipErrorInvalidValue;
         const size_t smem = std::max((size_t)a.M * (K + LN_PAD) * 2, (size_t)4 * (a.row_tiles + 1) * 4 * 64 * sizeof(float));
         if (smem > 65536) return hipErrorInvalidValue;
         switch (a.row_tiles) {

@@ -239,10 +239,12 @@ def layer_route(fmt, h, n_seqs, pos0=70):
 def test_layer_routes():
     """Where a decode layer forms its norms: inside the linears of few rows, behind the sums of a split out-projection, else in launches of their own."""
     for fmt in ((3, 1), (4, 1), (8, 1), (8, 2), (16, 0)):
-        for h, B in ((768, 1), (768, 8), (2048, 8), (4096, 4)):
+        for h, B in ((768, 1), (768, 8), (2048, 8), (2560, 4), (4096, 4)):
             assert layer_route(fmt, h, B)[:2] == (lpq.LPQ_NORM_IN_LINEAR, lpq.LPQ_NORM_IN_LINEAR), (fmt, h, B)
-        for h, B in ((5248, 1), (7168, 1), (4096, 5)):
+        for h, B in ((768, 9), (768, 12), (2048, 9), (2176, 5), (5248, 1), (7168, 1), (4096, 5)):
             assert layer_route(fmt, h, B)[:2] == (lpq.LPQ_NORM_LAUNCH, lpq.LPQ_NORM_LAUNCH), (fmt, h, B)
+        assert layer_route(fmt, 5120, 4)[0] == lpq.LPQ_NORM_IN_LINEAR
+        assert layer_route(fmt, 768, 16)[0] == lpq.LPQ_NORM_LAUNCH
         for h, B in ((2560, 16), (5120, 16), (7168, 43), (16384, 64)):
             assert layer_route(fmt, h, B)[:2] == (lpq.LPQ_NORM_LAUNCH, lpq.LPQ_NORM_BEHIND_SPLITS), (fmt, h, B)
     lib, r, d = lpq.load_library(), lpq.lpq_layer_route(), (lpq.lpq_qdesc * 4)(*[lpq.make_desc(4, 1, 128, 64)] * 4)
