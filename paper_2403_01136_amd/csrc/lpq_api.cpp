@@ -494,12 +494,17 @@ bool norm_inside(const DecodeLaunch& p) { return p.kernel == DECODE_ROWS && p.a.
 // Whether a launch of a single linear adds K splits in a kernel of their own, which can form a norm of the sums
 bool norm_behind(const DecodeLaunch& p) { return p.kernel != DECODE_EVEN_SHARE && p.a.lin[0].aux > 1; }
 
-// One new token per sequence: whether the attention kernel writes it to the caches itself, a launch less -- while the cache it reads is small: its stores of two
-// bytes then cost less than kv_append's launch.  Whole layer, 4 bit, us, in one launch / two, by the megabytes of cache: 8 (2 sequences, 2048 wide) 41.2 /
-// 41.9, 20 (4, 4096) 61.3 / 62.9, 49 (8, 5120) 86.8 / 88.9, 66 (16, 5120) 90.3 / 88.8, 184 (16, 5120) 107.4 / 105.9, 246 (8, 5120) 121.4 / 115.2, 344
-// (40, 7168) 212.9 / 199.5, 1648 (43, 7168) 436.5 / 395.2.  At the first position of a tile of 64 it also saves the reading of that tile: 1174 (64, 7168,
-// position 640) 375 / 386.
-bool append_in_attention(int32_t n_seqs, int64_t h, int32_t pos0) { return 4.0 * n_seqs * (double)h * pos0 <= 6.0e7 || pos0 % 64 == 0; }
+// One new token per sequence: whether the attention kernel writes it to the caches itself, a launch (some 2 us) less -- while its stores of two bytes to every
+// feature row cost less than that: little cache to read, or few rows, or a first position of a tile of 64, which it then need not read.  Whole layers of
+// 4 bit, caches of 1.2 GB and more in turn, us, one launch / two, by megabytes of cache: 2 sequences 2048 wide, 16 MB 40.2 / 42.1; 16 of 2048, 74 MB
+// 53.5 / 56.4, 131 MB 63.2 / 64.4; 8 of 5120, 92 MB 92.1 / 95.5, 164 MB 105.4 / 106.9, 328 MB 141.8 / 139.2; 16 of 5120, 98 MB 89.4 / 92.4, 184 MB 105.6 / 105.0, 655
+// MB 198.4 / 191.3; 64 of 5120, 131 MB 149.4 / 150.1, 393 MB 196.7 / 193.1; 32 of 14336, 184 MB 344.7 / 339.1; few rows: 8 of 4096, 524 MB 141.8 / 144.2, 32 of 1152, 590 MB 149.5 / 149.5.  First
+// positions: 64 of 7168, position 640 374 / 384, 1024 494 / 492, 4096 1411 / 1323; 16 of 5120, 1024 (336 MB) 200.5 / 204.2; 64 of 768, 2048 (403 MB) 115.7 / 119.3.
+bool append_in_attention(int32_t n_seqs, int64_t h, int32_t pos0)
+{
+    const double bytes = 4.0 * n_seqs * (double)h * pos0;
+    return bytes <= 1.7e8 || ((int64_t)n_seqs * h <= 36864 && bytes <= 1.0e9) || (pos0 % 64 == 0 && (pos0 <= 640 || bytes <= 4.5e8));
+}
 
 // Decode-phase dispatch of a list of independent linears: grouped launches of at most
 // MAX_LIN_PER_LAUNCH linears, 64 token rows per pass, each launch one round of equally loaded

@@ -247,6 +247,10 @@ def test_layer_routes():
         assert layer_route(fmt, 768, 16)[0] == lpq.LPQ_NORM_LAUNCH
         for h, B in ((2560, 16), (5120, 16), (7168, 43), (16384, 64)):
             assert layer_route(fmt, h, B)[:2] == (lpq.LPQ_NORM_LAUNCH, lpq.LPQ_NORM_BEHIND_SPLITS), (fmt, h, B)
+    # the new token: in the attention kernel for little cache, for few feature rows and at the first position of a tile, but not of a long context
+    for h, B, pos0, append in ((768, 64, 300, 1), (2048, 16, 1000, 1), (5120, 8, 1000, 1), (5120, 16, 562, 0), (14336, 32, 100, 0), (4096, 8, 4000, 1),
+                               (1152, 32, 4000, 1), (4096, 8, 8100, 0), (7168, 64, 640, 1), (7168, 64, 704, 0), (7168, 64, 4096, 0), (5120, 16, 1024, 1), (5120, 16, 0, 1)):
+        assert layer_route((4, 1), h, B, pos0)[2] == append, (h, B, pos0)
     lib, r, d = lpq.load_library(), lpq.lpq_layer_route(), (lpq.lpq_qdesc * 4)(*[lpq.make_desc(4, 1, 128, 64)] * 4)
     assert lib.lpq_layer_route_of(None, 1, 0, 256, ctypes.byref(r)) == 1 and lib.lpq_layer_route_of(d, 1, 0, 256, None) == 1
     for n_seqs, pos0, cus in ((0, 0, 256), (1, -1, 256), (1, 0, 0)):
