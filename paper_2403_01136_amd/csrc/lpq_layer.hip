@@ -150,8 +150,10 @@ constexpr float LOG2E = 1.4426950408889634f;
 // attention's reads up.  So the line is read first and the store hits it; only the two bytes are stored (the other positions may be another
 // stream's to write: what is read of them is not used).  kv_append and attention, us, with the store alone / behind the read: 43 sequences of 56 heads at
 // 1338 positions 292.3 / 262.2 (attention alone 241), 64 of 56 at 1339 428.5 / 395.8, 64 of 40 at 601 161.8 / 142.3, 16 of 40 at 563 40.8 / 36.6; with 64 of
-// the 128 bytes read 266.3, 403.7, 142.5, 36.5.
-template <int D>
+// the 128 bytes read 266.3, 403.7, 142.5, 36.5.  READ false: caches whose feature rows are no more than a few
+// lines, most of which the attention reads (43 sequences of 40 heads, the store alone / behind the read: max_seq 64, position 10 20.4 / 23.3; 192, position 10 22.8 /
+// 26.2, position 100 32.4 / 31.6; 256, position 10 23.2 / 24.5, position 250 52.5 / 49.6; 64 of 56, 2048, position 10 56.3 / 50.2).
+template <int D, bool READ>
 __global__ __launch_bounds__(256) void kv_append_token_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ kc, uint16_t* vtc, int pos, int H, int S)
 {
     constexpr int ROUNDS = D / 64;                     // 64 feature rows at a time, four lanes a row
@@ -163,14 +165,16 @@ __global__ __launch_bounds__(256) void kv_append_token_kernel(const uint16_t* __
     uint16_t v[ROUNDS];
 #pragma unroll
     for (int i = 0; i < ROUNDS; ++i) {
-        seen[i] = *reinterpret_cast<const u32x4*>(line + (size_t)64 * i * S);
+        if constexpr (READ) seen[i] = *reinterpret_cast<const u32x4*>(line + (size_t)64 * i * S);
         v[i] = src[2 * h + 64 * i + tid / 4];
     }
     if (tid < D / 8) *reinterpret_cast<h8*>(kc + ((size_t)bh * S + pos) * D + 8 * tid) = *reinterpret_cast<const h8*>(src + h + 8 * tid);
 #pragma unroll
     for (int i = 0; i < ROUNDS; ++i) {
-        const u32x4 rest = *reinterpret_cast<const u32x4*>(line + (size_t)64 * i * S + 8);
-        asm volatile("" ::"v"(seen[i]), "v"(rest) : "memory");                  // the reads are waited for ahead of the store
+        if constexpr (READ) {
+            const u32x4 rest = *reinterpret_cast<const u32x4*>(line + (size_t)64 * i * S + 8);
+            asm volatile("" ::"v"(seen[i]), "v"(rest) : "memory");              // the reads are waited for ahead of the store
+        }
         if (tid % 4 == 0) row[(size_t)64 * i * S + pos] = v[i];
     }
 }
@@ -674,6 +678,8 @@ hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, 
     return hipGetLastError();
 }
 
+constexpr int KV_SHORT_ROWS = 192;                     // positions of a feature row up to which an append reads nothing of it
+
 int layernorm_max_hidden() { return LN_MAX_HIDDEN; }
 
 hipError_t launch_kv_append(const void* qkv, void* kc, void* vtc, int n_seqs, int T, int pos0, int H, int d, int S, hipStream_t s)
@@ -682,8 +688,9 @@ hipError_t launch_kv_append(const void* qkv, void* kc, void* vtc, int n_seqs, in
     const uint16_t* q = static_cast<const uint16_t*>(qkv);
     if (T == 1) {
         uint16_t *k = static_cast<uint16_t*>(kc), *v = static_cast<uint16_t*>(vtc);
-        if (d == 128) kv_append_token_kernel<128><<<(unsigned)(n_seqs * H), 256, 0, s>>>(q, k, v, pos0, H, S);
-        else          kv_append_token_kernel<64><<<(unsigned)(n_seqs * H), 256, 0, s>>>(q, k, v, pos0, H, S);
+        auto run = [&](auto kernel) { kernel<<<(unsigned)(n_seqs * H), 256, 0, s>>>(q, k, v, pos0, H, S); };
+        if (S <= KV_SHORT_ROWS) d == 128 ? run(kv_append_token_kernel<128, false>) : run(kv_append_token_kernel<64, false>);
+        else                    d == 128 ? run(kv_append_token_kernel<128, true>) : run(kv_append_token_kernel<64, true>);
         return hipGetLastError();
     }
     if (d == 128) kv_append_kernel<128><<<grid, 256, 0, s>>>(q, static_cast<uint16_t*>(kc), static_cast<uint16_t*>(vtc), T, pos0, H, S);

@@ -533,11 +533,12 @@ def test_decode_layer_norms_against_64_bits(bits, scheme, heads, d, seqs):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S", [128, 256])
 @pytest.mark.parametrize("pos0", [0, 1, 30, 31, 32, 63, 64, 127])
-def test_kv_append_of_one_token(d, pos0):
-    """One token per sequence, at every place of a 16-byte chunk's halves and at the edges of the 32 positions that are stored together: its K and V
-    and nothing else change, beside positions that hold NaN and infinities."""
-    B, H, S = 3, 5, 128
+def test_kv_append_of_one_token(d, pos0, S):
+    """One token per sequence, at every place of a 16-byte chunk's halves and at the edges of a line, into short rows and into long ones, whose line is read
+    first: its K and V and nothing else change, beside positions that hold NaN and infinities."""
+    B, H = 3, 5
     st, _, _ = make_state(B, H, d, S, d)
     r = rng("kv1", d, pos0)
     qkv = f16(r.standard_normal((B, 3 * H * d)))
@@ -553,7 +554,7 @@ def test_kv_append_of_one_token(d, pos0):
 def test_kv_append_beside_another_writer(T):
     """Other positions of the same V rows, in the same 32, are another stream's to write at the same time: both writers' values are there afterwards."""
     import torch
-    B, H, d, S, pos0 = 8, 16, 128, 128, 69
+    B, H, d, S, pos0 = 8, 16, 128, 256, 69
     st, _, _ = make_state(B, H, d, S, 5)
     r = rng("kv2", T)
     qkv, other = to_dev(f16(r.standard_normal((B * T, 3 * H * d)))), to_dev(f16(r.standard_normal((2, B, H, d, S))))
