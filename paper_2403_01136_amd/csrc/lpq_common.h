@@ -1,6 +1,7 @@
 // Host-side declarations shared by the library's translation units (not part of the ABI).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 #include "../../include/lpq.h"
 
@@ -58,8 +59,11 @@ struct DecodeArgs {
     uint16_t* after_y;                                 // layer-normalises its rows into after_y; or null
     float ln_eps;
     int32_t pad3;
+    uint64_t pad4;                       // lin[0] from the beginning of a 64-byte line on: two lines of arguments to wait for.  From byte 120 on it took
+                                         // three: 28672 -> 64 at 64 rows 24.3 us, so 23.8; a layer of 16 sequences, 5120 wide, 100.2, so 99.2
     LinDesc lin[MAX_LIN_PER_LAUNCH];
 };
+static_assert(offsetof(DecodeArgs, lin) % 64 == 0, "lin[0] begins a line");
 enum { LN_LINEAR_MAX_K = 5120 };         // columns up to which a decode linear's kernel can normalise its rows itself
 static_assert(sizeof(DecodeArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
