@@ -18,7 +18,8 @@
 //
 // Up to 32 token rows per pass the scale is applied after the matrix cores, per 128-column group, and the zero term
 // (sum over groups of zero * sum of x) once per unit from the activations' group sums, which decode_prepare_kernel
-// computes in front of the launch.
+// computes in front of the launch.  From 33 on 3- and 4-bit weights are treated alike, but for the group sums, which the workgroup
+// forms itself, a chunk at a time.
 //
 // A launch that streams little (a single linear of a decoder layer) takes other kernels, further down, without a fix-up
 // pass: up to 16 token rows decode_rows_kernel (one workgroup per group of 16-row tiles whose waves split K, no LDS
@@ -39,8 +40,9 @@ namespace {
 template <int V> struct DecodeCfg { enum { RT = (V == V_F16) ? 2 : 4, DEPTH = (V == V_W3 || V == V_W4) ? 4 : 2 }; };
 
 // A launch is specialised on TOK, the token rows it covers: 16 or 32 (one or two 16-token tiles on the
-// 16x16x32 MFMA, scale and zero applied after the matrix cores) or 64 (32x32x16 MFMA at twice the
-// matrix-core rate, weights dequantised to fp16 in registers).  Activation staging: CHUNK 128-column steps per LDS
+// 16x16x32 MFMA) or 64 (32x32x16 MFMA: half the operand reads per multiply-accumulate, and vector instructions between two of
+// them cost next to nothing up to four or five of them).  Scale and zero are applied after the matrix cores, except for 8-bit codes
+// and fp16 weights at 64, which are multiplied as fp16 values.  Activation staging: CHUNK 128-column steps per LDS
 // buffer: at most CAP (8, or 16 where a launch of up to 16 token rows asks for it), and at most what lets two buffers
 // of a workgroup fit 128 KB of the CU's LDS.
 template <int TOK, int WAVES, int CAP> struct PipeCfg {
@@ -53,6 +55,13 @@ template <int TOK, int WAVES, int CAP> struct PipeCfg {
 // c16 ^ (row % 16) of that step: rows are a multiple of 256 bytes apart, and the swizzle makes the
 // 16-byte operand reads of 16 consecutive rows hit 16 different bank groups.
 template <int TOK, int WAVES, int CAP> struct DecodeSmem { uint16_t x[2][TOK][PipeCfg<TOK, WAVES, CAP>::ROW_HALVES]; };
+// 64 token rows: a fill of 1 KB is one token row's four steps, so rows can be 16 bytes further apart instead of swizzled, and an operand's address is the lane's
+// place plus a constant.  xsum: the sums of x of each of a chunk's groups, as the operand that the zero term takes (see fold_zeros).
+template <int WAVES, int CAP> struct DecodeSmem<64, WAVES, CAP> {
+    enum { ROW = PipeCfg<64, WAVES, CAP>::ROW_HALVES + 8 };
+    uint16_t x[2][64][ROW];
+    u32x4 xsum[2][PipeCfg<64, WAVES, CAP>::CHUNK][64];
+};
 
 // Halves per token row of a linear's group sums (see decode_prepare_kernel).
 __device__ __host__ __forceinline__ int group_sums_stride(int K) { return 2 * ((K / 128 + 15) & ~15) + 8; }
@@ -120,10 +129,11 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     constexpr int NP = RT / 2, MT2 = WIDE ? TOK / 32 : 1;      // wide path: tile pairs and 32-token tiles
     constexpr int CHUNK = PipeCfg<TOK, WAVES, CAP>::CHUNK, XQ = PipeCfg<TOK, WAVES, CAP>::XQ;
     // 32-token launches keep two steps in flight per wave: their second token tile needs the registers
-    constexpr int WANT = TOK == 32 ? 2 : (int)DecodeCfg<V>::DEPTH;
+    constexpr int WANT = TOK == 32 || (TOK > 32 && (V == V_W3 || V == V_W4)) ? 2 : (int)DecodeCfg<V>::DEPTH;
     constexpr int STAGES = WANT < CHUNK ? WANT : CHUNK;
     // vector-memory loads of one Stage: the tiles (one load per KB, the 768-byte 3-bit tile included) and scale + zero
     constexpr bool POST = TOK <= 32 && V != V_F16;   // scale and zero folded in after the matrix cores (see compute below)
+    constexpr bool WPOST = WIDE && (V == V_W3 || V == V_W4);      // the same on the 32x32x16 path
     constexpr bool INPLACE = POST && V == V_W3 && INPL;   // 3-bit codes masked where they lie, against activations scaled for it
     constexpr int STAGE_LOADS = RT * (VInfo<V>::TILE_BYTES >= 1024 ? VInfo<V>::TILE_BYTES / 1024 : 1) + (SCHEME == SCH_ASYM ? (POST ? 1 : 2) : 0);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -152,6 +162,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
 
     f4 acc[RT][MT];                   // narrow path
     f16x accw[NP][MT2];               // wide path: [tile pair][32-token tile]
+    uint32_t zc[CHUNK];               // WPOST: the zeros of the chunk's steps
     auto clear_acc = [&]() {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
@@ -221,11 +232,142 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     // FMAs per tile and token tile instead of the int -> fp16 conversions and packed FMAs per weight.
     // The zero term, sum over groups of zero[n][g] * sum_g(x[m]), is itself a small matrix product
     // (K / 128 deep): it is added once per unit, at its end, from the group sums that
-    // decode_prepare_kernel left in prep (add_zero_term below).  Otherwise (64 tokens, where the fp32
-    // work has outgrown the saving): dequantise each weight to fp16 once, w~ = scale * code + zero.
+    // decode_prepare_kernel left in prep (finish_unit below).  WPOST: the same at 64 tokens, see step_wide.  Otherwise
+    // (64 tokens, 8 bit and fp16): each weight as an fp16 number, w~ = scale * code + zero.
     // MFMA A operand: 8 consecutive columns (16-byte group c16 of 128-column step `step`) of a token row
     auto x_operand = [&](int buf, int row, int step, int c16) {
-        return *reinterpret_cast<const h8*>(&sm.x[buf][row][step * 128 + 8 * (c16 ^ (row & 15))]);
+        if constexpr (WIDE) return *reinterpret_cast<const h8*>(&sm.x[buf][row][step * 128 + 8 * c16]);
+        else return *reinterpret_cast<const h8*>(&sm.x[buf][row][step * 128 + 8 * (c16 ^ (row & 15))]);
+    };
+    // WPOST, the zero term, sum over groups of zero[n][g] * sum_g(x[m]): a matrix product four groups deep per chunk, one chunk behind, of numbers cut into bf16
+    // exactly -- a sum into three pieces, a zero into two -- so that no row's or group's size matters and a product of the smallest pieces (2^-24) alone is left out.
+    // sum_x forms the sums of the chunk in buffer buf: wave w those of step w / 2, tokens 32 (w % 2) .. + 31, from the matrix cores.
+    // (Both together 6 % of the time; a kernel ahead of the launch would need more workspace than a call asks for so far.)
+    auto sum_x = [&](int buf) {
+        if constexpr (WPOST) {
+            const int step = wave >> 1, t0 = 32 * (wave & 1);
+            const _Float16 one = (_Float16)1.0f;
+            const h8 ones = {one, one, one, one, one, one, one, one};
+            f4 xg[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) xg[m] = mfma16(x_operand(buf, t0 + 16 * m + r, step, 4 * j + kq), ones, xg[m]);
+            // lane (r, kq) takes token t0 + 16 (r / 4) + 4 kq + r % 4
+            float x1 = xg[0][0];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) x1 = r == i ? xg[i / 4][i % 4] : x1;
+            const uint32_t a = __builtin_bit_cast(uint32_t, x1) & 0xffff0000u;
+            const float r1 = x1 - __builtin_bit_cast(float, a);
+            const uint32_t b = __builtin_bit_cast(uint32_t, r1) & 0xffff0000u;
+            const uint32_t c = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, b));
+            if (r < 8) sm.xsum[buf][step][t0 + 16 * (r >> 2) + 4 * kq + (r & 3)] = u32x4{(a >> 16) | b, (c >> 16) | a, b >> 16, 0u};
+        }
+    };
+    // the product: the k slots of a group are x1 hi, x2 hi, x3 hi, x1 lo, x2 lo and three zeros
+    auto fold_zeros = [&](int buf) {
+        if constexpr (WPOST) {
+            typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+            const int half = lane >> 5;
+#pragma unroll
+            for (int i = 0; i < CHUNK / 2; ++i) {
+                b8 xs[MT2];
+#pragma unroll
+                for (int m2 = 0; m2 < MT2; ++m2) xs[m2] = __builtin_bit_cast(b8, sm.xsum[buf][2 * i + half][32 * m2 + (lane & 31)]);
+                const uint32_t z2 = half ? zc[2 * i + 1] : zc[2 * i];
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const float z = (float)as_h2(z2)[p];
+                    const uint32_t hi = __builtin_bit_cast(uint32_t, z) & 0xffff0000u;
+                    const uint32_t lo = __builtin_bit_cast(uint32_t, z - __builtin_bit_cast(float, hi));
+                    const b8 zb = __builtin_bit_cast(b8, u32x4{(hi >> 16) | hi, (hi >> 16) | lo, lo >> 16, 0u});
+#pragma unroll
+                    for (int m2 = 0; m2 < MT2; ++m2) accw[p][m2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xs[m2], zb, accw[p][m2], 0, 0, 0);
+                }
+            }
+        }
+    };
+    // One step on the 32x32x16 path, codes multiplied as they are (WPOST).  What bounds it is issue: 32 matrix instructions of 32 cycles and 206 (3 bit, 166 at
+    // 4) vector ones of about four a wave, which overlap only if they alternate, and behind that the board's power (1.55 GHz).  So a part of 16 columns is four
+    // matrix instructions with the next part's unpacking among them, and the products of a step (dw) go into the accumulators while the next step's first products
+    // are formed, of which they need the registers.  Four 14336-wide 3-bit layers at 64 rows, us: weights dequantised in front of the products 1430, so 1300 (error
+    // against 64 bits 2.7e-4 / 2.3e-4); 48 rows 1407 / 1279; three 4-bit layers, 40 rows 1107 / 1001; 7168-wide 3- and 4-bit layers, 33 rows 553 / 508, 64 580 / 533.
+    // Tried: a chain of eight products at a time for each of the four accumulators (evener, but half a step's operands held: 500 registers spilled); wave priorities
+    // by step, by part or for the younger wave of a SIMD (within 1 %); two more steps of weights in flight would not help (weights at hand in L2: 2 % faster).
+    // FIRST, LAST: of a chunk.  nb: the next step's stage; fill: the next activations; refill: asks for what b takes next.
+    h8 wv[2][NP], xv[2][WPOST ? MT2 : 1];
+    // the lane's place in the buffer in use: token row lane % 32, its half of a part's columns
+    uint32_t xlane = (uint32_t)((lane & 31) * sizeof(sm.x[0][0]) + 32 * (lane >> 5));
+    f16x dw[WPOST ? NP : 1][WPOST ? MT2 : 1];
+    float sfw[NP];
+    auto clear_products = [&]() {
+        if constexpr (WPOST)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                sfw[p] = 0.0f;
+#pragma unroll
+                for (int m2 = 0; m2 < MT2; ++m2)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) dw[p][m2][v] = 0.0f;
+            }
+    };
+    clear_products();
+    auto fold = [&](int p, int m2) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) accw[p][m2][v] = __builtin_fmaf(sfw[p], dw[p][m2][v], accw[p][m2][v]);
+        asm volatile("" : "+v"(accw[p][m2]));             // here and not when a later step wants it: dw's registers are taken over
+    };
+    auto step_wide = [&](Stage& b, Stage& nb, int buf, int step, auto first, auto last, auto fill, auto refill) {
+        constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
+        const f16x zero16 = {};
+        auto read_x = [&](int st_, int kk) {              // x_operand(buf, 32 * m2 + lane % 32, st_, 4 * (kk / 2) + 2 * (lane / 32) + kk % 2)
+            const uint8_t* at = reinterpret_cast<const uint8_t*>(&sm) + xlane + st_ * 256 + 64 * (kk >> 1) + 16 * (kk & 1);
+#pragma unroll
+            for (int m2 = 0; m2 < MT2; ++m2) xv[kk & 1][m2] = *reinterpret_cast<const h8*>(at + m2 * 32 * sizeof(sm.x[0][0]));
+        };
+        auto unpack = [&](Stage& g, int kk) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p) wv[kk & 1][p] = unpack_subnormal_step<V>(g.w[p + NP * (kk & 1)], kk >> 1);
+        };
+        if constexpr (FIRST) {
+            read_x(step, 0);
+            unpack(b, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        zc[step] = b.z[0];
+        float sfn[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) sfn[p] = (float)as_h2(b.s[0])[p] * 16777216.0f;       // codes are subnormals: times 2^24
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this part's activations; ahead of the next part's reads, or the compiler waits for those too
+            if (kk < 7) read_x(step, kk + 1);
+            else if constexpr (!LAST) read_x(step + 1, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (kk < 7) unpack(b, kk + 1);
+            else if constexpr (!LAST) unpack(nb, 0);
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int m2 = 0; m2 < MT2; ++m2) {
+                    if (kk == 0) fold(p, m2);
+                    dw[p][m2] = mfma32(xv[kk & 1][m2], wv[kk & 1][p], kk == 0 ? zero16 : dw[p][m2]);
+                    if (kk == 0) __builtin_amdgcn_sched_barrier(0);
+                }
+            if (kk & 1) fill(4 * step + (kk >> 1));
+            if (kk > 0) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        refill();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) sfw[p] = sfn[p];
     };
     auto compute = [&](Stage& b, int buf, int step) {
         if constexpr (WIDE) {
@@ -346,7 +488,21 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     // The loads are asynchronous: wait on vmcnt before the barrier that publishes the buffer.
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(xrows), (short)0,
                                                                           (int)(2u * (uint32_t)x_rows * (uint32_t)L.K()), 0x00020000);
+    // 64 token rows: load i of XQ, one token row's steps; the row rides in the scalar offset
+    auto fill_x_row = [&](const Chunk& c, int buf, int i, uint32_t lane_off) {
+        const int row = XQ * __builtin_amdgcn_readfirstlane(wave) + i;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, (lptr_t)&sm.x[buf][row][0], 16, (int)lane_off, 256 * c.kt0 + 2 * min(row, x_rows - 1) * L.K(), 0, 0);
+    };
+    auto fill_lane_off = [&](const Chunk& c) { return 256u * (uint32_t)max(0, min(lane >> 4, c.n - 1)) + 16u * (uint32_t)(lane & 15); };
     auto fill_x_chunk = [&](const Chunk& c, int buf) {
+        if constexpr (WIDE) {
+            static_assert(!WIDE || CHUNK == 4, "a load is a token row's chunk");
+            const uint32_t lane_off = fill_lane_off(c);
+#pragma unroll
+            for (int i = 0; i < XQ; ++i) fill_x_row(c, buf, i, lane_off);
+            asm volatile("" ::: "memory");
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < XQ; ++i) {
             const int q = XQ * wave + i;
@@ -356,6 +512,48 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, (lptr_t)(&sm.x[buf][0][0] + 512 * q), 16, (int)off, 256 * c.kt0, 0, 0);
         }
         asm volatile("" ::: "memory");      // weight loads issued later stay later: vmcnt counts in issue order
+    };
+
+    // Sums that are not finite, of tokens with an infinite activation: scale and zero behind the products make NaN of what the dequantised
+    // weights give an infinity for.  Formed again from those, slowly.
+    auto redo_not_finite = [&](int sb) {
+        if constexpr (WPOST) {
+#pragma unroll 1
+            for (int pm = 0; pm < NP * MT2; ++pm) {
+                bool bad = false;
+#pragma unroll
+                for (int u = 0; u < NP * MT2; ++u)
+                    if (u == pm)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) bad = bad || !__builtin_isfinite(accw[u / MT2][u % MT2][v]);
+                if (__builtin_expect(!__any(bad), 1)) continue;
+                const int p = pm / MT2, m2 = pm % MT2;
+                const long u0 = (long)sb * KT, k_lo = max(u0, s_begin) - u0, k_hi = min(u0 + KT, s_end) - u0;
+                const uint16_t* xp = xrows + (size_t)min(32 * m2 + (lane & 31), x_rows - 1) * L.K() + 16 * (lane >> 5);
+                const uint32_t sel = (uint32_t)(lane >> 4) & 1u;
+                f16x sum = {};
+#pragma unroll 1
+                for (long kt = k_lo; kt < k_hi; ++kt) {
+                    const uint8_t* tile = L.codes + ((size_t)row_block(sb) * KT + kt) * (4 * (size_t)TILE) + (2 * sel + p) * TILE + LANE_BYTES * (r + 32 * (lane >> 5));
+                    const size_t row = (size_t)kt * L.N + row_block(sb) * 64 + 4 * r + 2 * sel + p;
+#pragma unroll
+                    for (int which = 0; which < 2; ++which) {
+                        const WRaw<V> w = load_tile_at<V>(tile + which * 16 * LANE_BYTES);
+                        h8 o[4];
+                        unpack_codes<V>(w, o);
+                        apply_scale_zero(o, __builtin_bit_cast(_Float16, L.scales[row]), __builtin_bit_cast(_Float16, L.zeros[row]));
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) sum = mfma32(*reinterpret_cast<const h8*>(xp + (size_t)kt * 128 + 32 * j + 8 * which), o[j], sum);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < NP * MT2; ++u)
+                    if (u == pm)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            if (!__builtin_isfinite(accw[u / MT2][u % MT2][v])) accw[u / MT2][u % MT2][v] = sum[v];
+            }
+        }
     };
 
     // ---- end of a unit: lane holds tokens 4*kq + v of RT consecutive rows starting at nbase
@@ -371,6 +569,8 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             asm volatile("" : "+v"(thalf));
             const long nbase = (RT == 4) ? rb * 64 + 4 * (ncol & 15) + 2 * (ncol >> 4)
                                          : (rb >> 1) * 64 + 4 * (ncol & 15) + 2 * (rb & 1) + (ncol >> 4);
+            typedef float fv __attribute__((ext_vector_type(NP)));
+            typedef _Float16 hv __attribute__((ext_vector_type(NP)));
             float post[NP], bias[NP];
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
@@ -378,31 +578,54 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
                 if constexpr (SCHEME == SCH_SYM) post[p] = (float)__builtin_bit_cast(_Float16, L.scales[nbase + p]);
                 bias[p] = (L.bias && !partial) ? (float)__builtin_bit_cast(_Float16, L.bias[nbase + p]) : 0.0f;
             }
+            // All 64 outputs of a lane go through one operation after the other, so that what to do is asked once, not per output
+            if constexpr (SCHEME == SCH_SYM)
 #pragma unroll
-            for (int m2 = 0; m2 < MT2; ++m2)
+                for (int m2 = 0; m2 < MT2; ++m2)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int tok = m0 + 32 * m2 + 8 * (v / 4) + 4 * thalf + (v % 4);
-                    if (tok >= M) continue;
-                    if (!partial) {
-                        typedef _Float16 hv __attribute__((ext_vector_type(NP)));
-                        hv o, res;
-                        if (L.residual) res = *reinterpret_cast<const hv*>(L.residual + (size_t)tok * L.N + nbase);
+                    for (int p = 0; p < NP; ++p)
 #pragma unroll
-                        for (int p = 0; p < NP; ++p) {
-                            float val = apply_activation(accw[p][m2][v] * post[p] + bias[p], L.act);
-                            if (L.residual) val += (float)res[p];
-                            o[p] = (_Float16)val;
-                        }
-                        *reinterpret_cast<hv*>(L.y + (size_t)tok * L.N + nbase) = o;
-                    } else {
-                        typedef float fv __attribute__((ext_vector_type(NP)));
-                        fv o;
+                        for (int v = 0; v < 16; ++v) accw[p][m2][v] *= post[p];
+            const int t_lane = m0 + 4 * thalf;
+            auto for_rows = [&](auto&& fn) {       // fn(m2, v, token row) for the rows there are
 #pragma unroll
-                        for (int p = 0; p < NP; ++p) o[p] = accw[p][m2][v] * post[p];
-                        *reinterpret_cast<fv*>(partial + (size_t)(tok - m0) * (WAVES * 64) + (nbase - (long)sb * (WAVES * 16 * RT))) = o;
+                for (int m2 = 0; m2 < MT2; ++m2)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int tok = t_lane + 32 * m2 + 8 * (v / 4) + v % 4;
+                        if (tok < M) fn(m2, v, tok);
                     }
-                }
+            };
+            if (partial) {
+                float* at = partial + (nbase - (long)sb * (WAVES * 16 * RT)) + (size_t)(4 * thalf) * (WAVES * 64);
+                for_rows([&](int m2, int v, int) {
+                    fv o;
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) o[p] = accw[p][m2][v];
+                    *reinterpret_cast<fv*>(at + (32 * m2 + 8 * (v / 4) + v % 4) * (WAVES * 64)) = o;
+                });
+            } else {
+                if (L.bias || L.act != LPQ_ACT_NONE)
+#pragma unroll
+                    for (int m2 = 0; m2 < MT2; ++m2)
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) accw[p][m2][v] = apply_activation(accw[p][m2][v] + bias[p], L.act);
+                if (L.residual)
+                    for_rows([&](int m2, int v, int tok) {
+                        const hv res = *reinterpret_cast<const hv*>(L.residual + (size_t)tok * L.N + nbase);
+#pragma unroll
+                        for (int p = 0; p < NP; ++p) accw[p][m2][v] += (float)res[p];
+                    });
+                uint16_t* at = L.y + (size_t)t_lane * L.N + nbase;
+                for_rows([&](int m2, int v, int) {
+                    hv o;
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) o[p] = (_Float16)accw[p][m2][v];
+                    *reinterpret_cast<hv*>(at + (size_t)(32 * m2 + 8 * (v / 4) + v % 4) * L.N) = o;
+                });
+            }
         }
         if (!WIDE && rb < row_blocks) {
             const long nbase = (RT == 4) ? rb * 64 + 4 * r : (rb >> 1) * 64 + 4 * r + 2 * (rb & 1);
@@ -527,20 +750,43 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     wait_vmem_all_but<0>();
     lds_barrier();
     int buf = 0;
+    bool pending = false;                                    // WPOST: the zero term of the chunk before is still to come
     while (cur.n > 0) {
         const bool active = row_block(cur.sb) < row_blocks;
+        if constexpr (WPOST) {
+            if (pending && active) fold_zeros(buf ^ 1);
+            sum_x(buf);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // steady state: a chunk of N steps (a full one; in the 16-step form also a linear's remainder of exactly 8)
         // followed by enough steps to refill every slot -- no per-step conditions, so the whole chunk is one
         // schedulable block
         auto steady_chunk = [&](auto n_steps) {
             constexpr int N = decltype(n_steps)::value;
-            fill_x_chunk(nxt, buf ^ 1);                 // in this block, where the compiler can count the fill ahead of the stages' uses
+            uint32_t fill_off = WPOST ? fill_lane_off(nxt) : 0u;
+            asm volatile("" : "+v"(fill_off));
+            if constexpr (!WPOST) fill_x_chunk(nxt, buf ^ 1);     // in this block, where the compiler can count the fill ahead of the stages' uses
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                compute(st[i % STAGES], buf, i);
-                const int q = i + STAGES;                   // slot to refill
-                if (q < N) issue(st[i % STAGES], cur.sb, cur.kt0 + q, oc);
-                else       issue(st[i % STAGES], nxt.sb, nxt.kt0 + (q - N), on);
+                auto refill = [&] {
+                    const int q = i + STAGES;               // slot to refill
+                    if (q < N) issue(st[i % STAGES], cur.sb, cur.kt0 + q, oc);
+                    else       issue(st[i % STAGES], nxt.sb, nxt.kt0 + (q - N), on);
+                };
+                if constexpr (WPOST) {
+                    // the next chunk's activations: a load at a time through steps 0 and 1 (in a block they wait for one another's issue)
+                    auto fill = [&](int i) { if (i < XQ) fill_x_row(nxt, buf ^ 1, i, fill_off); };
+                    typedef std::true_type T;
+                    typedef std::false_type F;
+                    static_assert(!WPOST || N == 4, "chunks of four steps");
+                    if (i == 0)          step_wide(st[0], st[1], buf, 0, T(), F(), fill, refill);
+                    else if (i == N - 1) step_wide(st[1], st[0], buf, i, F(), T(), fill, refill);
+                    else if (i == 1)     step_wide(st[1], st[0], buf, i, F(), F(), fill, refill);
+                    else                 step_wide(st[0], st[1], buf, i, F(), F(), fill, refill);
+                } else {
+                    compute(st[i % STAGES], buf, i);
+                    refill();
+                }
                 if constexpr (WIDE) __builtin_amdgcn_sched_barrier(0);      // keeps a step's operand reads out of earlier steps (register pressure)
             }
             // the next chunk's activations were requested before this chunk's last STAGES refills, which stay in flight
@@ -554,7 +800,10 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             if (nxt.n > 0) fill_x_chunk(nxt, buf ^ 1);
 #pragma unroll
             for (int i = 0; i < CHUNK; ++i) {
-                if (i < cur.n && active) compute(st[i % STAGES], buf, i);
+                if constexpr (WPOST) {
+                    zc[i] = 0;
+                    if (i < cur.n && active) step_wide(st[i % STAGES], st[i % STAGES], buf, i, std::true_type(), std::true_type(), [](int) {}, [] {});
+                } else if (i < cur.n && active) compute(st[i % STAGES], buf, i);
                 const int q = i + STAGES;
                 if (q < CHUNK) { if (q < cur.n) issue(st[i % STAGES], cur.sb, cur.kt0 + q, oc); }
                 else           { if (q - CHUNK < nxt.n) issue(st[i % STAGES], nxt.sb, nxt.kt0 + (q - CHUNK), on); }
@@ -565,10 +814,24 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
         if (unit_ends) {
             const long u0 = (long)cur.sb * KT;               // the unit's first step
             const bool whole = u0 >= s_begin && u0 + KT <= s_end;
+            if constexpr (WPOST) {
+                lds_barrier();                               // everybody's sums of this chunk
+                if (active) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+#pragma unroll
+                        for (int m2 = 0; m2 < MT2; ++m2) fold(p, m2);
+                    fold_zeros(buf);
+                    redo_not_finite(cur.sb);
+                }
+            }
             finish_unit(cur.sb, whole ? nullptr : (u0 < s_begin ? slot_first : slot_last));
+            if constexpr (WPOST) clear_products();
         }
+        if constexpr (WPOST) pending = !unit_ends;
         lds_barrier();
         buf ^= 1;
+        if constexpr (WPOST) xlane += buf ? (uint32_t)sizeof(sm.x[0]) : 0u - (uint32_t)sizeof(sm.x[0]);
         cur = nxt;
         nxt = next_chunk(nxt);
         oc = on;
