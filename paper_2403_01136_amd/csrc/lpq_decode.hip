@@ -68,6 +68,17 @@ __device__ __host__ __forceinline__ int group_sums_stride(int K) { return 2 * ((
 
 typedef __attribute__((address_space(3))) void* lptr_t;
 
+// A pointer of the kernel's arguments for use in a loop: kept in scalar registers.  As a member of the arguments the compiler loads it again ahead of each
+// use, since it may, and waits for it: three loads and waits per step of the small launches' kernels.  With that and addresses as a scalar base and a
+// 32-bit lane offset (334 -> 303 instructions per step of five 4-bit tiles), us: 5120 -> 15360, 4 bit, 7 rows 12.38 / 11.85, 7168 -> 7168, per-row 8 bit, 3 rows
+// 12.40 / 11.82, 5120 -> 5120, 3 bit, 12 rows 10.95 / 10.73; layers of 5120, 4 sequences 73.2 / 71.7, of 2048, fp16, 2 sequences 52.6 / 51.5.
+template <typename T> __device__ __forceinline__ const T* keep(const T* p)
+{
+    uint64_t u = reinterpret_cast<uint64_t>(p);
+    asm("" : "+s"(u));
+    return (const T*)(const __attribute__((address_space(1))) T*)u;
+}
+
 // s_waitcnt vmcnt(N): all but the wave's newest N vector-memory operations have completed.  Also a
 // compiler barrier, so that no memory operation moves across it.
 template <int N> __device__ __forceinline__ void wait_vmem_all_but()
@@ -1306,6 +1317,20 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
     const int kt0 = split * share + min(split, extra), kt1 = kt0 + share + (split < extra ? 1 : 0);
     const int n_w = kt1 - kt0 > wave ? (kt1 - kt0 - wave + WAVES - 1) / WAVES : 0;      // this wave's steps
     const uint16_t* __restrict__ xrow = L.x + (size_t)min(m0 + r, M - 1) * L.K() + 8 * kq;       // rows past M repeat the last one
+    // A load's address is a scalar base and a 32-bit lane offset: into the group's first 64-row block at the step, the block's scales, the activations' columns
+    constexpr int TILE = VInfo<V>::TILE_BYTES, LANE_BYTES = V == V_W3 ? 12 : 16;
+    const uint8_t* const codes = keep(L.codes) + (size_t)(g0 >> 2) * KT * (4 * (size_t)TILE);
+    const uint8_t* const scales = keep(reinterpret_cast<const uint8_t*>(L.scales)) + (size_t)(g0 >> 2) * 128;
+    const uint8_t* const zeros = keep(reinterpret_cast<const uint8_t*>(L.zeros)) + (size_t)(g0 >> 2) * 128;
+    const uint8_t* const xs_base = keep(reinterpret_cast<const uint8_t*>(L.x));
+    const size_t group_bytes = (size_t)L.N * 2;
+    const int place = (int)(g0 & 3);                                // of the first tile in its block
+    uint32_t woff[ALIGNED ? 1 : RT];
+#pragma unroll
+    for (int t = 0; t < (ALIGNED ? 1 : RT); ++t)
+        woff[t] = (uint32_t)(LANE_BYTES * lane) + (uint32_t)((place + t) & 3) * TILE + (place + t >= 4 ? (uint32_t)KT * (4u * TILE) : 0u);
+    uint32_t soff = (uint32_t)(8 * r), xoff = ((uint32_t)min(m0 + r, M - 1) * (uint32_t)L.K() + 8u * (uint32_t)kq) * 2u;
+    const uint32_t last_block = place + RT > 4 ? 128u : 0u;         // the last tile's block, behind the first
 
     uint16_t* const xs_rows = reinterpret_cast<uint16_t*>(red);                                   // LN: the rows, then the waves' sums
     const uint16_t* const xs_lane = xs_rows + (size_t)min(r, M - 1) * (L.K() + LN_PAD) + 8 * kq;
@@ -1321,21 +1346,28 @@ __device__ __forceinline__ void run_rows(const LinDesc& L, int M, int m0, long r
     // flight constant, which is what the waits below rely on) and what they bring is never multiplied
     auto issue = [&](Stage& b, int i) {
         const int kt = min(kt0 + wave + WAVES * i, KT - 1);
+        const uint8_t* wbase = codes + (size_t)kt * (4 * (size_t)TILE);
 #pragma unroll
-        for (int t = 0; t < RT; ++t) b.w[t] = load_tile<V>(L.codes, (g0 + t) >> 2, KT, kt, (int)((g0 + t) & 3), lane);
+        for (int t = 0; t < RT; ++t) {
+            uint32_t& off = woff[ALIGNED ? 0 : t];
+            asm volatile("" : "+v"(off));                           // widened next to the load
+            b.w[t] = load_tile_at<V>(wbase + off + (ALIGNED ? t * TILE : 0));
+        }
         if constexpr (SCHEME == SCH_ASYM) {
-            const size_t idx = (size_t)kt * L.N + (g0 >> 2) * 64 + 4 * r;
-            b.s = *reinterpret_cast<const u32x2*>(L.scales + idx);
-            b.z = *reinterpret_cast<const u32x2*>(L.zeros + idx);
+            const size_t row0 = (size_t)kt * group_bytes;
+            asm volatile("" : "+v"(soff));
+            b.s = *reinterpret_cast<const u32x2*>(scales + row0 + soff);
+            b.z = *reinterpret_cast<const u32x2*>(zeros + row0 + soff);
             if constexpr (!ALIGNED) {
-                const size_t idx1 = (size_t)kt * L.N + ((g0 + RT - 1) >> 2) * 64 + 4 * r;    // the last tile's block
-                b.s1 = *reinterpret_cast<const u32x2*>(L.scales + idx1);
-                b.z1 = *reinterpret_cast<const u32x2*>(L.zeros + idx1);
+                b.s1 = *reinterpret_cast<const u32x2*>(scales + row0 + last_block + soff);
+                b.z1 = *reinterpret_cast<const u32x2*>(zeros + row0 + last_block + soff);
             }
         }
-        if constexpr (!LN)
+        if constexpr (!LN) {
+            asm volatile("" : "+v"(xoff));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b.a[j] = *reinterpret_cast<const h8*>(xrow + (size_t)kt * 128 + 32 * j);
+            for (int j = 0; j < 4; ++j) b.a[j] = *reinterpret_cast<const h8*>(xs_base + (size_t)kt * 256 + xoff + 64 * j);
+        }
     };
 
     f4 acc[RT], xsum = f4{0, 0, 0, 0};
@@ -1543,9 +1575,9 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
 {
     constexpr int SCHEME = VInfo<V>::SCHEME, TILE = VInfo<V>::TILE_BYTES, LANE_BYTES = V == V_W3 ? 12 : 16;
     constexpr int LOADS = 4 * (TILE >= 1024 ? TILE / 1024 : 1) + (SCHEME == SCH_ASYM ? 2 : 0);       // vector-memory loads of a stage
-    // Tiles whose group products are held at a time: all four where the registers allow it, else two, and the activations
+    // Tiles whose group products are held at a time: all four where the registers allow it (three token tiles: 214), else two, and the activations
     // are read from LDS twice.
-    constexpr int TG = MT <= 2 ? 4 : 2;
+    constexpr int TG = MT <= 3 ? 4 : 2;
     constexpr int KW = MidCfg<MT, RB>::KW, C = MidCfg<MT, RB>::C, SLOTS = MidCfg<MT, RB>::SLOTS;
     constexpr int FILL = SLOTS * MT / 2 < 1 ? 1 : SLOTS * MT / 2;               // 1 KB loads per wave and iteration of activations
     constexpr int SLOT = 16 * MT * 128;                // halves of one step's activations
@@ -1578,17 +1610,22 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
     };
     Stage st[2];
     uint32_t woff = (uint32_t)(LANE_BYTES * lane), soff = (uint32_t)(8 * r);
+    const uint8_t* const codes = keep(L.codes) + (size_t)rbc * KT * (4 * (size_t)TILE);
+    const uint8_t* const scales = keep(reinterpret_cast<const uint8_t*>(L.scales)) + (size_t)rbc * 128;
+    const uint8_t* const zeros = keep(reinterpret_cast<const uint8_t*>(L.zeros)) + (size_t)rbc * 128;
+    const size_t group_bytes = (size_t)L.N * 2;
     auto step_of = [&](int it, int c) { return kt0 + it * SLOTS + C * kw + c; };
     auto issue = [&](Stage& b, int kt) {
-        const uint8_t* base = L.codes + ((size_t)rbc * KT + min(kt, kt1 - 1)) * (4 * (size_t)TILE);
+        kt = min(kt, kt1 - 1);
+        const uint8_t* base = codes + (size_t)kt * (4 * (size_t)TILE);
         asm volatile("" : "+v"(woff));
 #pragma unroll
         for (int t = 0; t < 4; ++t) b.w[t] = load_tile_at<V>(base + woff + t * TILE);
         if constexpr (SCHEME == SCH_ASYM) {
-            const size_t row0 = ((size_t)min(kt, kt1 - 1) * L.N + (size_t)rbc * 64) * 2;
+            const size_t row0 = (size_t)kt * group_bytes;
             asm volatile("" : "+v"(soff));
-            b.s = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(L.scales) + row0 + soff);
-            b.z = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(L.zeros) + row0 + soff);
+            b.s = *reinterpret_cast<const u32x2*>(scales + row0 + soff);
+            b.z = *reinterpret_cast<const u32x2*>(zeros + row0 + soff);
         }
     };
     f4 acc[4][MT];
