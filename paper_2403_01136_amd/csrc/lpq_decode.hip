@@ -51,16 +51,15 @@ template <int TOK, int WAVES, int CAP> struct PipeCfg {
     enum { XQ = TOK * CHUNK / 4 / WAVES };          // 1 KB global-to-LDS loads per wave and chunk
 };
 
-// Token row `row` keeps the 16-byte column group c16 of each of its 128-column steps in slot
-// c16 ^ (row % 16) of that step: rows are a multiple of 256 bytes apart, and the swizzle makes the
-// 16-byte operand reads of 16 consecutive rows hit 16 different bank groups.
-template <int TOK, int WAVES, int CAP> struct DecodeSmem { uint16_t x[2][TOK][PipeCfg<TOK, WAVES, CAP>::ROW_HALVES]; };
-// 64 token rows: a fill of 1 KB is one token row's four steps, so rows can be 16 bytes further apart instead of swizzled, and an operand's address is the lane's
-// place plus a constant.  xsum: the sums of x of each of a chunk's groups, as the operand that the zero term takes (see fold_zeros).
-template <int WAVES, int CAP> struct DecodeSmem<64, WAVES, CAP> {
-    enum { ROW = PipeCfg<64, WAVES, CAP>::ROW_HALVES + 8 };
-    uint16_t x[2][64][ROW];
-    u32x4 xsum[2][PipeCfg<64, WAVES, CAP>::CHUNK][64];
+// A token row of the slab: its steps' columns in order, rows 16 bytes further apart than a multiple of 256, so that the 16-byte operand reads of 16 consecutive
+// rows hit 16 different bank groups and an operand's address is the lane's place plus a constant.  (Columns XOR-ed with the row instead, and addresses
+// formed per read, us: six layers of 7168, 3 and 4 bit, 32 rows 383.7, so 376.1; a 3- and an 8-bit layer of 9216, 24 rows 283.7 / 273.4; four of 5120, 8 bit, 32
+// rows 259.2 / 252.1; up to 16 rows the same.)
+// xsum, of 64 token rows: the sums of x of each of a chunk's groups, as the operand that the zero term takes (see fold_zeros).
+template <int TOK, int WAVES, int CAP> struct DecodeSmem {
+    enum { ROW = PipeCfg<TOK, WAVES, CAP>::ROW_HALVES + 8 };
+    uint16_t x[2][TOK][ROW];
+    u32x4 xsum[TOK == 64 ? 2 : 1][TOK == 64 ? PipeCfg<TOK, WAVES, CAP>::CHUNK : 1][TOK == 64 ? 64 : 1];
 };
 
 // Halves per token row of a linear's group sums (see decode_prepare_kernel).
@@ -143,7 +142,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     constexpr int WANT = TOK == 32 || (TOK > 32 && (V == V_W3 || V == V_W4)) ? 2 : (int)DecodeCfg<V>::DEPTH;
     constexpr int STAGES = WANT < CHUNK ? WANT : CHUNK;
     // vector-memory loads of one Stage: the tiles (one load per KB, the 768-byte 3-bit tile included) and scale + zero
-    constexpr bool POST = TOK <= 32 && V != V_F16;   // scale and zero folded in after the matrix cores (see compute below)
+    constexpr bool POST = TOK <= 32 && !WIDE && V != V_F16;   // scale and zero folded in after the matrix cores (see compute below)
     constexpr bool WPOST = WIDE && (V == V_W3 || V == V_W4);      // the same on the 32x32x16 path
     constexpr bool INPLACE = POST && V == V_W3 && INPL;   // 3-bit codes masked where they lie, against activations scaled for it
     constexpr int STAGE_LOADS = RT * (VInfo<V>::TILE_BYTES >= 1024 ? VInfo<V>::TILE_BYTES / 1024 : 1) + (SCHEME == SCH_ASYM ? (POST ? 1 : 2) : 0);
@@ -247,16 +246,15 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     // (64 tokens, 8 bit and fp16): each weight as an fp16 number, w~ = scale * code + zero.
     // MFMA A operand: 8 consecutive columns (16-byte group c16 of 128-column step `step`) of a token row
     auto x_operand = [&](int buf, int row, int step, int c16) {
-        if constexpr (WIDE) return *reinterpret_cast<const h8*>(&sm.x[buf][row][step * 128 + 8 * c16]);
-        else return *reinterpret_cast<const h8*>(&sm.x[buf][row][step * 128 + 8 * (c16 ^ (row & 15))]);
+        return *reinterpret_cast<const h8*>(&sm.x[buf][row][step * 128 + 8 * c16]);
     };
     // WPOST, the zero term, sum over groups of zero[n][g] * sum_g(x[m]): a matrix product four groups deep per chunk, one chunk behind, of numbers cut into bf16
     // exactly -- a sum into three pieces, a zero into two -- so that no row's or group's size matters and a product of the smallest pieces (2^-24) alone is left out.
-    // sum_x forms the sums of the chunk in buffer buf: wave w those of step w / 2, tokens 32 (w % 2) .. + 31, from the matrix cores.
+    // sum_x forms the sums of the chunk in buffer buf: a wave 32 tokens of a step, from the matrix cores.
     // (Both together 6 % of the time; a kernel ahead of the launch would need more workspace than a call asks for so far.)
     auto sum_x = [&](int buf) {
         if constexpr (WPOST) {
-            const int step = wave >> 1, t0 = 32 * (wave & 1);
+            const int step = wave * CHUNK / WAVES, t0 = 32 * (wave % (WAVES / CHUNK));
             const _Float16 one = (_Float16)1.0f;
             const h8 ones = {one, one, one, one, one, one, one, one};
             f4 xg[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
@@ -368,9 +366,9 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             if (kk & 1) fill(4 * step + (kk >> 1));
             if (kk > 0) {
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
+                for (int g = 0; g < NP * MT2; ++g) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, MT2 == 1 ? 10 : 5, 0);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -489,8 +487,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     const uint16_t* xrows = INPLACE ? prep + (size_t)L.aux * 8 + (size_t)32 * group_sums_stride(L.K()) : L.x + (size_t)m0 * L.K();
     const int x_rows = min(TOK, M - m0);
     // ---- activation staging: the x columns of one chunk, shared by the workgroup through LDS.
-    // Buffer loads to LDS, 1 KB per wave and instruction (four 256-byte row segments, at most 64 rows of 2^24 bytes); a lane fetches
-    // the column group that belongs in its 16-byte slot after swizzling.  (With global_load_lds under way the compiler takes loads for
+    // Buffer loads to LDS, 1 KB per wave and instruction (four steps of a token row; at most 64 rows of 2^24 bytes).  (With global_load_lds under way the compiler takes loads for
     // unordered and waits for all of them ahead of a weight stage's first use.  That, and the fence of __syncthreads, emptied
     // the weight pipeline once per chunk.  Buffer loads issued in the block that uses the stages, and lds_barrier, us per pass before and now:
     // 14336-wide layers, 3 bit, 24 rows 907 / 848, 40 1429 / 1361, 64 1455 / 1400; 7168-wide, 4 bit, 32 rows 813 / 773, 64 1217 / 1150;
@@ -499,29 +496,28 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     // The loads are asynchronous: wait on vmcnt before the barrier that publishes the buffer.
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(xrows), (short)0,
                                                                           (int)(2u * (uint32_t)x_rows * (uint32_t)L.K()), 0x00020000);
-    // 64 token rows: load i of XQ, one token row's steps; the row rides in the scalar offset
-    auto fill_x_row = [&](const Chunk& c, int buf, int i, uint32_t lane_off) {
-        const int row = XQ * __builtin_amdgcn_readfirstlane(wave) + i;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, (lptr_t)&sm.x[buf][row][0], 16, (int)lane_off, 256 * c.kt0 + 2 * min(row, x_rows - 1) * L.K(), 0, 0);
+    // Load i of XQ: four steps of a token row; the row rides in the scalar offset
+    constexpr int PARTS = CHUNK / 4;                         // loads of a row
+    struct FillOffs { uint32_t part[PARTS]; };
+    auto fill_x_row = [&](const Chunk& c, int buf, int i, const FillOffs& lane_off) {
+        const int row = (XQ * __builtin_amdgcn_readfirstlane(wave) + i) / PARTS, part = i % PARTS;
+        static_assert(CHUNK % 4 == 0 && XQ % PARTS == 0, "a wave's loads are whole rows");
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, (lptr_t)&sm.x[buf][row][512 * part], 16, (int)lane_off.part[part],
+                                                 256 * c.kt0 + 2 * min(row, x_rows - 1) * L.K(), 0, 0);
     };
-    auto fill_lane_off = [&](const Chunk& c) { return 256u * (uint32_t)max(0, min(lane >> 4, c.n - 1)) + 16u * (uint32_t)(lane & 15); };
+    auto fill_lane_offs = [&](const Chunk& c) {
+        FillOffs o;
+#pragma unroll
+        for (int part = 0; part < PARTS; ++part) {
+            o.part[part] = 256u * (uint32_t)max(0, min(4 * part + (lane >> 4), c.n - 1)) + 16u * (uint32_t)(lane & 15);
+            asm volatile("" : "+v"(o.part[part]));
+        }
+        return o;
+    };
     auto fill_x_chunk = [&](const Chunk& c, int buf) {
-        if constexpr (WIDE) {
-            static_assert(!WIDE || CHUNK == 4, "a load is a token row's chunk");
-            const uint32_t lane_off = fill_lane_off(c);
+        const FillOffs lane_off = fill_lane_offs(c);
 #pragma unroll
-            for (int i = 0; i < XQ; ++i) fill_x_row(c, buf, i, lane_off);
-            asm volatile("" ::: "memory");
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < XQ; ++i) {
-            const int q = XQ * wave + i;
-            const int u = 4 * q + (lane >> 4), row = u / CHUNK, seg = min(u % CHUNK, c.n - 1);
-            const int c16 = (lane & 15) ^ (row & 15);
-            const uint32_t off = ((uint32_t)min(row, x_rows - 1) * (uint32_t)L.K() + (uint32_t)(seg * 128 + c16 * 8)) * 2u;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, (lptr_t)(&sm.x[buf][0][0] + 512 * q), 16, (int)off, 256 * c.kt0, 0, 0);
-        }
+        for (int i = 0; i < XQ; ++i) fill_x_row(c, buf, i, lane_off);
         asm volatile("" ::: "memory");      // weight loads issued later stay later: vmcnt counts in issue order
     };
 
@@ -774,8 +770,8 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
         // schedulable block
         auto steady_chunk = [&](auto n_steps) {
             constexpr int N = decltype(n_steps)::value;
-            uint32_t fill_off = WPOST ? fill_lane_off(nxt) : 0u;
-            asm volatile("" : "+v"(fill_off));
+            FillOffs fill_off;
+            if constexpr (WPOST) fill_off = fill_lane_offs(nxt);
             if constexpr (!WPOST) fill_x_chunk(nxt, buf ^ 1);     // in this block, where the compiler can count the fill ahead of the stages' uses
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -789,11 +785,10 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
                     auto fill = [&](int i) { if (i < XQ) fill_x_row(nxt, buf ^ 1, i, fill_off); };
                     typedef std::true_type T;
                     typedef std::false_type F;
-                    static_assert(!WPOST || N == 4, "chunks of four steps");
-                    if (i == 0)          step_wide(st[0], st[1], buf, 0, T(), F(), fill, refill);
-                    else if (i == N - 1) step_wide(st[1], st[0], buf, i, F(), T(), fill, refill);
-                    else if (i == 1)     step_wide(st[1], st[0], buf, i, F(), F(), fill, refill);
-                    else                 step_wide(st[0], st[1], buf, i, F(), F(), fill, refill);
+                    static_assert(!WPOST || N % STAGES == 0, "a chunk ends with the stages where it began");
+                    if (i == 0)          step_wide(st[0], st[1 % STAGES], buf, 0, T(), F(), fill, refill);
+                    else if (i == N - 1) step_wide(st[i % STAGES], st[(i + 1) % STAGES], buf, i, F(), T(), fill, refill);
+                    else                 step_wide(st[i % STAGES], st[(i + 1) % STAGES], buf, i, F(), F(), fill, refill);
                 } else {
                     compute(st[i % STAGES], buf, i);
                     refill();
