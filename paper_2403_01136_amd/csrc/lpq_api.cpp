@@ -306,16 +306,30 @@ bool reads_in_place(const std::vector<LinearCall>& calls, size_t begin, size_t e
 // (1.2 G) 165 / 149, 222 / 200, 226 / 238; a 3-bit layer of 14336 (2.5 G) 259 / 290, 381 / 370, 393 / 455; 8 bit, 7168 -> 28672 93 / 42, 110 / 48, 119 / 56;
 // an 8-bit layer of 9216 (1.0 G) 227 / 193, 244 / 220, 252 / 252; fp16, 7168 -> 28672 114 / 66, 120 / 71, 129 / 73.
 // With the weight pipeline of the even-share kernel kept full across its chunks: three 4-bit layers of 5120 125 / 108 at 17 rows, 134 / 128 at 32, 182 / 198
-// at 64; a 3- and a 4-bit layer of 7168 (1.2 G) 143 / 139, 157 / 151, 240 / 244; three of them (1.85 G) 190 / 199, 203 / 212, 309 / 342.
+// at 64; three layers of 7168 of 3 and 4 bit (1.85 G) 190 / 199, 203 / 212, 309 / 342.
+// With its 3- and 4-bit codes of 33 to 64 rows multiplied as they are: even-share over this at 20, 32, 40, 48, 56, 64 rows, a 3- and a 4-bit layer of
+// 5120 (0.63 G) 1.07 1.13 1.15 1.13 0.96 0.98, of 6144 (0.91 G) 1.00 1.04 1.06 1.05 0.88 0.88, of 7168 (1.23 G) 1.01 1.00 1.02 1.04 0.84 0.84.
+// 8 bit at 18, 32, 44, 64 rows: two layers of 7168 (1.23 GB) 1.09 1.12 1.09 0.98, three (1.85 GB) 1.03 1.04 1.10 1.01, two of 9216 (2.04 GB) 1.06 1.08 1.05 0.94,
+// five of 7168 (3.1 GB) 1.05 1.05 1.08 0.93; fp16: 7168 (1.23 GB) 1.10 1.11 1.15 1.10, 9216 (2.04 GB) 1.06 1.06 1.09 1.06, three of 7168 (3.7 GB) 0.96 0.96 0.99 0.99;
+// but a single fp16 linear, 28672 -> 36864 (2.1 GB), 0.976 at 24 and 0.973 at 64 rows, and at 2 GB the first launch on new weights is 4-6 % slower in this one (466 / 488
+// on two 8-bit layers of 9216, 24 rows; 449 / 470 on fp16, 40 rows), at 1.85 GB (465 / 460) and 1.2 GB (308 / 310) not: the lines are below that.
+// (49-64 rows of 3 and 4 bit: 0.45 G 1.00, 0.51 G 0.96-0.99; the line stays a little above, where a launch without a fix-up pass needs less workspace.)
 // rows_max_mib of lpq_set_decode_routing (default 192) moves the line in proportion.
-bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
+struct MidLine { double weights34[3], bytes8[3], bytes16[3]; };       // [17-32, 33-48, 49-64 rows]
+const MidLine MID_LINE = {{1.0e9, 1.25e9, 0.55e9}, {1.9e9, 1.9e9, 1.0e9}, {1.4e9, 1.4e9, 1.4e9}};
+// The line of a single linear: its row blocks are all of one length, and their last round may be nearly empty (fp16, 28672 -> 24320, 1.39 GB, 380 row
+// blocks for 256 compute units: 0.994 at 18 rows, 0.957 at 48; 20480 -> 32768, 512 of them, 1.20 at 24 rows).  Above it a launch of several
+// asks for the even-share kernel's workspace all the same: other numbers of rows of the same linears take that one, and a workspace reserved for
+// the widest call of a program has to serve its narrower ones.
+const MidLine MID_LINE_ONE = {{1.0e9, 1.0e9, 0.55e9}, {1.0e9, 1.0e9, 1.0e9}, {1.0e9, 1.0e9, 1.0e9}};
+bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M, const MidLine& line)
 {
-    static const double weights34[3] = {1.0e9, 1.0e9, 0.55e9};              // 17-32, 33-48, 49-64 rows
+    const int m = (M + 15) / 16 - 2;
     double load = 0.0;
     for (size_t c = begin; c < end; ++c) {
         const lpq_qdesc& d = calls[c].w->d;
         const double weights = (double)d.K * (double)d.N;
-        load += d.bits <= 4 ? weights / weights34[(M + 15) / 16 - 2] : weights * d.bits / 8.0 / 1.0e9;
+        load += d.bits <= 4 ? weights / line.weights34[m] : weights * d.bits / 8.0 / (d.bits == 8 ? line.bytes8[m] : line.bytes16[m]);
     }
     return load <= g_rows_max_mb.load() / 192.0;
 }
@@ -325,7 +339,7 @@ bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, i
 bool small_launch(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
 {
     if (M > 64) return false;
-    if (M > 16) return mid_route(calls, begin, end, M);
+    if (M > 16) return mid_route(calls, begin, end, M, end - begin > 1 ? MID_LINE : MID_LINE_ONE);
     int64_t stream_bytes = 0;
     for (size_t c = begin; c < end; ++c) stream_bytes += (int64_t)calls[c].w->d.K * calls[c].w->d.N * calls[c].w->d.bits / 8;
     return stream_bytes <= (int64_t)g_rows_max_mb.load() << 20;
@@ -449,6 +463,8 @@ lpq_status plan_decode(const std::vector<LinearCall>& calls, size_t begin, size_
         }
         out->kernel = mid ? DECODE_MID : DECODE_ROWS;
         out->partial_bytes = out->workspace_bytes = (size_t)partial_floats * sizeof(float);
+        if (!prefill && M > 16 && !mid_route(calls, begin, end, M, MID_LINE_ONE))
+            out->workspace_bytes = std::max(out->workspace_bytes, partial_bytes + (last_rows <= 32 ? sums_off16 * 16 : 0));
         return LPQ_OK;
     }
     // A small launch (one linear of a decoder layer) is not cut into more ranges than it has chunks of
@@ -558,7 +574,7 @@ lpq_status run_decode(const std::vector<LinearCall>& calls, int32_t M, hipStream
     for (size_t li = 0; li < n_launch; ++li) {
         DecodeLaunch& p = plan[li];
         p.a.partial = ws;
-        if (p.workspace_bytes > p.partial_bytes)
+        if (p.kernel == DECODE_EVEN_SHARE && p.workspace_bytes > p.partial_bytes)
             p.a.prep = reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(ws) + p.partial_bytes);
         if (p.kernel != DECODE_EVEN_SHARE) {
             if ((p.kernel == DECODE_MID ? launch_decode_mid(p.a, stream) : launch_decode_rows(p.a, stream)) != hipSuccess) return LPQ_ERR_DEVICE;

@@ -232,6 +232,24 @@ def test_routes():
     assert lib.lpq_route_of(ctypes.byref(d), 1, 1, 1, 256, ctypes.byref(r)) == 8
 
 
+@pytest.mark.parametrize("bits,scheme,several,one", [
+    (3, 1, (1.0e9, 1.25e9, 0.55e9), (1.0e9, 1.0e9, 0.55e9)), (4, 1, (1.0e9, 1.25e9, 0.55e9), (1.0e9, 1.0e9, 0.55e9)),
+    (8, 1, (1.9e9, 1.9e9, 1.0e9), (1.0e9,) * 3), (8, 2, (1.9e9, 1.9e9, 1.0e9), (1.0e9,) * 3), (16, 0, (0.7e9,) * 3, (0.5e9,) * 3)])
+def test_routes_of_17_to_64_rows_by_weights(bits, scheme, several, one):
+    """The number of weights up to which a launch of 17-32, 33-48 and 49-64 rows goes to the kernel of few row blocks, of several linears and of
+    one; it moves with the first routing setting."""
+    kernel = lambda weights, n, M: lpq.lpq_route_of([(bits, scheme, 8192, round(weights / n / 8192 / 64) * 64)] * n, lpq.LPQ_DECODE, M)[0]
+    for n, lines in ((1, one), (3, several)):
+        for line, rows in zip(lines, ((17, 32), (33, 48), (49, 64))):
+            for M in rows:
+                assert kernel(0.99 * line, n, M) == lpq.LPQ_ROUTE_MID and kernel(1.01 * line, n, M) == lpq.LPQ_ROUTE_EVEN_SHARE, (n, M, line)
+    try:
+        lpq.lpq_set_decode_routing(2 * 192, -1)
+        assert kernel(1.99 * several[0], 3, 17) == lpq.LPQ_ROUTE_MID
+    finally:
+        lpq.lpq_set_decode_routing(-1, -1)
+
+
 def layer_route(fmt, h, n_seqs, pos0=70):
     return lpq.lpq_layer_route_of([fmt + kn for kn in ((h, 3 * h), (h, h), (h, 4 * h), (4 * h, h))], n_seqs, pos0)
 
