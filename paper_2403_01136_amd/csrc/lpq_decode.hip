@@ -68,9 +68,11 @@ __device__ __host__ __forceinline__ int group_sums_stride(int K) { return 2 * ((
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // A pointer of the kernel's arguments for use in a loop: kept in scalar registers.  As a member of the arguments the compiler loads it again ahead of each
-// use, since it may, and waits for it: three loads and waits per step of the small launches' kernels.  With that and addresses as a scalar base and a
+// use, since it may, and waits for it: three loads and waits per step of the kernel for up to 16 rows.  With that and addresses as a scalar base and a
 // 32-bit lane offset (334 -> 303 instructions per step of five 4-bit tiles), us: 5120 -> 15360, 4 bit, 7 rows 12.38 / 11.85, 7168 -> 7168, per-row 8 bit, 3 rows
-// 12.40 / 11.82, 5120 -> 5120, 3 bit, 12 rows 10.95 / 10.73; layers of 5120, 4 sequences 73.2 / 71.7, of 2048, fp16, 2 sequences 52.6 / 51.5.
+// 12.40 / 11.82, 5120 -> 5120, 3 bit, 12 rows 10.95 / 10.73; layers of 5120, 4 sequences 73.2 / 71.7, of 2048, fp16, 2 sequences 52.6 / 51.5.  The kernel for
+// 17 to 64 rows loads them per step: kept, its launches of one and two token tiles are up to 2 % slower (2048 -> 6144, 4 bit, 16 rows 6.41 / 6.53, 768 -> 2304, 24 rows
+// 5.41 / 5.45), those of three and four equal in the mean.
 template <typename T> __device__ __forceinline__ const T* keep(const T* p)
 {
     uint64_t u = reinterpret_cast<uint64_t>(p);
@@ -1609,22 +1611,17 @@ __device__ __forceinline__ void run_mid(const LinDesc& L, int M, int sb, int spl
     };
     Stage st[2];
     uint32_t woff = (uint32_t)(LANE_BYTES * lane), soff = (uint32_t)(8 * r);
-    const uint8_t* const codes = keep(L.codes) + (size_t)rbc * KT * (4 * (size_t)TILE);
-    const uint8_t* const scales = keep(reinterpret_cast<const uint8_t*>(L.scales)) + (size_t)rbc * 128;
-    const uint8_t* const zeros = keep(reinterpret_cast<const uint8_t*>(L.zeros)) + (size_t)rbc * 128;
-    const size_t group_bytes = (size_t)L.N * 2;
     auto step_of = [&](int it, int c) { return kt0 + it * SLOTS + C * kw + c; };
     auto issue = [&](Stage& b, int kt) {
-        kt = min(kt, kt1 - 1);
-        const uint8_t* base = codes + (size_t)kt * (4 * (size_t)TILE);
+        const uint8_t* base = L.codes + ((size_t)rbc * KT + min(kt, kt1 - 1)) * (4 * (size_t)TILE);
         asm volatile("" : "+v"(woff));
 #pragma unroll
         for (int t = 0; t < 4; ++t) b.w[t] = load_tile_at<V>(base + woff + t * TILE);
         if constexpr (SCHEME == SCH_ASYM) {
-            const size_t row0 = (size_t)kt * group_bytes;
+            const size_t row0 = ((size_t)min(kt, kt1 - 1) * L.N + (size_t)rbc * 64) * 2;
             asm volatile("" : "+v"(soff));
-            b.s = *reinterpret_cast<const u32x2*>(scales + row0 + soff);
-            b.z = *reinterpret_cast<const u32x2*>(zeros + row0 + soff);
+            b.s = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(L.scales) + row0 + soff);
+            b.z = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(L.zeros) + row0 + soff);
         }
     };
     f4 acc[4][MT];
