@@ -18,8 +18,7 @@
 //
 // Up to 32 token rows per pass the scale is applied after the matrix cores, per 128-column group, and the zero term
 // (sum over groups of zero * sum of x) once per unit from the activations' group sums, which decode_prepare_kernel
-// computes in front of the launch.  From 33 on 3- and 4-bit weights are treated alike, but for the group sums, which the workgroup
-// forms itself, a chunk at a time.
+// computes in front of the launch.  From 33 on each weight is an fp16 number again, w~ = scale * code + zero.
 //
 // A launch that streams little (a single linear of a decoder layer) takes other kernels, further down, without a fix-up
 // pass: up to 16 token rows decode_rows_kernel (one workgroup per group of 16-row tiles whose waves split K, no LDS
@@ -40,11 +39,10 @@ namespace {
 template <int V> struct DecodeCfg { enum { RT = (V == V_F16) ? 2 : 4, DEPTH = (V == V_W3 || V == V_W4) ? 4 : 2 }; };
 
 // A launch is specialised on TOK, the token rows it covers: 16 or 32 (one or two 16-token tiles on the
-// 16x16x32 MFMA) or 64 (32x32x16 MFMA: half the operand reads per multiply-accumulate, and vector instructions between two of
-// them cost next to nothing up to four or five of them).  Scale and zero are applied after the matrix cores, except for 8-bit codes
-// and fp16 weights at 64, which are multiplied as fp16 values.  Activation staging: CHUNK 128-column steps per LDS
+// 16x16x32 MFMA, scale and zero applied after the matrix cores) or 64 (32x32x16 MFMA: half the operand reads per
+// multiply-accumulate; weights dequantised to fp16 in registers).  Activation staging: CHUNK 128-column steps per LDS
 // buffer: at most CAP (8, or 16 where a launch of up to 16 token rows asks for it), and at most what lets two buffers
-// of a workgroup fit 128 KB of the CU's LDS.
+// of a workgroup fit 128 KB of the CU's LDS (and the rows' padding, up to 2 KB).
 template <int TOK, int WAVES, int CAP> struct PipeCfg {
     enum { FIT = 32 * WAVES / TOK, CHUNK = FIT < CAP ? FIT : CAP };
     enum { ROW_HALVES = CHUNK * 128 };
@@ -55,11 +53,9 @@ template <int TOK, int WAVES, int CAP> struct PipeCfg {
 // rows hit 16 different bank groups and an operand's address is the lane's place plus a constant.  (Columns XOR-ed with the row instead, and addresses
 // formed per read, us: six layers of 7168, 3 and 4 bit, 32 rows 383.7, so 376.1; a 3- and an 8-bit layer of 9216, 24 rows 283.7 / 273.4; four of 5120, 8 bit, 32
 // rows 259.2 / 252.1; up to 16 rows the same.)
-// xsum, of 64 token rows: the sums of x of each of a chunk's groups, as the operand that the zero term takes (see fold_zeros).
 template <int TOK, int WAVES, int CAP> struct DecodeSmem {
     enum { ROW = PipeCfg<TOK, WAVES, CAP>::ROW_HALVES + 8 };
     uint16_t x[2][TOK][ROW];
-    u32x4 xsum[TOK == 64 ? 2 : 1][TOK == 64 ? PipeCfg<TOK, WAVES, CAP>::CHUNK : 1][TOK == 64 ? 64 : 1];
 };
 
 // Halves per token row of a linear's group sums (see decode_prepare_kernel).
@@ -144,8 +140,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     constexpr int WANT = TOK == 32 || (TOK > 32 && (V == V_W3 || V == V_W4)) ? 2 : (int)DecodeCfg<V>::DEPTH;
     constexpr int STAGES = WANT < CHUNK ? WANT : CHUNK;
     // vector-memory loads of one Stage: the tiles (one load per KB, the 768-byte 3-bit tile included) and scale + zero
-    constexpr bool POST = TOK <= 32 && !WIDE && V != V_F16;   // scale and zero folded in after the matrix cores (see compute below)
-    constexpr bool WPOST = WIDE && (V == V_W3 || V == V_W4);      // the same on the 32x32x16 path
+    constexpr bool POST = !WIDE && V != V_F16;   // scale and zero folded in after the matrix cores (see compute below)
     constexpr bool INPLACE = POST && V == V_W3 && INPL;   // 3-bit codes masked where they lie, against activations scaled for it
     constexpr int STAGE_LOADS = RT * (VInfo<V>::TILE_BYTES >= 1024 ? VInfo<V>::TILE_BYTES / 1024 : 1) + (SCHEME == SCH_ASYM ? (POST ? 1 : 2) : 0);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -174,7 +169,6 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
 
     f4 acc[RT][MT];                   // narrow path
     f16x accw[NP][MT2];               // wide path: [tile pair][32-token tile]
-    uint32_t zc[CHUNK];               // WPOST: the zeros of the chunk's steps
     auto clear_acc = [&]() {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
@@ -244,141 +238,63 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     // FMAs per tile and token tile instead of the int -> fp16 conversions and packed FMAs per weight.
     // The zero term, sum over groups of zero[n][g] * sum_g(x[m]), is itself a small matrix product
     // (K / 128 deep): it is added once per unit, at its end, from the group sums that
-    // decode_prepare_kernel left in prep (finish_unit below).  WPOST: the same at 64 tokens, see step_wide.  Otherwise
-    // (64 tokens, 8 bit and fp16): each weight as an fp16 number, w~ = scale * code + zero.
+    // decode_prepare_kernel left in prep (finish_unit below).  Otherwise (64 tokens): dequantise each weight to fp16 once,
+    // w~ = scale * code + zero.
     // MFMA A operand: 8 consecutive columns (16-byte group c16 of 128-column step `step`) of a token row
     auto x_operand = [&](int buf, int row, int step, int c16) {
         return *reinterpret_cast<const h8*>(&sm.x[buf][row][step * 128 + 8 * c16]);
     };
-    // WPOST, the zero term, sum over groups of zero[n][g] * sum_g(x[m]): a matrix product four groups deep per chunk, one chunk behind, of numbers cut into bf16
-    // exactly -- a sum into three pieces, a zero into two -- so that no row's or group's size matters and a product of the smallest pieces (2^-24) alone is left out.
-    // sum_x forms the sums of the chunk in buffer buf: a wave 32 tokens of a step, from the matrix cores.
-    // (Both together 6 % of the time; a kernel ahead of the launch would need more workspace than a call asks for so far.)
-    auto sum_x = [&](int buf) {
-        if constexpr (WPOST) {
-            const int step = wave * CHUNK / WAVES, t0 = 32 * (wave % (WAVES / CHUNK));
-            const _Float16 one = (_Float16)1.0f;
-            const h8 ones = {one, one, one, one, one, one, one, one};
-            f4 xg[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int m = 0; m < 2; ++m) xg[m] = mfma16(x_operand(buf, t0 + 16 * m + r, step, 4 * j + kq), ones, xg[m]);
-            // lane (r, kq) takes token t0 + 16 (r / 4) + 4 kq + r % 4
-            float x1 = xg[0][0];
-#pragma unroll
-            for (int i = 1; i < 8; ++i) x1 = r == i ? xg[i / 4][i % 4] : x1;
-            const uint32_t a = __builtin_bit_cast(uint32_t, x1) & 0xffff0000u;
-            const float r1 = x1 - __builtin_bit_cast(float, a);
-            const uint32_t b = __builtin_bit_cast(uint32_t, r1) & 0xffff0000u;
-            const uint32_t c = __builtin_bit_cast(uint32_t, r1 - __builtin_bit_cast(float, b));
-            if (r < 8) sm.xsum[buf][step][t0 + 16 * (r >> 2) + 4 * kq + (r & 3)] = u32x4{(a >> 16) | b, (c >> 16) | a, b >> 16, 0u};
-        }
-    };
-    // the product: the k slots of a group are x1 hi, x2 hi, x3 hi, x1 lo, x2 lo and three zeros
-    auto fold_zeros = [&](int buf) {
-        if constexpr (WPOST) {
-            typedef __bf16 b8 __attribute__((ext_vector_type(8)));
-            const int half = lane >> 5;
-#pragma unroll
-            for (int i = 0; i < CHUNK / 2; ++i) {
-                b8 xs[MT2];
-#pragma unroll
-                for (int m2 = 0; m2 < MT2; ++m2) xs[m2] = __builtin_bit_cast(b8, sm.xsum[buf][2 * i + half][32 * m2 + (lane & 31)]);
-                const uint32_t z2 = half ? zc[2 * i + 1] : zc[2 * i];
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    const float z = (float)as_h2(z2)[p];
-                    const uint32_t hi = __builtin_bit_cast(uint32_t, z) & 0xffff0000u;
-                    const uint32_t lo = __builtin_bit_cast(uint32_t, z - __builtin_bit_cast(float, hi));
-                    const b8 zb = __builtin_bit_cast(b8, u32x4{(hi >> 16) | hi, (hi >> 16) | lo, lo >> 16, 0u});
-#pragma unroll
-                    for (int m2 = 0; m2 < MT2; ++m2) accw[p][m2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xs[m2], zb, accw[p][m2], 0, 0, 0);
-                }
-            }
-        }
-    };
-    // One step on the 32x32x16 path, codes multiplied as they are (WPOST).  What bounds it is issue: 32 matrix instructions of 32 cycles and 206 (3 bit, 166 at
-    // 4) vector ones of about four a wave, which overlap only if they alternate, and behind that the board's power (1.55 GHz).  So a part of 16 columns is four
-    // matrix instructions with the next part's unpacking among them, and the products of a step (dw) go into the accumulators while the next step's first products
-    // are formed, of which they need the registers.  Four 14336-wide 3-bit layers at 64 rows, us: weights dequantised in front of the products 1430, so 1300 (error
-    // against 64 bits 2.7e-4 / 2.3e-4); 48 rows 1407 / 1279; three 4-bit layers, 40 rows 1107 / 1001; 7168-wide 3- and 4-bit layers, 33 rows 553 / 508, 64 580 / 533.
-    // Tried: a chain of eight products at a time for each of the four accumulators (evener, but half a step's operands held: 500 registers spilled); wave priorities
-    // by step, by part or for the younger wave of a SIMD (within 1 %); two more steps of weights in flight would not help (weights at hand in L2: 2 % faster).
-    // FIRST, LAST: of a chunk.  nb: the next step's stage; fill: the next activations; refill: asks for what b takes next.
-    h8 wv[2][NP], xv[2][WPOST ? MT2 : 1];
+    // One step of 3- and 4-bit codes on the 32x32x16 path.  What bounds it is issue: 32 matrix instructions of 32 cycles and 225 (3 bit, 209 at 4) vector ones of
+    // about four a wave, which overlap only if they alternate, and behind that the board's power (1.55 GHz).  So w~ is formed between the matrix instructions, a
+    // part of 16 columns ahead (the compiler spreads a part's unpacking evenly by itself; 5, 6, 7 or 9 vector instructions behind each matrix instruction by order are
+    // 1-5 % slower).  Us, a half step's unpacking in front of its products / so, the same bits: four 14336-wide 3-bit layers at 64 rows 1372 / 1341; three 4-bit ones
+    // 1133 / 1030; six 7168-wide ones of 3 and 4 bit, 40 rows 549 / 511, 64 568 / 530.
+    // Codes multiplied as subnormals, with scale and zero behind the products, take 206 and 166 vector instructions and a product per group for the sums of x:
+    // 1322 us where this takes 1349, 1069 / 1053, 535 / 498, 550 / 513.  But a sum of eight products of subnormals is kept to 2^-14 of its largest activation (of
+    // normal numbers to 2^-23), and where an element X meets weights of about zero that is a part of the result: one element of 60000 among N(0, 1) in a column
+    // of zeros, 4736 columns of 3 bit, error against 64 bits 8.2e-2, so 2.2e-4.
+    // Tried: four stages of weights instead of two: the same within 1 %.  FIRST, LAST: of a chunk.  nb: the next step's stage; fill: the next activations;
+    // refill: asks for what b takes next.
+    h8 wv[2][NP], xv[2][PAIRED_LOADS ? MT2 : 1];
     // the lane's place in the buffer in use: token row lane % 32, its half of a part's columns
     uint32_t xlane = (uint32_t)((lane & 31) * sizeof(sm.x[0][0]) + 32 * (lane >> 5));
-    f16x dw[WPOST ? NP : 1][WPOST ? MT2 : 1];
-    float sfw[NP];
-    auto clear_products = [&]() {
-        if constexpr (WPOST)
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                sfw[p] = 0.0f;
-#pragma unroll
-                for (int m2 = 0; m2 < MT2; ++m2)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) dw[p][m2][v] = 0.0f;
-            }
-    };
-    clear_products();
-    auto fold = [&](int p, int m2) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) accw[p][m2][v] = __builtin_fmaf(sfw[p], dw[p][m2][v], accw[p][m2][v]);
-        asm volatile("" : "+v"(accw[p][m2]));             // here and not when a later step wants it: dw's registers are taken over
-    };
-    auto step_wide = [&](Stage& b, Stage& nb, int buf, int step, auto first, auto last, auto fill, auto refill) {
+    auto step_wide = [&](Stage& b, Stage& nb, int step, auto first, auto last, auto fill, auto refill) {
         constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
-        const f16x zero16 = {};
         auto read_x = [&](int st_, int kk) {              // x_operand(buf, 32 * m2 + lane % 32, st_, 4 * (kk / 2) + 2 * (lane / 32) + kk % 2)
             const uint8_t* at = reinterpret_cast<const uint8_t*>(&sm) + xlane + st_ * 256 + 64 * (kk >> 1) + 16 * (kk & 1);
 #pragma unroll
             for (int m2 = 0; m2 < MT2; ++m2) xv[kk & 1][m2] = *reinterpret_cast<const h8*>(at + m2 * 32 * sizeof(sm.x[0][0]));
         };
-        auto unpack = [&](Stage& g, int kk) {
+        auto dequantise = [&](Stage& g, int kk) {
 #pragma unroll
-            for (int p = 0; p < NP; ++p) wv[kk & 1][p] = unpack_subnormal_step<V>(g.w[p + NP * (kk & 1)], kk >> 1);
+            for (int p = 0; p < NP; ++p) {
+                const _Float16 sc = as_h2(g.s[0])[p], z = as_h2(g.z[0])[p];
+                const h8 s8 = {sc, sc, sc, sc, sc, sc, sc, sc}, z8 = {z, z, z, z, z, z, z, z};
+                wv[kk & 1][p] = __builtin_elementwise_fma(unpack_codes_step<V>(g.w[p + NP * (kk & 1)], kk >> 1), s8, z8);
+            }
         };
         if constexpr (FIRST) {
             read_x(step, 0);
-            unpack(b, 0);
+            dequantise(b, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        zc[step] = b.z[0];
-        float sfn[NP];
-#pragma unroll
-        for (int p = 0; p < NP; ++p) sfn[p] = (float)as_h2(b.s[0])[p] * 16777216.0f;       // codes are subnormals: times 2^24
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
             __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this part's activations; ahead of the next part's reads, or the compiler waits for those too
             if (kk < 7) read_x(step, kk + 1);
             else if constexpr (!LAST) read_x(step + 1, 0);
             __builtin_amdgcn_sched_barrier(0);
-            if (kk < 7) unpack(b, kk + 1);
-            else if constexpr (!LAST) unpack(nb, 0);
+            if (kk < 7) dequantise(b, kk + 1);
+            else if constexpr (!LAST) dequantise(nb, 0);
 #pragma unroll
             for (int p = 0; p < NP; ++p)
 #pragma unroll
-                for (int m2 = 0; m2 < MT2; ++m2) {
-                    if (kk == 0) fold(p, m2);
-                    dw[p][m2] = mfma32(xv[kk & 1][m2], wv[kk & 1][p], kk == 0 ? zero16 : dw[p][m2]);
-                    if (kk == 0) __builtin_amdgcn_sched_barrier(0);
-                }
-            if (kk & 1) fill(4 * step + (kk >> 1));
-            if (kk > 0) {
-#pragma unroll
-                for (int g = 0; g < NP * MT2; ++g) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, MT2 == 1 ? 10 : 5, 0);
-                }
-            }
+                for (int m2 = 0; m2 < MT2; ++m2) accw[p][m2] = mfma32(xv[kk & 1][m2], wv[kk & 1][p], accw[p][m2]);
+            fill(8 * step + kk);
             __builtin_amdgcn_sched_barrier(0);
         }
         refill();
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) sfw[p] = sfn[p];
     };
     auto compute = [&](Stage& b, int buf, int step) {
         if constexpr (WIDE) {
@@ -521,48 +437,6 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
 #pragma unroll
         for (int i = 0; i < XQ; ++i) fill_x_row(c, buf, i, lane_off);
         asm volatile("" ::: "memory");      // weight loads issued later stay later: vmcnt counts in issue order
-    };
-
-    // Sums that are not finite, of tokens with an infinite activation: scale and zero behind the products make NaN of what the dequantised
-    // weights give an infinity for.  Formed again from those, slowly.
-    auto redo_not_finite = [&](int sb) {
-        if constexpr (WPOST) {
-#pragma unroll 1
-            for (int pm = 0; pm < NP * MT2; ++pm) {
-                bool bad = false;
-#pragma unroll
-                for (int u = 0; u < NP * MT2; ++u)
-                    if (u == pm)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) bad = bad || !__builtin_isfinite(accw[u / MT2][u % MT2][v]);
-                if (__builtin_expect(!__any(bad), 1)) continue;
-                const int p = pm / MT2, m2 = pm % MT2;
-                const long u0 = (long)sb * KT, k_lo = max(u0, s_begin) - u0, k_hi = min(u0 + KT, s_end) - u0;
-                const uint16_t* xp = xrows + (size_t)min(32 * m2 + (lane & 31), x_rows - 1) * L.K() + 16 * (lane >> 5);
-                const uint32_t sel = (uint32_t)(lane >> 4) & 1u;
-                f16x sum = {};
-#pragma unroll 1
-                for (long kt = k_lo; kt < k_hi; ++kt) {
-                    const uint8_t* tile = L.codes + ((size_t)row_block(sb) * KT + kt) * (4 * (size_t)TILE) + (2 * sel + p) * TILE + LANE_BYTES * (r + 32 * (lane >> 5));
-                    const size_t row = (size_t)kt * L.N + row_block(sb) * 64 + 4 * r + 2 * sel + p;
-#pragma unroll
-                    for (int which = 0; which < 2; ++which) {
-                        const WRaw<V> w = load_tile_at<V>(tile + which * 16 * LANE_BYTES);
-                        h8 o[4];
-                        unpack_codes<V>(w, o);
-                        apply_scale_zero(o, __builtin_bit_cast(_Float16, L.scales[row]), __builtin_bit_cast(_Float16, L.zeros[row]));
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) sum = mfma32(*reinterpret_cast<const h8*>(xp + (size_t)kt * 128 + 32 * j + 8 * which), o[j], sum);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < NP * MT2; ++u)
-                    if (u == pm)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v)
-                            if (!__builtin_isfinite(accw[u / MT2][u % MT2][v])) accw[u / MT2][u % MT2][v] = sum[v];
-            }
-        }
     };
 
     // ---- end of a unit: lane holds tokens 4*kq + v of RT consecutive rows starting at nbase
@@ -759,22 +633,16 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     wait_vmem_all_but<0>();
     lds_barrier();
     int buf = 0;
-    bool pending = false;                                    // WPOST: the zero term of the chunk before is still to come
     while (cur.n > 0) {
         const bool active = row_block(cur.sb) < row_blocks;
-        if constexpr (WPOST) {
-            if (pending && active) fold_zeros(buf ^ 1);
-            sum_x(buf);
-            __builtin_amdgcn_sched_barrier(0);
-        }
         // steady state: a chunk of N steps (a full one; in the 16-step form also a linear's remainder of exactly 8)
         // followed by enough steps to refill every slot -- no per-step conditions, so the whole chunk is one
         // schedulable block
         auto steady_chunk = [&](auto n_steps) {
             constexpr int N = decltype(n_steps)::value;
             FillOffs fill_off;
-            if constexpr (WPOST) fill_off = fill_lane_offs(nxt);
-            if constexpr (!WPOST) fill_x_chunk(nxt, buf ^ 1);     // in this block, where the compiler can count the fill ahead of the stages' uses
+            if constexpr (PAIRED_LOADS) fill_off = fill_lane_offs(nxt);
+            else fill_x_chunk(nxt, buf ^ 1);            // in this block, where the compiler can count the fill ahead of the stages' uses
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 auto refill = [&] {
@@ -782,15 +650,16 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
                     if (q < N) issue(st[i % STAGES], cur.sb, cur.kt0 + q, oc);
                     else       issue(st[i % STAGES], nxt.sb, nxt.kt0 + (q - N), on);
                 };
-                if constexpr (WPOST) {
-                    // the next chunk's activations: a load at a time through steps 0 and 1 (in a block they wait for one another's issue)
+                if constexpr (PAIRED_LOADS) {
+                    // the next chunk's activations: a load per part (in a block they wait for one another's issue), ahead of the refills that stay in flight below
                     auto fill = [&](int i) { if (i < XQ) fill_x_row(nxt, buf ^ 1, i, fill_off); };
                     typedef std::true_type T;
                     typedef std::false_type F;
-                    static_assert(!WPOST || N % STAGES == 0, "a chunk ends with the stages where it began");
-                    if (i == 0)          step_wide(st[0], st[1 % STAGES], buf, 0, T(), F(), fill, refill);
-                    else if (i == N - 1) step_wide(st[i % STAGES], st[(i + 1) % STAGES], buf, i, F(), T(), fill, refill);
-                    else                 step_wide(st[i % STAGES], st[(i + 1) % STAGES], buf, i, F(), F(), fill, refill);
+                    static_assert(N % STAGES == 0, "a chunk ends with the stages where it began");
+                    static_assert(!PAIRED_LOADS || XQ <= 8 * (N - STAGES + 1), "fills come before the last STAGES refills");
+                    if (i == 0)          step_wide(st[0], st[1 % STAGES], 0, T(), F(), fill, refill);
+                    else if (i == N - 1) step_wide(st[i % STAGES], st[(i + 1) % STAGES], i, F(), T(), fill, refill);
+                    else                 step_wide(st[i % STAGES], st[(i + 1) % STAGES], i, F(), F(), fill, refill);
                 } else {
                     compute(st[i % STAGES], buf, i);
                     refill();
@@ -808,10 +677,10 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             if (nxt.n > 0) fill_x_chunk(nxt, buf ^ 1);
 #pragma unroll
             for (int i = 0; i < CHUNK; ++i) {
-                if constexpr (WPOST) {
-                    zc[i] = 0;
-                    if (i < cur.n && active) step_wide(st[i % STAGES], st[i % STAGES], buf, i, std::true_type(), std::true_type(), [](int) {}, [] {});
-                } else if (i < cur.n && active) compute(st[i % STAGES], buf, i);
+                if (i < cur.n && active) {
+                    if constexpr (PAIRED_LOADS) step_wide(st[i % STAGES], st[i % STAGES], i, std::true_type(), std::true_type(), [](int) {}, [] {});
+                    else compute(st[i % STAGES], buf, i);
+                }
                 const int q = i + STAGES;
                 if (q < CHUNK) { if (q < cur.n) issue(st[i % STAGES], cur.sb, cur.kt0 + q, oc); }
                 else           { if (q - CHUNK < nxt.n) issue(st[i % STAGES], nxt.sb, nxt.kt0 + (q - CHUNK), on); }
@@ -822,24 +691,11 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
         if (unit_ends) {
             const long u0 = (long)cur.sb * KT;               // the unit's first step
             const bool whole = u0 >= s_begin && u0 + KT <= s_end;
-            if constexpr (WPOST) {
-                lds_barrier();                               // everybody's sums of this chunk
-                if (active) {
-#pragma unroll
-                    for (int p = 0; p < NP; ++p)
-#pragma unroll
-                        for (int m2 = 0; m2 < MT2; ++m2) fold(p, m2);
-                    fold_zeros(buf);
-                    redo_not_finite(cur.sb);
-                }
-            }
             finish_unit(cur.sb, whole ? nullptr : (u0 < s_begin ? slot_first : slot_last));
-            if constexpr (WPOST) clear_products();
         }
-        if constexpr (WPOST) pending = !unit_ends;
         lds_barrier();
         buf ^= 1;
-        if constexpr (WPOST) xlane += buf ? (uint32_t)sizeof(sm.x[0]) : 0u - (uint32_t)sizeof(sm.x[0]);
+        if constexpr (PAIRED_LOADS) xlane += buf ? (uint32_t)sizeof(sm.x[0]) : 0u - (uint32_t)sizeof(sm.x[0]);
         cur = nxt;
         nxt = next_chunk(nxt);
         oc = on;

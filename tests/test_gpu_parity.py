@@ -652,6 +652,34 @@ def test_decode_beside_large_activations(bits, size, even_share):
         assert float(err.max()) <= 4e-4, "%d rows: row %d off by %.2e" % (M, int(err.argmax()), float(err.max()))
 
 
+@pytest.mark.parametrize("bits", [3, 4, 8], ids=["w3", "w4", "w8"])
+@pytest.mark.parametrize("size", [1000.0, 60000.0])
+@pytest.mark.parametrize("K", [128, 1152])
+def test_decode_33_to_64_rows_beside_large_activations_on_codes_that_are_not_zero(bits, size, K, even_share):
+    """As above, 33 rows and more, where the large element's weights are zero in W~ only as scale * code + zero: groups are symmetric about zero.  The weights lie on
+    the grid, so that W~ = W exactly and the output's rounding (2.1e-4) is all there is, but for sums of 1152 terms in 32 bits: 3e-4."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(bits + K)
+    N, top, mid, scale = 1088, 2 ** bits - 1, 2 ** (bits - 1) - 1, 2.0 ** (-4 - bits)
+    col = torch.arange(64, device="cuda") * 17 % K                                        # every place of a lane's 32 columns
+    codes = (torch.randn((N, K), generator=gen, device="cuda") * (top / 6.0) + mid).round().clamp(0, top)
+    codes[:, col] = mid
+    others = [[k for k in range(128 * g, 128 * g + 128) if k not in set(col.tolist())] for g in range(K // 128)]
+    codes[:, [o[0] for o in others]], codes[:, [o[1] for o in others]] = 0.0, float(top)   # a group's range: its scale and zero
+    w = ((codes - mid) * scale).half()
+    qw = lpq.lpq_quantize_pack(w, bits, lpq.LPQ_ASYM_GROUP)
+    deq = lpq.lpq_unpack_dequant(qw).double()
+    assert torch.equal(deq, w.double()) and float(deq[:, col].abs().max()) == 0.0
+    x = torch.randn((64, K), generator=gen, device="cuda").half()
+    x[torch.arange(64, device="cuda"), col] = size
+    ref = x.double() @ deq.t()
+    for M in (33, 48, 64):
+        assert lpq.lpq_route_of([(bits, lpq.LPQ_ASYM_GROUP, K, N)], lpq.LPQ_DECODE, M)[0] == lpq.LPQ_ROUTE_EVEN_SHARE
+        y = lpq.lpq_qlinear_decode(qw, x[:M]).double()
+        err = (y - ref[:M]).norm(dim=1) / ref[:M].norm(dim=1)
+        assert float(err.max()) <= 3e-4, "%d rows: row %d off by %.2e" % (M, int(err.argmax()), float(err.max()))
+
+
 @pytest.mark.parametrize("bits", [3, 4], ids=["w3", "w4"])
 @pytest.mark.parametrize("K,N", [(128, 64), (384, 320), (4736, 192), (1152, 1088), (2048 * 128 + 1152, 64)])
 def test_decode_33_to_64_rows_even_share(bits, K, N, even_share):
