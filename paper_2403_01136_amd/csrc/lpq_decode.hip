@@ -308,17 +308,16 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
                 for (int t = 0; t < RT; ++t) {
                     unpack_codes_half<V>(b.w[t], half, wb[t]);
                     if constexpr (SCHEME == SCH_ASYM) {
-                        const uint32_t sp = b.s[PAIRED_LOADS ? 0 : t >> 1], zp = b.z[PAIRED_LOADS ? 0 : t >> 1];      // PAIRED_LOADS: operand t belongs to pair t & 1
+                        const uint32_t sp = b.s[t >> 1], zp = b.z[t >> 1];
                         const uint16_t sh = (uint16_t)((t & 1) ? (sp >> 16) : (sp & 0xffffu));
                         const uint16_t zh = (uint16_t)((t & 1) ? (zp >> 16) : (zp & 0xffffu));
                         apply_scale_zero_half(wb[t], __builtin_bit_cast(_Float16, sh), __builtin_bit_cast(_Float16, zh));
                     }
                 }
-                if constexpr (!PAIRED_LOADS)
 #pragma unroll
-                    for (int p = 0; p < NP; ++p)
+                for (int p = 0; p < NP; ++p)
 #pragma unroll
-                        for (int jj = 0; jj < 2; ++jj) pair_tiles_for_mfma32(wb[p][jj], wb[p + NP][jj]);
+                    for (int jj = 0; jj < 2; ++jj) pair_tiles_for_mfma32(wb[p][jj], wb[p + NP][jj]);
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj) {
                     const int j = 2 * half + jj;
@@ -336,7 +335,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
             }
             return;
         }
-        if constexpr (POST && !WIDE) {
+        if constexpr (POST) {
             // In-order issue: vector work in front of a run of matrix instructions is not hidden by
             // them, vector work between them is.  So the codes of MFMA step j + 1 are unpacked in the
             // same scheduling group as the matrix instructions of step j.
@@ -378,25 +377,14 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
                         for (int v = 0; v < 4; ++v) acc[t][mt][v] = __builtin_fmaf(sf, d[t][mt][v], acc[t][mt][v]);
                 }
             }
-        } else {
-            h8 wb[RT][4];
-#pragma unroll
-            for (int t = 0; t < RT; ++t) {
-                unpack_codes<V>(b.w[t], wb[t]);
-                if constexpr (SCHEME == SCH_ASYM) {
-                    const uint32_t sp = b.s[t >> 1], zp = b.z[t >> 1];
-                    const uint16_t sh = (uint16_t)((t & 1) ? (sp >> 16) : (sp & 0xffffu));
-                    const uint16_t zh = (uint16_t)((t & 1) ? (zp >> 16) : (zp & 0xffffu));
-                    apply_scale_zero(wb[t], __builtin_bit_cast(_Float16, sh), __builtin_bit_cast(_Float16, zh));
-                }
-            }
+        } else {                            // fp16 weights
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     const h8 a = x_operand(buf, 16 * mt + r, step, 4 * j + kq);
 #pragma unroll
-                    for (int t = 0; t < RT; ++t) acc[t][mt] = mfma16(a, wb[t][j], acc[t][mt]);
+                    for (int t = 0; t < RT; ++t) acc[t][mt] = mfma16(a, unpack_codes_step<V>(b.w[t], j), acc[t][mt]);
                 }
         }
     };
