@@ -300,25 +300,29 @@ bool reads_in_place(const std::vector<LinearCall>& calls, size_t begin, size_t e
 // Whether a decode launch of 17 to 64 token rows goes to the kernel of few row blocks per workgroup instead of the even-share
 // kernel.  That one has some 30 us of preparation, fix-up pass and partial tiles, this one a higher cost per 3- or 4-bit weight
 // (both tiles' FMAs against the zero term outside the loop; at 33-64 rows a product per group against weights
-// dequantised once), so the line lies at a number of weights; 8- and 16-bit codes cost about the same in both.  Measured, us,
+// dequantised between the matrix instructions), so the line lies at a number of weights; 8- and 16-bit codes cost about the same in both.  Measured, us,
 // even-share / this, at 32, 48 and 64 rows: a 4-bit layer of 5120 (315 M weights) 81 / 46, 90 / 55, 93 / 65; a 3- and a 4-bit layer
 // of 5120 (629 M) 107 / 83, 131 / 109, 138 / 130; three 4-bit layers of 5120 (944 M) 143 / 128, 173 / 162, 182 / 198; a 3- and a 4-bit layer of 7168
 // (1.2 G) 165 / 149, 222 / 200, 226 / 238; a 3-bit layer of 14336 (2.5 G) 259 / 290, 381 / 370, 393 / 455; 8 bit, 7168 -> 28672 93 / 42, 110 / 48, 119 / 56;
 // an 8-bit layer of 9216 (1.0 G) 227 / 193, 244 / 220, 252 / 252; fp16, 7168 -> 28672 114 / 66, 120 / 71, 129 / 73.
 // With the weight pipeline of the even-share kernel kept full across its chunks: three 4-bit layers of 5120 125 / 108 at 17 rows, 134 / 128 at 32, 182 / 198
 // at 64; three layers of 7168 of 3 and 4 bit (1.85 G) 190 / 199, 203 / 212, 309 / 342.
-// With its 3- and 4-bit codes of 33 to 64 rows multiplied as they are: even-share over this at 20, 32, 40, 48, 56, 64 rows, a 3- and a 4-bit layer of
-// 5120 (0.63 G) 1.07 1.13 1.15 1.13 0.96 0.98, of 6144 (0.91 G) 1.00 1.04 1.06 1.05 0.88 0.88, of 7168 (1.23 G) 1.01 1.00 1.02 1.04 0.84 0.84.
+// With its 3- and 4-bit weights of 33 to 64 rows dequantised between the matrix instructions: even-share over this at 33, 40, 48, 56, 64 rows, a 3- and a 4-bit layer of
+// 4608 (0.51 G) 1.00 1.04 1.07 0.89 0.92, of 5120 (0.63 G) 1.05 1.10 1.11 0.93 0.95, of 6144 (0.91 G) 0.98 1.00 1.00 0.84 0.86, of 7168 (1.23 G) 0.93 0.92 0.95 0.78 0.80; one
+// linear, 3 bit, 14336 -> 57344 (0.82 G) 1.01 1.04 1.07 0.91 0.90, 4 bit, 28672 -> 36864 (1.06 G) 1.00 1.06 1.04 0.90 0.93.
 // 8 bit at 18, 32, 44, 64 rows: two layers of 7168 (1.23 GB) 1.09 1.12 1.09 0.98, three (1.85 GB) 1.03 1.04 1.10 1.01, two of 9216 (2.04 GB) 1.06 1.08 1.05 0.94,
 // five of 7168 (3.1 GB) 1.05 1.05 1.08 0.93; fp16: 7168 (1.23 GB) 1.10 1.11 1.15 1.10, 9216 (2.04 GB) 1.06 1.06 1.09 1.06, three of 7168 (3.7 GB) 0.96 0.96 0.99 0.99;
 // but a single fp16 linear, 28672 -> 36864 (2.1 GB), 0.976 at 24 and 0.973 at 64 rows, and at 2 GB the first launch on new weights is 4-6 % slower in this one (466 / 488
 // on two 8-bit layers of 9216, 24 rows; 449 / 470 on fp16, 40 rows), at 1.85 GB (465 / 460) and 1.2 GB (308 / 310) not: the lines are below that.
-// (49-64 rows of 3 and 4 bit: 0.45 G 1.00, 0.51 G 0.96-0.99; the line stays a little above, where a launch without a fix-up pass needs less workspace.)
+// (49-64 rows of 3 and 4 bit: they meet at some 0.45 G; the line stays a little above, where a launch without a fix-up pass needs less workspace, and a reservation
+// that served a call has to serve it still.)
 // rows_max_mib of lpq_set_decode_routing (default 192) moves the line in proportion.
 struct MidLine { double weights34[3], bytes8[3], bytes16[3]; };       // [17-32, 33-48, 49-64 rows]
-const MidLine MID_LINE = {{1.0e9, 1.25e9, 0.55e9}, {1.9e9, 1.9e9, 1.0e9}, {1.4e9, 1.4e9, 1.4e9}};
+const MidLine MID_LINE = {{1.0e9, 1.0e9, 0.55e9}, {1.9e9, 1.9e9, 1.0e9}, {1.4e9, 1.4e9, 1.4e9}};
 // The line of a single linear: its row blocks are all of one length, and their last round may be nearly empty (fp16, 28672 -> 24320, 1.39 GB, 380 row
-// blocks for 256 compute units: 0.994 at 18 rows, 0.957 at 48; 20480 -> 32768, 512 of them, 1.20 at 24 rows).  Above it a launch of several
+// blocks for 256 compute units: 0.994 at 18 rows, 0.957 at 48; 20480 -> 32768, 512 of them, 1.20 at 24 rows).  Also that of launches of several of 33 rows and more with
+// grouped weights among them: there even-share dequantises, and next to an activation thousands of times the others, in a column of zero weights, codes multiplied as
+// they are lose (one of 60000 among N(0, 1), 1152 columns of 8 bit: 4.2e-3 against 64 bits, 2.2e-4 dequantised).  Above it a launch of several
 // asks for the even-share kernel's workspace all the same: other numbers of rows of the same linears take that one, and a workspace reserved for
 // the widest call of a program has to serve its narrower ones.
 const MidLine MID_LINE_ONE = {{1.0e9, 1.0e9, 0.55e9}, {1.0e9, 1.0e9, 1.0e9}, {1.0e9, 1.0e9, 1.0e9}};
@@ -339,7 +343,11 @@ bool mid_route(const std::vector<LinearCall>& calls, size_t begin, size_t end, i
 bool small_launch(const std::vector<LinearCall>& calls, size_t begin, size_t end, int32_t M)
 {
     if (M > 64) return false;
-    if (M > 16) return mid_route(calls, begin, end, M, end - begin > 1 ? MID_LINE : MID_LINE_ONE);
+    if (M > 16) {
+        bool far = end - begin > 1;
+        for (size_t c = begin; c < end; ++c) far = far && (M <= 32 || calls[c].w->d.scheme != LPQ_ASYM_GROUP);
+        return mid_route(calls, begin, end, M, far ? MID_LINE : MID_LINE_ONE);
+    }
     int64_t stream_bytes = 0;
     for (size_t c = begin; c < end; ++c) stream_bytes += (int64_t)calls[c].w->d.K * calls[c].w->d.N * calls[c].w->d.bits / 8;
     return stream_bytes <= (int64_t)g_rows_max_mb.load() << 20;

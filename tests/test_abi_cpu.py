@@ -233,8 +233,8 @@ def test_routes():
 
 
 @pytest.mark.parametrize("bits,scheme,several,one", [
-    (3, 1, (1.0e9, 1.25e9, 0.55e9), (1.0e9, 1.0e9, 0.55e9)), (4, 1, (1.0e9, 1.25e9, 0.55e9), (1.0e9, 1.0e9, 0.55e9)),
-    (8, 1, (1.9e9, 1.9e9, 1.0e9), (1.0e9,) * 3), (8, 2, (1.9e9, 1.9e9, 1.0e9), (1.0e9,) * 3), (16, 0, (0.7e9,) * 3, (0.5e9,) * 3)])
+    (3, 1, (1.0e9, 1.0e9, 0.55e9), (1.0e9, 1.0e9, 0.55e9)), (4, 1, (1.0e9, 1.0e9, 0.55e9), (1.0e9, 1.0e9, 0.55e9)),
+    (8, 1, (1.9e9, 1.0e9, 1.0e9), (1.0e9,) * 3), (8, 2, (1.9e9, 1.9e9, 1.0e9), (1.0e9,) * 3), (16, 0, (0.7e9,) * 3, (0.5e9,) * 3)])
 def test_routes_of_17_to_64_rows_by_weights(bits, scheme, several, one):
     """The number of weights up to which a launch of 17-32, 33-48 and 49-64 rows goes to the kernel of few row blocks, of several linears and of
     one; it moves with the first routing setting."""
@@ -248,6 +248,19 @@ def test_routes_of_17_to_64_rows_by_weights(bits, scheme, several, one):
         assert kernel(1.99 * several[0], 3, 17) == lpq.LPQ_ROUTE_MID
     finally:
         lpq.lpq_set_decode_routing(-1, -1)
+
+
+@pytest.mark.parametrize("grouped", [(3, 1), (4, 1), (8, 1)], ids=["w3", "w4", "w8"])
+@pytest.mark.parametrize("other", [(8, 2), (16, 0)], ids=["i8", "f16"])
+def test_grouped_weights_of_33_rows_and_more_keep_the_near_line(grouped, other):
+    """Up to 64 rows symmetric 8-bit and fp16 weights go farther with the kernel of few row blocks, but not beside a grouped linear, whose weights the
+    even-share kernel dequantises from 33 rows on and that one does not."""
+    far, small = other + (8192, 73728 if other[0] == 8 else 36864), grouped + (128, 64)       # two of them: 1.2 GB
+    kernel = lambda descs, M: lpq.lpq_route_of(descs, lpq.LPQ_DECODE, M)[0]
+    for M in (17, 32):
+        assert kernel([far, far], M) == kernel([far, small, far], M) == lpq.LPQ_ROUTE_MID
+    for M in (33, 48):
+        assert kernel([far, far], M) == lpq.LPQ_ROUTE_MID and kernel([far, small, far], M) == lpq.LPQ_ROUTE_EVEN_SHARE
 
 
 def layer_route(fmt, h, n_seqs, pos0=70):
