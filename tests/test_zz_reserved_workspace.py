@@ -61,10 +61,41 @@ print("reserved ok")
 """
 
 
-def run_child(code):
+# Four linears between the two lines of the kernel of few row blocks (1 MiB: the lines at 5.2 and 9.9 MB of codes).
+CHILD_LINE = r"""
+import sys
+import torch
+import paper_2403_01136_amd as lpq
+dev = torch.device("cuda")
+even_share = sys.argv[1] == "even_share"
+qw = lpq.lpq_quantize_pack((torch.randn((896, 2048), device=dev) * 0.02).half(), 8, lpq.LPQ_SYM_CHANNEL)
+def call(M):
+    xs = {n: torch.randn((M, 2048), device=dev).half() for n in lpq.LINEARS}
+    ys = {n: torch.empty((M, 896), dtype=torch.float16, device=dev) for n in lpq.LINEARS}
+    lpq.lpq_stage_linears(lpq.Stage([{n: qw for n in lpq.LINEARS}], [xs], [ys]), lpq.LPQ_DECODE)
+    return lpq.lpq_workspace_bytes()
+lpq.lpq_set_decode_routing(0 if even_share else 1, -1)
+descs = [(8, lpq.LPQ_SYM_CHANNEL, 2048, 896)] * 4
+for M in (24, 43):
+    assert lpq.lpq_route_of(descs, lpq.LPQ_DECODE, M)[0] == (lpq.LPQ_ROUTE_EVEN_SHARE if even_share else lpq.LPQ_ROUTE_MID)
+assert lpq.lpq_route_of(descs, lpq.LPQ_DECODE, 64)[0] == lpq.LPQ_ROUTE_EVEN_SHARE
+if not even_share:
+    lpq.lpq_qlinear_decode(qw, torch.randn((24, 2048), device=dev).half())
+    assert lpq.lpq_workspace_bytes() <= 8 << 20, "a launch below both lines"
+print("bytes", call(24), call(43), call(64))
+lpq.lpq_workspace_reserve(1)
+for M in (17, 24, 32, 33, 43, 48, 64):
+    call(M)
+torch.cuda.synchronize()
+print("reserved ok")
+"""
+
+
+def run_child(code, *args):
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    r = subprocess.run([sys.executable, "-c", code, *args], cwd=root, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "reserved ok" in r.stdout, r.stdout + r.stderr
+    return r.stdout
 
 
 @pytest.mark.gpu
@@ -75,3 +106,11 @@ def test_small_reservation_runs_unsplit():
 @pytest.mark.gpu
 def test_small_reservation_refuses_before_the_first_launch():
     run_child(CHILD_REFUSED)
+
+
+@pytest.mark.gpu
+def test_launches_between_the_lines_ask_for_the_even_share_kernels_workspace():
+    """A launch of several linears that goes to the kernel of few row blocks only because of the farther line has the workspace grow as the even-share
+    kernel's would: a reservation serves, or refuses, the calls it did, whichever kernel takes them."""
+    sizes = [next(line for line in run_child(CHILD_LINE, kernel).splitlines() if line.startswith("bytes")) for kernel in ("mid", "even_share")]
+    assert sizes[0] == sizes[1] and int(sizes[0].split()[1]) > 32 << 20, sizes
