@@ -714,28 +714,36 @@ def test_decode_33_to_64_rows_even_share(bits, K, N, even_share):
         check_output(z, (torch.relu(ref) + res.double()).cpu().numpy(), "even share, %d rows" % M)
 
 
-@pytest.mark.parametrize("bits", [3, 4], ids=["w3", "w4"])
+@pytest.mark.parametrize("small", [False, True], ids=["even_share", "small"])
+@pytest.mark.parametrize("bits", [3, 4, 8], ids=["w3", "w4", "w8"])
 @pytest.mark.parametrize("K,N", [(4736, 1088), (1920, 576)])
-def test_decode_33_to_64_rows_even_share_zero_term(bits, K, N, even_share):
-    """3- and 4-bit codes of 33 to 64 rows are multiplied without their zero points: zero times the sum of a group's activations is added behind.  Where
-    it is largest, activations of one sign (the code's and the zero's products are tens of times the result they leave) in rows of magnitudes up to 2^12
-    apart, at waves with a partial last chunk.  Against 64 bits, row by row: the output's rounding is 2.1e-4; the two 32-bit sums of
-    K / 32 terms, |terms| up to 16 times the result, leave at most 16 * sqrt(K) * 2^-24 = 6.6e-5, and the sums' pieces 2^-16 of a term that is 16 times
-    the result, of random sign over the groups: 4e-4 in all."""
+def test_decode_zero_term_of_one_signed_activations(bits, K, N, small):
+    """Codes multiplied without their zero points, zero times the sum of a group's activations behind: the even-share kernel up to 32 rows, the kernels of small
+    launches.  Where that term is largest, activations of one sign against weights about zero: it is 100 to 170 times the result, in rows of magnitudes up to 2^12 apart.  Against
+    64 bits, row by row: the output's rounding is 2.1e-4; 32-bit sums of terms 170 times the result leave some 170 * 2^-24 * sqrt(K / 32) = 1.2e-4, 2.5e-4 together, 3e-4 with
+    room for the worst row (sums kept as one fp16 number instead of two would leave 8e-3).  From 33 rows on the even-share kernel multiplies weights rounded to fp16, the same few
+    values many times over: the library's tolerance."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(K + N + bits)
-    w = (torch.randn((N, K), generator=gen, device="cuda") * 0.02 + 0.01).half()
+    w = (torch.randn((N, K), generator=gen, device="cuda") * 0.02).half()
     qw = lpq.lpq_quantize_pack(w, bits, lpq.LPQ_ASYM_GROUP)
     deq = lpq.lpq_unpack_dequant(qw).double()
     x = torch.rand((64, K), generator=gen, device="cuda") + 0.5
     scale = torch.tensor([1.0, 2.0 ** -8, -(2.0 ** 4)], device="cuda")[torch.arange(64, device="cuda") % 3]
     x = (x * scale[:, None]).half()
     ref = x.double() @ deq.t()
-    for M in (33, 64):
-        assert lpq.lpq_route_of([(bits, lpq.LPQ_ASYM_GROUP, K, N)], lpq.LPQ_DECODE, M)[0] == lpq.LPQ_ROUTE_EVEN_SHARE
-        y = lpq.lpq_qlinear_decode(qw, x[:M]).double()
-        err = (y - ref[:M]).norm(dim=1) / ref[:M].norm(dim=1)
-        assert float(err.max()) <= 4e-4, "%d rows: row %d off by %.2e" % (M, int(err.argmax()), float(err.max()))
+    zeros = qw.zeros.view(K // 128, N).double()                                          # the term itself, of the first row
+    term = x[0].double().view(K // 128, 128).sum(1) @ zeros
+    assert 90.0 <= float(term.norm() / ref[0].norm()) <= 200.0
+    lpq.lpq_set_decode_routing(-1 if small else 0, 0)
+    try:
+        for M in (1, 8, 16, 17, 32, 33, 64):
+            assert (lpq.lpq_route_of([(bits, lpq.LPQ_ASYM_GROUP, K, N)], lpq.LPQ_DECODE, M)[0] != lpq.LPQ_ROUTE_EVEN_SHARE) == small
+            y = lpq.lpq_qlinear_decode(qw, x[:M]).double()
+            err = (y - ref[:M]).norm(dim=1) / ref[:M].norm(dim=1)
+            assert float(err.max()) <= (3e-4 if small or M <= 32 else 1e-3), "%d rows: row %d off by %.2e" % (M, int(err.argmax()), float(err.max()))
+    finally:
+        lpq.lpq_set_decode_routing(-1, -1)
 
 
 @pytest.mark.parametrize("M", [40, 64])
