@@ -771,3 +771,21 @@ def test_decode_of_long_rows_without_allocation(M, even_share):
         ref = xs[0][name].double() @ lpq.lpq_unpack_dequant(layer[name]).double().t()
         for ys in out:
             check_output(ys[n - 1][name], ref.cpu().numpy(), "%s, %d rows" % (name, M))
+
+
+@pytest.mark.parametrize("bits,scheme,M", [(8, 1, 20), (8, 2, 20), (8, 2, 43), (16, 0, 30), (16, 0, 64)], ids=["w8_20", "i8_20", "i8_43", "fp16_30", "fp16_64"])
+def test_decode_mid_kernel_between_the_lines(bits, scheme, M):
+    """Launches of four linears of 1.2 GB of codes, with which a single linear would take the even-share kernel."""
+    import torch
+    K, N = 8192, 18432 * 16 // bits
+    assert lpq.lpq_route_of([(bits, scheme, K, N)] * 4, lpq.LPQ_DECODE, M)[0] == lpq.LPQ_ROUTE_MID
+    assert lpq.lpq_route_of([(bits, scheme, K, 4 * N)], lpq.LPQ_DECODE, M)[0] == lpq.LPQ_ROUTE_EVEN_SHARE
+    gen = torch.Generator(device="cuda").manual_seed(bits + M)
+    bias = torch.randn((N,), generator=gen, device="cuda").half()
+    qw = lpq.lpq_quantize_pack(torch.randn((N, K), generator=gen, device="cuda", dtype=torch.float16) * 0.02, bits, scheme, bias=bias)
+    names = ("qkv", "out", "fc1", "fc2")
+    xs = {n: torch.randn((M, K), generator=gen, device="cuda").half() for n in names}
+    ys = {n: torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for n in names}
+    lpq.lpq_stage_linears(lpq.Stage([{n: qw for n in names}], [xs], [ys]), lpq.LPQ_DECODE)
+    for n in names:
+        check_output(ys[n], _prefill_reference(qw, xs[n], bias), "%s, %d rows" % (n, M))
