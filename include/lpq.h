@@ -39,6 +39,10 @@
  *     An infinite x[m][k] gives what the weights rounded to fp16 give: an infinity of the weight's sign,
  *     NaN where infinities of both signs or a zero weight meet.  In decode calls of up to 32 rows, and in
  *     the last up to 32 rows of one of more than 64 (which runs 64 at a time), it may give NaN instead.
+ *     Decode calls, and prefill calls of up to 64 rows, may multiply codes ahead of their scale and zero
+ *     point; products of eight columns are then kept to 2^-14 of the largest |x| among them, times the
+ *     weights' scale.  That shows beside an x some hundred times its row's others (8 bit: some thousand)
+ *     in a column whose weights are about zero: 1e-3 of the result where rounding gives 2e-4.
  *
  * Storage format of a quantised weight W [N][K] (K contiguous); N % 64 == 0, K % 128 == 0
  *   A block is 64 rows x 128 columns (one quantisation group per row); blocks are stored in

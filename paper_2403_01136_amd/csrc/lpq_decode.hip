@@ -248,7 +248,7 @@ __device__ __forceinline__ void run_range(const LinDesc& L, int M, int m0, long 
     // about four a wave, which overlap only if they alternate, and behind that the board's power (1.55 GHz).  So w~ is formed between the matrix instructions, a
     // part of 16 columns ahead (the compiler spreads a part's unpacking evenly by itself; 5, 6, 7 or 9 vector instructions behind each matrix instruction by order are
     // 1-5 % slower).  Us, a half step's unpacking in front of its products / so, the same bits: four 14336-wide 3-bit layers at 64 rows 1372 / 1341; three 4-bit ones
-    // 1133 / 1030; six 7168-wide ones of 3 and 4 bit, 40 rows 549 / 511, 64 568 / 530.
+    // 1133 / 1030; six 7168-wide ones of 3 and 4 bit, 40 rows 549 / 511, 64 568 / 530 (on a card with less power to spare 1408 / 1372, 551 / 529, 570 / 559).
     // Codes multiplied as subnormals, with scale and zero behind the products, take 206 and 166 vector instructions and a product per group for the sums of x:
     // 1322 us where this takes 1349, 1069 / 1053, 535 / 498, 550 / 513.  But a sum of eight products of subnormals is kept to 2^-14 of its largest activation (of
     // normal numbers to 2^-23), and where an element X meets weights of about zero that is a part of the result: one element of 60000 among N(0, 1) in a column
